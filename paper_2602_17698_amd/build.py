@@ -3,6 +3,8 @@
 Variants (compile-time switches of the arithmetic, one library each):
   ""   -> libscalebits.so      cost = sum s * d^2
   "l1" -> libscalebits_l1.so   cost = sum s * |d|   (-DSBITS_COST_POWER=1)
+  "impatient" -> libscalebits_impatient.so   the search's workgroups give up waiting for each other at once, so that
+                                             the tests reach the single-workgroup search behind it
 """
 from __future__ import annotations
 
@@ -14,7 +16,8 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
-VARIANTS = {"": [], "l1": ["-DSBITS_COST_POWER=1"]}
+VARIANTS = {"": [], "l1": ["-DSBITS_COST_POWER=1"], "impatient": ["-DSBITS_SPIN_LIMIT=0"]}
+ONLY = {"impatient": ["alloc.hip"]}             # sources a variant compiles anew; the rest are the default build's objects
 SOURCES = ["api.hip", "reorder.hip", "cost.hip", "fused.hip", "alloc.hip", "pack.hip", "mpgemm.hip", "dequant.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -31,6 +34,8 @@ def lib_path(variant: str = "") -> str:
 
 
 def _compile(src: str, force: bool, variant: str) -> str:
+    if src not in ONLY.get(variant, SOURCES):
+        force, variant = False, ""
     objdir = os.path.join(HERE, "_build" + ("_" + variant if variant else ""))
     obj = os.path.join(objdir, src.replace(".hip", ".o"))
     deps = [os.path.join(CSRC, src)] + [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".hpp")]
