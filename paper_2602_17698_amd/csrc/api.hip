@@ -458,9 +458,10 @@ int sbits_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t ld_x, i
     if (!sbits_mp_gemm_shapes_ok(plan)) return SBITS_ERR_UNIMPLEMENTED;
     int rc = need_device(plan);
     if (rc) return rc;
-    // 32 rows of x per launch (two batch tiles of the kernel); launches share the scratch in stream order
-    for (int b0 = 0; b0 < batch; b0 += 32) {
-        const int nb = batch - b0 < 32 ? batch - b0 : 32;
+    // launches share the scratch in stream order
+    const int per = sbits_mp_gemm_rows(ld_x);
+    for (int b0 = 0; b0 < batch; b0 += per) {
+        const int nb = batch - b0 < per ? batch - b0 : per;
         rc = sbits_launch_mp_gemm(plan, mat, static_cast<const uint16_t *>(x_bf16) + (int64_t)b0 * ld_x, ld_x, nb, level,
                                   byte_off, codes, scale, zero, y + (int64_t)b0 * plan->rows[mat],
                                   sbits_scratch(plan, ws));

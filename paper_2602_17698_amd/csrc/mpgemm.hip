@@ -21,6 +21,7 @@
 //   block columns (4 waves per row group, 4 blocks per wave, two or three of them in flight in a ring
 //   of register slots); the x slice of those columns sits in LDS.  Block columns beyond the first 16
 //   go to further workgroups (grid.y), whose partial sums a second kernel adds in a fixed order.
+// More than 32 batch rows take the kernel further down.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -370,6 +371,506 @@ void mp_gemm_kernel(MpArgs a)
             }
 }
 
+// ================================================================ more than 32 batch rows
+// A workgroup of 8 waves takes RG = 4 or 2 row groups of 32 channels and up to 64 batch rows (NB tiles of 16; more rows
+// are the grid's third dimension); the JL = 8 / RG waves of a row group walk the block columns together, JL columns a
+// step.  Codes are unpacked once for all NB tiles.  x goes straight into LDS, one or two steps ahead of its use (two or
+// three stages, what fits): a wave reads whole rows of a block column (256 or 128 bytes each), and a row's 16-byte
+// chunks land at positions exclusive-ored with the row, so that the operand reads (16 rows, the same chunk) are free of
+// bank conflicts.  Workgroups start at different block columns: rows of x lie a power of two apart, and all of them at
+// the same column would queue at one L2 channel.  sum_j x of a block column is the same for every channel: the waves of
+// a column share the batch tiles (a product with ones) and exchange the sums through LDS.
+// Codes and scales are requested two steps ahead, block offsets four: loads come back in order, and whoever waits for
+// one request waits for every older one, so with everything one step ahead a step is as long as a load from memory
+// (47 us for 14336 x 4096 at 100 rows).  The operand reads are written out with their wait: the compiler would wait for
+// the requests under way before any read of LDS.
+// What bounds it: vector issue (260 instructions a step and wave, 36 matrix instructions) and the barrier of each step.
+// Against launches of the kernel above, 32 rows each: 14336 x 4096 at 100 rows, bitwidths 1 .. 8, 75 -> 42 us (280 TFLOP/s), at 64 rows
+// 40 -> 26 us, at 33 rows 35 -> 23 us; 8192 x 8192 at 100 rows 78 -> 45 us; 4096 x 4096 in 64-column blocks at 70 rows
+// 47 -> 32 us.  (128 batch rows in one workgroup, 64 channels: 45 us at 100 rows.)
+// Operands are unpacked in stream order, two codes in three instructions whatever the bitwidth c <= 7:
+// field extraction, spread to the two halves, mask and exponent.  c <= 5: B = 1 + q / 2^c (the code at the top of the
+// mantissa: the offset taken out again is no larger than the codes' range), c = 6, 7: B = 128 + q, c = 8: B = q.  1 bit has a
+// block product of its own.
+constexpr int WG_WAVES = 8, WG_THREADS = WG_WAVES * 64;
+constexpr int WG_LDS = 144 * 1024;                            // for the stages of x
+
+// the exponents of a pair (in a vector register) and the codes' places (in a scalar one): held in registers the last two
+// operations are one instruction, which takes no literals
+template <int C> struct PairConst {
+    static constexpr uint32_t one = C <= 5 ? 0x3f803f80u : 0x43004300u;
+    static constexpr uint32_t field = C <= 5 ? ((1u << C) - 1u) << (7 - C) : (1u << C) - 1u;
+};
+template <int C>
+__device__ __forceinline__ uint32_t code_pair(const uint32_t *r, int e, uint32_t one, uint32_t mask)   // codes e, e + 1 (e even) as two bf16
+{
+    if constexpr (C == 8) {
+        const uint32_t w = r[e >> 2];
+        const uint32_t f0 = __float_as_uint((float)((w >> (8 * (e & 3))) & 255u)), f1 = __float_as_uint((float)((w >> (8 * (e & 3) + 8)) & 255u));
+        return __builtin_amdgcn_perm(f1, f0, 0x07060302u);
+    } else {
+        const int bit = e * C, idx = bit >> 5, sh = bit & 31;
+        const uint32_t x = sh + 2 * C <= 32 ? __builtin_amdgcn_ubfe(r[idx], sh, 2 * C)
+                                            : __builtin_amdgcn_alignbit(r[idx + 1], r[idx], sh) & ((1u << (2 * C)) - 1u);
+        // C <= 5: the copies of the two codes do not overlap where the mask looks, nor carry into it
+        const uint32_t y = C <= 5 ? __umul24(x, (1u << (7 - C)) + (1u << (23 - 2 * C))) : x | x << (16 - C);
+        return (y & mask) | one;
+    }
+}
+
+// the block's scale and zero as they apply to sum B x (1 bit: to sum q x) and sum x
+template <int C>
+__device__ __forceinline__ void term_factors(float sc, float ze, float &f, float &z)
+{
+    if constexpr (C == 1) { f = sc; z = ze; return; }
+    f = C <= 5 ? sc * (float)(1 << C) : sc;
+    z = C <= 5 ? fmaf(-(float)(1 << C), sc, ze) : C < 8 ? fmaf(-128.0f, sc, ze) : ze;
+}
+
+// The lane's codes of one block row quarter, `at` bytes into the block, as raw as they come: always the same two loads
+// into the same registers, whatever the bitwidth (a choice by bitwidth ends in copies, and a copy waits for its load).
+// They go through a descriptor of exactly the block's bytes: what lies past its end reads as zero and is not fetched.
+// 128 columns: up to 8 dwords from a multiple of 4 bytes on.  64 columns: up to 16 bytes from a multiple of 2 on, so the
+// 5 aligned dwords around them, which align_quarter() shifts into place.
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+template <int N_COLS>
+struct Quarter { uint32_t r[N_COLS == 128 ? 8 : 5]; };
+template <int N_COLS>
+__device__ __forceinline__ void load_quarter(rsrc_t rs, uint32_t at, Quarter<N_COLS> &o)
+{
+    const int off = (int)(N_COLS == 128 ? at : at & ~3u);
+    const u32x4_t v = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
+    o.r[0] = v.x; o.r[1] = v.y; o.r[2] = v.z; o.r[3] = v.w;
+    if constexpr (N_COLS == 128) {
+        const u32x4_t h = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16, 0, 0));
+        o.r[4] = h.x; o.r[5] = h.y; o.r[6] = h.z; o.r[7] = h.w;
+    } else {
+        o.r[4] = __builtin_amdgcn_raw_buffer_load_b32(rs, off + 16, 0, 0);
+    }
+}
+template <int N_COLS>
+__device__ __forceinline__ void align_quarter(const Quarter<N_COLS> &q, uint32_t at, uint32_t (&r)[N_COLS / 16])
+{
+#pragma unroll
+    for (int i = 0; i < N_COLS / 16; ++i)
+        r[i] = N_COLS == 128 ? q.r[i] : __builtin_amdgcn_alignbit(q.r[i + 1 < 5 ? i + 1 : 4], q.r[i], (at & 2u) * 8u);
+}
+
+template <int NB, int SUMS>
+struct WideState {
+    f32x4v_t d[2][NB], s[SUMS];                               // sum B x of the block; sum x of this wave's batch tiles
+};
+
+// the operands of NB batch tiles, TILE bytes apart, of one step, and those of the tiles (every WG_WAVES / JL-th) whose sums
+// this wave makes
+template <int NB, int TILE, int SUMS>
+__device__ __forceinline__ void read_operands(uint32_t at, uint32_t sum_at, u32x4_t (&x)[NB], u32x4_t (&xs)[SUMS])
+{
+    static_assert((NB == 3 || NB == 4) && (SUMS == 1 || SUMS == 2), "written out");
+    if constexpr (NB == 3 && SUMS == 1)
+        asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:%6\n\tds_read_b128 %2, %4 offset:%7\n\tds_read_b128 %3, %5\n\t"
+                     "s_waitcnt lgkmcnt(0)"
+                     : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(xs[0]) : "v"(at), "v"(sum_at), "n"(TILE), "n"(2 * TILE) : "memory");
+    else if constexpr (NB == 3)
+        asm volatile("ds_read_b128 %0, %5\n\tds_read_b128 %1, %5 offset:%7\n\tds_read_b128 %2, %5 offset:%8\n\tds_read_b128 %3, %6\n\t"
+                     "ds_read_b128 %4, %6 offset:%8\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(xs[0]), "=&v"(xs[SUMS - 1])
+                     : "v"(at), "v"(sum_at), "n"(TILE), "n"(2 * TILE) : "memory");
+    else if constexpr (SUMS == 1)
+        asm volatile("ds_read_b128 %0, %5\n\tds_read_b128 %1, %5 offset:%7\n\tds_read_b128 %2, %5 offset:%8\n\tds_read_b128 %3, %5 offset:%9\n\t"
+                     "ds_read_b128 %4, %6\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[NB - 1]), "=&v"(xs[0])
+                     : "v"(at), "v"(sum_at), "n"(TILE), "n"(2 * TILE), "n"(3 * TILE) : "memory");
+    else
+        asm volatile("ds_read_b128 %0, %6\n\tds_read_b128 %1, %6 offset:%8\n\tds_read_b128 %2, %6 offset:%9\n\tds_read_b128 %3, %6 offset:%10\n\t"
+                     "ds_read_b128 %4, %7\n\tds_read_b128 %5, %7 offset:%9\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[NB - 1]), "=&v"(xs[0]), "=&v"(xs[SUMS - 1])
+                     : "v"(at), "v"(sum_at), "n"(TILE), "n"(2 * TILE), "n"(3 * TILE) : "memory");
+}
+
+// the two halves, as the kernel above takes them for 1 bit, of NB operands TILE bytes apart
+template <int NB, int TILE, int HALF>
+__device__ __forceinline__ void read_halves(uint32_t at, uint32_t bt, u32x2_t (&a)[NB], u32x2_t (&b)[NB])
+{
+    if constexpr (NB == 3)
+        asm volatile("ds_read_b64 %0, %6 offset:%8\n\tds_read_b64 %1, %6 offset:%9\n\tds_read_b64 %2, %6 offset:%10\n\t"
+                     "ds_read_b64 %3, %7 offset:%8\n\tds_read_b64 %4, %7 offset:%9\n\tds_read_b64 %5, %7 offset:%10\n\t"
+                     "s_waitcnt lgkmcnt(0)"
+                     : "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(b[0]), "=&v"(b[1]), "=&v"(b[2])
+                     : "v"(at), "v"(bt), "n"(HALF), "n"(TILE + HALF), "n"(2 * TILE + HALF) : "memory");
+    else
+        asm volatile("ds_read_b64 %0, %8 offset:%10\n\tds_read_b64 %1, %8 offset:%11\n\tds_read_b64 %2, %8 offset:%12\n\tds_read_b64 %3, %8 offset:%13\n\t"
+                     "ds_read_b64 %4, %9 offset:%10\n\tds_read_b64 %5, %9 offset:%11\n\tds_read_b64 %6, %9 offset:%12\n\tds_read_b64 %7, %9 offset:%13\n\t"
+                     "s_waitcnt lgkmcnt(0)"
+                     : "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[NB - 1]), "=&v"(b[0]), "=&v"(b[1]), "=&v"(b[2]), "=&v"(b[NB - 1])
+                     : "v"(at), "v"(bt), "n"(HALF), "n"(TILE + HALF), "n"(2 * TILE + HALF), "n"(3 * TILE + HALF) : "memory");
+}
+
+// A block of 1 bit: the same products as in the kernel above, 128 + q and columns in its order (pair order for 128
+// columns), with sums of x of its own.  d = sum q x then has the rounding of that kernel, which for 1 bit is the largest
+// there is (128 against codes of 0 and 1), and what a row of x gives differs little between batches of 32 and 33 rows:
+// 14336 x 4096, bitwidths 1 .. 8: by 1.3e-4 of the root mean square at most, 4.3e-4 with 1 + q / 2.
+template <int N_COLS, int NB, int SUMS>
+__device__ __forceinline__ void wide_block_1bit(const uint32_t (&cw)[2][N_COLS / 16], const uint32_t (&at)[N_COLS / 32], uint32_t sum_tile,
+                                                WideState<NB, SUMS> &w)
+{
+    constexpr int STEPS = N_COLS / 32, TILE = 16 * N_COLS * 2;
+    const bf16x8_t ones = as_bf16x8(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
+    const f32x4v_t zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
+    f32x4v_t s1[NB];
+    auto products = [&](int st, const bf16x8_t (&x)[NB], const bf16x8_t (&b)[2]) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            w.d[0][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[nb], b[0], st == 0 ? zero4 : w.d[0][nb], 0, 0, 0);
+            w.d[1][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[nb], b[1], st == 0 ? zero4 : w.d[1][nb], 0, 0, 0);
+            s1[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[nb], ones, st == 0 ? zero4 : s1[nb], 0, 0, 0);
+        }
+    };
+    bf16x8_t x[NB], b[2];
+#pragma unroll
+    for (int st = 0; st < STEPS; ++st) {
+        u32x2_t wa[NB], wb[NB];
+        if constexpr (N_COLS == 128) {
+            if (st & 1) read_halves<NB, TILE, 8>(at[st >> 1], at[2 + (st >> 1)], wa, wb);
+            else read_halves<NB, TILE, 0>(at[st >> 1], at[2 + (st >> 1)], wa, wb);
+        } else {
+            read_halves<NB, TILE, 0>(at[st], at[st] + 8u, wa, wb);
+        }
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+            x[nb] = N_COLS == 64 ? as_bf16x8(wa[nb].x, wa[nb].y, wb[nb].x, wb[nb].y)
+                                 : as_bf16x8(__builtin_amdgcn_perm(wb[nb].x, wa[nb].x, 0x05040100u), __builtin_amdgcn_perm(wb[nb].x, wa[nb].x, 0x07060302u),
+                                             __builtin_amdgcn_perm(wb[nb].y, wa[nb].y, 0x05040100u), __builtin_amdgcn_perm(wb[nb].y, wa[nb].y, 0x07060302u));
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            uint32_t o[4];
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                if constexpr (N_COLS == 128) o[p] = ((cw[t][0] >> (4 * st + p)) & 0x00010001u) | 0x43004300u;
+                else o[p] = ((cw[t][0] >> (8 * st + 2 * p)) & 1u) | ((cw[t][0] >> (8 * st + 2 * p + 1)) & 1u) << 16 | 0x43004300u;
+            }
+            b[t] = as_bf16x8(o[0], o[1], o[2], o[3]);
+        }
+        products(st, x, b);
+    }
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            w.d[0][nb][r] = fmaf(-128.0f, s1[nb][r], w.d[0][nb][r]);
+            w.d[1][nb][r] = fmaf(-128.0f, s1[nb][r], w.d[1][nb][r]);
+        }
+#pragma unroll
+    for (int q = 0; q < SUMS; ++q) {                          // (tile 3 of three: dropped by the caller)
+        w.s[q] = s1[(4 / SUMS) * q];
+#pragma unroll
+        for (int k = 1; k < 4 / SUMS; ++k)
+            if ((4 / SUMS) * q + k < NB) w.s[q] = sum_tile == (uint32_t)(k * TILE) ? s1[(4 / SUMS) * q + k] : w.s[q];
+    }
+}
+
+// all steps (32 columns each) of a block; at[st]: the LDS address of the lane's operand of step st, sum_tile: how far from
+// there that of the wave's first tile for the sums of x is.  The first step starts the sums.
+template <int C, int N_COLS, int NB, int SUMS>
+__device__ __forceinline__ void wide_block(const uint32_t (&cw)[2][N_COLS / 16], const uint32_t (&at)[N_COLS / 32], uint32_t sum_tile,
+                                           WideState<NB, SUMS> &w)
+{
+    if constexpr (C == 1) { wide_block_1bit<N_COLS, NB, SUMS>(cw, at, sum_tile, w); return; }
+    const bf16x8_t ones = as_bf16x8(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
+    const f32x4v_t zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
+    uint32_t one = PairConst<C>::one, mask = PairConst<C>::field | PairConst<C>::field << 16;
+    asm volatile("" : "+v"(one), "+s"(mask));
+#pragma unroll
+    for (int st = 0; st < N_COLS / 32; ++st) {
+        u32x4_t x[NB], xs[SUMS];
+        read_operands<NB, 16 * N_COLS * 2, SUMS>(at[st], at[st] + sum_tile, x, xs);
+        bf16x8_t b[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            uint32_t o[4];
+#pragma unroll
+            for (int p = 0; p < 4; ++p) o[p] = code_pair<C>(cw[t], 8 * st + 2 * p, one, mask);
+            b[t] = as_bf16x8(o[0], o[1], o[2], o[3]);
+        }
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const bf16x8_t xa = __builtin_bit_cast(bf16x8_t, x[nb]);
+            w.d[0][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, b[0], st == 0 ? zero4 : w.d[0][nb], 0, 0, 0);
+            w.d[1][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, b[1], st == 0 ? zero4 : w.d[1][nb], 0, 0, 0);
+        }
+#pragma unroll
+        for (int q = 0; q < SUMS; ++q)
+            w.s[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, xs[q]), ones, st == 0 ? zero4 : w.s[q], 0, 0, 0);
+    }
+}
+
+// the sums of x of this lane's rows, NB batch tiles
+template <int NB>
+__device__ __forceinline__ void read_sums(uint32_t at, f32x4v_t (&s)[NB])
+{
+    if constexpr (NB == 3)
+        asm volatile("ds_read_b128 %0, %3\n\tds_read_b128 %1, %3 offset:64\n\tds_read_b128 %2, %3 offset:128\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(s[0]), "=&v"(s[1]), "=&v"(s[2]) : "v"(at) : "memory");
+    else
+        asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:64\n\tds_read_b128 %2, %4 offset:128\n\tds_read_b128 %3, %4 offset:192\n\t"
+                     "s_waitcnt lgkmcnt(0)" : "=&v"(s[0]), "=&v"(s[1]), "=&v"(s[2]), "=&v"(s[3]) : "v"(at) : "memory");
+}
+
+#define WG_SWITCH(c, F)                                                                                           \
+    switch (c) {                                                                                                  \
+    case 0: break;                                                                                                \
+    case 1: F(1); break;                                                                                          \
+    case 2: F(2); break;                                                                                          \
+    case 3: F(3); break;                                                                                          \
+    case 4: F(4); break;                                                                                          \
+    case 5: F(5); break;                                                                                          \
+    case 6: F(6); break;                                                                                          \
+    case 7: F(7); break;                                                                                          \
+    default: F(8); break;                                                                                         \
+    }
+
+template <int N_COLS, int NB, int RG>
+__global__ __launch_bounds__(WG_THREADS, 2)
+void mp_gemm_wide_kernel(MpArgs a, int cols_per_split)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    constexpr int KL = N_COLS / 4;                            // codes per lane and block row
+    constexpr int STEPS = N_COLS / 32;                        // of a block: 32 columns each
+    constexpr int CHUNKS = N_COLS / 8, RPL = 64 / CHUNKS;     // 16-byte chunks of a row; rows a wave reads with one load
+    constexpr int ROWS = NB * 16;                             // batch rows
+    constexpr int JL = WG_WAVES / RG, SUMS = 4 / RG;          // block columns of a step; tiles whose sum of x a wave makes
+    constexpr int STAGE = JL * ROWS * N_COLS * 2;          // [block column][batch row][chunk ^ row]
+    constexpr int LPW = STAGE / 1024 / WG_WAVES;              // loads of a wave and stage
+    constexpr int LPC = ROWS / RPL;                           // loads of one block column
+    constexpr int STAGES = 3 * STAGE <= WG_LDS ? 3 : 2, AHEAD = STAGES - 1;
+    static_assert(LPW * 1024 * WG_WAVES == STAGE && LPC % LPW == 0, "whole loads per wave, of one block column");
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rg = wave & (RG - 1), jl = wave / RG;
+    const int li = lane & 15, g = lane >> 4;
+    const int batch0 = (int)blockIdx.z * 64, batch = min(a.batch - batch0, 64);   // this workgroup's batch rows
+    const int row0 = (int)blockIdx.x * (RG * 32) + rg * 32;               // this wave's 32 channels
+    const bool rows_ok = row0 < a.R;                          // (R is a multiple of 32)
+    const int I = rows_ok ? row0 / a.m : 0, rin = rows_ok ? row0 - I * a.m : 0;
+    const int J0 = (int)blockIdx.y * cols_per_split, J1 = min(J0 + cols_per_split, a.nbc);
+    const int nblk = (J1 - J0 + JL - 1) / JL;           // steps of JL block columns
+    const int turn0 = (int)(blockIdx.x >> 3) % nblk;          // the one this workgroup starts with (workgroups go round the 8 XCDs, each with an L2)
+    float *const xsum = reinterpret_cast<float *>(smem + STAGES * STAGE);          // [parity][jl][ROWS]
+
+    // What this wave brings in of a stage: loads wave * LPW + i, each RPL rows of one block column, through a descriptor
+    // of the batch's rows (rows beyond it read as zero; their outputs are not stored).
+    const int lrow = lane / CHUNKS, lpos = lane % CHUNKS;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
+    const uint32_t ldx2 = 2u * (uint32_t)a.ld_x;
+    const rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.x) + (int64_t)batch0 * a.ld_x, 0,
+                                                         (int)((uint32_t)(batch - 1) * ldx2 + 2u * (uint32_t)a.C), 0x00027000);
+    const int fj = wave * LPW / LPC, frow = wave * LPW % LPC * RPL;
+    const uint32_t vrow = (uint32_t)(frow + lrow) * ldx2, vchunk = (uint32_t)((lpos ^ lrow) & (CHUNKS - 1));
+    auto fetch = [&](int t, int stage) {
+        const int J = min(J0 + t * JL + fj, a.nbc - 1);    // (past the split: in bounds, not used)
+#pragma unroll
+        for (int i = 0; i < LPW; ++i) {                       // row frow + RPL i + lrow; frow and RPL i are multiples of RPL > lrow
+            const uint32_t at = vrow + (uint32_t)(i * RPL) * ldx2 + (vchunk ^ (uint32_t)((frow + i * RPL) & (CHUNKS - 1))) * 16u;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(xrs, (__attribute__((address_space(3))) void *)(lds0 + (uint32_t)(stage * STAGE + (wave * LPW + i) * 1024)),
+                                                     16, (int)at, J * N_COLS * 2, 0, 0);
+        }
+    };
+    // Everybody's x of the step is in LDS.  A step requests the x of the step AHEAD of it, then codes, scales and offsets of
+    // later ones (LATER loads, all of them used): what this wave has requested behind this step's x may still be under way.
+    constexpr int LATER = 9;
+    auto sync_x = [&]() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(AHEAD * LATER + (AHEAD - 1) * LPW) : "memory"); };
+    auto sync_all = [&]() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+
+    // the wave's blocks: bitwidth (0: no such block column, or a pruned block), codes, scales
+    const uint32_t lane_units = (uint32_t)((rin + li) * (N_COLS / 8) + g * (KL / 8));   // x c = the lane's byte offset in the block
+    const uint32_t block_bytes_per_bit = (uint32_t)a.m * (N_COLS / 8);
+    // The bitwidths of all steps, a step per lane (at most 256 steps: 512 block columns): a level is a byte, and a byte
+    // loaded step by step is masked, hence waited for, as soon as the compiler likes.
+    constexpr int LVL = N_COLS == 128 ? 2 : 4;
+    int lvl[LVL];
+#pragma unroll
+    for (int k = 0; k < LVL; ++k)
+        lvl[k] = a.level[a.block_base + (int64_t)I * a.nbc + min(J0 + (64 * k + lane) * JL + jl, a.nbc - 1)];
+    struct Meta { int64_t off, blk; };
+    auto meta = [&](int t) {
+        Meta o;
+        o.blk = a.block_base + (int64_t)I * a.nbc + min(J0 + t * JL + jl, a.nbc - 1);
+        o.off = a.byte_off[o.blk];
+        return o;
+    };
+    auto bits_of = [&](int t) {
+        int lv = __builtin_amdgcn_readlane(lvl[0], t & 63);
+#pragma unroll
+        for (int k = 1; k < LVL; ++k) lv = t >> 6 == k ? __builtin_amdgcn_readlane(lvl[k], t & 63) : lv;
+        int b = a.bits[0];
+#pragma unroll
+        for (int k = 1; k < MAX_CAND; ++k) b = lv == k ? a.bits[k] : b;
+        return rows_ok && J0 + t * JL + jl < J1 ? b : 0;
+    };
+    struct Block { Quarter<N_COLS> q[2]; float sc[2], ze[2]; };
+    // metadata that has arrived, as scalars
+    auto scalars = [&](const Meta &mt) {
+        Meta o;
+        o.off = (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)mt.off >> 32)) << 32 |
+                          (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)mt.off));
+        o.blk = mt.blk;
+        return o;
+    };
+    auto request = [&](Block &o, int c, const Meta &mt) {
+        const uint64_t off = (uint64_t)mt.off;
+        const rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(a.codes) + off, 0,
+                                                            (int)(block_bytes_per_bit * (uint32_t)c), 0x00027000);
+#pragma unroll
+        for (int tl = 0; tl < 2; ++tl) {
+            o.sc[tl] = a.scale[mt.blk * a.m + rin + 16 * tl + li];
+            o.ze[tl] = a.zero[mt.blk * a.m + rin + 16 * tl + li];
+            load_quarter<N_COLS>(rs, (lane_units + (uint32_t)(tl * 16 * (N_COLS / 8))) * (uint32_t)c, o.q[tl]);
+        }
+    };
+
+    f32x4v_t acc[2][NB];
+    WideState<NB, SUMS> w;
+    const f32x4v_t zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[0][nb] = acc[1][nb] = w.d[0][nb] = w.d[1][nb] = zero4;
+
+    // a finished block: its sums with scale and zero applied (xsum of its parity is complete)
+    auto apply = [&](const float (&sc)[2], const float (&ze)[2], int c, int u) {
+        if (c == 0) return;
+        float f[2], z[2];
+#define WG_TERM(C) term_factors<C>(sc[0], ze[0], f[0], z[0]); term_factors<C>(sc[1], ze[1], f[1], z[1])
+        f[0] = f[1] = z[0] = z[1] = 0.0f;
+        WG_SWITCH(c, WG_TERM)
+#undef WG_TERM
+        f32x4v_t xs[NB];
+        read_sums<NB>(lds0 + (uint32_t)(STAGES * STAGE + ((u & 1) * JL + jl) * (ROWS * 4) + 16 * g), xs);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int tl = 0; tl < 2; ++tl)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[tl][nb][r] = fmaf(f[tl], w.d[tl][nb][r], fmaf(z[tl], xs[nb][r], acc[tl][nb][r]));
+    };
+
+    // the u-th step's block columns (past the last: the last once more, requested so that every step makes the same number
+    // of loads, and not used)
+    auto nth = [&](int u) { const int t = turn0 + min(u, nblk - 1); return t < nblk ? t : t - nblk; };
+    // slots of even and odd steps: the codes of that step, and the metadata of the one after next
+    Meta me = meta(nth(0)), mo = meta(nth(1));
+    Block ce, co;
+    int bits_e, bits_o, c_cur = 0;
+    {
+        const Meta m0 = scalars(me), m1 = scalars(mo);
+        bits_e = bits_of(nth(0));
+        bits_o = nblk > 1 ? bits_of(nth(1)) : 0;
+        request(ce, bits_e, m0);
+        request(co, bits_o, m1);
+    }
+    me = meta(nth(2));
+    mo = meta(nth(3));
+    for (int u = 0; u < AHEAD; ++u) fetch(nth(u), u);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    auto arrived = [](Block &k, Meta &mt) {                   // (for the compiler, which would wait in the loop for what the loop never leaves open)
+#pragma unroll
+        for (int tl = 0; tl < 2; ++tl) {
+#pragma unroll
+            for (uint32_t &r : k.q[tl].r) asm volatile("" : "+v"(r));
+            asm volatile("" : "+v"(k.sc[tl]), "+v"(k.ze[tl]));
+        }
+        asm volatile("" : "+v"(mt.off));
+    };
+    arrived(ce, me);
+    arrived(co, mo);
+    Quarter<N_COLS> cq[2];
+    float sc[2] = {0.0f, 0.0f}, ze[2] = {0.0f, 0.0f};
+    // Step u takes over the codes that slot k received and requests those of step u + 2 into it.  The copies are written
+    // out: the compiler cannot merge them with the slot, whose new values would then be moved, and waited for, at the
+    // loop's end.
+    auto turn_over = [&](int u, int stage, Block &k, Meta &mt, int &bits_k) {
+#pragma unroll
+        for (int tl = 0; tl < 2; ++tl) {
+#pragma unroll
+            for (size_t i = 0; i < sizeof cq[tl].r / 4; ++i) asm volatile("v_mov_b32 %0, %1" : "=v"(cq[tl].r[i]) : "v"(k.q[tl].r[i]));
+            asm volatile("v_mov_b32 %0, %2\n\tv_mov_b32 %1, %3" : "=&v"(sc[tl]), "=&v"(ze[tl]) : "v"(k.sc[tl]), "v"(k.ze[tl]));
+        }
+        c_cur = bits_k;
+        const Meta m2 = scalars(mt);
+        bits_k = u + 2 < nblk ? bits_of(nth(u + 2)) : 0;
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(nth(u + AHEAD), stage);
+        asm volatile("" ::: "memory");                        // (x first, then the LATER ones)
+        __builtin_amdgcn_sched_barrier(0);
+        request(k, bits_k, m2);
+        mt = meta(nth(u + 4));
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    int stage = 0;                                            // of step u
+    auto step = [&](int u, Block &slot, Meta &mt, int &bits_slot) {
+        sync_x();                                             // (and the stage before has been read)
+        const float sc_old[2] = {sc[0], sc[1]}, ze_old[2] = {ze[0], ze[1]};
+        const int c_old = c_cur;
+        turn_over(u, stage == 0 ? STAGES - 1 : stage - 1, slot, mt, bits_slot);
+        if (u > 0) apply(sc_old, ze_old, c_old, u - 1);       // the step before, whose sums of x the barrier completed
+        uint32_t cw[2][N_COLS / 16], at[STEPS];
+#pragma unroll
+        for (int tl = 0; tl < 2; ++tl) align_quarter<N_COLS>(cq[tl], (lane_units + (uint32_t)(tl * 16 * (N_COLS / 8))) * (uint32_t)c_cur, cw[tl]);
+        const uint32_t xl = lds0 + (uint32_t)(stage * STAGE + (jl * ROWS + li) * (N_COLS * 2));
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) at[st] = xl + (uint32_t)(((g * STEPS + st) ^ li) & (CHUNKS - 1)) * 16u;
+        // (tile 3 of three is read all the same: it is inside the stages, or among the sums behind them, and its sum dropped)
+        const uint32_t sum_tile = (uint32_t)(rg * 16 * N_COLS * 2);
+#define WG_BLOCK(C) wide_block<C, N_COLS, NB, SUMS>(cw, at, sum_tile, w)
+        if (c_cur != 0) { WG_SWITCH(c_cur, WG_BLOCK) }
+        else {                                                // (the other row groups may still need this column's sum of x)
+            const uint32_t none[2][N_COLS / 16] = {};
+            wide_block<8, N_COLS, NB, SUMS>(none, at, sum_tile, w);
+        }
+#undef WG_BLOCK
+        // (column 0 of the product with ones: every channel's column is the same)
+        if (li == 0) {
+#pragma unroll
+            for (int q = 0; q < SUMS; ++q)
+                if (rg + RG * q < NB) *reinterpret_cast<f32x4v_t *>(xsum + ((u & 1) * JL + jl) * ROWS + 16 * (rg + RG * q) + 4 * g) = w.s[q];
+        }
+        stage = stage == STAGES - 1 ? 0 : stage + 1;
+    };
+    // Two steps at a time, so that each slot stays in its registers: a slot chosen at run time ends in copies, which wait.
+    // (With an odd number of steps the last one has no codes and adds nothing.)
+    const int nstep = (nblk + 1) & ~1;
+    for (int u = 0; u < nstep; u += 2) {
+        step(u, ce, me, bits_e);
+        step(u + 1, co, mo, bits_o);
+    }
+    sync_all();
+    apply(sc, ze, c_cur, nstep - 1);
+    sync_all();                                               // x has been read: LDS is free
+
+    // the JL waves of a row group add up, in a fixed order; wave jl finishes the batch tiles jl, jl + JL, ..
+    float *red = reinterpret_cast<float *>(smem);             // [wave][tile][nb][lane][4]
+#pragma unroll
+    for (int tl = 0; tl < 2; ++tl)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+            *reinterpret_cast<f32x4v_t *>(red + (((wave * 2 + tl) * NB + nb) * 64 + lane) * 4) = acc[tl][nb];
+    __syncthreads();
+    if (!rows_ok) return;
+    float *dst = a.out + ((int64_t)blockIdx.y * a.batch + batch0) * a.R;
+    for (int nb = jl; nb < NB; nb += JL) {
+#pragma unroll
+        for (int tl = 0; tl < 2; ++tl) {
+            f32x4v_t v = *reinterpret_cast<const f32x4v_t *>(red + (((rg * 2 + tl) * NB + nb) * 64 + lane) * 4);
+#pragma unroll
+            for (int j = 1; j < JL; ++j) v = v + *reinterpret_cast<const f32x4v_t *>(red + ((((j * RG + rg) * 2 + tl) * NB + nb) * 64 + lane) * 4);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int b = 16 * nb + 4 * g + r;
+                if (b < batch) dst[(int64_t)b * a.R + row0 + 16 * tl + li] = v[r];
+            }
+        }
+    }
+}
+
 // y = sum over the column splits of the partials, split 0 first
 __global__ __launch_bounds__(256)
 void mp_gemm_finish_kernel(const float *__restrict__ part, int64_t n, int n_split, float *__restrict__ y)
@@ -419,6 +920,32 @@ static int launch_mp(sbits_ctx *ctx, const MpArgs &a, dim3 grid)
     return SBITS_OK;
 }
 
+template <int N_COLS, int NB, int RG>
+static int launch_wide(sbits_ctx *ctx, const MpArgs &a, dim3 grid, int cols_per_split)
+{
+    constexpr int stage = (WG_WAVES / RG) * NB * 16 * N_COLS * 2;
+    constexpr size_t stages = (size_t)(3 * stage <= WG_LDS ? 3 : 2) * stage + (size_t)2 * (WG_WAVES / RG) * NB * 16 * 4;
+    constexpr size_t past = (size_t)16 * N_COLS * 2;          // (a tile more than three may be read behind the last stage)
+    constexpr size_t red = (size_t)WG_WAVES * 2 * NB * 64 * 16;
+    constexpr size_t lds = stages + past > red ? stages + past : red;
+    auto *fn = &mp_gemm_wide_kernel<N_COLS, NB, RG>;
+    SBITS_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL(fn, grid, dim3(WG_THREADS), lds, ctx->stream, a, cols_per_split);
+    SBITS_HIP(ctx, hipGetLastError());
+    return SBITS_OK;
+}
+
+template <int RG>
+static int launch_wide_rg(sbits_ctx *ctx, int n, const MpArgs &a, dim3 grid, int cols_per_split)
+{
+    if (n == 64) return launch_wide<64, 4, RG>(ctx, a, grid, cols_per_split);
+    return a.batch <= 48 ? launch_wide<128, 3, RG>(ctx, a, grid, cols_per_split) : launch_wide<128, 4, RG>(ctx, a, grid, cols_per_split);
+}
+
+// Rows of x a launch takes: 128 (two batch groups) while a group's byte offsets fit the 32 bits of a descriptor, else the
+// 32 of the first kernel, whose addresses have 64.
+int sbits_mp_gemm_rows(int64_t ld_x) { return ld_x <= 1 << 20 ? 128 : 32; }
+
 int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t ld_x, int batch,
                          const uint8_t *level, const int64_t *byte_off, const uint8_t *codes, const float *scale,
                          const float *zero, float *y, void *scratch)
@@ -430,13 +957,30 @@ int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t 
     a.block_base = plan->base[mat]; a.ld_x = ld_x;
     a.R = (int)plan->rows[mat]; a.C = (int)plan->cols[mat]; a.m = plan->m; a.nbc = a.C / plan->n;
     a.batch = batch;
-    a.n_split = sbits_mp_gemm_splits(a.C, plan->n);
+    const bool wide = batch > 32;
+    int per_split = a.nbc, rg = 4;
+    if (wide) {
+        // 128 channels a workgroup where that gives three quarters of the CUs one (x is staged half as often), else 64 and
+        // column splits until every CU has one, as far as the scratch holds the splits' partial sums.  (14336 x 4096 at 64
+        // rows: 38 us with 128 channels on 112 CUs, 26 us with 64 on 224.)
+        const int64_t z = (batch + 63) / 64;
+        if ((a.R + 127) / 128 * z < 192) rg = 2;
+        const int64_t tiles = (a.R + rg * 32 - 1) / (rg * 32) * z, jl = WG_WAVES / rg;
+        const int64_t room = (int64_t)(plan->ws_bytes - plan->head_bytes) / ((int64_t)batch * a.R * 4);
+        int64_t want = 256 / tiles, steps = (a.nbc + jl - 1) / jl;
+        if (want > steps) want = steps;
+        if (want > room) want = room;
+        if (want > 1) per_split = (int)((steps + want - 1) / want * jl);
+    }
+    a.n_split = wide ? (a.nbc + per_split - 1) / per_split : sbits_mp_gemm_splits(a.C, plan->n);
     for (int c = 0; c < sbits::MAX_CAND; ++c) a.bits[c] = c < plan->K ? plan->bits[c] : plan->bits[plan->K - 1];
     a.out = a.n_split > 1 ? static_cast<float *>(scratch) : y;
-    const dim3 grid((unsigned)((a.R + MG_RG * 32 - 1) / (MG_RG * 32)), (unsigned)a.n_split);
+    const int rows = wide ? rg * 32 : MG_RG * 32;
+    const dim3 grid((unsigned)((a.R + rows - 1) / rows), (unsigned)a.n_split, (unsigned)(wide ? (batch + 63) / 64 : 1));
     const int nb = batch <= 16 ? 1 : 2;
     int rc;
-    if (plan->n == 128) rc = nb == 1 ? launch_mp<128, 1>(ctx, a, grid) : launch_mp<128, 2>(ctx, a, grid);
+    if (wide) rc = rg == 4 ? launch_wide_rg<4>(ctx, plan->n, a, grid, per_split) : launch_wide_rg<2>(ctx, plan->n, a, grid, per_split);
+    else if (plan->n == 128) rc = nb == 1 ? launch_mp<128, 1>(ctx, a, grid) : launch_mp<128, 2>(ctx, a, grid);
     else rc = nb == 1 ? launch_mp<64, 1>(ctx, a, grid) : launch_mp<64, 2>(ctx, a, grid);
     if (rc) return rc;
     if (a.n_split > 1) {

@@ -1,0 +1,70 @@
+"""The product for more than 32 batch rows at the edges of its work split: batch tiles and groups, row groups past the
+matrix's end, odd numbers of block columns, column splits, both workgroup shapes, every bitwidth with and without pruned
+blocks.  Tolerance: the kernel sums terms of size |B| scale |x| in fp32, where B scale is at most 2 spans of the block row
+(span = 2^c scale; 129 scale for 1 bit and 191 scale for 6 bits, whose offset is 128) and zero |x|.  The bound is 2^-22 of
+the sum of all of them for the largest error and 2^-24 for the root mean square."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2602_17698_amd import binding as sb
+from paper_2602_17698_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+ALL = [1, 2, 3, 4, 5, 6, 7, 8]
+
+
+@pytest.mark.parametrize("R,C,m,n,bits,batch,pad", [
+    (32, 128, 32, 128, [4], 33, 0),                       # one block; three of four row groups past the end
+    (160, 128 * 5, 32, 128, ALL, 48, 8),                  # odd block columns, three tiles, ragged row groups, wide pitch
+    (192, 128 * 8, 64, 128, [0] + ALL, 49, 0),            # pruned blocks, four tiles
+    (96, 64 * 9, 32, 64, ALL, 64, 16),
+    (128, 64 * 16, 64, 64, [0, 3, 5, 7, 8], 65, 0),       # a second batch group of one row
+    (256, 128 * 6, 128, 128, [2, 6], 113, 0),
+    (8192, 256, 128, 128, [1, 4, 8], 70, 0),              # 64 workgroups of 128 channels a batch group: the 64-channel shape
+    (12288, 256, 128, 128, [3, 8], 128, 0),               # 192 of them: the 128-channel shape
+    (12288, 192, 64, 64, ALL, 100, 0),
+    (64, 128 * 3, 32, 128, [2, 4, 8], 200, 0),            # a second launch
+    (32, 128, 32, 128, ALL[2:3], 40, 1 << 20),            # a pitch past 32-bit offsets of a batch group: 32 rows a launch
+    (64, 128 * 4, 32, 128, [1], 80, 0),                   # 1 bit: products of its own
+    (64, 64 * 5, 32, 64, [1], 50, 0),
+])
+def test_wide_product(orc, R, C, m, n, bits, batch, pad):
+    print("[case] wide product", R, C, m, n, bits, batch, flush=True)
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(R + C + batch)
+    ctx = sb.Context(0, torch.cuda.current_stream().cuda_stream)
+    plan = sb.Plan(ctx, [(m, n), (R, C)], m, n, bits)
+    N, base = plan.num_blocks(), 1
+    ws = torch.empty(plan.workspace_bytes(), dtype=torch.uint8, device=dev)
+    level = rng.integers(0, len(bits), N).astype(np.uint8)
+    off = orc.offsets(level, m, n, bits)
+    codes = np.zeros(max(int(off[-1]), 16), np.uint8)
+    scale, zero = np.zeros(N * m, np.float32), np.zeros(N * m, np.float32)
+    W = orc.f32_to_bf16(0.02 * rng.standard_t(4, size=(R, C)))
+    orc.pack(W, m, n, bits, level, off, base, codes, scale, zero)
+    xb = orc.f32_to_bf16(rng.standard_normal((batch, C)))
+    x = torch.full((batch, C + pad), float("nan"), dtype=torch.bfloat16, device=dev)   # what lies past the columns is not read
+    x[:, :C] = torch.from_numpy(xb.view(np.int16)).view(torch.bfloat16)
+    args = [torch.from_numpy(t).to(dev) for t in (level, off, codes, scale, zero)]
+    y = torch.full((batch + 1, R), -7.0, device=dev)
+    plan.mp_gemm(1, x[:, :C], *args, y, ws)
+    again = torch.empty_like(y[:batch])
+    plan.mp_gemm(1, x[:, :C], *args, again, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(y[:batch], again) and torch.all(y[batch] == -7.0)
+    What = orc.dequant(codes, scale, zero, level, off, base, R, C, m, n, bits).astype(np.float64)
+    xf = orc.bf16_to_f32(xb).astype(np.float64)
+    ref = xf @ What.T
+    nbc = C // n
+    most = np.array([{1: 129.0, 6: 191.0}.get(b, 2.0 ** (b + 1)) for b in bits])      # of |B|, in codes
+    mag = (np.abs(zero.reshape(N, m)) + scale.reshape(N, m) * most[level][:, None])[base:]
+    mag = mag.reshape(R // m, nbc, m).transpose(0, 2, 1).reshape(R, nbc)
+    bound = np.abs(xf).reshape(batch, nbc, n).sum(2) @ mag.T
+    err = np.abs(y[:batch].cpu().numpy().astype(np.float64) - ref)
+    assert np.all(err <= bound * 2.0 ** -22 + 1e-30), float((err / (bound + 1e-300)).max())
+    assert np.sqrt((err ** 2).mean()) <= 2.0 ** -24 * np.sqrt((bound ** 2).mean())
+    plan.close()
+    ctx.close()
