@@ -14,9 +14,9 @@
 // whole band.  The partial trees (per row and 512-column segment; per column
 // and 256-row band) go to the workspace and a small kernel finishes them.
 //
-// Argsort.  Descending by score, ties to the lower index: a stable LSD radix
-// sort (4 passes of 8 bits) of the inverted ordered-float keys, one workgroup
-// of 16 waves per channel array, all arrays of the plan side by side.
+// Argsort.  Descending by score, ties to the lower index: inverted ordered-float
+// keys with the index behind them, sorted in chunks of 1024; what an array has
+// of chunks is merged by rank.  All arrays of the plan side by side.
 //
 // Gather.  out[i][j] = in[rp[i]][cp[j]]: the source row is staged in LDS with
 // coalesced 128-bit loads and read out permuted, so global traffic stays
@@ -255,8 +255,13 @@ __global__ void score_finish_kernel(const MatDesc *__restrict__ descs, MatDesc o
 }
 
 // ================================================================ argsort
-constexpr int RS_THREADS = 1024;
-constexpr int RS_WAVES = RS_THREADS / 64;
+// Bound by the latency of a chain of dependent steps, not by memory, so the chain is cut short: chunks of 1024 channels are
+// sorted side by side, a lane per channel (bitonic network: 45 steps inside the wave, 10 through LDS), and the rank of a
+// channel in its array is its place in its own chunk plus, for every other chunk, the number of keys there that go before
+// it (binary search in LDS, all the chunks of the array).  A layer with arrays of up to 28672 channels: 42 us, where one
+// workgroup an array with four radix passes took 242; up to 14336: 22 (104); 512, the chunk sort alone: 6.7 (10.7).
+constexpr int CS_LEN = 1024, CS_THREADS = CS_LEN;             // channels of a chunk, one a thread
+constexpr int RK_THREADS = 512;                               // of the ranking: half a chunk, so that more CUs share an array
 
 __device__ __forceinline__ unsigned int sort_key(float f)
 {
@@ -266,114 +271,136 @@ __device__ __forceinline__ unsigned int sort_key(float f)
 }
 
 // Array a of the launch: a < n_mats -> the rows of matrix a, else the columns of matrix a - n_mats.
-// k0/k1/i0/i1 are ping-pong buffers with the same indexing as the score array.
 // arr_mode (may be null = all SORT): what to do with array a; arr_segment (with arr_mode): 0 or the
 // length of the pieces that are sorted one by one (a permutation that stays inside attention heads).
 enum { ARR_SORT = 0, ARR_IDENTITY = 1, ARR_SKIP = 2 };
-__global__ __launch_bounds__(RS_THREADS)
-void radix_argsort_kernel(const MatDesc *__restrict__ descs, MatDesc one, int n_mats, int64_t sum_rows,
-                          const float *__restrict__ scores, unsigned int *__restrict__ k0,
-                          unsigned int *__restrict__ k1, unsigned int *__restrict__ i0,
-                          unsigned int *__restrict__ i1, int32_t *__restrict__ row_perm,
-                          int32_t *__restrict__ col_perm, const int *__restrict__ arr_mode,
-                          const int *__restrict__ arr_segment)
+
+struct SortArrays {
+    const MatDesc *descs;
+    MatDesc one;
+    int n_mats, per;                                          // workgroups per array: they take its chunks in turn
+    int64_t sum_rows;
+    const int *mode, *segment;
+    int32_t *row_perm, *col_perm;
+};
+struct SortArray {
+    int n, piece, mode;                                       // channels, channels per piece
+    int64_t off;                                              // of its scores, keys and indices
+    int32_t *perm;
+};
+__device__ __forceinline__ SortArray sort_array(const SortArrays &s, int a)
 {
-    __shared__ unsigned int hist[RS_WAVES][256];     // per-wave digit counts, then running offsets
-    __shared__ unsigned int total[256];
-    const int a = blockIdx.x;
-    const bool is_row = a < n_mats;
-    const MatDesc &d = descs ? descs[is_row ? a : a - n_mats] : one;
-    const int n_all = (int)(is_row ? d.rows : d.cols);
-    const int64_t off_all = is_row ? d.row_off : sum_rows + d.col_off;
-    int32_t *__restrict__ perm_all = is_row ? row_perm + d.row_off : col_perm + d.col_off;
-    const int mode = arr_mode ? arr_mode[a] : ARR_SORT;
-    if (mode == ARR_SKIP) return;
-    if (mode == ARR_IDENTITY) {
-        for (int i = threadIdx.x; i < n_all; i += RS_THREADS) perm_all[i] = i;
+    const bool is_row = a < s.n_mats;
+    const MatDesc &d = s.descs ? s.descs[is_row ? a : a - s.n_mats] : s.one;
+    SortArray o;
+    o.n = (int)(is_row ? d.rows : d.cols);
+    o.off = is_row ? d.row_off : s.sum_rows + d.col_off;
+    o.perm = is_row ? s.row_perm + d.row_off : s.col_perm + d.col_off;
+    o.mode = s.mode ? s.mode[a] : ARR_SORT;
+    o.piece = (s.mode && s.segment[a] > 0) ? s.segment[a] : o.n;
+    return o;
+}
+
+// x of lane ^ J
+template <int J>
+__device__ __forceinline__ uint32_t from_lane_xor(uint32_t x)
+{
+    if constexpr (J == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, DPP_XOR1, 0xf, 0xf, true);
+    else if constexpr (J == 2) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, DPP_XOR2, 0xf, 0xf, true);
+    else if constexpr (J == 8) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xf, 0xf, true);   // row_ror:8
+    else if constexpr (J < 32) return (uint32_t)__builtin_amdgcn_ds_swizzle((int)x, J << 10 | 0x1f);
+    else return (uint32_t)__shfl_xor((int)x, J);
+}
+
+// one step of the network: the thread keeps the smaller or the larger of its key and thread (tid ^ J)'s
+template <int K, int J>
+__device__ __forceinline__ void sort_step(uint64_t &x, int tid, uint64_t (*buf)[CS_LEN], int &turn)
+{
+    uint64_t y;
+    if constexpr (J >= 64) {
+        buf[turn][tid] = x;
+        __syncthreads();                                      // (the other buffer is written next: its readers are past this)
+        y = buf[turn][tid ^ J];
+        turn ^= 1;
+    } else {
+        y = (uint64_t)from_lane_xor<J>((uint32_t)(x >> 32)) << 32 | from_lane_xor<J>((uint32_t)x);
+    }
+    const bool keep_min = ((tid & K) == 0) == ((tid & J) == 0);
+    x = (x < y) == keep_min ? x : y;                          // (keys are distinct: they end in the index)
+    if constexpr (J > 1) sort_step<K, J / 2>(x, tid, buf, turn);
+}
+template <int K>
+__device__ __forceinline__ void sort_merge(uint64_t &x, int tid, uint64_t (*buf)[CS_LEN], int &turn)
+{
+    if constexpr (K > 2) sort_merge<K / 2>(x, tid, buf, turn);
+    sort_step<K, K / 2>(x, tid, buf, turn);
+}
+
+// Array a of the launch: a < n_mats -> the rows of matrix a, else the columns of matrix a - n_mats.  Chunks of a piece in
+// ascending (key, index) order to keys / idx (indexed as the scores; idx counts from the piece's start); a piece of one
+// chunk is finished here.
+__global__ __launch_bounds__(CS_THREADS)
+void chunk_sort_kernel(SortArrays s, const float *__restrict__ scores, uint32_t *__restrict__ keys, uint32_t *__restrict__ idx)
+{
+    __shared__ uint64_t buf[2][CS_LEN];
+    const int tid = threadIdx.x;
+    const SortArray ar = sort_array(s, (int)blockIdx.x / s.per);
+    const int first = (int)blockIdx.x % s.per;
+    if (ar.mode == ARR_SKIP) return;
+    if (ar.mode == ARR_IDENTITY) {
+        for (int i = first * CS_THREADS + tid; i < ar.n; i += s.per * CS_THREADS) ar.perm[i] = i;
         return;
     }
-    const int piece = (arr_mode && arr_segment[a] > 0) ? arr_segment[a] : n_all;
-    for (int p0 = 0; p0 < n_all; p0 += piece) {      // (uniform over the workgroup)
-    const int n = min(piece, n_all - p0);
-    const int64_t off = off_all + p0;
-    int32_t *__restrict__ perm = perm_all + p0;
-    const float *__restrict__ sc = scores + off;
-    unsigned int *kb[2] = {k0 + off, k1 + off};
-    unsigned int *ib[2] = {i0 + off, i1 + off};
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // each wave owns a contiguous segment (a multiple of 64 long) of the current order
-    const int seg = ((n + RS_WAVES - 1) / RS_WAVES + 63) / 64 * 64;
-    const int beg = wave * seg, end = min(beg + seg, n);
-
-    for (int i = tid; i < n; i += RS_THREADS) {
-        kb[0][i] = sort_key(sc[i]);
-        ib[0][i] = (unsigned int)i;
+    const int cpp = (ar.piece + CS_LEN - 1) / CS_LEN, total = (ar.n + ar.piece - 1) / ar.piece * cpp;
+    int turn = 0;
+    for (int t = first; t < total; t += s.per) {              // (uniform over the workgroup)
+        const int p0 = t / cpp * ar.piece, c0 = t % cpp * CS_LEN;
+        const int len = min(CS_LEN, min(ar.piece, ar.n - p0) - c0), at = p0 + c0;
+        // what fills up the chunk goes behind every channel
+        const uint32_t k = tid < len ? sort_key(scores[ar.off + at + tid]) : ~0u;
+        uint64_t x = (uint64_t)k << 32 | (uint32_t)tid;
+        sort_merge<CS_LEN>(x, tid, buf, turn);
+        if (tid < len) {
+            if (cpp == 1) {
+                ar.perm[at + tid] = at + (int)(uint32_t)x;
+            } else {
+                keys[ar.off + at + tid] = (uint32_t)(x >> 32);
+                idx[ar.off + at + tid] = (uint32_t)c0 + (uint32_t)x;
+            }
+        }
     }
-    __syncthreads();
+}
 
-    for (int pass = 0; pass < 4; ++pass) {
-        const unsigned int *__restrict__ kin = kb[pass & 1];
-        const unsigned int *__restrict__ iin = ib[pass & 1];
-        unsigned int *__restrict__ kout = kb[(pass + 1) & 1];
-        unsigned int *__restrict__ iout = ib[(pass + 1) & 1];
-        const int shift = 8 * pass;
-
-        for (int b = lane; b < 256; b += 64) hist[wave][b] = 0;
+// Pieces of several sorted chunks: every channel's rank, and the permutation.
+__global__ __launch_bounds__(RK_THREADS)
+void rank_kernel(SortArrays s, const uint32_t *__restrict__ keys, const uint32_t *__restrict__ idx)
+{
+    extern __shared__ __attribute__((aligned(16))) uint32_t piece_keys[];    // all chunks of the piece
+    const int tid = threadIdx.x;
+    const SortArray ar = sort_array(s, (int)blockIdx.x / s.per);
+    const int cpp = (ar.piece + CS_LEN - 1) / CS_LEN;
+    if (ar.mode != ARR_SORT || cpp == 1) return;
+    const int halves = (ar.piece + RK_THREADS - 1) / RK_THREADS, total = (ar.n + ar.piece - 1) / ar.piece * halves;
+    for (int t = (int)blockIdx.x % s.per; t < total; t += s.per) {
+        const int p0 = t / halves * ar.piece, e0 = t % halves * RK_THREADS, len = min(ar.piece, ar.n - p0);
+        for (int i = tid; i < cpp * CS_LEN; i += RK_THREADS) piece_keys[i] = i < len ? keys[ar.off + p0 + i] : ~0u;
         __syncthreads();
-        for (int i = beg + lane; i < end; i += 64) atomicAdd(&hist[wave][(kin[i] >> shift) & 255u], 1u);
-        __syncthreads();
-        // offsets in (digit, wave) order: first the per-digit totals and the per-wave prefix inside a digit
-        if (tid < 256) {
-            unsigned int run = 0;
-            for (int w = 0; w < RS_WAVES; ++w) {
-                const unsigned int c = hist[w][tid];
-                hist[w][tid] = run;
-                run += c;
-            }
-            total[tid] = run;
-        }
-        __syncthreads();
-        if (wave == 0) {                             // exclusive scan of the 256 totals by one wave
-            unsigned int v[4], s = 0;
+        const int e = e0 + tid, own = e0 / CS_LEN;
+        const uint32_t k = piece_keys[e];                     // (e < cpp * CS_LEN)
+        int rank = e & (CS_LEN - 1);
+        // keys of a chunk that go before k: those below it and, in the chunks before (lower indices), those equal to it
+        auto count = [&](const uint32_t *c, auto before) {
+            int b = 0;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) { v[j] = total[lane * 4 + j]; s += v[j]; }
-            unsigned int inc = s;
-            for (int o = 1; o < 64; o <<= 1) {
-                const unsigned int t = __shfl_up(inc, o);
-                if (lane >= o) inc += t;
-            }
-            unsigned int ex = inc - s;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) { total[lane * 4 + j] = ex; ex += v[j]; }
-        }
+            for (int w = CS_LEN / 2; w >= 1; w >>= 1) b += before(c[b + w - 1]) ? w : 0;
+            return b + (before(c[b]) ? 1 : 0);
+        };
+#pragma unroll 4
+        for (int c = 0; c < own; ++c) rank += count(piece_keys + c * CS_LEN, [&](uint32_t v) { return v <= k; });
+#pragma unroll 4
+        for (int c = own + 1; c < cpp; ++c) rank += count(piece_keys + c * CS_LEN, [&](uint32_t v) { return v < k; });
+        if (e < len) ar.perm[p0 + rank] = p0 + (int)idx[ar.off + p0 + e];
         __syncthreads();
-        for (int b = lane; b < 256; b += 64) hist[wave][b] += total[b];
-        __syncthreads();
-        // stable scatter: the wave walks its segment in order, 64 elements at a time
-        for (int i = beg + lane; i - lane < end; i += 64) {
-            const bool valid = i < end;
-            const unsigned int key = valid ? kin[i] : 0u;
-            const unsigned int idx = valid ? iin[i] : 0u;
-            const unsigned int dg = (key >> shift) & 255u;
-            unsigned long long same = __ballot(valid);
-#pragma unroll
-            for (int b = 0; b < 8; ++b) {
-                const unsigned long long bal = __ballot((dg >> b) & 1u);
-                same &= ((dg >> b) & 1u) ? bal : ~bal;
-            }
-            const unsigned long long lt = (1ull << lane) - 1ull;
-            const unsigned int rank = __popcll(same & lt);
-            if (valid) {
-                const unsigned int base = hist[wave][dg];
-                const unsigned int dst = base + rank;
-                if (pass == 3) perm[dst] = (int32_t)idx + p0;
-                else { kout[dst] = key; iout[dst] = idx; }
-                if (rank == 0) hist[wave][dg] = base + __popcll(same);
-            }
-        }
-        __syncthreads();
-    }
     }
 }
 
@@ -523,11 +550,11 @@ static int gather_rows_per_wg(int64_t C, size_t elem)
 using namespace sbits;
 
 // ---- workspace of the reorder stage (after the head) ---------------------------------
-//   scores [L] | rowpart [RP] | colpart [CP] | k0 [L] | k1 [L] | i0 [L] | i1 [L]
+//   scores [L] | rowpart [RP] | colpart [CP] | keys [L] | idx [L]
 // with L = channels (rows + cols), RP = sum rows*nseg, CP = sum nband*cols.
 struct ReorderWs {
     float *scores, *rowpart, *colpart;
-    unsigned int *k0, *k1, *i0, *i1;
+    uint32_t *keys, *idx;
 };
 
 static size_t reorder_ws_layout(void *base, int64_t L, int64_t RP, int64_t CP, ReorderWs *out)
@@ -538,12 +565,9 @@ static size_t reorder_ws_layout(void *base, int64_t L, int64_t RP, int64_t CP, R
     float *scores = reinterpret_cast<float *>(take((size_t)L * 4));
     float *rowpart = reinterpret_cast<float *>(take((size_t)RP * 4));
     float *colpart = reinterpret_cast<float *>(take((size_t)CP * 4));
-    unsigned int *k0 = reinterpret_cast<unsigned int *>(take((size_t)L * 4));
-    unsigned int *k1 = reinterpret_cast<unsigned int *>(take((size_t)L * 4));
-    unsigned int *i0 = reinterpret_cast<unsigned int *>(take((size_t)L * 4));
-    unsigned int *i1 = reinterpret_cast<unsigned int *>(take((size_t)L * 4));
-    if (out) { out->scores = scores; out->rowpart = rowpart; out->colpart = colpart;
-               out->k0 = k0; out->k1 = k1; out->i0 = i0; out->i1 = i1; }
+    uint32_t *keys = reinterpret_cast<uint32_t *>(take((size_t)L * 4));
+    uint32_t *idx = reinterpret_cast<uint32_t *>(take((size_t)L * 4));
+    if (out) { out->scores = scores; out->rowpart = rowpart; out->colpart = colpart; out->keys = keys; out->idx = idx; }
     return b;
 }
 
@@ -587,6 +611,23 @@ static int run_scores(sbits_ctx *ctx, const MatDesc *descs, const MatDesc &one, 
     return SBITS_OK;
 }
 
+// max_len, max_piece: the longest array and the longest run of channels that is sorted as one
+static int run_argsort(sbits_ctx *ctx, SortArrays s, int64_t max_len, int64_t max_piece, const ReorderWs &w)
+{
+    const int64_t na = 2 * (int64_t)s.n_mats, most = na < 1 << 21 ? (1 << 21) / na : 1;   // (launches stay below 2^32 threads)
+    auto per = [&](int64_t len) { const int64_t c = (max_len + len - 1) / len; return (int)(c < most ? c : most); };
+    s.per = per(CS_LEN);
+    hipLaunchKernelGGL(chunk_sort_kernel, dim3((unsigned)(na * s.per)), dim3(CS_THREADS), 0, ctx->stream, s, w.scores, w.keys, w.idx);
+    SBITS_HIP(ctx, hipGetLastError());
+    if (max_piece <= CS_LEN) return SBITS_OK;
+    s.per = per(RK_THREADS);
+    SBITS_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&rank_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024));
+    hipLaunchKernelGGL(rank_kernel, dim3((unsigned)(na * s.per)), dim3(RK_THREADS), sbits_align_up((size_t)max_piece, CS_LEN) * 4,
+                       ctx->stream, s, w.keys, w.idx);
+    SBITS_HIP(ctx, hipGetLastError());
+    return SBITS_OK;
+}
+
 // ---- single matrix ----------------------------------------------------------------------
 int sbits_launch_scores(sbits_ctx *ctx, const float *S, int64_t R, int64_t C, int64_t ld,
                         float *row_score, float *col_score, void *scratch)
@@ -611,11 +652,8 @@ int sbits_launch_reorder(sbits_ctx *ctx, const float *S, int64_t R, int64_t C, i
     reorder_ws_layout(scratch, R + C, R * one.nseg, (int64_t)one.nband * C, &w);
     int rc = run_scores(ctx, nullptr, one, nullptr, 1, sbits_score_wgs(one.nseg, one.nband), R, C, w);
     if (rc) return rc;
-    hipLaunchKernelGGL(radix_argsort_kernel, dim3(2), dim3(RS_THREADS), 0, ctx->stream,
-                       (const MatDesc *)nullptr, one, 1, R, w.scores, w.k0, w.k1, w.i0, w.i1, row_perm, col_perm,
-                       (const int *)nullptr, (const int *)nullptr);
-    SBITS_HIP(ctx, hipGetLastError());
-    return SBITS_OK;
+    const int64_t len = R > C ? R : C;
+    return run_argsort(ctx, SortArrays{nullptr, one, 1, 1, R, nullptr, nullptr, row_perm, col_perm}, len, len, w);
 }
 
 static int gather_attr(sbits_ctx *ctx)
@@ -668,11 +706,9 @@ int sbits_launch_reorder_all(sbits_plan *plan, int32_t *row_perm, int32_t *col_p
     int rc = run_scores(ctx, sbits_desc_ptr(ws), none, d_pre, plan->n_mats, plan->score_wg_start.back(),
                         plan->sum_rows, plan->sum_cols, w);
     if (rc) return rc;
-    hipLaunchKernelGGL(radix_argsort_kernel, dim3((unsigned)(2 * plan->n_mats)), dim3(RS_THREADS), 0, ctx->stream,
-                       (const MatDesc *)sbits_desc_ptr(ws), none, plan->n_mats, plan->sum_rows, w.scores,
-                       w.k0, w.k1, w.i0, w.i1, row_perm, col_perm, (const int *)nullptr, (const int *)nullptr);
-    SBITS_HIP(ctx, hipGetLastError());
-    return SBITS_OK;
+    const int64_t len = plan->max_rows > plan->max_cols ? plan->max_rows : plan->max_cols;
+    return run_argsort(ctx, SortArrays{sbits_desc_ptr(ws), none, plan->n_mats, 1, plan->sum_rows, nullptr, nullptr, row_perm, col_perm},
+                       len, len, w);
 }
 
 // Host part of the coupled reordering: validates the groups and builds, per array a (rows of matrix
@@ -760,9 +796,13 @@ int sbits_launch_reorder_coupled_all(sbits_plan *plan, const int32_t *row_group,
     const dim3 g2((unsigned)((maxlen + 255) / 256), (unsigned)na);
     hipLaunchKernelGGL(group_sum_kernel, g2, dim3(256), 0, ctx->stream, descs, nm, plan->sum_rows, w.scores,
                        (const int *)d_mode, (const int *)d_next, (const int *)d_seg, (const int *)d_rep);
-    hipLaunchKernelGGL(radix_argsort_kernel, dim3((unsigned)na), dim3(RS_THREADS), 0, ctx->stream, descs, none, nm,
-                       plan->sum_rows, w.scores, w.k0, w.k1, w.i0, w.i1, row_perm, col_perm, (const int *)d_mode,
-                       (const int *)d_seg);
+    int64_t max_piece = 1;
+    for (int a = 0; a < na; ++a) {
+        const int64_t len = mode[a] != ARR_SORT ? 1 : seg[a] > 0 ? seg[a] : a < nm ? plan->rows[a] : plan->cols[a - nm];
+        if (len > max_piece) max_piece = len;
+    }
+    rc = run_argsort(ctx, SortArrays{descs, none, nm, 1, plan->sum_rows, d_mode, d_seg, row_perm, col_perm}, maxlen, max_piece, w);
+    if (rc) return rc;
     hipLaunchKernelGGL(replicate_perm_kernel, g2, dim3(256), 0, ctx->stream, descs, nm, row_perm, col_perm,
                        (const int *)d_mode, (const int *)d_leader, (const int *)d_seg, (const int *)d_rep);
     SBITS_HIP(ctx, hipGetLastError());
