@@ -93,6 +93,7 @@ int sbits_plan_create(sbits_ctx *ctx, const int64_t *rows, const int64_t *cols, 
     p->sum_rows = p->sum_cols = p->sum_elems = 0;
     p->sum_rowpart = p->sum_colpart = 0;
     int64_t score_wgs = 0;
+    p->score_rows = sbits_score_rows(rows, cols, n_mats);
     for (int i = 0; i < n_mats; ++i) {
         if (rows[i] <= 0 || cols[i] <= 0 || rows[i] % block_rows || cols[i] % block_cols ||
             rows[i] > 32768 || cols[i] > 32768) {
@@ -108,7 +109,7 @@ int sbits_plan_create(sbits_ctx *ctx, const int64_t *rows, const int64_t *cols, 
         d.elem_off = p->sum_elems; d.block_base = p->N;
         d.row_off = p->sum_rows; d.col_off = p->sum_cols;
         d.nbr = (int)(rows[i] / block_rows); d.nbc = (int)(cols[i] / block_cols);
-        sbits_score_geometry(rows[i], cols[i], &d.nseg, &d.nband);
+        sbits_score_geometry(rows[i], cols[i], p->score_rows, &d.nseg, &d.nband);
         d.rowpart_off = p->sum_rowpart; d.colpart_off = p->sum_colpart;
         p->sum_rowpart += rows[i] * d.nseg; p->sum_colpart += (int64_t)d.nband * cols[i];
         p->score_wg_start.push_back((int)score_wgs);
@@ -251,7 +252,7 @@ int sbits_channel_scores(sbits_plan *plan, int mat, const sbits_matrix *M, float
     if (!row_score || !col_score || !ws_ok(ws)) return SBITS_ERR_INVALID_ARG;
     if (!ws_fits(plan)) return SBITS_ERR_WORKSPACE;
     if ((rc = need_device(plan))) return rc;
-    return sbits_launch_scores(plan->ctx, M->sens, M->rows, M->cols, M->ld_s, row_score, col_score,
+    return sbits_launch_scores(plan->ctx, M->sens, M->rows, M->cols, M->ld_s, plan->score_rows, row_score, col_score,
                                sbits_scratch(plan, ws));
 }
 
@@ -263,7 +264,7 @@ int sbits_reorder(sbits_plan *plan, int mat, const sbits_matrix *M, int32_t *row
     if (!row_perm || !col_perm || !ws_ok(ws)) return SBITS_ERR_INVALID_ARG;
     if (!ws_fits(plan)) return SBITS_ERR_WORKSPACE;
     if ((rc = need_device(plan))) return rc;
-    return sbits_launch_reorder(plan->ctx, M->sens, M->rows, M->cols, M->ld_s, row_perm, col_perm,
+    return sbits_launch_reorder(plan->ctx, M->sens, M->rows, M->cols, M->ld_s, plan->score_rows, row_perm, col_perm,
                                 sbits_scratch(plan, ws));
 }
 

@@ -7,12 +7,12 @@
 // column, each summed in the canonical order: runs of 8 consecutive elements
 // left to right from +0, then an adjacent-pair tree over the runs (zero padded
 // to a power of two).  One pass over S serves both directions.  A workgroup of
-// four waves walks a band of 256 rows over a panel of 4096 columns, row by row
+// four waves walks a band of up to 256 rows over a panel of 4096 columns, row by row
 // (16 KiB of consecutive bytes per row); a wave owns two 512-column segments of
 // the panel and reads each with two 1 KiB loads, so a run of 8 columns sits in a
 // lane pair and the 16 columns of a lane keep their sums in registers for the
 // whole band.  The partial trees (per row and 512-column segment; per column
-// and 256-row band) go to the workspace and a small kernel finishes them.
+// and band) go to the workspace and a small kernel finishes them.
 //
 // Argsort.  Descending by score, ties to the lower index: inverted ordered-float
 // keys with the index behind them, sorted in chunks of 1024; what an array has
@@ -32,22 +32,23 @@ namespace sbits {
 
 // ================================================================ scores
 constexpr int SC_THREADS = 256;
-constexpr int SC_ROWS = 256;    // rows per band (32 octets): one workgroup walks a whole band
+constexpr int SC_ROWS = 256;    // most rows per band (32 octets): one workgroup walks a whole band
 constexpr int SC_COLS = 512;    // columns per segment: one wave, two 1 KiB loads per row
 constexpr int SC_PANEL = 8;     // segments per workgroup: 4 waves x 2 segments = 4096 columns = 16 KiB per row
 
 // rowpart[r][seg]  : tree over the 64 column runs of segment seg (zero beyond C)
-// colpart[band][c] : tree over the 32 row runs of band (zero beyond R)
+// colpart[band][c] : tree over the row runs (8 rows each) of band (zero beyond R)
 //
 // A workgroup reads rows of 16 KiB (its panel of 8 segments) top to bottom, so HBM sees long
 // consecutive runs, and every load instruction of a wave covers 1 KiB of consecutive bytes (whole
 // cache lines), which is what non-temporal loads need to run at full rate.  Wave w owns segments
 // w and w + 4 of the panel.  Inside a segment lane l owns columns 4l..4l+3 and 256+4l..256+4l+3:
 // a run of 8 consecutive columns sits in the lane pair (2k, 2k+1).  Column sums stay in registers
-// for the whole band (16 columns per lane, a 5-level adjacent-pair tree over the 32 octets).
+// for the whole band (16 columns per lane, an adjacent-pair tree of up to 5 levels over its octets).
+// A band has band_rows rows, a power of two: see sbits_score_rows().
 __global__ __launch_bounds__(SC_THREADS, 2)
 void score_partial_kernel(const MatDesc *__restrict__ descs, MatDesc one, const int *__restrict__ wg_start,
-                          int n_mats, float *__restrict__ rowpart_all, float *__restrict__ colpart_all)
+                          int n_mats, int band_rows, float *__restrict__ rowpart_all, float *__restrict__ colpart_all)
 {
     const int mat = descs ? find_matrix(wg_start, n_mats, (int)blockIdx.x) : 0;
     const MatDesc d = descs ? descs[mat] : one;
@@ -78,7 +79,7 @@ void score_partial_kernel(const MatDesc *__restrict__ descs, MatDesc one, const 
             voff[j][h] = (uint32_t)(ok[j][h] ? col0[j][h] : C - 4) * 4u;   // clamped: in bounds, value dropped
         }
     }
-    const int rbase = band * SC_ROWS;
+    const int rbase = band * band_rows;
 
     // two rows of the panel per pipeline stage: 8 loads of 16 bytes per lane
     struct Stage { float4 v[2][2][2]; };             // [row][segment][half of the segment]
@@ -144,7 +145,7 @@ void score_partial_kernel(const MatDesc *__restrict__ descs, MatDesc one, const 
                 if (lane == 0 && rok && seg[j] < d.nseg) rowpart[(int64_t)(rbase + rb) * d.nseg + seg[j]] = rs;
             }
             if ((rb & 7) == 7) {
-                // columns: adjacent-pair tree over the band's 32 octets, fed one octet at a time
+                // columns: adjacent-pair tree over the band's octets, fed one octet at a time
                 const int oc = rb >> 3;
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
@@ -180,10 +181,10 @@ void score_partial_kernel(const MatDesc *__restrict__ descs, MatDesc one, const 
     Stage A, B;
     load_stage(A, 0);
 #pragma unroll 1
-    for (int r0 = 0; r0 < SC_ROWS; r0 += 4) {
+    for (int r0 = 0; r0 < band_rows; r0 += 4) {
         load_stage(B, r0 + 2);
         process(A, r0);
-        load_stage(A, r0 + 4 < SC_ROWS ? r0 + 4 : SC_ROWS - 2);   // the last reload is redundant and harmless
+        load_stage(A, r0 + 4 < band_rows ? r0 + 4 : band_rows - 2);   // the last reload is redundant and harmless
         process(B, r0 + 2);
     }
 #pragma unroll
@@ -578,10 +579,30 @@ static size_t reorder_ws_layout(void *base, int64_t L, int64_t RP, int64_t CP, R
 // workgroups of score_partial_kernel for a matrix with nseg segments and nband bands
 int sbits_score_wgs(int nseg, int nband) { return nband * ((nseg + SC_PANEL - 1) / SC_PANEL); }
 
-void sbits_score_geometry(int64_t R, int64_t C, int *nseg, int *nband)
+void sbits_score_geometry(int64_t R, int64_t C, int band_rows, int *nseg, int *nband)
 {
     *nseg = (int)((C + SC_COLS - 1) / SC_COLS);
-    *nband = (int)((R + SC_ROWS - 1) / SC_ROWS);
+    *nband = (int)((R + band_rows - 1) / band_rows);
+}
+
+// Rows per band for a plan of these matrices: as many as the kernel takes (long bands read S in the longest runs and leave
+// the fewest partial sums: a layer with 907 workgroups of 256 rows takes 685 us, with 128 rows a band 694, with 64 716),
+// halved while there would be fewer than 192 workgroups, whose rows come one after the other, and as long as one tree of
+// 128 adds up a column.  Scores and permutations: 512 x 512 136 us with 256 rows, 34 with 8; 2048 x 2048 145 -> 47 (16
+// rows); 4096 x 4096 159 -> 58 (32); 2048 x 8192 twice 161 -> 60 (32); a 2048-wide layer (100 workgroups) 163 -> 104 (128).
+// The line: 216 workgroups take 190 us, with half the rows 187, with a quarter 204.
+int sbits_score_rows(const int64_t *rows, const int64_t *cols, int n_mats)
+{
+    int64_t wgs = 0, max_rows = 0;
+    for (int i = 0; i < n_mats; ++i) {
+        int nseg, nband;
+        sbits_score_geometry(rows[i], cols[i], SC_ROWS, &nseg, &nband);
+        wgs += sbits_score_wgs(nseg, nband);
+        if (rows[i] > max_rows) max_rows = rows[i];
+    }
+    int r = SC_ROWS;
+    while (r > 8 && wgs * (SC_ROWS / r) < 192 && max_rows <= 128 * (r / 2)) r >>= 1;
+    return r;
 }
 
 size_t sbits_reorder_ws_bytes(int64_t L, int64_t RP, int64_t CP)
@@ -590,22 +611,22 @@ size_t sbits_reorder_ws_bytes(int64_t L, int64_t RP, int64_t CP)
 }
 
 // descriptor of a single matrix with its own (offset-free) layout
-static MatDesc single_desc(const void *W, const float *S, int64_t R, int64_t C, int64_t ld_w, int64_t ld_s)
+static MatDesc single_desc(const void *W, const float *S, int64_t R, int64_t C, int64_t ld_w, int64_t ld_s, int band_rows)
 {
     MatDesc d;
     memset(&d, 0, sizeof d);
     d.w = static_cast<const uint16_t *>(W);
     d.s = S;
     d.rows = R; d.cols = C; d.ld_w = ld_w; d.ld_s = ld_s;
-    sbits_score_geometry(R, C, &d.nseg, &d.nband);
+    sbits_score_geometry(R, C, band_rows, &d.nseg, &d.nband);
     return d;
 }
 
 static int run_scores(sbits_ctx *ctx, const MatDesc *descs, const MatDesc &one, const int *d_wg_start,
-                      int n_mats, int total_wg, int64_t sum_rows, int64_t sum_cols, const ReorderWs &w)
+                      int n_mats, int total_wg, int band_rows, int64_t sum_rows, int64_t sum_cols, const ReorderWs &w)
 {
     hipLaunchKernelGGL(score_partial_kernel, dim3((unsigned)total_wg), dim3(SC_THREADS), 0, ctx->stream,
-                       descs, one, d_wg_start, n_mats, w.rowpart, w.colpart);
+                       descs, one, d_wg_start, n_mats, band_rows, w.rowpart, w.colpart);
     SBITS_HIP(ctx, hipGetLastError());
     const int64_t L = sum_rows + sum_cols;
     hipLaunchKernelGGL(score_finish_kernel, dim3((unsigned)((L + 255) / 256)), dim3(256), 0, ctx->stream,
@@ -639,13 +660,13 @@ static int run_argsort(sbits_ctx *ctx, SortArrays s, int64_t max_len, int64_t ma
 }
 
 // ---- single matrix ----------------------------------------------------------------------
-int sbits_launch_scores(sbits_ctx *ctx, const float *S, int64_t R, int64_t C, int64_t ld,
+int sbits_launch_scores(sbits_ctx *ctx, const float *S, int64_t R, int64_t C, int64_t ld, int band_rows,
                         float *row_score, float *col_score, void *scratch)
 {
-    MatDesc one = single_desc(nullptr, S, R, C, C, ld);
+    MatDesc one = single_desc(nullptr, S, R, C, C, ld, band_rows);
     ReorderWs w;
     reorder_ws_layout(scratch, R + C, R * one.nseg, (int64_t)one.nband * C, &w);
-    int rc = run_scores(ctx, nullptr, one, nullptr, 1, sbits_score_wgs(one.nseg, one.nband), R, C, w);
+    int rc = run_scores(ctx, nullptr, one, nullptr, 1, sbits_score_wgs(one.nseg, one.nband), band_rows, R, C, w);
     if (rc) return rc;
     if (row_score)
         SBITS_HIP(ctx, hipMemcpyAsync(row_score, w.scores, (size_t)R * 4, hipMemcpyDeviceToDevice, ctx->stream));
@@ -654,13 +675,13 @@ int sbits_launch_scores(sbits_ctx *ctx, const float *S, int64_t R, int64_t C, in
     return SBITS_OK;
 }
 
-int sbits_launch_reorder(sbits_ctx *ctx, const float *S, int64_t R, int64_t C, int64_t ld,
+int sbits_launch_reorder(sbits_ctx *ctx, const float *S, int64_t R, int64_t C, int64_t ld, int band_rows,
                          int32_t *row_perm, int32_t *col_perm, void *scratch)
 {
-    MatDesc one = single_desc(nullptr, S, R, C, C, ld);
+    MatDesc one = single_desc(nullptr, S, R, C, C, ld, band_rows);
     ReorderWs w;
     reorder_ws_layout(scratch, R + C, R * one.nseg, (int64_t)one.nband * C, &w);
-    int rc = run_scores(ctx, nullptr, one, nullptr, 1, sbits_score_wgs(one.nseg, one.nband), R, C, w);
+    int rc = run_scores(ctx, nullptr, one, nullptr, 1, sbits_score_wgs(one.nseg, one.nband), band_rows, R, C, w);
     if (rc) return rc;
     const int64_t len = R > C ? R : C;
     return run_argsort(ctx, SortArrays{nullptr, one, 1, 1, R, nullptr, nullptr, row_perm, col_perm}, len, len, w);
@@ -682,7 +703,7 @@ int sbits_launch_gather(sbits_ctx *ctx, const void *W, const float *S, int64_t R
     if ((size_t)C * 4 > 160 * 1024) return SBITS_ERR_BAD_SHAPE;
     int rc = gather_attr(ctx);
     if (rc) return rc;
-    MatDesc one = single_desc(W, S, R, C, ld_w, ld_s);
+    MatDesc one = single_desc(W, S, R, C, ld_w, ld_s, SC_ROWS);
     const int *nul = nullptr;
     if (w_out) {
         const int rpw = gather_rows_per_wg(C, 2);
@@ -714,7 +735,7 @@ int sbits_launch_reorder_all(sbits_plan *plan, int32_t *row_perm, int32_t *col_p
     MatDesc none;
     memset(&none, 0, sizeof none);
     int rc = run_scores(ctx, sbits_desc_ptr(ws), none, d_pre, plan->n_mats, plan->score_wg_start.back(),
-                        plan->sum_rows, plan->sum_cols, w);
+                        plan->score_rows, plan->sum_rows, plan->sum_cols, w);
     if (rc) return rc;
     const int64_t len = plan->max_rows > plan->max_cols ? plan->max_rows : plan->max_cols;
     return run_argsort(ctx, SortArrays{sbits_desc_ptr(ws), none, plan->n_mats, 1, plan->sum_rows, nullptr, nullptr, row_perm, col_perm},
@@ -800,7 +821,7 @@ int sbits_launch_reorder_coupled_all(sbits_plan *plan, const int32_t *row_group,
     MatDesc none;
     memset(&none, 0, sizeof none);
     const MatDesc *descs = sbits_desc_ptr(ws);
-    int rc = run_scores(ctx, descs, none, d_pre, nm, plan->score_wg_start.back(), plan->sum_rows, plan->sum_cols, w);
+    int rc = run_scores(ctx, descs, none, d_pre, nm, plan->score_wg_start.back(), plan->score_rows, plan->sum_rows, plan->sum_cols, w);
     if (rc) return rc;
     const int64_t maxlen = plan->max_rows > plan->max_cols ? plan->max_rows : plan->max_cols;
     const dim3 g2((unsigned)((maxlen + 255) / 256), (unsigned)na);

@@ -31,6 +31,7 @@ struct sbits_plan {
     int64_t max_rows, max_cols;
     int64_t sum_rows, sum_cols, sum_elems;
     int64_t sum_rowpart, sum_colpart;        // score partials over all matrices
+    int score_rows;                          // rows per band of the score kernel
     std::vector<int> score_wg_start;         // workgroup prefixes of the batched launches
     std::vector<int> cost_unit_start;
     std::vector<int> pack_wg_start;
@@ -74,15 +75,16 @@ static inline size_t sbits_align_up(size_t v, size_t a) { return (v + a - 1) / a
 // ---- stage launchers (each returns an sbits_status) ------------------------
 
 // workspace sizes in bytes
-void sbits_score_geometry(int64_t R, int64_t C, int *nseg, int *nband);
+void sbits_score_geometry(int64_t R, int64_t C, int band_rows, int *nseg, int *nband);
+int sbits_score_rows(const int64_t *rows, const int64_t *cols, int n_mats);
 int sbits_score_wgs(int nseg, int nband);
 size_t sbits_reorder_ws_bytes(int64_t channels, int64_t rowpart, int64_t colpart);
 size_t sbits_alloc_ws_bytes(int64_t N);
 size_t sbits_offsets_ws_bytes(int64_t N);
 
-int sbits_launch_scores(sbits_ctx *ctx, const float *S, int64_t R, int64_t C, int64_t ld,
+int sbits_launch_scores(sbits_ctx *ctx, const float *S, int64_t R, int64_t C, int64_t ld, int band_rows,
                         float *row_score, float *col_score, void *ws);
-int sbits_launch_reorder(sbits_ctx *ctx, const float *S, int64_t R, int64_t C, int64_t ld,
+int sbits_launch_reorder(sbits_ctx *ctx, const float *S, int64_t R, int64_t C, int64_t ld, int band_rows,
                          int32_t *row_perm, int32_t *col_perm, void *scratch);
 int sbits_launch_reorder_all(sbits_plan *plan, int32_t *row_perm, int32_t *col_perm, void *ws);
 int sbits_coupling_tables(const sbits_plan *plan, const int32_t *row_group, const int32_t *col_group, int n_groups,
