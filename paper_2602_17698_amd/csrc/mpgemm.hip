@@ -21,7 +21,7 @@
 //   block columns (4 waves per row group, 4 blocks per wave, two or three of them in flight in a ring
 //   of register slots); the x slice of those columns sits in LDS.  Block columns beyond the first 16
 //   go to further workgroups (grid.y), whose partial sums a second kernel adds in a fixed order.
-// More than 32 batch rows take the kernel further down.
+// More than 32 batch rows, and many products of up to 16, take the kernels further down.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -871,6 +871,142 @@ void mp_gemm_wide_kernel(MpArgs a, int cols_per_split)
     }
 }
 
+// ================================================================ up to 16 batch rows
+// Few rows of x are small next to the codes, so nothing is staged and no columns are split off: a workgroup takes 32
+// channels and all columns, its 16 waves every 16th block column each, with x straight from the caches into the operand
+// registers, two blocks in flight, and one exchange through LDS at the end.  Against the first kernel this takes the
+// second launch, the partial sums in memory and the wait for x out, and four times as many CUs share a small matrix; the
+// price is x read once per 32 channels instead of once per 128.  Products as there, in its column order.  Latency bounds
+// it: level and offset, then codes, then the exchange.
+// 1024 x 4096, bitwidths 1 .. 4, one row: 11.3 -> 5.8 us; 4096 x 4096, 4 bits: 11.2 -> 5.9, 16 rows 11.5 -> 8.3; 14336 x 4096,
+// one row: 12.5 -> 10.7; 64-column blocks (whose codes the first kernel reads two bytes at a time): 11008 x 4096 44 -> 17.
+constexpr int ND_WAVES = 16, ND_THREADS = ND_WAVES * 64;
+
+// x operand of step st from the lane's KL values in registers: natural or, for the bitwidths of PairOrder, pair order
+template <int C, int KL>
+__device__ __forceinline__ bf16x8_t x_held(const u32x4_t (&x)[KL / 8], int st)
+{
+    if constexpr (!PairOrder<C, KL>::value) {
+        return __builtin_bit_cast(bf16x8_t, x[st]);
+    } else {
+        const int ea = C == 4 ? 8 * st : C == 2 ? 16 * (st >> 1) + 4 * (st & 1) : 4 * st, eb = ea + 16 / C;   // (multiples of 4)
+        auto word = [&](int e, int k) { return x[e >> 3][((e & 7) >> 1) + k]; };
+        return as_bf16x8(__builtin_amdgcn_perm(word(eb, 0), word(ea, 0), 0x05040100u), __builtin_amdgcn_perm(word(eb, 0), word(ea, 0), 0x07060302u),
+                         __builtin_amdgcn_perm(word(eb, 1), word(ea, 1), 0x05040100u), __builtin_amdgcn_perm(word(eb, 1), word(ea, 1), 0x07060302u));
+    }
+}
+
+template <int C, int N_COLS>
+__device__ __forceinline__ void narrow_block(const uint32_t (&cw)[2][8], const float (&sc)[2], const float (&ze)[2],
+                                             const u32x4_t (&x)[N_COLS / 32], f32x4v_t (&acc)[2])
+{
+    constexpr int KL = N_COLS / 4;
+    const bf16x8_t ones = as_bf16x8(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
+    f32x4v_t d[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}}, d1 = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int st = 0; st < N_COLS / 32; ++st) {
+        const bf16x8_t xa = x_held<C, KL>(x, st);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            bf16x8_t b;
+            if constexpr (PairOrder<C, KL>::value) b = operand_pairs<C>(cw[t], st);
+            else b = operand<C>(cw[t], st);
+            d[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, b, d[t], 0, 0, 0);
+        }
+        d1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, ones, d1, 0, 0, 0);
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const float zz = C < 8 ? fmaf(-128.0f, sc[t], ze[t]) : ze[t];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[t][r] = fmaf(sc[t], d[t][r], fmaf(zz, d1[r], acc[t][r]));
+    }
+}
+
+template <int N_COLS>
+__global__ __launch_bounds__(ND_THREADS)
+void mp_gemm_narrow_kernel(MpArgs a)
+{
+    __shared__ float red[ND_WAVES][2][4][64];
+    constexpr int KL = N_COLS / 4, XL = KL / 8;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 15, g = lane >> 4;
+    const int row0 = (int)blockIdx.x * 32;                    // (R is a multiple of 32)
+    const int I = row0 / a.m, rin = row0 - I * a.m;
+    const int64_t blk0 = a.block_base + (int64_t)I * a.nbc;
+    // level and offset of this wave's t-th block column, wave + 16 t, in lane t (at most 512 block columns)
+    const int mine = min(wave + ND_WAVES * lane, a.nbc - 1);
+    const int lvl = a.level[blk0 + mine];
+    const int64_t off = a.byte_off[blk0 + mine];
+    const int nt = (a.nbc - wave + ND_WAVES - 1) / ND_WAVES;  // 0 or less: none
+    const uint16_t *const xrow = a.x + (int64_t)min(li, a.batch - 1) * a.ld_x + g * KL;   // (rows past the batch: not stored)
+    const uint32_t lane_units = (uint32_t)((rin + li) * (N_COLS / 8) + g * (KL / 8));   // x c = the lane's byte offset in the block
+    const uint32_t block_bytes_per_bit = (uint32_t)a.m * (N_COLS / 8);
+
+    struct Slot { Quarter<N_COLS> q[2]; float sc[2], ze[2]; u32x4_t x[XL]; int c; };
+    auto request = [&](Slot &o, int t) {
+        const int tt = min(t, nt - 1), J = wave + ND_WAVES * tt;
+        const int lv = __builtin_amdgcn_readlane(lvl, tt);
+        int c = a.bits[0];
+#pragma unroll
+        for (int k = 1; k < MAX_CAND; ++k) c = lv == k ? a.bits[k] : c;
+        o.c = t < nt ? c : 0;
+        const uint64_t at = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)((uint64_t)off >> 32), tt) << 32 |
+                            (uint32_t)__builtin_amdgcn_readlane((uint32_t)off, tt);
+        const rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(a.codes) + at, 0, (int)(block_bytes_per_bit * (uint32_t)o.c), 0x00027000);
+        const float *ps = a.scale + (blk0 + J) * a.m + rin, *pz = a.zero + (blk0 + J) * a.m + rin;
+#pragma unroll
+        for (int tl = 0; tl < 2; ++tl) load_quarter<N_COLS>(rs, (lane_units + (uint32_t)(tl * 16 * (N_COLS / 8))) * (uint32_t)o.c, o.q[tl]);
+#pragma unroll
+        for (int i = 0; i < XL; ++i) o.x[i] = *(const __attribute__((address_space(1))) u32x4_t *)(xrow + J * N_COLS + 8 * i);
+#pragma unroll
+        for (int tl = 0; tl < 2; ++tl) {
+            o.sc[tl] = ps[16 * tl + li];
+            o.ze[tl] = pz[16 * tl + li];
+        }
+    };
+    f32x4v_t acc[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
+    auto add = [&](const Slot &o) {
+        if (o.c == 0) return;                                 // no such block column, or a pruned block
+        uint32_t cw[2][8];
+#pragma unroll
+        for (int tl = 0; tl < 2; ++tl) {
+            uint32_t r[N_COLS / 16];
+            align_quarter<N_COLS>(o.q[tl], (lane_units + (uint32_t)(tl * 16 * (N_COLS / 8))) * (uint32_t)o.c, r);
+#pragma unroll
+            for (int i = 0; i < N_COLS / 16; ++i) cw[tl][i] = r[i];
+        }
+#define ND_BLOCK(C) narrow_block<C, N_COLS>(cw, o.sc, o.ze, o.x, acc)
+        WG_SWITCH(o.c, ND_BLOCK)
+#undef ND_BLOCK
+    };
+    if (nt > 0) {
+        Slot s0, s1;
+        request(s0, 0);
+        request(s1, 1);
+        for (int t = 0; t < nt; t += 2) {
+            add(s0);
+            if (t + 2 < nt) request(s0, t + 2);
+            add(s1);
+            if (t + 2 < nt) request(s1, t + 3);
+        }
+    }
+#pragma unroll
+    for (int tl = 0; tl < 2; ++tl)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[wave][tl][r][lane] = acc[tl][r];
+    __syncthreads();
+    // D layout: batch row 4 (lane / 16) + r, channel lane % 16
+    const int ch = tid & 31, b = tid >> 5;                    // 32 channels x 16 batch rows in the first 512 threads
+    if (b < a.batch && b < 16) {
+        float v = red[0][ch >> 4][b & 3][(b >> 2) * 16 + (ch & 15)];
+#pragma unroll
+        for (int w = 1; w < ND_WAVES; ++w) v = v + red[w][ch >> 4][b & 3][(b >> 2) * 16 + (ch & 15)];
+        a.out[(int64_t)b * a.R + row0 + ch] = v;
+    }
+}
+
 // y = sum over the column splits of the partials, split 0 first
 __global__ __launch_bounds__(256)
 void mp_gemm_finish_kernel(const float *__restrict__ part, int64_t n, int n_split, float *__restrict__ y)
@@ -942,6 +1078,21 @@ static int launch_wide_rg(sbits_ctx *ctx, int n, const MpArgs &a, dim3 grid, int
     return a.batch <= 48 ? launch_wide<128, 3, RG>(ctx, a, grid, cols_per_split) : launch_wide<128, 4, RG>(ctx, a, grid, cols_per_split);
 }
 
+// The narrow kernel or the first one for up to 16 rows: by the blocks that a wave of the busiest CU takes one after the
+// other (both kernels put 16 waves on a CU).  As many are as good for the narrow one, which saves the second launch
+// (14336 x 4096, 4 blocks in both: 10.7 against 12.5 us at one row, 12.4 and 12.9 at 8), but for more rows (16: 15.3 and 13.1)
+// and where the first kernel has no second launch (32768 x 1024: 11.1 and 8.6) it has to be a fifth less; more are worse
+// (4096 x 14336, 7 and 4: 17.6 and 16.3 us; 256 x 32768, 16 and 4: 26.9 and 14.2).  64-column blocks: up to twice as many
+// (4096 x 14336, 14 and 8: 26 and 48 us; 1024 x 16384, 16 and 4: 20 and 14).
+static bool takes_narrow(const MpArgs &a, int n)
+{
+    if (a.batch > 16) return false;
+    const int64_t per_wave = (a.nbc + ND_WAVES - 1) / ND_WAVES, spans = (a.nbc + MG_SPAN - 1) / MG_SPAN;
+    const int64_t narrow = (a.R / 32 + 255) / 256 * per_wave, first = ((a.R + 127) / 128 * spans + 255) / 256 * MG_NBLK;
+    if (n == 64) return narrow <= 2 * first;
+    return a.batch > 8 || spans == 1 ? narrow * 5 <= first * 4 : narrow <= first;
+}
+
 // Rows of x a launch takes: 128 (two batch groups) while a group's byte offsets fit the 32 bits of a descriptor, else the
 // 32 of the first kernel, whose addresses have 64.
 int sbits_mp_gemm_rows(int64_t ld_x) { return ld_x <= 1 << 20 ? 128 : 32; }
@@ -971,6 +1122,15 @@ int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t 
         if (want > steps) want = steps;
         if (want > room) want = room;
         if (want > 1) per_split = (int)((steps + want - 1) / want * jl);
+    }
+    if (takes_narrow(a, plan->n)) {
+        a.n_split = 1;
+        a.out = y;
+        for (int c = 0; c < sbits::MAX_CAND; ++c) a.bits[c] = c < plan->K ? plan->bits[c] : plan->bits[plan->K - 1];
+        auto *fn = plan->n == 128 ? &mp_gemm_narrow_kernel<128> : &mp_gemm_narrow_kernel<64>;
+        hipLaunchKernelGGL(fn, dim3((unsigned)(a.R / 32)), dim3(ND_THREADS), 0, ctx->stream, a);
+        SBITS_HIP(ctx, hipGetLastError());
+        return SBITS_OK;
     }
     a.n_split = wide ? (a.nbc + per_split - 1) / per_split : sbits_mp_gemm_splits(a.C, plan->n);
     for (int c = 0; c < sbits::MAX_CAND; ++c) a.bits[c] = c < plan->K ? plan->bits[c] : plan->bits[plan->K - 1];

@@ -1,8 +1,9 @@
-"""The product for more than 32 batch rows at the edges of its work split: batch tiles and groups, row groups past the
-matrix's end, odd numbers of block columns, column splits, both workgroup shapes, every bitwidth with and without pruned
-blocks.  Tolerance: the kernel sums terms of size |B| scale |x| in fp32, where B scale is at most 2 spans of the block row
-(span = 2^c scale; 129 scale for 1 bit and 191 scale for 6 bits, whose offset is 128) and zero |x|.  The bound is 2^-22 of
-the sum of all of them for the largest error and 2^-24 for the root mean square."""
+"""The products for up to 16 and for more than 32 batch rows at the edges of their work split: batch tiles and groups, row
+groups past the matrix's end, odd numbers of block columns, column splits, both workgroup shapes, every bitwidth with and
+without pruned blocks.  Tolerance: a kernel sums terms of size |B| scale |x| in fp32, where B scale is at most the span of
+the block row (2^c scale) and the offset that the codes carry (128 scale; 2^c scale for most bitwidths of the products for
+many rows), and zero |x|.  The bound is 2^-22 of the sum of all of them for the largest error and 2^-24 for the root mean
+square."""
 import numpy as np
 import pytest
 
@@ -17,6 +18,16 @@ ALL = [1, 2, 3, 4, 5, 6, 7, 8]
 
 
 @pytest.mark.parametrize("R,C,m,n,bits,batch,pad", [
+    # up to 16 rows: fewer block columns than waves, one more than the waves, odd numbers of blocks a wave; rules' both sides
+    (32, 128, 32, 128, [3], 1, 0),
+    (96, 128 * 17, 32, 128, [0] + ALL, 3, 8),
+    (64, 128 * 35, 64, 128, ALL, 8, 0),
+    (96, 128 * 16, 32, 128, ALL, 9, 0),
+    (64, 128 * 48, 64, 128, [2, 5, 7], 16, 24),
+    (64, 64 * 33, 32, 64, [0] + ALL, 2, 0),
+    (160, 64 * 130, 32, 64, [1, 3, 6, 8], 16, 8),
+    (64, 128 * 80, 32, 128, [2, 4], 1, 0),                # 5 blocks a wave against 4: the first kernel
+    (64, 64 * 144, 32, 64, [2, 4], 5, 0),                 # 9 against 4
     (32, 128, 32, 128, [4], 33, 0),                       # one block; three of four row groups past the end
     (160, 128 * 5, 32, 128, ALL, 48, 8),                  # odd block columns, three tiles, ragged row groups, wide pitch
     (192, 128 * 8, 64, 128, [0] + ALL, 49, 0),            # pruned blocks, four tiles
@@ -31,8 +42,8 @@ ALL = [1, 2, 3, 4, 5, 6, 7, 8]
     (64, 128 * 4, 32, 128, [1], 80, 0),                   # 1 bit: products of its own
     (64, 64 * 5, 32, 64, [1], 50, 0),
 ])
-def test_wide_product(orc, R, C, m, n, bits, batch, pad):
-    print("[case] wide product", R, C, m, n, bits, batch, flush=True)
+def test_product_edges(orc, R, C, m, n, bits, batch, pad):
+    print("[case] product", R, C, m, n, bits, batch, flush=True)
     dev = torch.device("cuda:0")
     rng = np.random.default_rng(R + C + batch)
     ctx = sb.Context(0, torch.cuda.current_stream().cuda_stream)
@@ -59,7 +70,8 @@ def test_wide_product(orc, R, C, m, n, bits, batch, pad):
     xf = orc.bf16_to_f32(xb).astype(np.float64)
     ref = xf @ What.T
     nbc = C // n
-    most = np.array([{1: 129.0, 6: 191.0}.get(b, 2.0 ** (b + 1)) for b in bits])      # of |B|, in codes
+    offset = {1: 128, 6: 128, 7: 128} if batch > 32 else {b: 128 for b in range(1, 8)}
+    most = np.array([2.0 ** b + offset.get(b, 2.0 ** b) for b in bits])      # of |B|, in codes
     mag = (np.abs(zero.reshape(N, m)) + scale.reshape(N, m) * most[level][:, None])[base:]
     mag = mag.reshape(R // m, nbc, m).transpose(0, 2, 1).reshape(R, nbc)
     bound = np.abs(xf).reshape(batch, nbc, n).sum(2) @ mag.T
