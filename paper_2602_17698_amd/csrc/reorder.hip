@@ -477,22 +477,24 @@ void replicate_perm_kernel(const MatDesc *__restrict__ descs, int n_mats, int32_
 }
 
 // ================================================================ gather
-constexpr int GA_THREADS = 512;
 constexpr int GA_LDS_TARGET = 48 * 1024;            // rows per workgroup are chosen to fill about this much
 
 // T = uint16_t (bf16) or float.  A workgroup stages rpw consecutive output rows of one matrix
 // (their source rows) in LDS and emits them permuted; the column indices are read once per
 // column chunk and serve all rpw rows.  A launch covers the matrices of one "class" (equal
 // column count, hence equal LDS need): members[] lists them, wg_start[] is their workgroup prefix.
-template <class T>
-__global__ __launch_bounds__(GA_THREADS)
+// Bound by HBM: the rows come in by direct loads to LDS, all of a workgroup's rows under way at once (through registers a
+// wave had one load of 1 KiB in flight), and the column indices of a thread are requested a chunk ahead, the first behind
+// the rows.  8192 x 28672: fp32 477 -> 373 us (5.0 TB/s), bf16 198 -> 209; two matrices of 4096
+// and 14336 columns: fp32 651 -> 633, bf16 346 -> 324.
+template <class T, int TH>
+__global__ __launch_bounds__(TH)
 void gather_kernel(const MatDesc *__restrict__ descs, MatDesc one, const int *__restrict__ members,
                    const int *__restrict__ wg_start, int n_members, int rpw,
                    const int32_t *__restrict__ row_perm, const int32_t *__restrict__ col_perm,
                    T *__restrict__ out_all)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    T *rows = reinterpret_cast<T *>(smem);
     constexpr int V = 16 / sizeof(T);               // elements per 128-bit access
     typedef const T __attribute__((address_space(1))) *gtp;
 
@@ -506,34 +508,48 @@ void gather_kernel(const MatDesc *__restrict__ descs, MatDesc one, const int *__
     const int64_t ld = sizeof(T) == 2 ? d.ld_w : d.ld_s;
     const int32_t *__restrict__ rp = row_perm + d.row_off;
     const int32_t *__restrict__ cp = col_perm + d.col_off;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int bytes = C * (int)sizeof(T), pieces = (bytes + 1023) / 1024;       // a row takes whole KiB of LDS
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
 
-    for (int r = 0; r < nr; ++r) {
+    for (int q = wave; q < nr * pieces; q += TH / 64) {       // a piece (1 KiB of a row) per wave and turn
+        const int r = q / pieces, p = q - r * pieces;
         int sr = rp[i0 + r];
         sr = sr < 0 ? 0 : (sr >= R ? R - 1 : sr);   // a permutation never trips this; keeps a bad one in bounds
         const T *src = in + (int64_t)sr * ld;
-        T *dstl = rows + (size_t)r * C;
-        if ((reinterpret_cast<uintptr_t>(src) & 15) == 0) {
-            for (int j = threadIdx.x * V; j < C; j += GA_THREADS * V)
-            {
-                const u32x4_t v = __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x4_t *)(src + j));
-                *reinterpret_cast<uint4 *>(dstl + j) = make_uint4(v.x, v.y, v.z, v.w);
-            }
+        const uint32_t at = (uint32_t)q * 1024u;
+        if ((reinterpret_cast<uintptr_t>(src) & 15) == 0) {   // (lanes past the row's end: its last 16 bytes, into the padding)
+            const uint32_t off = min((uint32_t)p * 1024u + (uint32_t)lane * 16u, (uint32_t)bytes - 16u);
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(reinterpret_cast<const char *>(src) + off),
+                                             (__attribute__((address_space(3))) void *)(lds0 + at), 16, 0, 2);
         } else {
-            for (int j = threadIdx.x; j < C; j += GA_THREADS) dstl[j] = *(gtp)(src + j);
+            for (int j = lane; j < 1024 / (int)sizeof(T); j += 64) {
+                const int c = p * (1024 / (int)sizeof(T)) + j;
+                if (c < C) reinterpret_cast<T *>(smem + at)[j] = *(gtp)(src + c);
+            }
         }
     }
+    struct Index { int4 a, b; };
+    auto indices = [&](int j) {
+        Index o;
+        j = min(j, C - V);
+        o.a = *reinterpret_cast<const int4 *>(cp + j);
+        if constexpr (V == 8) o.b = *reinterpret_cast<const int4 *>(cp + j + 4);
+        return o;
+    };
+    const int j0 = (int)threadIdx.x * V;
+    Index next = indices(j0);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // this wave's pieces (and its first indices)
     __syncthreads();
     T *dst = out_all + d.elem_off + (int64_t)i0 * C;      // dense output, C % 8 == 0: 16-byte aligned rows
-    for (int j = threadIdx.x * V; j < C; j += GA_THREADS * V) {
+    for (int j = j0; j < C; j += TH * V) {
+        const Index ix = next;
+        next = indices(j + TH * V);
         int ci[V];
-        const int4 c0 = *reinterpret_cast<const int4 *>(cp + j);
-        ci[0] = c0.x; ci[1] = c0.y; ci[2] = c0.z; ci[3] = c0.w;
-        if constexpr (V == 8) {
-            const int4 c1 = *reinterpret_cast<const int4 *>(cp + j + 4);
-            ci[4] = c1.x; ci[5] = c1.y; ci[6] = c1.z; ci[7] = c1.w;
-        }
+        ci[0] = ix.a.x; ci[1] = ix.a.y; ci[2] = ix.a.z; ci[3] = ix.a.w;
+        if constexpr (V == 8) { ci[4] = ix.b.x; ci[5] = ix.b.y; ci[6] = ix.b.z; ci[7] = ix.b.w; }
         for (int r = 0; r < nr; ++r) {
-            const T *srcl = rows + (size_t)r * C;
+            const T *srcl = reinterpret_cast<const T *>(smem + (size_t)r * pieces * 1024);
             T tmp[V];
 #pragma unroll
             for (int e = 0; e < V; ++e) tmp[e] = srcl[ci[e]];
@@ -687,12 +703,18 @@ int sbits_launch_reorder(sbits_ctx *ctx, const float *S, int64_t R, int64_t C, i
     return run_argsort(ctx, SortArrays{nullptr, one, 1, 1, R, nullptr, nullptr, row_perm, col_perm}, len, len, w);
 }
 
-static int gather_attr(sbits_ctx *ctx)
+// Workgroups of 512 threads, of 1024 where fewer than three fit a CU's LDS (8192 x 28672 bf16, two: 209 us against 222).
+template <class T>
+static int launch_gather(sbits_ctx *ctx, const MatDesc *descs, const MatDesc &one, const int *members, const int *wg_start,
+                         int n_members, int64_t total_wg, int rpw, int64_t C, const int32_t *rp, const int32_t *cp, T *out)
 {
-    SBITS_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&gather_kernel<float>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
-    SBITS_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&gather_kernel<uint16_t>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+    const size_t lds = (size_t)rpw * (((size_t)C * sizeof(T) + 1023) / 1024 * 1024);
+    const bool large = lds > 53 * 1024;
+    auto *fn = large ? &gather_kernel<T, 1024> : &gather_kernel<T, 512>;
+    SBITS_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+    hipLaunchKernelGGL(fn, dim3((unsigned)total_wg), dim3(large ? 1024 : 512), lds, ctx->stream, descs, one, members, wg_start,
+                       n_members, rpw, rp, cp, out);
+    SBITS_HIP(ctx, hipGetLastError());
     return SBITS_OK;
 }
 
@@ -701,25 +723,17 @@ int sbits_launch_gather(sbits_ctx *ctx, const void *W, const float *S, int64_t R
                         void *w_out, float *s_out)
 {
     if ((size_t)C * 4 > 160 * 1024) return SBITS_ERR_BAD_SHAPE;
-    int rc = gather_attr(ctx);
-    if (rc) return rc;
     MatDesc one = single_desc(W, S, R, C, ld_w, ld_s, SC_ROWS);
-    const int *nul = nullptr;
+    int rc = SBITS_OK;
     if (w_out) {
         const int rpw = gather_rows_per_wg(C, 2);
-        hipLaunchKernelGGL(gather_kernel<uint16_t>, dim3((unsigned)((R + rpw - 1) / rpw)), dim3(GA_THREADS),
-                           (size_t)rpw * C * 2, ctx->stream, (const MatDesc *)nullptr, one, nul, nul, 1, rpw,
-                           rp, cp, static_cast<uint16_t *>(w_out));
-        SBITS_HIP(ctx, hipGetLastError());
+        rc = launch_gather(ctx, nullptr, one, nullptr, nullptr, 1, (R + rpw - 1) / rpw, rpw, C, rp, cp, static_cast<uint16_t *>(w_out));
     }
-    if (s_out) {
+    if (!rc && s_out) {
         const int rpw = gather_rows_per_wg(C, 4);
-        hipLaunchKernelGGL(gather_kernel<float>, dim3((unsigned)((R + rpw - 1) / rpw)), dim3(GA_THREADS),
-                           (size_t)rpw * C * 4, ctx->stream, (const MatDesc *)nullptr, one, nul, nul, 1, rpw,
-                           rp, cp, s_out);
-        SBITS_HIP(ctx, hipGetLastError());
+        rc = launch_gather(ctx, nullptr, one, nullptr, nullptr, 1, (R + rpw - 1) / rpw, rpw, C, rp, cp, s_out);
     }
-    return SBITS_OK;
+    return rc;
 }
 
 // ---- all matrices of the plan (descriptor table already in the workspace head) ------------
@@ -849,8 +863,6 @@ int sbits_launch_gather_all(sbits_plan *plan, const int32_t *row_perm, const int
 {
     sbits_ctx *ctx = plan->ctx;
     if ((size_t)plan->max_cols * 4 > 160 * 1024) return SBITS_ERR_BAD_SHAPE;
-    int rc = gather_attr(ctx);
-    if (rc) return rc;
     if (plan->gather_members.empty()) {
         std::vector<int64_t> classes;
         for (int i = 0; i < plan->n_mats; ++i) {
@@ -895,21 +907,14 @@ int sbits_launch_gather_all(sbits_plan *plan, const int32_t *row_perm, const int
     memset(&none, 0, sizeof none);
     const MatDesc *descs = sbits_desc_ptr(ws);
     for (const sbits_plan::GatherClass &gc : plan->gather_classes) {
-        if (w_re) {
-            const int tot = plan->gather_pre_w[gc.pre_first + gc.n];
-            hipLaunchKernelGGL(gather_kernel<uint16_t>, dim3((unsigned)tot), dim3(GA_THREADS),
-                               (size_t)gc.rpw_w * gc.cols * 2, ctx->stream, descs, none, d_mem + gc.first,
-                               d_pw + gc.pre_first, gc.n, gc.rpw_w, row_perm, col_perm,
-                               static_cast<uint16_t *>(w_re));
-            SBITS_HIP(ctx, hipGetLastError());
-        }
-        if (s_re) {
-            const int tot = plan->gather_pre_s[gc.pre_first + gc.n];
-            hipLaunchKernelGGL(gather_kernel<float>, dim3((unsigned)tot), dim3(GA_THREADS),
-                               (size_t)gc.rpw_s * gc.cols * 4, ctx->stream, descs, none, d_mem + gc.first,
-                               d_ps + gc.pre_first, gc.n, gc.rpw_s, row_perm, col_perm, s_re);
-            SBITS_HIP(ctx, hipGetLastError());
-        }
+        int rc = SBITS_OK;
+        if (w_re)
+            rc = launch_gather(ctx, descs, none, d_mem + gc.first, d_pw + gc.pre_first, gc.n, plan->gather_pre_w[gc.pre_first + gc.n],
+                               gc.rpw_w, gc.cols, row_perm, col_perm, static_cast<uint16_t *>(w_re));
+        if (!rc && s_re)
+            rc = launch_gather(ctx, descs, none, d_mem + gc.first, d_ps + gc.pre_first, gc.n, plan->gather_pre_s[gc.pre_first + gc.n],
+                               gc.rpw_s, gc.cols, row_perm, col_perm, s_re);
+        if (rc) return rc;
     }
     return SBITS_OK;
 }
