@@ -286,13 +286,14 @@ __device__ __forceinline__ unsigned int wave_prefix(unsigned int v)
 // most w_max step bits: of the keyU, or (down) of the keyD of the blocks outside the set keyU >= excl_tau.
 // v = key >> 8 is compared; the first round's bins cover [lo, hi), where nearly all values lie, and its
 // outermost bins everything below and above, so values outside are found as well, a round later.
-// sh.hist is all zero before and after.
+// A negative limit (levels over budget by more than a swap frees) lets nothing in.  sh.hist is all zero before and after.
 template <bool RES>
 __device__ __forceinline__ Sel select(Team &t, AllocShared &sh, Slice<RES> &own, bool down, u64 excl_tau, u64 key_min,
                                       int cnt_max, int w_max, u64 lo, u64 hi, int TB)
 {
     const int tid = (int)threadIdx.x;
     Sel r;
+    if (cnt_max < 0 || w_max < 0) { r.tau = ~0ull; r.n_sel = r.w_sel = 0; return r; }   // (the same in every workgroup: no exchange)
     int c0 = 0, w0 = 0;                              // totals of the keys above the current interval
     u64 from = 0, to = 0;                            // the interval after the first round
     int sh_bin = 0;

@@ -113,6 +113,49 @@ def test_propose_at_the_edges_of_the_work_split(orc, ctx, dev, N):
     plan.close()
 
 
+def _freed(s_up, s_dn, level, bits, k):
+    """Step bits that the lowered set of a swap frees: the first h by s_down outside the first h by s_up."""
+    h, K, widths = max(1, k // 2), len(bits), np.asarray(bits)
+    up = np.flatnonzero(level < K - 1)
+    raised = up[np.argsort(-s_up[up], kind="stable")][:h]
+    dn = np.setdiff1d(np.flatnonzero(level > 0), raised)
+    dn = dn[np.argsort(s_dn[dn], kind="stable")][:h]
+    return int((widths[level[dn]] - widths[level[dn] - 1]).sum())
+
+
+@pytest.mark.parametrize("N", [1500, 6000, 524304])       # one workgroup, several, blocks in memory
+def test_propose_on_levels_over_budget(orc, ctx, dev, N):
+    """The bits in use exceed the budget by more, as much and less than the lowered set frees: what does not fit is not
+    proposed, and the counts are those of the levels written."""
+    say("propose over budget", N, sb.LIB_PATH)
+    bits = [1, 2, 4, 5]
+    plan, ws = plan_with_blocks(ctx, N, bits, dev)
+    rng = np.random.default_rng(N + 1)
+    for case in ("far", "one too many", "all of it", "one left", "nobody to lower", "nobody to raise"):
+        level = rng.integers(0, len(bits), N).astype(np.uint8)
+        s_up, s_dn = rng.standard_normal(N).astype(np.float32), np.abs(rng.standard_normal(N)).astype(np.float32)
+        k = N // 20
+        if case == "nobody to lower":                     # all above the lowest candidate are in the raised set
+            level[:] = 0
+            some = rng.choice(N, k // 4, replace=False)
+            level[some], s_up[some] = 1, 50.0 + s_up[some]
+        elif case == "nobody to raise":
+            level[:] = len(bits) - 1
+        used, freed = int(np.asarray(bits)[level].sum()), _freed(s_up, s_dn, level, bits, k)
+        over = {"far": N, "one too many": freed + 1, "all of it": freed, "one left": freed - 1, "nobody to lower": k // 4,
+                "nobody to raise": 2 * N}[case]
+        avg = (used - over) / N + 1e-9
+        kind, want, winfo = orc.propose(s_up, s_dn, level, bits, avg, k)
+        out = torch.full((N,), 77, dtype=torch.uint8, device=dev)
+        info = plan.propose(torch.from_numpy(s_up).to(dev), torch.from_numpy(s_dn).to(dev), torch.from_numpy(level).to(dev),
+                            avg, k, out, ws)
+        got = out.cpu().numpy()
+        assert info["kind"] == kind and all(info[f] == winfo[f] for f in winfo), (case, info, kind, winfo)
+        np.testing.assert_array_equal(got, want, err_msg=case)
+        assert int(np.asarray(bits)[got].sum()) == info["bits_after"], case
+    plan.close()
+
+
 def test_propose_replays_from_a_captured_graph(orc, dev):
     say("propose in a graph")
     N, bits = 9000, [1, 2, 3, 4]
