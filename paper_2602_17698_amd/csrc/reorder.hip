@@ -485,8 +485,8 @@ constexpr int GA_LDS_TARGET = 48 * 1024;            // rows per workgroup are ch
 // column count, hence equal LDS need): members[] lists them, wg_start[] is their workgroup prefix.
 // Bound by HBM: the rows come in by direct loads to LDS, all of a workgroup's rows under way at once (through registers a
 // wave had one load of 1 KiB in flight), and the column indices of a thread are requested a chunk ahead, the first behind
-// the rows.  8192 x 28672: fp32 477 -> 373 us (5.0 TB/s), bf16 198 -> 209; two matrices of 4096
-// and 14336 columns: fp32 651 -> 633, bf16 346 -> 324.
+// the rows.  Through registers -> now: 8192 x 28672 fp32 477 -> 341 us (5.5 TB/s), bf16 197 -> 171; 8192 x 14336 193 -> 163
+// and 98 -> 88; 16384 x 2048 57 -> 47 and 40 -> 25.
 template <class T, int TH>
 __global__ __launch_bounds__(TH)
 void gather_kernel(const MatDesc *__restrict__ descs, MatDesc one, const int *__restrict__ members,
@@ -512,12 +512,14 @@ void gather_kernel(const MatDesc *__restrict__ descs, MatDesc one, const int *__
     const int bytes = C * (int)sizeof(T), pieces = (bytes + 1023) / 1024;       // a row takes whole KiB of LDS
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
 
-    for (int q = wave; q < nr * pieces; q += TH / 64) {       // a piece (1 KiB of a row) per wave and turn
-        const int r = q / pieces, p = q - r * pieces;
-        int sr = rp[i0 + r];
-        sr = sr < 0 ? 0 : (sr >= R ? R - 1 : sr);   // a permutation never trips this; keeps a bad one in bounds
-        const T *src = in + (int64_t)sr * ld;
-        const uint32_t at = (uint32_t)q * 1024u;
+    // Source rows: one load, a row per lane (at most 8).  An index loaded per piece is a wait per piece, and with one long row
+    // per workgroup that chain is longer than the row's own loads (8192 x 28672: bf16 202 us, fp32 369).  A permutation
+    // never trips the clamp; it keeps a bad one in bounds.
+    const int source = min(max(rp[i0 + min(lane, nr - 1)], 0), R - 1);
+    int r = wave / pieces, p = wave - r * pieces;             // this wave's piece: 1 KiB of a row, one per turn
+    while (r < nr) {
+        const T *src = in + (int64_t)__builtin_amdgcn_readlane(source, r) * ld;
+        const uint32_t at = (uint32_t)(r * pieces + p) * 1024u;
         if ((reinterpret_cast<uintptr_t>(src) & 15) == 0) {   // (lanes past the row's end: its last 16 bytes, into the padding)
             const uint32_t off = min((uint32_t)p * 1024u + (uint32_t)lane * 16u, (uint32_t)bytes - 16u);
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(reinterpret_cast<const char *>(src) + off),
@@ -528,6 +530,7 @@ void gather_kernel(const MatDesc *__restrict__ descs, MatDesc one, const int *__
                 if (c < C) reinterpret_cast<T *>(smem + at)[j] = *(gtp)(src + c);
             }
         }
+        for (p += TH / 64; p >= pieces; p -= pieces) ++r;
     }
     struct Index { int4 a, b; };
     auto indices = [&](int j) {
@@ -703,7 +706,8 @@ int sbits_launch_reorder(sbits_ctx *ctx, const float *S, int64_t R, int64_t C, i
     return run_argsort(ctx, SortArrays{nullptr, one, 1, 1, R, nullptr, nullptr, row_perm, col_perm}, len, len, w);
 }
 
-// Workgroups of 512 threads, of 1024 where fewer than three fit a CU's LDS (8192 x 28672 bf16, two: 209 us against 222).
+// Workgroups of 512 threads, of 1024 where fewer than three fit a CU's LDS (fp32 8192 x 16384, two: 192 us against 198; 8192 x
+// 32768, one: 380 against 391; bf16 8192 x 28672, two: no difference beyond the noise).
 template <class T>
 static int launch_gather(sbits_ctx *ctx, const MatDesc *descs, const MatDesc &one, const int *members, const int *wg_start,
                          int n_members, int64_t total_wg, int rpw, int64_t C, const int32_t *rp, const int32_t *cp, T *out)
