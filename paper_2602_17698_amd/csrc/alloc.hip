@@ -30,7 +30,7 @@
 // written back or invalidated.  A round takes 4 to 6 us that way, 2 us within one workgroup (512 threads: a
 // wave's share of the scan is repeated per wave; 1024 threads spill and 256 leave the LDS atomics too few waves).
 // Whole searches, launch per round before -> now: 107 k blocks, 24 iterations 2.72 -> 0.75 ms; 430 k blocks, 22 iterations
-// 2.27 -> 0.79 ms; 4.3 M blocks 5.1 -> 3.9 ms; one proposal on 430 k blocks 157 -> 72 us.
+// 2.27 -> 0.79 ms; 4.2 M blocks 4.9 -> 3.6 ms; one proposal on 430 k blocks 157 -> 72 us.
 #include <math.h>
 #include <string.h>
 
@@ -223,9 +223,9 @@ struct Slice {
     long long n0, n1;
 
     // f(first block of the batch, batch): block u of it is first + u * AL_THREADS, there if < n1 (else its keys are 0).
-    // What f changes is kept (WR) in all three arrays.
+    // What f changes is kept (WR) in all three arrays.  need_kd: f looks at keyD (from memory it is half of the bytes).
     template <bool LV, bool WR, class F>
-    __device__ __forceinline__ void visit(F &&f)
+    __device__ __forceinline__ void visit(F &&f, bool need_kd = true)
     {
         if constexpr (RES) {
             f(n0 + (int)threadIdx.x, reg);
@@ -236,8 +236,15 @@ struct Slice {
                 for (int u = 0; u < AL_KPT; ++u) {
                     const long long i = i0 + (long long)u * AL_THREADS;
                     b.ku[u] = i < n1 ? mu[i] : 0ull;
-                    b.kd[u] = i < n1 ? md[i] : 0ull;
+                    b.kd[u] = 0ull;
                     b.lv[u] = LV && i < n1 ? (int)level[i] : 0;
+                }
+                if (need_kd) {
+#pragma unroll
+                    for (int u = 0; u < AL_KPT; ++u) {
+                        const long long i = i0 + (long long)u * AL_THREADS;
+                        b.kd[u] = i < n1 ? md[i] : 0ull;
+                    }
                 }
                 f(i0, b);
                 if constexpr (WR) store(i0, b);
@@ -286,14 +293,13 @@ __device__ __forceinline__ unsigned int wave_prefix(unsigned int v)
 // most w_max step bits: of the keyU, or (down) of the keyD of the blocks outside the set keyU >= excl_tau.
 // v = key >> 8 is compared; the first round's bins cover [lo, hi), where nearly all values lie, and its
 // outermost bins everything below and above, so values outside are found as well, a round later.
-// A negative limit (levels over budget by more than a swap frees) lets nothing in.  sh.hist is all zero before and after.
+// Neither limit is negative.  sh.hist is all zero before and after.
 template <bool RES>
 __device__ __forceinline__ Sel select(Team &t, AllocShared &sh, Slice<RES> &own, bool down, u64 excl_tau, u64 key_min,
                                       int cnt_max, int w_max, u64 lo, u64 hi, int TB)
 {
     const int tid = (int)threadIdx.x;
     Sel r;
-    if (cnt_max < 0 || w_max < 0) { r.tau = ~0ull; r.n_sel = r.w_sel = 0; return r; }   // (the same in every workgroup: no exchange)
     int c0 = 0, w0 = 0;                              // totals of the keys above the current interval
     u64 from = 0, to = 0;                            // the interval after the first round
     int sh_bin = 0;
@@ -317,7 +323,7 @@ __device__ __forceinline__ Sel select(Team &t, AllocShared &sh, Slice<RES> &own,
                 }
                 atomicAdd(&sh.hist[SEL_BINS - 1 - bin], ((key & 255ull) << 32) | 1ull);   // descending: the top bin first
             }
-        });
+        }, down);
         __syncthreads();
         if (t.G > 1) {
             AllocXchg *x = xchg(t);
@@ -428,8 +434,9 @@ struct Ranges { u64 loU, hiU, loD, hiD; int TB, IB; };
 // The sets of one iteration of Algorithm 2.  e: the expansion (not tried without slack): the first k blocks by
 // keyU with a value above zero that fit the slack.  If it is empty, the balanced swap: u = the first h by keyU,
 // d = the first h by keyD outside u, u2 = the longest prefix of u whose step bits fit the slack plus the bits d
-// frees.  (One loop around one copy of the selection: inlined four times it spills.)
-template <bool RES>
+// frees.  (One loop around one copy of the selection: inlined four times it spills.)  STEP: the levels are the caller's and
+// may be over budget; the search's own never are.
+template <bool STEP, bool RES>
 __device__ __forceinline__ void choose_sets(Team &t, AllocShared &sh, Slice<RES> &own, long long k, long long slack,
                                             const Ranges &rg, Sel &e, Sel &u, Sel &d, Sel &u2)
 {
@@ -457,6 +464,8 @@ __device__ __forceinline__ void choose_sets(Team &t, AllocShared &sh, Slice<RES>
             d = r;
             u2 = u;
             if (u.w_sel <= slack + d.w_sel) return;                  // all of u fits
+            if constexpr (STEP)
+                if (slack + d.w_sel < 0) { u2 = Sel{~0ull, 0, 0}; return; }   // over by more than d frees: nothing of u does
             phase = UP2;
         } else {
             u2 = r;
@@ -512,23 +521,34 @@ void search_kernel(AllocState *st, const float *__restrict__ cost, const float *
 
     if constexpr (STEP) {
         u64 red[5] = {0, 0, 0, 0, 0};                // s_up: largest, smallest inverted; s_down: the same; bits in use
-        // (the keys go to memory in either form: the kernel that applies the step reads them)
+        // (The keys go to memory in either form: the kernel that applies the step reads them.  All loads of a batch are
+        // requested before any is used, the estimates whether the level needs them or not: one level after the other, each
+        // followed by its estimates, an expansion over 16.7 M blocks takes 100 us longer.)
         for (long long i0 = own.n0 + tid; i0 < own.n1; i0 += (long long)AL_KPT * AL_THREADS) {
+            int lv[AL_KPT];
+            float up[AL_KPT], dn[AL_KPT];
+#pragma unroll
+            for (int q = 0; q < AL_KPT; ++q) {
+                const long long i = i0 + (long long)q * AL_THREADS;
+                lv[q] = i < own.n1 ? (int)level[i] : 0;
+                up[q] = i < own.n1 ? s_up[i] : 0.0f;
+                dn[q] = i < own.n1 ? s_down[i] : 0.0f;
+            }
 #pragma unroll
             for (int q = 0; q < AL_KPT; ++q) {
                 const long long i = i0 + (long long)q * AL_THREADS;
                 if (i >= own.n1) continue;
-                const int l = min((int)level[i], K - 1);
+                const int l = min(lv[q], K - 1);
                 red[4] += (u64)bits[l];
                 const u64 low = (u64)(N - 1 - i) << 8;
                 u64 ku = 0, kd = 0;
                 if (l < K - 1) {
-                    const unsigned int o = ord_f32(s_up[i]);
+                    const unsigned int o = ord_f32(up[q]);
                     ku = ((u64)o << (IB + 8)) | low | (unsigned)(bits[l + 1] - bits[l]);
                     if (o > 0x80000000u) { red[0] = max(red[0], (u64)o); red[1] = max(red[1], (u64)~o); }
                 }
                 if (l > 0) {
-                    const unsigned int o = ord_f32(s_down[i]);
+                    const unsigned int o = ord_f32(dn[q]);
                     kd = ((u64)(~o) << (IB + 8)) | low | (unsigned)(bits[l] - bits[l - 1]);
                     if (o > 0x80000000u) { red[2] = max(red[2], (u64)o); red[3] = max(red[3], (u64)~o); }
                 }
@@ -544,7 +564,7 @@ void search_kernel(AllocState *st, const float *__restrict__ cost, const float *
         value_range(red[2], red[3], IB, q0, q1, rg.loD, rg.hiD);
         used = (long long)red[4];
         Sel e, u, d, u2;
-        choose_sets(t, sh, own, k, T - used, rg, e, u, d, u2);
+        choose_sets<STEP>(t, sh, own, k, T - used, rg, e, u, d, u2);
         if (!t.ok) return;
         // (a swap is a proposal: the caller accepts or rejects it)
         const int mode = e.n_sel > 0 ? MODE_EXPAND : u2.n_sel > 0 && d.n_sel > 0 ? MODE_ACCEPT : MODE_NONE;
@@ -626,7 +646,7 @@ void search_kernel(AllocState *st, const float *__restrict__ cost, const float *
         };
         while (!done) {
             Sel e, u, d, u2;
-            choose_sets(t, sh, own, k, T - used, rg, e, u, d, u2);
+            choose_sets<STEP>(t, sh, own, k, T - used, rg, e, u, d, u2);
             if (!t.ok) return;
             if (e.n_sel > 0) {
                 move([&](u64 ku, u64) { return ku >= e.tau ? 1 : 0; });
@@ -730,11 +750,15 @@ static int ceil_log2_ll(long long v) { int p = 0; while ((1ll << p) < v) ++p; re
 // Workgroups of a search over N blocks: 2048 blocks each (four to a thread) up to 32 workgroups, beyond that
 // 4096, the most their registers hold (14 k blocks, 23 iterations: 360 us with 7 workgroups, 401 with 4; 430 k blocks,
 // 22 iterations: 788 us with 105, 837 with 128).  At most half of the device's CUs, so that two searches fit side
-// by side; larger tables live in memory then (4.3 M blocks: 3.9 ms; 5.1 ms with a launch per round).
-static unsigned search_wgs(int64_t N)
+// by side; larger tables live in memory then (4.2 M blocks: 3.6 ms; 4.9 ms with a launch per round).  A single step over a
+// table in memory is a pass or two over it and needs a third of the registers, so beyond 2 M blocks it takes a workgroup
+// per 16384 blocks, up to twice as many (16.7 M blocks: 371 us, 533 with 128, 535 with a launch per round; 1 M: 76 and 72).
+static unsigned search_wgs(int64_t N, bool step)
 {
     const int64_t g = N <= 32 * 2048 ? (N + 2047) / 2048 : (N + 4095) / 4096;
-    return (unsigned)(g < AL_MAX_WG ? g : AL_MAX_WG);
+    int64_t most = AL_MAX_WG;
+    if (step && N / 16384 > most) most = N / 16384 < 2 * AL_MAX_WG ? N / 16384 : 2 * AL_MAX_WG;
+    return (unsigned)(g < most ? g : most);
 }
 
 // A wait between workgroups polls this often before it is given up (about half a second).
@@ -833,7 +857,7 @@ int sbits_run_allocate(sbits_plan *plan, const float *cost, double avg_bits,
     // The workgroups wait for each other.  Should the device be so full that they never run together, they
     // give up (see grid_sync) and one workgroup, which waits for nobody, does the search.
     AllocHead h;
-    for (unsigned G = search_wgs(N);; G = 1) {
+    for (unsigned G = search_wgs(N, false);; G = 1) {
         hipLaunchKernelGGL(set_state_kernel, dim3(1), dim3(AL_THREADS), 0, sm, w.st, h0);
         launch_search<false>(sm, G, w, N, cost, nullptr, nullptr, level, 0);
         SBITS_HIP(ctx, hipGetLastError());
@@ -870,7 +894,7 @@ int sbits_run_propose(sbits_plan *plan, const float *s_up, const float *s_down, 
     h.k = k;
     // the start state travels as a kernel argument: nothing to keep alive, nothing to wait for
     hipLaunchKernelGGL(set_state_kernel, dim3(1), dim3(AL_THREADS), 0, sm, w.st, h);
-    const unsigned G = search_wgs(N);
+    const unsigned G = search_wgs(N, true);
     uint8_t *const lv = const_cast<uint8_t *>(level_in);             // (only read by the step)
     launch_search<true>(sm, G, w, N, nullptr, s_up, s_down, lv, 0);
     if (G > 1) launch_search<true>(sm, 1, w, N, nullptr, s_up, s_down, lv, 1);   // returns at once unless the first gave up

@@ -88,7 +88,7 @@ def test_allocate_where_values_lie_outside_the_first_bins(orc, ctx, dev):
         plan.close()
 
 
-@pytest.mark.parametrize("N", [2048, 2050, 524304])
+@pytest.mark.parametrize("N", [2048, 2050, 524304, 3147776])     # the last: more workgroups than a search takes
 def test_propose_at_the_edges_of_the_work_split(orc, ctx, dev, N):
     say("propose", N, sb.LIB_PATH)
     bits = [1, 2, 3, 4, 8]
