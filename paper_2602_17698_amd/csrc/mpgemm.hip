@@ -1029,15 +1029,57 @@ bool sbits_mp_gemm_shapes_ok(const sbits_plan *plan)
     return (plan->n == 64 || plan->n == 128) && plan->m % 32 == 0;
 }
 
-// partial sums of the largest matrix at the largest batch (32)
+// Work split of the product of more than 32 rows, by the matrix and the batch groups alone, so that a product's sums do not
+// depend on what else is in its plan.
+// Workgroups of 128 or of 64 channels, one per CU at a time.  Column splits while every CU has at most one: an even number of
+// steps each (the kernel takes them in pairs: three cost as much as four; three in all of a small matrix are split one by one), at most 32 of
+// them (one thread adds their partial sums: 64 x 32768 in 64-column blocks 128 splits of one step 37 us, 64 of two 23, 32 of
+// four 19), and not to save two steps where the partial sums are large (8192 x 1024, 64-column blocks, 64 rows: 11.6 us,
+// 12.5 with two splits).  They take 8 MiB at most.
+// The shape that takes less time by this estimate is taken (in hundredths of a microsecond above the launch: a turn of the CUs
+// costs 3 us and 1.65 or, in 64-column blocks, 1.25 a step): 14336 x 4096 at 64 rows 26 us with 224 workgroups of 64, 38 with
+// 112 of 128; 11008 x 4096 at 100 rows 36 with 172 of 128, 43 with 344 of 64 in two turns; 10240 x 8192 at 33 rows 29 with three
+// splits of 80 of 128, 36 with 160 of 64.
+struct WideSplit { int rg, per_split, n_split; int64_t cost; };
+static WideSplit wide_split(int64_t R, int nbc, int n, int batch)
+{
+    const int64_t z = (batch + 63) / 64;
+    auto with = [&](int rg) {
+        WideSplit o;
+        const int64_t tiles = (R + rg * 32 - 1) / (rg * 32) * z, jl = WG_WAVES / rg, steps = (nbc + jl - 1) / jl;
+        const int64_t most = 256 / tiles < 32 ? 256 / tiles : 32;
+        o.rg = rg;
+        o.per_split = nbc;
+        if (most > 1 && !(steps <= 4 && R * z * 64 > 1 << 18)) {
+            const int64_t cols = (steps == 3 && most > 2 && R * z * 64 <= 1 << 17 ? 1 : ((steps + most - 1) / most + 1) / 2 * 2) * jl;
+            if (cols < nbc) o.per_split = (int)cols;
+        }
+        o.n_split = (nbc + o.per_split - 1) / o.per_split;
+        const int64_t pairs = ((o.per_split + jl - 1) / jl + 1) / 2, turns = (tiles * o.n_split + 255) / 256;
+        o.cost = turns * (300 + pairs * 2 * (n == 128 ? 165 : 125));
+        if (turns > 1 && rg == 2) o.cost += o.cost / 20;
+        if (o.n_split > 1) o.cost += 200 + 20 * o.n_split + o.n_split * z * R / 160;   // the second launch and the partial sums
+        return o;
+    };
+    const WideSplit a = with(4), b = with(2);
+    return a.cost < b.cost ? a : b;
+}
+
+// partial sums of the largest matrix: 32 rows of the first kernel, 64 or 128 (one and two batch groups: fewer rows have the
+// same splits) of the one for many rows
 size_t sbits_mp_gemm_ws_bytes(const sbits_plan *plan)
 {
     if (!sbits_mp_gemm_shapes_ok(plan)) return 0;
     size_t mx = 0;
     for (int i = 0; i < plan->n_mats; ++i) {
-        const int s = sbits_mp_gemm_splits(plan->cols[i], plan->n);
-        const size_t b = s > 1 ? (size_t)s * 32 * (size_t)plan->rows[i] * 4 : 0;
-        if (b > mx) mx = b;
+        const int nbc = (int)(plan->cols[i] / plan->n);
+        auto need = [&](int splits, int batch) {
+            const size_t b = splits > 1 ? (size_t)splits * batch * (size_t)plan->rows[i] * 4 : 0;
+            if (b > mx) mx = b;
+        };
+        need(sbits_mp_gemm_splits(plan->cols[i], plan->n), 32);
+        need(wide_split(plan->rows[i], nbc, plan->n, 64).n_split, 64);
+        need(wide_split(plan->rows[i], nbc, plan->n, 128).n_split, 128);
     }
     return sbits_align_up(mx, 256);
 }
@@ -1109,20 +1151,7 @@ int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t 
     a.R = (int)plan->rows[mat]; a.C = (int)plan->cols[mat]; a.m = plan->m; a.nbc = a.C / plan->n;
     a.batch = batch;
     const bool wide = batch > 32;
-    int per_split = a.nbc, rg = 4;
-    if (wide) {
-        // 128 channels a workgroup where that gives three quarters of the CUs one (x is staged half as often), else 64 and
-        // column splits until every CU has one, as far as the scratch holds the splits' partial sums.  (14336 x 4096 at 64
-        // rows: 38 us with 128 channels on 112 CUs, 26 us with 64 on 224.)
-        const int64_t z = (batch + 63) / 64;
-        if ((a.R + 127) / 128 * z < 192) rg = 2;
-        const int64_t tiles = (a.R + rg * 32 - 1) / (rg * 32) * z, jl = WG_WAVES / rg;
-        const int64_t room = (int64_t)(plan->ws_bytes - plan->head_bytes) / ((int64_t)batch * a.R * 4);
-        int64_t want = 256 / tiles, steps = (a.nbc + jl - 1) / jl;
-        if (want > steps) want = steps;
-        if (want > room) want = room;
-        if (want > 1) per_split = (int)((steps + want - 1) / want * jl);
-    }
+    const WideSplit ws = wide ? wide_split(a.R, a.nbc, plan->n, batch) : WideSplit{0, 0, 0, 0};
     if (takes_narrow(a, plan->n)) {
         a.n_split = 1;
         a.out = y;
@@ -1132,14 +1161,14 @@ int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t 
         SBITS_HIP(ctx, hipGetLastError());
         return SBITS_OK;
     }
-    a.n_split = wide ? (a.nbc + per_split - 1) / per_split : sbits_mp_gemm_splits(a.C, plan->n);
+    a.n_split = wide ? ws.n_split : sbits_mp_gemm_splits(a.C, plan->n);
     for (int c = 0; c < sbits::MAX_CAND; ++c) a.bits[c] = c < plan->K ? plan->bits[c] : plan->bits[plan->K - 1];
     a.out = a.n_split > 1 ? static_cast<float *>(scratch) : y;
-    const int rows = wide ? rg * 32 : MG_RG * 32;
+    const int rows = wide ? ws.rg * 32 : MG_RG * 32;
     const dim3 grid((unsigned)((a.R + rows - 1) / rows), (unsigned)a.n_split, (unsigned)(wide ? (batch + 63) / 64 : 1));
     const int nb = batch <= 16 ? 1 : 2;
     int rc;
-    if (wide) rc = rg == 4 ? launch_wide_rg<4>(ctx, plan->n, a, grid, per_split) : launch_wide_rg<2>(ctx, plan->n, a, grid, per_split);
+    if (wide) rc = ws.rg == 4 ? launch_wide_rg<4>(ctx, plan->n, a, grid, ws.per_split) : launch_wide_rg<2>(ctx, plan->n, a, grid, ws.per_split);
     else if (plan->n == 128) rc = nb == 1 ? launch_mp<128, 1>(ctx, a, grid) : launch_mp<128, 2>(ctx, a, grid);
     else rc = nb == 1 ? launch_mp<64, 1>(ctx, a, grid) : launch_mp<64, 2>(ctx, a, grid);
     if (rc) return rc;

@@ -41,6 +41,9 @@ ALL = [1, 2, 3, 4, 5, 6, 7, 8]
     (32, 128, 32, 128, ALL[2:3], 40, 1 << 20),            # a pitch past 32-bit offsets of a batch group: 32 rows a launch
     (64, 128 * 4, 32, 128, [1], 80, 0),                   # 1 bit: products of its own
     (64, 64 * 5, 32, 64, [1], 50, 0),
+    (96, 128 * 10, 32, 128, ALL, 40, 0),                  # column splits: three of one step, 25 of four, six of an even number
+    (64, 64 * 400, 64, 64, [2, 5, 8], 64, 0),
+    (320, 128 * 46, 32, 128, [1, 3, 7], 90, 0),
 ])
 def test_product_edges(orc, R, C, m, n, bits, batch, pad):
     print("[case] product", R, C, m, n, bits, batch, flush=True)
@@ -79,4 +82,40 @@ def test_product_edges(orc, R, C, m, n, bits, batch, pad):
     assert np.all(err <= bound * 2.0 ** -22 + 1e-30), float((err / (bound + 1e-300)).max())
     assert np.sqrt((err ** 2).mean()) <= 2.0 ** -24 * np.sqrt((bound ** 2).mean())
     plan.close()
+    ctx.close()
+
+
+@pytest.mark.parametrize("R,C,m,n,batch", [(1024, 4096, 128, 128, 100), (256, 8192, 32, 64, 64), (32, 16384, 32, 128, 33), (64, 32768, 64, 64, 128),
+                                           (2048, 4096, 128, 128, 250)])
+def test_product_does_not_depend_on_the_rest_of_the_plan(R, C, m, n, batch):
+    """A matrix alone in its plan and next to one whose stages need a far larger workspace: the same bits, and nothing is
+    written behind the workspace that the plan asks for."""
+    print("[case] product alone and in company", R, C, m, n, batch, flush=True)
+    dev = torch.device("cuda:0")
+    bits, g = [2, 3, 4, 8], torch.Generator(device=dev)
+    g.manual_seed(R + C)
+    ctx = sb.Context(0, torch.cuda.current_stream().cuda_stream)
+    w = (0.02 * torch.randn(R, C, generator=g, device=dev)).to(torch.bfloat16)
+    x = torch.randn(batch, C, generator=g, device=dev).to(torch.bfloat16)
+    nb = (R // m) * (C // n)
+    lv = torch.randint(0, 4, (nb,), generator=g, device=dev).to(torch.uint8)
+    out = []
+    for shapes in ([(R, C)], [(R, C), (16384, 16384)]):
+        plan = sb.Plan(ctx, shapes, m, n, bits)
+        N, need = plan.num_blocks(), plan.workspace_bytes()
+        ws = torch.full((need + 65536,), 0x5A, dtype=torch.uint8, device=dev)
+        level = torch.zeros(N, dtype=torch.uint8, device=dev)
+        level[:nb] = lv
+        off = torch.empty(N + 1, dtype=torch.int64, device=dev)
+        plan.offsets(level, off, ws)
+        codes = torch.zeros(int(off[-1]), dtype=torch.uint8, device=dev)
+        scale, zero = torch.zeros(N * m, device=dev), torch.zeros(N * m, device=dev)
+        plan.pack(0, w, level, off, codes, scale, zero)
+        y = torch.full((batch, R), -7.0, device=dev)
+        plan.mp_gemm(0, x, level, off, codes, scale, zero, y, ws)
+        torch.cuda.synchronize()
+        assert torch.all(ws[need:] == 0x5A)
+        out.append(y)
+        plan.close()
+    assert torch.equal(out[0], out[1])
     ctx.close()
