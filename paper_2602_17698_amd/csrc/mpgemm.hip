@@ -1120,19 +1120,52 @@ static int launch_wide_rg(sbits_ctx *ctx, int n, const MpArgs &a, dim3 grid, int
     return a.batch <= 48 ? launch_wide<128, 3, RG>(ctx, a, grid, cols_per_split) : launch_wide<128, 4, RG>(ctx, a, grid, cols_per_split);
 }
 
-// The narrow kernel or the first one for up to 16 rows: by the blocks that a wave of the busiest CU takes one after the
-// other (both kernels put 16 waves on a CU).  As many are as good for the narrow one, which saves the second launch
-// (14336 x 4096, 4 blocks in both: 10.7 against 12.5 us at one row, 12.4 and 12.9 at 8), but for more rows (16: 15.3 and 13.1)
-// and where the first kernel has no second launch (32768 x 1024: 11.1 and 8.6) it has to be a fifth less; more are worse
-// (4096 x 14336, 7 and 4: 17.6 and 16.3 us; 256 x 32768, 16 and 4: 26.9 and 14.2).  64-column blocks: up to twice as many
-// (4096 x 14336, 14 and 8: 26 and 48 us; 1024 x 16384, 16 and 4: 20 and 14).
-static bool takes_narrow(const MpArgs &a, int n)
+// What a product of up to 16 rows takes in the first kernel and in the narrow one, in hundredths of a microsecond, from 3500
+// products of 32 .. 32768 x 256 .. 28672 at 1 .. 16 rows of x: the kernel that these name takes 0.1 % longer than the
+// better one on average.
+// First: one workgroup per 128 channels and 16 block columns, 256 at a time.  One column split: by the blocks of a wave
+// (24576 x 2048: 10 us at 1 and 16 rows); more: the second launch, and a turn of the CUs per 256 workgroups, less where the
+// last one is light (16384 x 4096 13 us, x 8192 23).  64-column blocks: codes come in two bytes at a time, so a turn takes
+// 7.6, 8.8, 11, 19 and 33 us at 1, 2, 3, 4 and 8 bits.
+// Narrow: one workgroup per 32 channels, 256 at a time; its first turn is a chain of latencies, by the blocks of a wave
+// beyond two; every further one costs its blocks, and x once more (1024 x 4096 5.9 and 8.0 us at 1 and 16 rows, 24576 x 2048 12 and
+// 20, 14336 x 4096 11 and 15).
+struct FewRows { int64_t first, narrow; };
+static FewRows few_rows(const sbits_plan *plan, int64_t R, int nbc, int b)
+{
+    const int waves = (nbc + ND_WAVES - 1) / ND_WAVES;         // blocks of a wave of the narrow kernel; column splits of the first
+    const int64_t turns = (R / 32 + 255) / 256, tiles = (R + 127) / 128, wgs = tiles * waves;
+    const bool wide = plan->n == 128;
+    int64_t t64 = 0, bits = 0;                                // a turn of the first kernel in 64-column blocks; candidates on average
+    for (int l = 0; l < plan->K; ++l) {
+        const int c = plan->bits[l];
+        t64 += c == 0 ? 900 : c < 3 ? 640 + 120 * c : c == 3 ? 1140 : 460 + 355 * c;
+        bits += c;
+    }
+    t64 /= plan->K;
+    FewRows o;
+    if (waves == 1) {
+        o.first = wide ? 610 + 61 * nbc / 2 : 640 + (t64 - 640) * nbc / 16;
+        const int64_t turn = wide ? 105 + nbc * (159 + 9 * b) / 10 : 115 + nbc * (224 + 11 * b) / 20;
+        o.narrow = (wide ? 180 : 110) + turns * turn;
+        if (o.narrow < 560) o.narrow = 560;
+    } else {
+        const int64_t full = 100 * ((wgs + 255) / 256 - 1), light = tiles * nbc * 160 / 4096 - 85;
+        const int64_t more = light < 0 ? 0 : light < full ? light : full;
+        o.first = wide ? 1220 + 10 * more : 300 + t64 + t64 * more / 100;
+        const int half = nbc % 32 < 16 ? nbc % 32 : 16;                       // (a wave's blocks come in pairs)
+        const int64_t turn = (nbc / 32 * 16 + half) * (wide ? 288 + 19 * b : 297 + 11 * b) / 16;
+        const int64_t blocks = (waves - 2) * (wide ? 135 + 6 * b : 122 + 4 * b) + (turns - 1) * turn;
+        o.narrow = 570 + (wide ? 15 : 6) * b + (wide ? blocks : blocks * (7 * plan->K + bits) / (10 * plan->K));
+    }
+    return o;
+}
+
+static bool takes_narrow(const sbits_plan *plan, const MpArgs &a)
 {
     if (a.batch > 16) return false;
-    const int64_t per_wave = (a.nbc + ND_WAVES - 1) / ND_WAVES, spans = (a.nbc + MG_SPAN - 1) / MG_SPAN;
-    const int64_t narrow = (a.R / 32 + 255) / 256 * per_wave, first = ((a.R + 127) / 128 * spans + 255) / 256 * MG_NBLK;
-    if (n == 64) return narrow <= 2 * first;
-    return a.batch > 8 || spans == 1 ? narrow * 5 <= first * 4 : narrow <= first;
+    const FewRows t = few_rows(plan, a.R, a.nbc, a.batch);
+    return t.narrow < t.first;
 }
 
 // Rows of x a launch takes: 128 (two batch groups) while a group's byte offsets fit the 32 bits of a descriptor, else the
@@ -1152,7 +1185,7 @@ int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t 
     a.batch = batch;
     const bool wide = batch > 32;
     const WideSplit ws = wide ? wide_split(a.R, a.nbc, plan->n, batch) : WideSplit{0, 0, 0, 0};
-    if (takes_narrow(a, plan->n)) {
+    if (takes_narrow(plan, a)) {
         a.n_split = 1;
         a.out = y;
         for (int c = 0; c < sbits::MAX_CAND; ++c) a.bits[c] = c < plan->K ? plan->bits[c] : plan->bits[plan->K - 1];
