@@ -460,9 +460,8 @@ int sbits_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t ld_x, i
     int rc = need_device(plan);
     if (rc) return rc;
     // launches share the scratch in stream order
-    const int per = sbits_mp_gemm_rows(ld_x);
-    for (int b0 = 0; b0 < batch; b0 += per) {
-        const int nb = batch - b0 < per ? batch - b0 : per;
+    for (int b0 = 0, nb; b0 < batch; b0 += nb) {
+        nb = sbits_mp_gemm_rows(plan, mat, ld_x, batch - b0);
         rc = sbits_launch_mp_gemm(plan, mat, static_cast<const uint16_t *>(x_bf16) + (int64_t)b0 * ld_x, ld_x, nb, level,
                                   byte_off, codes, scale, zero, y + (int64_t)b0 * plan->rows[mat],
                                   sbits_scratch(plan, ws));

@@ -1168,9 +1168,22 @@ static bool takes_narrow(const sbits_plan *plan, const MpArgs &a)
     return t.narrow < t.first;
 }
 
-// Rows of x a launch takes: 128 (two batch groups) while a group's byte offsets fit the 32 bits of a descriptor, else the
-// 32 of the first kernel, whose addresses have 64.
-int sbits_mp_gemm_rows(int64_t ld_x) { return ld_x <= 1 << 20 ? 128 : 32; }
+// Rows of x the next launch takes of those that are left: 128 (two batch groups) while a group's byte offsets fit the 32 bits
+// of a descriptor, else the 32 of the first kernel, whose addresses have 64.  A second group of up to 32 rows costs the wide
+// kernel as much as one of 64, so it is left to the kernels for few rows where that is faster: 16640 x 4096 at 65 rows 51
+// us instead of 69, 20480 x 2048 33 instead of 39 (1024 x 4096: 12 us at once, 18 in two).
+int sbits_mp_gemm_rows(const sbits_plan *plan, int mat, int64_t ld_x, int left)
+{
+    if (ld_x > 1 << 20) return left < 32 ? left : 32;
+    if (left > 64 && left <= 96) {
+        const int64_t R = plan->rows[mat];
+        const int n = plan->n, nbc = (int)(plan->cols[mat] / n);
+        const FewRows t = few_rows(plan, R, nbc, left - 64 < 16 ? left - 64 : 16);
+        const int64_t rest = left - 64 > 16 ? t.first * 5 / 4 : t.narrow < t.first ? t.narrow : t.first;
+        if (wide_split(R, nbc, n, 64).cost + rest + 300 <= wide_split(R, nbc, n, left).cost) return 64;
+    }
+    return left < 128 ? left : 128;
+}
 
 int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t ld_x, int batch,
                          const uint8_t *level, const int64_t *byte_off, const uint8_t *codes, const float *scale,

@@ -125,7 +125,7 @@ int sbits_launch_dequant(sbits_plan *plan, int mat, const uint8_t *level, const 
 // mpgemm.hip
 bool sbits_mp_gemm_shapes_ok(const sbits_plan *plan);
 size_t sbits_mp_gemm_ws_bytes(const sbits_plan *plan);
-int sbits_mp_gemm_rows(int64_t ld_x);
+int sbits_mp_gemm_rows(const sbits_plan *plan, int mat, int64_t ld_x, int left);
 int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t ld_x, int batch,
                          const uint8_t *level, const int64_t *byte_off, const uint8_t *codes, const float *scale,
                          const float *zero, float *y, void *scratch);

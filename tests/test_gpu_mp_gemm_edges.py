@@ -44,6 +44,8 @@ ALL = [1, 2, 3, 4, 5, 6, 7, 8]
     (96, 128 * 10, 32, 128, ALL, 40, 0),                  # column splits: three of one step, 25 of four, six of an even number
     (64, 64 * 400, 64, 64, [2, 5, 8], 64, 0),
     (320, 128 * 46, 32, 128, [1, 3, 7], 90, 0),
+    (16512, 128 * 16, 128, 128, [2, 3], 70, 0),           # two batch groups would take turns: 64 rows, then 6
+    (16512, 64 * 40, 128, 64, [3, 4], 81, 0),             # and 17
     (12288, 128 * 16, 128, 128, [2, 6], 16, 0),           # few rows, several turns: the first kernel, then the narrow one
     (8224, 128 * 3, 32, 128, [4, 8], 7, 0),
 ])
