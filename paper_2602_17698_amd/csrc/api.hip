@@ -80,6 +80,9 @@ int sbits_plan_create(sbits_ctx *ctx, const int64_t *rows, const int64_t *cols, 
     if (!is_pow2(block_rows) || !is_pow2(block_cols) || block_rows < 8 || block_rows > 1024 ||
         block_cols < 8 || block_cols > 512)
         return SBITS_ERR_BAD_SHAPE;
+    for (int i = 0; i < n_mats; ++i)
+        if (rows[i] <= 0 || cols[i] <= 0 || rows[i] % block_rows || cols[i] % block_cols || rows[i] > 32768 || cols[i] > 32768)
+            return SBITS_ERR_BAD_SHAPE;
     sbits_plan *p = new (std::nothrow) sbits_plan;
     if (!p) return SBITS_ERR_INVALID_ARG;
     p->ctx = ctx;
@@ -95,11 +98,6 @@ int sbits_plan_create(sbits_ctx *ctx, const int64_t *rows, const int64_t *cols, 
     int64_t score_wgs = 0;
     p->score_rows = sbits_score_rows(rows, cols, n_mats);
     for (int i = 0; i < n_mats; ++i) {
-        if (rows[i] <= 0 || cols[i] <= 0 || rows[i] % block_rows || cols[i] % block_cols ||
-            rows[i] > 32768 || cols[i] > 32768) {
-            delete p;
-            return SBITS_ERR_BAD_SHAPE;
-        }
         p->rows.push_back(rows[i]);
         p->cols.push_back(cols[i]);
         p->base.push_back(p->N);

@@ -244,3 +244,12 @@ def test_plan_limits(ctx):
         with pytest.raises(sb.SbitsError) as e:
             sb.Plan(ctx, shapes, m, n, [2])
         assert e.value.status == sb.ERR_BAD_SHAPE
+
+
+def test_absurd_sizes_are_refused_before_anything_is_computed_from_them(ctx):
+    """Sums and products of such sizes overflow (the sanitizer build of this file's checks stops there)."""
+    big = 2**63 - 128
+    for shapes in ([(big, big)], [(256, big)], [(big, 256)], [(256, 256), (big, big)], [(-256, 256)], [(256, -2**63)]):
+        with pytest.raises(sb.SbitsError) as e:
+            sb.Plan(ctx, shapes, 128, 128, [2, 4])
+        assert e.value.status == sb.ERR_BAD_SHAPE
