@@ -9,8 +9,10 @@ Variants (compile-time switches of the arithmetic, one library each):
 from __future__ import annotations
 
 import os
+import re
 import subprocess
 import sys
+import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -47,7 +49,47 @@ def _compile(src: str, force: bool, variant: str) -> str:
     if r.returncode != 0:
         sys.stderr.write(r.stdout)
         raise RuntimeError("hipcc failed on " + src)
+    if src == "mpgemm.hip":
+        try:
+            if check_counted_waits(device_listing(obj)) == 0:
+                raise RuntimeError("no kernel with counted waits found in " + src)
+        except Exception:
+            os.remove(obj)                          # not taken by a later build either
+            raise
     return obj
+
+
+def device_listing(obj: str) -> str:
+    """The gfx950 assembly of an object file of this build."""
+    def tool(name):
+        return subprocess.check_output([HIPCC, "-print-prog-name=" + name], text=True).strip()
+    with tempfile.TemporaryDirectory() as d:
+        bundle, code = os.path.join(d, "bundle"), os.path.join(d, "code")
+        subprocess.check_call([tool("llvm-objcopy"), "--dump-section", ".hip_fatbin=" + bundle, obj, os.path.join(d, "rest")])
+        subprocess.check_call([tool("clang-offload-bundler"), "--type=o", "--unbundle", "--input=" + bundle, "--output=" + code,
+                               "--targets=hipv4-amdgcn-amd-amdhsa--gfx950"])
+        return subprocess.check_output([tool("llvm-objdump"), "-d", "--no-show-raw-insn", code], text=True)
+
+
+def check_counted_waits(listing: str) -> int:
+    """The product of many rows waits for the x of a step by counting the loads that it requested behind it: its loads to LDS
+    in one run, then nine others in every step (see sync_x in mpgemm.hip).  A compiler that made fewer of them, out of a scalar load or
+    out of two neighbouring ones, would let a wave read x too early.  Returns how many kernels were checked."""
+    kernels = re.findall(r"<(\w*mp_gemm_wide_kernelILi(\d+)ELi(\d+)ELi(\d+)E\w*)>:\n(.*?)(?=\n\n|\Z)", listing, re.S)
+    for name, n_cols, tiles, groups, text in kernels:
+        stage = 8 // int(groups) * int(tiles) * 16 * int(n_cols) * 2          # bytes of x per step, eight waves of 1 KiB loads
+        x_loads, ahead = stage // 8192, 2 if 3 * stage <= 144 * 1024 else 1
+        allowed = ahead * 9 + (ahead - 1) * x_loads
+        steps = re.split(r"s_waitcnt vmcnt\(%d\) lgkmcnt\(0\)[^\n]*\n\s*s_barrier" % allowed, text)[1:]
+        if len(steps) != 2:
+            raise RuntimeError("%s: %d counted waits, 2 expected" % (name, len(steps)))
+        for step in steps:
+            step = re.split(r"\n\s*s_barrier", step)[0]
+            loads = re.findall(r"\n\s*((?:buffer|global|flat)_load_\w+)([^\n]*)", step)
+            kinds = "".join("x" if re.search(r"\blds\b", args) else "." for _, args in loads)
+            if kinds[:x_loads] != "x" * x_loads or "x" in kinds[x_loads:] or len(kinds) < x_loads + 9:
+                raise RuntimeError("%s: a step requests %s, %d loads to LDS and nine others expected" % (name, kinds, x_loads))
+    return len(kernels)
 
 
 def build(force: bool = False, variant: str = "") -> str:

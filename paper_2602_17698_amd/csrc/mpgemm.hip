@@ -677,6 +677,7 @@ void mp_gemm_wide_kernel(MpArgs a, int cols_per_split)
     };
     // Everybody's x of the step is in LDS.  A step requests the x of the step AHEAD of it, then codes, scales and offsets of
     // later ones (LATER loads, all of them used): what this wave has requested behind this step's x may still be under way.
+    // (build.py counts the loads of a step in what the compiler made of them.)
     constexpr int LATER = 9;
     auto sync_x = [&]() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(AHEAD * LATER + (AHEAD - 1) * LPW) : "memory"); };
     auto sync_all = [&]() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
