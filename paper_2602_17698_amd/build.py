@@ -3,8 +3,11 @@
 Variants (compile-time switches of the arithmetic, one library each):
   ""   -> libscalebits.so      cost = sum s * d^2
   "l1" -> libscalebits_l1.so   cost = sum s * |d|   (-DSBITS_COST_POWER=1)
+For the tests only (--tests):
   "impatient" -> libscalebits_impatient.so   the search's workgroups give up waiting for each other at once, so that
-                                             the tests reach the single-workgroup search behind it
+                                             the single-workgroup search behind it is reached
+  "late31", "late32" -> ...                  the search's count of arrivals starts where 31 or 32 bits end, and a search
+                                             that was given up is not repeated
 """
 from __future__ import annotations
 
@@ -18,8 +21,11 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
-VARIANTS = {"": [], "l1": ["-DSBITS_COST_POWER=1"], "impatient": ["-DSBITS_SPIN_LIMIT=0"]}
-ONLY = {"impatient": ["alloc.hip"]}             # sources a variant compiles anew; the rest are the default build's objects
+VARIANTS = {"": [], "l1": ["-DSBITS_COST_POWER=1"]}
+TEST_VARIANTS = {"impatient": ["-DSBITS_SPIN_LIMIT=0"],
+                 "late31": ["-DSBITS_FIRST_ARRIVALS=0x7ffffff0u", "-DSBITS_SECOND_TRY=0"],
+                 "late32": ["-DSBITS_FIRST_ARRIVALS=0xfffffff0u", "-DSBITS_SECOND_TRY=0"]}
+ONLY = {v: ["alloc.hip"] for v in TEST_VARIANTS}       # sources a variant compiles anew; the rest are the default build's objects
 SOURCES = ["api.hip", "reorder.hip", "cost.hip", "fused.hip", "alloc.hip", "pack.hip", "mpgemm.hip", "dequant.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -44,7 +50,7 @@ def _compile(src: str, force: bool, variant: str) -> str:
     deps.append(os.path.join(INCLUDE, "scalebits.h"))
     if not force and os.path.exists(obj) and os.path.getmtime(obj) >= max(os.path.getmtime(d) for d in deps):
         return obj
-    cmd = [HIPCC, *FLAGS, *VARIANTS[variant], "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [HIPCC, *FLAGS, *{**VARIANTS, **TEST_VARIANTS}[variant], "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if r.returncode != 0:
         sys.stderr.write(r.stdout)
@@ -104,10 +110,10 @@ def build(force: bool = False, variant: str = "") -> str:
     return LIB
 
 
-def build_all(force: bool = False) -> list:
-    return [build(force, v) for v in VARIANTS]
+def build_all(force: bool = False, tests: bool = False) -> list:
+    return [build(force, v) for v in [*VARIANTS, *(TEST_VARIANTS if tests else [])]]
 
 
 if __name__ == "__main__":
-    for path in build_all(force="--force" in sys.argv):
+    for path in build_all(force="--force" in sys.argv, tests="--tests" in sys.argv):
         print(path)

@@ -61,7 +61,7 @@ struct AllocHead {
     int bits[MAX_CAND];
     long long prop_up, prop_dn, prop_after;   // the single step on caller-supplied estimates: its result
     unsigned long long tauE, tauU, tauD, tauU2;
-    unsigned int aborted;                     // a workgroup gave up waiting for the others: nothing here is valid
+    unsigned int aborted;                     // workgroups that gave up waiting for the others: if any, nothing here is valid
     unsigned int pad_;
 };
 // One exchange between the workgroups; three of them take turns (see grid_sync).
@@ -71,16 +71,21 @@ struct AllocXchg {
 };
 struct AllocState {
     AllocHead head;
-    unsigned int arrived;                     // workgroups that reached the current exchange, counted on; top bit: given up
+    unsigned int arrived;                     // workgroups that reached the current exchange, counted on (past 32 bits: from 0 again)
     unsigned int pad_[63];
     AllocXchg x[3];
 };
+
+// What the count of arrivals starts from.
+#ifndef SBITS_FIRST_ARRIVALS
+#define SBITS_FIRST_ARRIVALS 0u
+#endif
 
 // The start state from a kernel argument: no host buffer has to outlive the call, so nothing waits.
 __global__ __launch_bounds__(AL_THREADS)
 void set_state_kernel(AllocState *st, AllocHead head)
 {
-    if (threadIdx.x == 0) { st->head = head; st->arrived = 0; }
+    if (threadIdx.x == 0) { st->head = head; st->arrived = SBITS_FIRST_ARRIVALS; }
     unsigned long long *j = reinterpret_cast<unsigned long long *>(st->x);
     for (unsigned i = threadIdx.x; i < sizeof(st->x) / 8; i += AL_THREADS) j[i] = 0ull;
 }
@@ -130,23 +135,22 @@ __device__ __forceinline__ AllocXchg *xchg(const Team &t) { return &t.st->x[t.tu
 // All workgroups have added their part to the exchange buffer of this turn; afterwards its sums are
 // complete for everybody.  The atomics are performed at the point of coherence: waiting for their
 // acknowledgement (vmcnt) orders them before the arrival.
-// The wait is bounded: a workgroup that never got a place on the device makes all of them leave.
+// The wait is bounded: if a workgroup gets no place on the device, the others leave, each after its own wait, at this
+// exchange or the next one; so do those that start later, at their first exchange that somebody is missing from.
 __device__ __forceinline__ void grid_sync(Team &t, AllocShared &sh)
 {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) {
-        const unsigned int target = (unsigned int)t.G * (t.turn + 1u);
+        const unsigned int target = SBITS_FIRST_ARRIVALS + (unsigned int)t.G * (t.turn + 1u);
         (void)__hip_atomic_fetch_add(&t.st->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         unsigned int seen;
         int left = t.spin_limit;
-        while ((seen = __hip_atomic_load(&t.st->arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) < target && left-- > 0)
+        // (the count is less than 2 G away from the target: the difference has a sign wherever 32 bits end)
+        while ((int)((seen = __hip_atomic_load(&t.st->arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) - target) < 0 && left-- > 0)
             __builtin_amdgcn_s_sleep(1);
-        const bool ok = seen >= target && !(seen & 0x80000000u);
-        if (!ok) {
-            (void)__hip_atomic_fetch_or(&t.st->arrived, 0x80000000u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&t.st->head.aborted, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        const bool ok = (int)(seen - target) >= 0;
+        if (!ok) (void)__hip_atomic_fetch_add(&t.st->head.aborted, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         sh.ok = ok;
     }
     __syncthreads();
@@ -765,6 +769,10 @@ static unsigned search_wgs(int64_t N, bool step)
 #ifndef SBITS_SPIN_LIMIT
 #define SBITS_SPIN_LIMIT (1 << 18)
 #endif
+// What a search that was given up is followed by: 1 the single workgroup's, 0 an error or no result (for tests).
+#ifndef SBITS_SECOND_TRY
+#define SBITS_SECOND_TRY 1
+#endif
 
 }  // namespace sbits
 
@@ -864,7 +872,7 @@ int sbits_run_allocate(sbits_plan *plan, const float *cost, double avg_bits,
         const int rc = read_head(ctx, w.st, &h);
         if (rc) return rc;
         if (!h.aborted) break;
-        if (G == 1) return SBITS_ERR_INTERNAL;
+        if (G == 1 || !SBITS_SECOND_TRY) return SBITS_ERR_INTERNAL;
     }
     if (host_stats) {
         host_stats->iters = h.iters; host_stats->expansions = h.expansions;
@@ -897,7 +905,7 @@ int sbits_run_propose(sbits_plan *plan, const float *s_up, const float *s_down, 
     const unsigned G = search_wgs(N, true);
     uint8_t *const lv = const_cast<uint8_t *>(level_in);             // (only read by the step)
     launch_search<true>(sm, G, w, N, nullptr, s_up, s_down, lv, 0);
-    if (G > 1) launch_search<true>(sm, 1, w, N, nullptr, s_up, s_down, lv, 1);   // returns at once unless the first gave up
+    if (G > 1 && SBITS_SECOND_TRY) launch_search<true>(sm, 1, w, N, nullptr, s_up, s_down, lv, 1);   // returns at once unless the first gave up
     const unsigned grid = (unsigned)((N + 255) / 256 < 1024 ? (N + 255) / 256 : 1024);
     hipLaunchKernelGGL(step_apply_kernel, dim3(grid), dim3(256), 0, sm, (const AllocState *)w.st,
                        (const u64 *)w.keyU, (const u64 *)w.keyD, level_in, level_out);

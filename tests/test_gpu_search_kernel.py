@@ -26,7 +26,7 @@ def dev():
 def ctx(request, dev):
     """A context of the default build, and of the one whose workgroups give up waiting for each other at once."""
     prev, path = sb.LIB_PATH, sb.variant_path(request.param)
-    assert os.path.exists(path), "build the variant first: python -m paper_2602_17698_amd.build"
+    assert os.path.exists(path), "build the variant first: python -m paper_2602_17698_amd.build --tests"
     sb.use_library(path)
     try:
         c = sb.Context(device=0, stream=torch.cuda.current_stream().cuda_stream)
@@ -154,6 +154,35 @@ def test_propose_on_levels_over_budget(orc, ctx, dev, N):
         np.testing.assert_array_equal(got, want, err_msg=case)
         assert int(np.asarray(bits)[got].sum()) == info["bits_after"], case
     plan.close()
+
+
+@pytest.mark.parametrize("bits_end", [31, 32])
+def test_the_count_of_arrivals_goes_on(orc, dev, bits_end):
+    """A library whose count starts just below 2^31 or 2^32, as after some million exchanges, and that does not repeat a search."""
+    prev, path = sb.LIB_PATH, sb.variant_path("late%d" % bits_end)
+    assert os.path.exists(path), "build the variant first: python -m paper_2602_17698_amd.build --tests"
+    sb.use_library(path)
+    try:
+        ctx = sb.Context(device=0, stream=torch.cuda.current_stream().cuda_stream)
+        for N in (6000, 524304):
+            say("late", bits_end, N)
+            bits = [1, 2, 3, 4]
+            cost = table(N, bits, N)
+            plan, ws = plan_with_blocks(ctx, N, bits, dev)
+            level = torch.full((N,), 255, dtype=torch.uint8, device=dev)
+            rc, st, tr = plan.allocate(torch.from_numpy(cost).to(dev), 2.5, level, ws, trace_cap=500)
+            rc_o, level_o, st_o, tr_o = orc.allocate(cost, bits, 2.5, want_trace=True)
+            assert (rc, st, tr) == (rc_o, st_o, tr_o)
+            np.testing.assert_array_equal(level.cpu().numpy(), level_o)
+            s_up, s_dn = (np.ascontiguousarray(cost[:, i]) for i in (0, 2))
+            kind, want, winfo = orc.propose(s_up, s_dn, level_o, bits, 2.6, N // 20)
+            info = plan.propose(torch.from_numpy(s_up).to(dev), torch.from_numpy(s_dn).to(dev), level, 2.6, N // 20, level, ws)
+            assert info["kind"] == kind and all(info[f] == winfo[f] for f in winfo)
+            np.testing.assert_array_equal(level.cpu().numpy(), want)
+            plan.close()
+        ctx.close()
+    finally:
+        sb.use_library(prev)
 
 
 def test_propose_replays_from_a_captured_graph(orc, dev):
