@@ -34,7 +34,7 @@
 #include <math.h>
 #include <string.h>
 
-
+#include "alloc_split.hpp"
 #include "sbits_internal.hpp"
 
 namespace sbits {
@@ -46,7 +46,6 @@ constexpr int SEL_DB = 10;                    // digit bits of a selection round
 constexpr int SEL_BINS = 1 << SEL_DB;
 constexpr int AL_KPT = 8;                     // blocks a thread holds in registers, or has in flight from memory
 constexpr int AL_BPT = SEL_BINS / AL_THREADS;       // bins per thread
-constexpr int AL_MAX_WG = 128;
 constexpr int AL_SUMS = 8;                    // values of one reduction
 
 enum { MODE_NONE = 0, MODE_EXPAND = 1, MODE_ACCEPT = 2 };
@@ -751,20 +750,6 @@ void step_apply_kernel(const AllocState *st, const u64 *__restrict__ keyU, const
 
 static int ceil_log2_ll(long long v) { int p = 0; while ((1ll << p) < v) ++p; return p; }
 
-// Workgroups of a search over N blocks: 2048 blocks each (four to a thread) up to 32 workgroups, beyond that
-// 4096, the most their registers hold (14 k blocks, 23 iterations: 360 us with 7 workgroups, 401 with 4; 430 k blocks,
-// 22 iterations: 788 us with 105, 837 with 128).  At most half of the device's CUs, so that two searches fit side
-// by side; larger tables live in memory then (4.2 M blocks: 3.6 ms; 4.9 ms with a launch per round).  A single step over a
-// table in memory is a pass or two over it and needs a third of the registers, so beyond 2 M blocks it takes a workgroup
-// per 16384 blocks, up to twice as many (16.7 M blocks: 371 us, 533 with 128, 535 with a launch per round; 1 M: 76 and 72).
-static unsigned search_wgs(int64_t N, bool step)
-{
-    const int64_t g = N <= 32 * 2048 ? (N + 2047) / 2048 : (N + 4095) / 4096;
-    int64_t most = AL_MAX_WG;
-    if (step && N / 16384 > most) most = N / 16384 < 2 * AL_MAX_WG ? N / 16384 : 2 * AL_MAX_WG;
-    return (unsigned)(g < most ? g : most);
-}
-
 // A wait between workgroups polls this often before it is given up (about half a second).
 #ifndef SBITS_SPIN_LIMIT
 #define SBITS_SPIN_LIMIT (1 << 18)
@@ -865,7 +850,7 @@ int sbits_run_allocate(sbits_plan *plan, const float *cost, double avg_bits,
     // The workgroups wait for each other.  Should the device be so full that they never run together, they
     // give up (see grid_sync) and one workgroup, which waits for nobody, does the search.
     AllocHead h;
-    for (unsigned G = search_wgs(N, false);; G = 1) {
+    for (unsigned G = search_wgs(N, false, ctx->cus);; G = 1) {
         hipLaunchKernelGGL(set_state_kernel, dim3(1), dim3(AL_THREADS), 0, sm, w.st, h0);
         launch_search<false>(sm, G, w, N, cost, nullptr, nullptr, level, 0);
         SBITS_HIP(ctx, hipGetLastError());
@@ -902,7 +887,7 @@ int sbits_run_propose(sbits_plan *plan, const float *s_up, const float *s_down, 
     h.k = k;
     // the start state travels as a kernel argument: nothing to keep alive, nothing to wait for
     hipLaunchKernelGGL(set_state_kernel, dim3(1), dim3(AL_THREADS), 0, sm, w.st, h);
-    const unsigned G = search_wgs(N, true);
+    const unsigned G = search_wgs(N, true, ctx->cus);
     uint8_t *const lv = const_cast<uint8_t *>(level_in);             // (only read by the step)
     launch_search<true>(sm, G, w, N, nullptr, s_up, s_down, lv, 0);
     if (G > 1 && SBITS_SECOND_TRY) launch_search<true>(sm, 1, w, N, nullptr, s_up, s_down, lv, 1);   // returns at once unless the first gave up

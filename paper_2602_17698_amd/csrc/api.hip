@@ -39,7 +39,7 @@ int sbits_create(sbits_ctx **out, int device, void *hip_stream)
     c->stream = static_cast<hipStream_t>(hip_stream);
     c->last_hip = 0;
     c->pinned = nullptr;
-    c->readback = nullptr;
+    c->cus = 0;
     c->d16_zero_fill = true;
     if (device >= 0) {
         hipError_t e = hipSetDevice(device);
@@ -49,6 +49,7 @@ int sbits_create(sbits_ctx **out, int device, void *hip_stream)
         hipDeviceProp_t prop;
         e = hipGetDeviceProperties(&prop, device);
         if (e != hipSuccess) { c->last_hip = (int)e; delete c; return SBITS_ERR_HIP; }
+        c->cus = prop.multiProcessorCount;
         c->d16_zero_fill = strstr(prop.gcnArchName, "sramecc+") != nullptr;
     }
     *out = c;
@@ -59,7 +60,6 @@ int sbits_destroy(sbits_ctx *ctx)
 {
     if (!ctx) return SBITS_ERR_INVALID_ARG;
     if (ctx->pinned) (void)hipHostFree(ctx->pinned);
-    if (ctx->readback) (void)hipEventDestroy(ctx->readback);
     delete ctx;
     return SBITS_OK;
 }
