@@ -272,9 +272,13 @@ int  sbits_surrogates_all(sbits_plan *plan, const sbits_matrix *mats, const int3
 
 /* ---- scalable greedy search (paper Algorithm 2 with the relaxed step Eq. 5) ---
  * Runs on the device over the cost table: marginal change per bit from the
- * table, radix selection of the top-k / bottom-k sets on (value, index) keys,
- * budget prefix, fixed-point acceptance test.  level[N] out (uint8 candidate
- * index).  host_stats (HOST, may be NULL) and trace (HOST, may be NULL, at most
+ * table, selection of the top-k / bottom-k sets on (value, index) keys by bins
+ * that close in on the last key taken, budget prefix, fixed-point acceptance
+ * test.  One launch: its workgroups stay on the chip for the whole search and
+ * wait for each other, every wait bounded; if other work on the device keeps
+ * some of them from a place for so long, the search is done again from the start by
+ * one workgroup (same results, several times slower; tables that start with one workgroup never
+ * wait).  level[N] out (uint8 candidate index).  host_stats (HOST, may be NULL) and trace (HOST, may be NULL, at most
  * trace_cap records) are filled after the stream has been waited for.
  * Returns SBITS_ERR_INFEASIBLE_BUDGET if avg_bits < smallest candidate,
  * SBITS_ERR_MAX_ITERS if the cap ended the loop.  Uses ws.                      */
@@ -394,11 +398,15 @@ int  sbits_dequant(sbits_plan *plan, int mat, const uint8_t *level, const int64_
  * the permuted weights and keeps connected layers consistent, App. "Channel
  * Reordering").  x_bf16: [batch][ld_x] bfloat16, 16-byte aligned, ld_x >= cols and a
  * multiple of 8; y: [batch][rows] float32; batch >= 1.  The kernel is built for the
- * small batches of decoding: up to 32 rows of x in one launch, more rows 128 to a
- * launch, each launch reading the whole code stream of the matrix; for large batches
+ * small batches of decoding: rows of x go up to 128 to a launch (65 .. 96 rows as 64 and
+ * the rest where that is faster; 32 to a launch if ld_x is above 2^20), each launch
+ * reading the whole code stream of the matrix; for large batches
  * (prefill) take sbits_dequant to bf16 once and an ordinary dense product instead.  Products are exact (integer codes
  * times bf16) and summed in fp32 on the matrix cores; scale and zero are applied per
- * block row in fp32.
+ * block row in fp32.  The same call gives the same bits again, whatever else is in the
+ * plan.  The order of the fp32 sums goes with the number of rows in a launch, the
+ * candidate list and the matrix's shape, so that a row of x may get other last bits in
+ * a batch of another size.
  * SBITS_ERR_UNIMPLEMENTED unless block_cols is 64 or 128 and block_rows a multiple
  * of 32.  Uses ws.                                                               */
 int  sbits_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t ld_x, int batch,

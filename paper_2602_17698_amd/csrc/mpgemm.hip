@@ -21,7 +21,7 @@
 //   block columns (4 waves per row group, 4 blocks per wave, two or three of them in flight in a ring
 //   of register slots); the x slice of those columns sits in LDS.  Block columns beyond the first 16
 //   go to further workgroups (grid.y), whose partial sums a second kernel adds in a fixed order.
-// More than 32 batch rows, and many products of up to 16, take the kernels further down.
+// More than 32 batch rows, and most products of up to 16 (few_rows), take the kernels further down.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -384,8 +384,10 @@ void mp_gemm_kernel(MpArgs a)
 // one request waits for every older one, so with everything one step ahead a step is as long as a load from memory
 // (47 us for 14336 x 4096 at 100 rows).  The operand reads are written out with their wait: the compiler would wait for
 // the requests under way before any read of LDS.
-// What bounds it: vector issue (260 instructions a step and wave, 36 matrix instructions) and the barrier of each step.
-// Against launches of the kernel above, 32 rows each: 14336 x 4096 at 100 rows, bitwidths 1 .. 8, 75 -> 42 us (280 TFLOP/s), at 64 rows
+// What bounds it: steps of 270 vector and 37 matrix instructions a wave, two waves per SIMD, with a barrier each (14336 x 4096
+// at 100 rows, by counters: vector issue 39 % of the clocks, matrix cores 21 %, 37 % of the waves' cycles wait for loads or the
+// barrier).
+// Against launches of the kernel above, 32 rows each: 14336 x 4096 at 100 rows, bitwidths 1 .. 8, 72 -> 39 us (300 TFLOP/s), at 64 rows
 // 40 -> 26 us, at 33 rows 35 -> 23 us; 8192 x 8192 at 100 rows 78 -> 45 us; 4096 x 4096 in 64-column blocks at 70 rows
 // 47 -> 32 us.  (128 batch rows in one workgroup, 64 channels: 45 us at 100 rows.)
 // Operands are unpacked in stream order, two codes in three instructions whatever the bitwidth c <= 7:
