@@ -52,16 +52,19 @@ enum { MODE_NONE = 0, MODE_EXPAND = 1, MODE_ACCEPT = 2 };
 
 struct AllocHead {
     long long N, T, k, kmin, used;
-    long long cost_fixed, bits_check;
-    int K, IB, shift, l0;
-    int iters, max_iters, expansions, swaps_ok, swaps_rej;
-    int done, status, mode;
+    int K, IB, l0, max_iters, done, mode;
     int ceil_log2_n;
     int bits[MAX_CAND];
-    long long prop_up, prop_dn, prop_after;   // the single step on caller-supplied estimates: its result
-    unsigned long long tauE, tauU, tauD, tauU2;
+    unsigned long long tauE, tauU, tauD, tauU2;   // the single step on caller-supplied estimates: what it raises and lowers
     unsigned int aborted;                     // workgroups that gave up waiting for the others: if any, nothing here is valid
     unsigned int pad_;
+};
+// What the host learns: written to page-locked host memory by the workgroup that leads, so that it takes neither a copy nor
+// a wait of its own.
+struct AllocResult {
+    long long k, used, budget, cost_fixed, bits_check;
+    long long prop_up, prop_dn, prop_after;
+    int shift, status, iters, expansions, swaps_ok, swaps_rej, mode, valid;
 };
 // One exchange between the workgroups; three of them take turns (see grid_sync).
 struct AllocXchg {
@@ -495,7 +498,7 @@ template <bool STEP, bool RES>
 __global__ __launch_bounds__(AL_THREADS)
 void search_kernel(AllocState *st, const float *__restrict__ cost, const float *__restrict__ s_up,
                    const float *__restrict__ s_down, uint8_t *level, u64 *__restrict__ keyU, u64 *__restrict__ keyD,
-                   sbits_trace *tr, int spin_limit, int only_if_aborted)
+                   sbits_trace *tr, AllocResult *result, int spin_limit, int only_if_aborted)
 {
     __shared__ AllocShared sh;
     const int tid = (int)threadIdx.x;
@@ -573,12 +576,18 @@ void search_kernel(AllocState *st, const float *__restrict__ cost, const float *
         const int mode = e.n_sel > 0 ? MODE_EXPAND : u2.n_sel > 0 && d.n_sel > 0 ? MODE_ACCEPT : MODE_NONE;
         if (lead) {
             AllocHead &hd = st->head;
-            hd.used = used;
             hd.mode = mode;
-            hd.prop_up = mode == MODE_EXPAND ? e.n_sel : mode == MODE_ACCEPT ? u2.n_sel : 0;
-            hd.prop_dn = mode == MODE_ACCEPT ? d.n_sel : 0;
-            hd.prop_after = used + (mode == MODE_EXPAND ? e.w_sel : mode == MODE_ACCEPT ? u2.w_sel - d.w_sel : 0);
             hd.tauE = e.tau; hd.tauU = u.tau; hd.tauD = d.tau; hd.tauU2 = u2.tau;
+            if (result) {
+                AllocResult r = {};
+                r.used = used; r.budget = T;
+                r.mode = mode;
+                r.prop_up = mode == MODE_EXPAND ? e.n_sel : mode == MODE_ACCEPT ? u2.n_sel : 0;
+                r.prop_dn = mode == MODE_ACCEPT ? d.n_sel : 0;
+                r.prop_after = used + (mode == MODE_EXPAND ? e.w_sel : mode == MODE_ACCEPT ? u2.w_sel - d.w_sel : 0);
+                r.valid = 1;
+                *result = r;
+            }
         }
     } else {
         const int l0 = st->head.l0;
@@ -718,10 +727,12 @@ void search_kernel(AllocState *st, const float *__restrict__ cost, const float *
         team_reduce<0>(t, sh, fin);
         if (!t.ok) return;
         if (lead) {
-            AllocHead &hd = st->head;
-            hd.used = used; hd.k = k; hd.shift = shift; hd.status = status;
-            hd.iters = iters; hd.expansions = expansions; hd.swaps_ok = swaps_ok; hd.swaps_rej = swaps_rej;
-            hd.cost_fixed = (long long)fin[0]; hd.bits_check = (long long)fin[1];
+            AllocResult r = {};
+            r.used = used; r.k = k; r.budget = T; r.shift = shift; r.status = status;
+            r.iters = iters; r.expansions = expansions; r.swaps_ok = swaps_ok; r.swaps_rej = swaps_rej;
+            r.cost_fixed = (long long)fin[0]; r.bits_check = (long long)fin[1];
+            r.valid = 1;
+            *result = r;
         }
     }
 }
@@ -789,10 +800,10 @@ static AllocWs alloc_ws(void *ws, int64_t N)
 
 template <bool STEP>
 static void launch_search(hipStream_t sm, unsigned G, const AllocWs &w, int64_t N, const float *cost, const float *s_up,
-                          const float *s_down, uint8_t *level, int only_if_aborted)
+                          const float *s_down, uint8_t *level, AllocResult *result, int only_if_aborted)
 {
     auto *fn = (N + G - 1) / G <= (int64_t)AL_KPT * AL_THREADS ? &search_kernel<STEP, true> : &search_kernel<STEP, false>;
-    hipLaunchKernelGGL(fn, dim3(G), dim3(AL_THREADS), 0, sm, w.st, cost, s_up, s_down, level, w.keyU, w.keyD, w.tr, SBITS_SPIN_LIMIT,
+    hipLaunchKernelGGL(fn, dim3(G), dim3(AL_THREADS), 0, sm, w.st, cost, s_up, s_down, level, w.keyU, w.keyD, w.tr, result, SBITS_SPIN_LIMIT,
                        only_if_aborted);
 }
 
@@ -809,20 +820,26 @@ static AllocHead start_head(const sbits_plan *plan, double avg_bits)
     return h;
 }
 
-// The state's head through page-locked memory: a pageable target makes the copy a staged one.
-static int read_head(sbits_ctx *ctx, const AllocState *st, AllocHead *h)
+// The context's page-locked buffer, ready for the next result.
+static int result_buffer(sbits_ctx *ctx, AllocResult **out)
 {
-    static_assert(sizeof(AllocHead) <= SBITS_PINNED_BYTES, "state head must fit the pinned buffer");
+    static_assert(sizeof(AllocResult) <= SBITS_PINNED_BYTES, "a result must fit the pinned buffer");
     if (!ctx->pinned) SBITS_HIP(ctx, hipHostMalloc(&ctx->pinned, SBITS_PINNED_BYTES, hipHostMallocDefault));
-    SBITS_HIP(ctx, hipMemcpyAsync(ctx->pinned, &st->head, sizeof(AllocHead), hipMemcpyDeviceToHost, ctx->stream));
-    SBITS_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    memcpy(h, ctx->pinned, sizeof(AllocHead));
+    *out = static_cast<AllocResult *>(ctx->pinned);
+    (*out)->valid = 0;
     return SBITS_OK;
 }
 
-int sbits_run_allocate(sbits_plan *plan, const float *cost, double avg_bits,
-                       const sbits_params *prm, uint8_t *level, sbits_stats *host_stats,
-                       sbits_trace *host_trace, int64_t trace_cap, void *ws)
+// A search that gave up and is not repeated (for tests) left nothing that may be used.
+static int stop_if_aborted(sbits_ctx *ctx, const AllocState *st)
+{
+    AllocHead h;
+    SBITS_HIP(ctx, hipMemcpyAsync(&h, &st->head, sizeof h, hipMemcpyDeviceToHost, ctx->stream));
+    SBITS_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    return h.aborted ? SBITS_ERR_INTERNAL : SBITS_OK;
+}
+
+int sbits_enqueue_allocate(sbits_plan *plan, const float *cost, double avg_bits, const sbits_params *prm, uint8_t *level, void *ws)
 {
     sbits_ctx *ctx = plan->ctx;
     hipStream_t sm = ctx->stream;
@@ -830,6 +847,9 @@ int sbits_run_allocate(sbits_plan *plan, const float *cost, double avg_bits,
     const int K = plan->K;
     if (avg_bits < (double)plan->bits[0]) return SBITS_ERR_INFEASIBLE_BUDGET;
     const AllocWs w = alloc_ws(ws, N);
+    AllocResult *result;
+    const int rc = result_buffer(ctx, &result);
+    if (rc) return rc;
 
     AllocHead h0 = start_head(plan, avg_bits);
     h0.k = (long long)floor(prm->gamma0 * (double)N);
@@ -849,27 +869,30 @@ int sbits_run_allocate(sbits_plan *plan, const float *cost, double avg_bits,
 
     // The workgroups wait for each other.  Should the device be so full that they never run together, they
     // give up (see grid_sync) and one workgroup, which waits for nobody, does the search.
-    AllocHead h;
-    for (unsigned G = search_wgs(N, false, ctx->cus);; G = 1) {
-        hipLaunchKernelGGL(set_state_kernel, dim3(1), dim3(AL_THREADS), 0, sm, w.st, h0);
-        launch_search<false>(sm, G, w, N, cost, nullptr, nullptr, level, 0);
-        SBITS_HIP(ctx, hipGetLastError());
-        const int rc = read_head(ctx, w.st, &h);
-        if (rc) return rc;
-        if (!h.aborted) break;
-        if (G == 1 || !SBITS_SECOND_TRY) return SBITS_ERR_INTERNAL;
-    }
+    const unsigned G = search_wgs(N, false, ctx->cus);
+    hipLaunchKernelGGL(set_state_kernel, dim3(1), dim3(AL_THREADS), 0, sm, w.st, h0);
+    launch_search<false>(sm, G, w, N, cost, nullptr, nullptr, level, result, 0);
+    if (G > 1 && SBITS_SECOND_TRY) launch_search<false>(sm, 1, w, N, cost, nullptr, nullptr, level, result, 1);   // returns at once unless the first gave up
+    SBITS_HIP(ctx, hipGetLastError());
+    return SBITS_SECOND_TRY ? SBITS_OK : stop_if_aborted(ctx, w.st);
+}
+
+int sbits_finish_allocate(sbits_plan *plan, sbits_stats *host_stats, sbits_trace *host_trace, int64_t trace_cap, void *ws)
+{
+    sbits_ctx *ctx = plan->ctx;
+    const AllocResult h = *static_cast<const AllocResult *>(ctx->pinned);
+    if (!h.valid) return SBITS_ERR_INTERNAL;
     if (host_stats) {
         host_stats->iters = h.iters; host_stats->expansions = h.expansions;
         host_stats->swaps_ok = h.swaps_ok; host_stats->swaps_rej = h.swaps_rej;
-        host_stats->k_final = h.k; host_stats->bits_used = h.bits_check; host_stats->bits_budget = h.T;
+        host_stats->k_final = h.k; host_stats->bits_used = h.bits_check; host_stats->bits_budget = h.budget;
         host_stats->cost_fixed = h.cost_fixed; host_stats->cost_shift = h.shift; host_stats->pad_ = 0;
     }
     if (host_trace && trace_cap > 0 && h.iters > 0) {
         int64_t nrec = h.iters < trace_cap ? h.iters : trace_cap;
         if (nrec > TRACE_CAP) nrec = TRACE_CAP;
-        SBITS_HIP(ctx, hipMemcpyAsync(host_trace, w.tr, (size_t)nrec * sizeof(sbits_trace), hipMemcpyDeviceToHost, sm));
-        SBITS_HIP(ctx, hipStreamSynchronize(sm));
+        SBITS_HIP(ctx, hipMemcpyAsync(host_trace, alloc_ws(ws, plan->N).tr, (size_t)nrec * sizeof(sbits_trace), hipMemcpyDeviceToHost, ctx->stream));
+        SBITS_HIP(ctx, hipStreamSynchronize(ctx->stream));
     }
     if (h.bits_check != h.used) return SBITS_ERR_INTERNAL;      // the loop's running total and a recount must agree
     return h.status;
@@ -883,28 +906,32 @@ int sbits_run_propose(sbits_plan *plan, const float *s_up, const float *s_down, 
     hipStream_t sm = ctx->stream;
     const int64_t N = plan->N;
     const AllocWs w = alloc_ws(ws, N);
+    AllocResult *result = nullptr;                                   // (without a host output nothing is waited for)
+    const int rc = host_out ? result_buffer(ctx, &result) : SBITS_OK;
+    if (rc) return rc;
     AllocHead h = start_head(plan, avg_bits);
     h.k = k;
     // the start state travels as a kernel argument: nothing to keep alive, nothing to wait for
     hipLaunchKernelGGL(set_state_kernel, dim3(1), dim3(AL_THREADS), 0, sm, w.st, h);
     const unsigned G = search_wgs(N, true, ctx->cus);
     uint8_t *const lv = const_cast<uint8_t *>(level_in);             // (only read by the step)
-    launch_search<true>(sm, G, w, N, nullptr, s_up, s_down, lv, 0);
-    if (G > 1 && SBITS_SECOND_TRY) launch_search<true>(sm, 1, w, N, nullptr, s_up, s_down, lv, 1);   // returns at once unless the first gave up
+    launch_search<true>(sm, G, w, N, nullptr, s_up, s_down, lv, result, 0);
+    if (G > 1 && SBITS_SECOND_TRY) launch_search<true>(sm, 1, w, N, nullptr, s_up, s_down, lv, result, 1);   // returns at once unless the first gave up
     const unsigned grid = (unsigned)((N + 255) / 256 < 1024 ? (N + 255) / 256 : 1024);
     hipLaunchKernelGGL(step_apply_kernel, dim3(grid), dim3(256), 0, sm, (const AllocState *)w.st,
                        (const u64 *)w.keyU, (const u64 *)w.keyD, level_in, level_out);
     SBITS_HIP(ctx, hipGetLastError());
     if (host_out) {
-        const int rc = read_head(ctx, w.st, &h);
-        if (rc) return rc;
-        host_out->kind = h.mode == MODE_EXPAND ? 1 : h.mode == MODE_ACCEPT ? 2 : 0;
+        SBITS_HIP(ctx, hipStreamSynchronize(sm));
+        const AllocResult r = *result;
+        if (!r.valid) return SBITS_ERR_INTERNAL;
+        host_out->kind = r.mode == MODE_EXPAND ? 1 : r.mode == MODE_ACCEPT ? 2 : 0;
         host_out->pad_ = 0;
-        host_out->n_up = h.prop_up;
-        host_out->n_dn = h.prop_dn;
-        host_out->bits_before = h.used;
-        host_out->bits_after = h.prop_after;
-        host_out->bits_budget = h.T;
+        host_out->n_up = r.prop_up;
+        host_out->n_dn = r.prop_dn;
+        host_out->bits_before = r.used;
+        host_out->bits_after = r.prop_after;
+        host_out->bits_budget = r.budget;
     }
     return SBITS_OK;
 }

@@ -193,16 +193,37 @@ static int need_device(const sbits_plan *plan)
 
 }  // extern "C"
 
-// Copies the descriptor table into the workspace head.  mats == nullptr: shapes only.
-// The image a copy reads must not change while the copy is pending: the table is built in one of two
+// Copies the workspace head: the descriptor table (mats == nullptr: shapes only), the tables that follow from the shapes
+// and, for a coupled reordering, its tables; one copy, where a copy per table from pageable memory cost a search of one small
+// matrix 20 us between its kernels.
+// The image a copy reads must not change while the copy is pending: the head is built in one of two
 // page-locked buffers of the plan, taken in turns; before a buffer is rewritten the host waits for the
 // event recorded behind the copy that last read it (two uploads back: as good as always complete).
-int sbits_upload_descs(sbits_plan *plan, const sbits_matrix *mats, void *ws)
+int sbits_upload_head(sbits_plan *plan, const sbits_matrix *mats, const sbits_coupling *cpl, void *ws)
 {
     sbits_ctx *ctx = plan->ctx;
-    const size_t bytes = (size_t)plan->n_mats * sizeof(sbits::MatDesc);
+    const size_t bytes = plan->head_bytes;
+    auto table = [&](char *img, int slot, const std::vector<int> &t) {
+        if (!t.empty()) memcpy(sbits_prefix_ptr(plan, img, slot), t.data(), t.size() * 4);
+    };
     if (!plan->desc_pinned) {
+        sbits_cost_tables(plan);
+        sbits_pack_tables(plan);
+        sbits_fused_tables(plan);
+        sbits_gather_tables(plan);
         SBITS_HIP(ctx, hipHostMalloc(&plan->desc_pinned, 2 * bytes, hipHostMallocDefault));
+        for (int i = 0; i < 2; ++i) {
+            char *img = static_cast<char *>(plan->desc_pinned) + (size_t)i * bytes;
+            memset(img, 0, bytes);
+            table(img, SLOT_COST_UNITS, plan->cost_unit_start);
+            table(img, SLOT_SCORE_WGS, plan->score_wg_start);
+            table(img, SLOT_PACK_WGS, plan->pack_wg_start);
+            table(img, SLOT_FUSED_MEMBERS, plan->fused_members);
+            table(img, SLOT_FUSED_WGS, plan->fused_pre);
+            table(img, SLOT_GATHER_MEMBERS, plan->gather_members);
+            table(img, SLOT_GATHER_WGS_W, plan->gather_pre_w);
+            table(img, SLOT_GATHER_WGS_S, plan->gather_pre_s);
+        }
         for (int i = 0; i < 2; ++i) SBITS_HIP(ctx, hipEventCreateWithFlags(&plan->desc_done[i], hipEventDisableTiming));
         plan->desc_turn = 0;
         plan->desc_used[0] = plan->desc_used[1] = false;
@@ -210,7 +231,8 @@ int sbits_upload_descs(sbits_plan *plan, const sbits_matrix *mats, void *ws)
     const int t = plan->desc_turn;
     plan->desc_turn ^= 1;
     if (plan->desc_used[t]) SBITS_HIP(ctx, hipEventSynchronize(plan->desc_done[t]));
-    sbits::MatDesc *img = reinterpret_cast<sbits::MatDesc *>(static_cast<char *>(plan->desc_pinned) + (size_t)t * bytes);
+    char *const head = static_cast<char *>(plan->desc_pinned) + (size_t)t * bytes;
+    sbits::MatDesc *img = sbits_desc_ptr(head);
     for (int i = 0; i < plan->n_mats; ++i) {
         sbits::MatDesc &d = plan->descs[i];
         if (mats) {
@@ -223,7 +245,14 @@ int sbits_upload_descs(sbits_plan *plan, const sbits_matrix *mats, void *ws)
         }
         img[i] = d;
     }
-    SBITS_HIP(ctx, hipMemcpyAsync(ws, img, bytes, hipMemcpyHostToDevice, ctx->stream));
+    if (cpl) {
+        table(head, SLOT_ARR_MODE, cpl->mode);
+        table(head, SLOT_ARR_SEG, cpl->seg);
+        table(head, SLOT_ARR_NEXT, cpl->next);
+        table(head, SLOT_ARR_LEADER, cpl->leader);
+        table(head, SLOT_ARR_REP, cpl->rep);
+    }
+    SBITS_HIP(ctx, hipMemcpyAsync(ws, head, bytes, hipMemcpyHostToDevice, ctx->stream));
     SBITS_HIP(ctx, hipEventRecord(plan->desc_done[t], ctx->stream));
     plan->desc_used[t] = true;
     return SBITS_OK;
@@ -283,7 +312,7 @@ int sbits_reorder_all(sbits_plan *plan, const sbits_matrix *mats, int32_t *row_p
     if (!row_perm || !col_perm || !ws_ok(ws)) return SBITS_ERR_INVALID_ARG;
     if (!ws_fits(plan)) return SBITS_ERR_WORKSPACE;
     if ((rc = need_device(plan))) return rc;
-    if ((rc = sbits_upload_descs(plan, mats, ws))) return rc;
+    if ((rc = sbits_upload_head(plan, mats, nullptr, ws))) return rc;
     return sbits_launch_reorder_all(plan, row_perm, col_perm, ws);
 }
 
@@ -296,13 +325,11 @@ int sbits_reorder_coupled_all(sbits_plan *plan, const sbits_matrix *mats, const 
     if (rc) return rc;
     if (!row_group || !col_group || n_groups < 0 || !row_perm || !col_perm || !ws_ok(ws)) return SBITS_ERR_INVALID_ARG;
     if (!ws_fits(plan)) return SBITS_ERR_WORKSPACE;
-    if ((rc = sbits_coupling_tables(plan, row_group, col_group, n_groups, group_segment, row_repeat, col_repeat,
-                                    nullptr, nullptr, nullptr, nullptr, nullptr)))
-        return rc;
+    sbits_coupling cpl;
+    if ((rc = sbits_coupling_tables(plan, row_group, col_group, n_groups, group_segment, row_repeat, col_repeat, &cpl))) return rc;
     if ((rc = need_device(plan))) return rc;
-    if ((rc = sbits_upload_descs(plan, mats, ws))) return rc;
-    return sbits_launch_reorder_coupled_all(plan, row_group, col_group, n_groups, group_segment, row_repeat,
-                                            col_repeat, row_perm, col_perm, ws);
+    if ((rc = sbits_upload_head(plan, mats, &cpl, ws))) return rc;
+    return sbits_launch_reorder_coupled_all(plan, cpl, row_perm, col_perm, ws);
 }
 
 int sbits_gather_all(sbits_plan *plan, const sbits_matrix *mats, const int32_t *row_perm,
@@ -315,7 +342,7 @@ int sbits_gather_all(sbits_plan *plan, const sbits_matrix *mats, const int32_t *
         return SBITS_ERR_INVALID_ARG;
     if (!ws_fits(plan)) return SBITS_ERR_WORKSPACE;
     if ((rc = need_device(plan))) return rc;
-    if ((rc = sbits_upload_descs(plan, mats, ws))) return rc;
+    if ((rc = sbits_upload_head(plan, mats, nullptr, ws))) return rc;
     return sbits_launch_gather_all(plan, row_perm, col_perm, w_re_bf16, s_re, ws);
 }
 
@@ -350,7 +377,7 @@ int sbits_cost_table_all(sbits_plan *plan, const void *w_re_bf16, const float *s
     if (!aligned16(w_re_bf16) || !aligned16(s_re)) return SBITS_ERR_INVALID_ARG;
     int rc = need_device(plan);
     if (rc) return rc;
-    if ((rc = sbits_upload_descs(plan, nullptr, ws))) return rc;
+    if ((rc = sbits_upload_head(plan, nullptr, nullptr, ws))) return rc;
     return sbits_launch_cost_all(plan, w_re_bf16, s_re, cost, ws);
 }
 
@@ -366,7 +393,7 @@ int sbits_gather_cost_all(sbits_plan *plan, const sbits_matrix *mats, const int3
     if (!ws_fits(plan)) return SBITS_ERR_WORKSPACE;
     if (!sbits_fused_shapes_ok(plan)) return SBITS_ERR_UNIMPLEMENTED;
     if ((rc = need_device(plan))) return rc;
-    if ((rc = sbits_upload_descs(plan, mats, ws))) return rc;
+    if ((rc = sbits_upload_head(plan, mats, nullptr, ws))) return rc;
     if (!sbits_fused_layout_ok(plan, true)) return SBITS_ERR_UNIMPLEMENTED;
     return sbits_launch_gather_cost_all(plan, row_perm, col_perm, w_re_bf16, cost, ws);
 }
@@ -381,7 +408,7 @@ int sbits_surrogates_all(sbits_plan *plan, const sbits_matrix *mats, const int32
     if (!ws_fits(plan)) return SBITS_ERR_WORKSPACE;
     if (!sbits_fused_all_staged(plan)) return SBITS_ERR_UNIMPLEMENTED;
     if ((rc = need_device(plan))) return rc;
-    if ((rc = sbits_upload_descs(plan, mats, ws))) return rc;
+    if ((rc = sbits_upload_head(plan, mats, nullptr, ws))) return rc;
     if (!sbits_fused_layout_ok(plan, true)) return SBITS_ERR_UNIMPLEMENTED;
     return sbits_launch_surrogates_all(plan, row_perm, col_perm, level, s_up, s_down, ws);
 }
@@ -398,9 +425,14 @@ int sbits_gather_pack_all(sbits_plan *plan, const sbits_matrix *mats, const int3
     if (!ws_fits(plan)) return SBITS_ERR_WORKSPACE;
     if (!sbits_fused_shapes_ok(plan)) return SBITS_ERR_UNIMPLEMENTED;
     if ((rc = need_device(plan))) return rc;
-    if ((rc = sbits_upload_descs(plan, mats, ws))) return rc;
+    if ((rc = sbits_upload_head(plan, mats, nullptr, ws))) return rc;
     if (!sbits_fused_layout_ok(plan, false)) return SBITS_ERR_UNIMPLEMENTED;
     return sbits_launch_gather_pack_all(plan, row_perm, col_perm, level, byte_off, codes, scale, zero, ws);
+}
+
+static bool params_ok(const sbits_params *p, double avg_bits)
+{
+    return p->gamma0 >= 0 && p->gammaT >= 0 && p->max_iters >= 1 && (p->init_mode == 0 || p->init_mode == 1) && avg_bits == avg_bits;
 }
 
 int sbits_allocate(sbits_plan *plan, const float *cost, double avg_bits, const sbits_params *params,
@@ -409,14 +441,13 @@ int sbits_allocate(sbits_plan *plan, const float *cost, double avg_bits, const s
 {
     if (!plan || !cost || !params || !level || !ws_ok(ws)) return SBITS_ERR_INVALID_ARG;
     if (!ws_fits(plan)) return SBITS_ERR_WORKSPACE;
-    if (!(params->gamma0 >= 0) || !(params->gammaT >= 0) || params->max_iters < 1 ||
-        (params->init_mode != 0 && params->init_mode != 1) || !(avg_bits == avg_bits))
-        return SBITS_ERR_INVALID_ARG;
+    if (!params_ok(params, avg_bits)) return SBITS_ERR_INVALID_ARG;
     if (avg_bits < (double)plan->bits[0]) return SBITS_ERR_INFEASIBLE_BUDGET;
     int rc = need_device(plan);
     if (rc) return rc;
-    return sbits_run_allocate(plan, cost, avg_bits, params, level, host_stats, host_trace, trace_cap,
-                              sbits_scratch(plan, ws));
+    if ((rc = sbits_enqueue_allocate(plan, cost, avg_bits, params, level, sbits_scratch(plan, ws)))) return rc;
+    SBITS_HIP(plan->ctx, hipStreamSynchronize(plan->ctx->stream));
+    return sbits_finish_allocate(plan, host_stats, host_trace, trace_cap, sbits_scratch(plan, ws));
 }
 
 int sbits_propose(sbits_plan *plan, const float *s_up, const float *s_down, const uint8_t *level_in,
@@ -508,7 +539,7 @@ int sbits_pack_all(sbits_plan *plan, const void *w_re_bf16, const uint8_t *level
     if (!aligned16(w_re_bf16) || !aligned16(codes)) return SBITS_ERR_INVALID_ARG;
     int rc = need_device(plan);
     if (rc) return rc;
-    if ((rc = sbits_upload_descs(plan, nullptr, ws))) return rc;
+    if ((rc = sbits_upload_head(plan, nullptr, nullptr, ws))) return rc;
     return sbits_launch_pack_all(plan, w_re_bf16, level, byte_off, codes, scale, zero, ws);
 }
 
@@ -534,14 +565,15 @@ static int search_impl(sbits_plan *plan, const sbits_matrix *mats, const Couplin
     int rc = need_device(plan);
     if (rc) return rc;
     if ((rc = check_all(plan, mats, true, true))) return rc;
+    sbits_coupling tables;
     if (cpl.row_group &&
         (rc = sbits_coupling_tables(plan, cpl.row_group, cpl.col_group, cpl.n_groups, cpl.group_segment, cpl.row_repeat,
-                                    cpl.col_repeat, nullptr, nullptr, nullptr, nullptr, nullptr)))
+                                    cpl.col_repeat, &tables)))
         return rc;
-    if ((rc = sbits_upload_descs(plan, mats, ws))) return rc;
+    if (!params_ok(params, avg_bits)) return SBITS_ERR_INVALID_ARG;
+    if ((rc = sbits_upload_head(plan, mats, cpl.row_group ? &tables : nullptr, ws))) return rc;
     if (cpl.row_group)
-        rc = sbits_launch_reorder_coupled_all(plan, cpl.row_group, cpl.col_group, cpl.n_groups, cpl.group_segment,
-                                              cpl.row_repeat, cpl.col_repeat, out->row_perm, out->col_perm, ws);
+        rc = sbits_launch_reorder_coupled_all(plan, tables, out->row_perm, out->col_perm, ws);
     else
         rc = sbits_launch_reorder_all(plan, out->row_perm, out->col_perm, ws);
     if (rc) return rc;
@@ -555,10 +587,12 @@ static int search_impl(sbits_plan *plan, const sbits_matrix *mats, const Couplin
             return rc;
         if ((rc = sbits_launch_cost_all(plan, out->w_re_bf16, out->s_re, out->cost, ws))) return rc;
     }
-    rc = sbits_allocate(plan, out->cost, avg_bits, params, out->level, host_stats, nullptr, 0, ws);
-    const int alloc_rc = rc;
-    if (rc && rc != SBITS_ERR_MAX_ITERS) return rc;
-    if ((rc = sbits_offsets(plan, out->level, out->byte_off, ws))) return rc;
+    // Nothing of what follows waits for the host: the levels are valid whatever the search ends with, and its result is read
+    // at the end (a wait in between left the device idle for 40 us while the host woke up and enqueued the rest).
+    void *const scratch = sbits_scratch(plan, ws);
+    if ((rc = sbits_enqueue_allocate(plan, out->cost, avg_bits, params, out->level, scratch))) return rc;
+    if ((rc = sbits_launch_offsets(plan->ctx, out->level, plan->N, plan->m, plan->n, plan->bits, plan->K, out->byte_off, scratch)))
+        return rc;
     if (one_pass)
         rc = sbits_launch_gather_pack_all(plan, out->row_perm, out->col_perm, out->level, out->byte_off, out->codes,
                                           out->scale, out->zero, ws);
@@ -567,7 +601,7 @@ static int search_impl(sbits_plan *plan, const sbits_matrix *mats, const Couplin
                                    out->zero, ws);
     if (rc) return rc;
     SBITS_HIP(plan->ctx, hipStreamSynchronize(plan->ctx->stream));
-    return alloc_rc;
+    return sbits_finish_allocate(plan, host_stats, nullptr, 0, scratch);
 }
 
 extern "C" {

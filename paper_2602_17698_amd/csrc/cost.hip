@@ -479,6 +479,19 @@ int sbits_launch_cost(sbits_ctx *ctx, const void *Wp, const float *Sp, int64_t R
     return launch(n, bits, K, ctx, a);
 }
 
+// units per matrix, summed up
+void sbits_cost_tables(sbits_plan *plan)
+{
+    const int bpu = sbits::blocks_per_unit(plan->m, plan->n);
+    int64_t t = 0;
+    for (int i = 0; i < plan->n_mats; ++i) {
+        plan->cost_unit_start.push_back((int)t);
+        t += (int64_t)plan->descs[i].nbr * ((plan->descs[i].nbc + bpu - 1) / bpu);
+        if (t > 0x7fffffff) { plan->cost_unit_start.clear(); return; }
+    }
+    plan->cost_unit_start.push_back((int)t);
+}
+
 // all matrices of the plan in one launch; the descriptor table is already in the workspace head
 int sbits_launch_cost_all(sbits_plan *plan, const void *w_re, const float *s_re, float *cost, void *ws)
 {
@@ -486,22 +499,10 @@ int sbits_launch_cost_all(sbits_plan *plan, const void *w_re, const float *s_re,
     sbits_ctx *ctx = plan->ctx;
     CostLaunch a;
     memset(&a, 0, sizeof a);
-    if (plan->cost_unit_start.empty()) {             // depends on shapes only: computed once, kept for the copies
-        const int bpu = blocks_per_unit(plan->m, plan->n);
-        int64_t t = 0;
-        for (int i = 0; i < plan->n_mats; ++i) {
-            plan->cost_unit_start.push_back((int)t);
-            t += (int64_t)plan->descs[i].nbr * ((plan->descs[i].nbc + bpu - 1) / bpu);
-            if (t > 0x7fffffff) { plan->cost_unit_start.clear(); return SBITS_ERR_BAD_SHAPE; }
-        }
-        plan->cost_unit_start.push_back((int)t);
-    }
+    if (plan->cost_unit_start.empty()) return SBITS_ERR_BAD_SHAPE;
     const int64_t tot = plan->cost_unit_start.back();
-    int *d_pre = sbits_prefix_ptr(plan, ws, 0);
-    SBITS_HIP(ctx, hipMemcpyAsync(d_pre, plan->cost_unit_start.data(), plan->cost_unit_start.size() * 4,
-                                  hipMemcpyHostToDevice, ctx->stream));
     a.descs = sbits_desc_ptr(ws);
-    a.unit_start = d_pre;
+    a.unit_start = sbits_prefix_ptr(plan, ws, SLOT_COST_UNITS);
     a.n_mats = plan->n_mats;
     a.total_units = tot;
     a.W = static_cast<const uint16_t *>(w_re);

@@ -1082,57 +1082,51 @@ bool sbits_fused_layout_ok(const sbits_plan *plan, bool need_s)
     return !need_s || plan->ctx->d16_zero_fill;
 }
 
-// matrices grouped by column count; members and workgroup prefixes go to slots 3 and 4 of the
-// workspace head (the tables depend on shapes only: built once, kept in the plan)
-static int fused_classes(sbits_plan *plan, void *ws, int **d_mem, int **d_pre)
+// matrices grouped by column count: members and workgroup prefixes, class after class
+void sbits_fused_tables(sbits_plan *plan)
 {
-    sbits_ctx *ctx = plan->ctx;
-    if (plan->fused_members.empty()) {
-        std::vector<int64_t> classes;
-        for (int i = 0; i < plan->n_mats; ++i) {
-            bool seen = false;
-            for (int64_t c : classes) seen = seen || c == plan->cols[i];
-            if (!seen) classes.push_back(plan->cols[i]);
-        }
-        for (int64_t c : classes) {
-            sbits_plan::FusedClass fc;
-            fc.cols = c;
-            fc.first = (int)plan->fused_members.size();
-            fc.pre_first = (int)plan->fused_pre.size();
-            fc.n = 0;
-            // octets per workgroup: FU_OPU, halved while the class would not even give every CU a few
-            // workgroups (one decoder layer of a streamed model is such a plan)
-            int opu = FU_OPU;
-            auto class_wgs = [&](int o) {
-                int64_t t = 0;
-                for (int i = 0; i < plan->n_mats; ++i)
-                    if (plan->cols[i] == c) t += (plan->rows[i] / 8 + o - 1) / o;
-                return t;
-            };
-            while (opu > 2 && class_wgs(opu) < 2048) opu >>= 1;
-            fc.opu = opu;
-            int64_t t = 0;
-            for (int i = 0; i < plan->n_mats; ++i) {
-                if (plan->cols[i] != c) continue;
-                plan->fused_members.push_back(i);
-                plan->fused_pre.push_back((int)t);
-                t += (plan->rows[i] / 8 + opu - 1) / opu;
-                ++fc.n;
-            }
-            if (t > 0x7fffffff) {
-                plan->fused_members.clear(); plan->fused_pre.clear(); plan->fused_classes.clear();
-                return SBITS_ERR_BAD_SHAPE;
-            }
-            plan->fused_pre.push_back((int)t);
-            plan->fused_classes.push_back(fc);
-        }
+    std::vector<int64_t> classes;
+    for (int i = 0; i < plan->n_mats; ++i) {
+        bool seen = false;
+        for (int64_t c : classes) seen = seen || c == plan->cols[i];
+        if (!seen) classes.push_back(plan->cols[i]);
     }
-    *d_mem = sbits_prefix_ptr(plan, ws, 3);
-    *d_pre = sbits_prefix_ptr(plan, ws, 4);
-    SBITS_HIP(ctx, hipMemcpyAsync(*d_mem, plan->fused_members.data(), plan->fused_members.size() * 4,
-                                  hipMemcpyHostToDevice, ctx->stream));
-    SBITS_HIP(ctx, hipMemcpyAsync(*d_pre, plan->fused_pre.data(), plan->fused_pre.size() * 4,
-                                  hipMemcpyHostToDevice, ctx->stream));
+    for (int64_t c : classes) {
+        sbits_plan::FusedClass fc;
+        fc.cols = c;
+        fc.first = (int)plan->fused_members.size();
+        fc.pre_first = (int)plan->fused_pre.size();
+        fc.n = 0;
+        // octets per workgroup: FU_OPU, halved while the class would not even give every CU a few
+        // workgroups (one decoder layer of a streamed model is such a plan)
+        int opu = FU_OPU;
+        auto class_wgs = [&](int o) {
+            int64_t t = 0;
+            for (int i = 0; i < plan->n_mats; ++i)
+                if (plan->cols[i] == c) t += (plan->rows[i] / 8 + o - 1) / o;
+            return t;
+        };
+        while (opu > 2 && class_wgs(opu) < 2048) opu >>= 1;
+        fc.opu = opu;
+        int64_t t = 0;
+        for (int i = 0; i < plan->n_mats; ++i) {
+            if (plan->cols[i] != c) continue;
+            plan->fused_members.push_back(i);
+            plan->fused_pre.push_back((int)t);
+            t += (plan->rows[i] / 8 + opu - 1) / opu;
+            ++fc.n;
+        }
+        if (t > 0x7fffffff) { plan->fused_members.clear(); plan->fused_pre.clear(); plan->fused_classes.clear(); return; }
+        plan->fused_pre.push_back((int)t);
+        plan->fused_classes.push_back(fc);
+    }
+}
+
+static int fused_classes(sbits_plan *plan, void *ws, const int **d_mem, const int **d_pre)
+{
+    if (plan->fused_classes.empty()) return SBITS_ERR_BAD_SHAPE;
+    *d_mem = sbits_prefix_ptr(plan, ws, SLOT_FUSED_MEMBERS);
+    *d_pre = sbits_prefix_ptr(plan, ws, SLOT_FUSED_WGS);
     return SBITS_OK;
 }
 
@@ -1143,7 +1137,7 @@ int sbits_launch_gather_cost_all(sbits_plan *plan, const int32_t *row_perm, cons
 {
     sbits_ctx *ctx = plan->ctx;
     if (!sbits_fused_shapes_ok(plan) || !sbits_fused_layout_ok(plan, true)) return SBITS_ERR_BAD_SHAPE;
-    int *d_mem, *d_pre;
+    const int *d_mem, *d_pre;
     int rc0 = fused_classes(plan, ws, &d_mem, &d_pre);
     if (rc0) return rc0;
     FusedLaunch a;
@@ -1201,7 +1195,7 @@ int sbits_launch_gather_pack_all(sbits_plan *plan, const int32_t *row_perm, cons
 {
     sbits_ctx *ctx = plan->ctx;
     if (!sbits_fused_shapes_ok(plan) || !sbits_fused_layout_ok(plan, false)) return SBITS_ERR_BAD_SHAPE;
-    int *d_mem, *d_pre;
+    const int *d_mem, *d_pre;
     int rc0 = fused_classes(plan, ws, &d_mem, &d_pre);
     if (rc0) return rc0;
     FusedPackLaunch a;
@@ -1234,7 +1228,7 @@ int sbits_launch_surrogates_all(sbits_plan *plan, const int32_t *row_perm, const
 {
     sbits_ctx *ctx = plan->ctx;
     if (!sbits_fused_all_staged(plan) || !sbits_fused_layout_ok(plan, true)) return SBITS_ERR_BAD_SHAPE;
-    int *d_mem, *d_pre;
+    const int *d_mem, *d_pre;
     int rc0 = fused_classes(plan, ws, &d_mem, &d_pre);
     if (rc0) return rc0;
     FusedLaunch a;

@@ -321,6 +321,18 @@ int sbits_launch_pack(sbits_ctx *ctx, const void *Wp, int64_t R, int64_t C, int 
     return launch_pack(n, ctx, a);
 }
 
+// workgroups per matrix, summed up
+void sbits_pack_tables(sbits_plan *plan)
+{
+    int64_t tot = 0;
+    for (int i = 0; i < plan->n_mats; ++i) {
+        plan->pack_wg_start.push_back((int)tot);
+        tot += pack_wgs(plan->m, plan->n, plan->descs[i].nbr, plan->descs[i].nbc);
+        if (tot > 0x7fffffff) { plan->pack_wg_start.clear(); return; }
+    }
+    plan->pack_wg_start.push_back((int)tot);
+}
+
 // all matrices of the plan in one launch; the descriptor table is already in the workspace head
 int sbits_launch_pack_all(sbits_plan *plan, const void *w_re, const uint8_t *level, const int64_t *byte_off,
                           uint8_t *codes, float *scale, float *zero, void *ws)
@@ -329,20 +341,9 @@ int sbits_launch_pack_all(sbits_plan *plan, const void *w_re, const uint8_t *lev
     PackLaunch a;
     memset(&a, 0, sizeof a);
     sbits_fill_grid_consts(plan->bits, plan->K, &a.gc);
-    if (plan->pack_wg_start.empty()) {
-        int64_t tot = 0;
-        for (int i = 0; i < plan->n_mats; ++i) {
-            plan->pack_wg_start.push_back((int)tot);
-            tot += pack_wgs(plan->m, plan->n, plan->descs[i].nbr, plan->descs[i].nbc);
-            if (tot > 0x7fffffff) { plan->pack_wg_start.clear(); return SBITS_ERR_BAD_SHAPE; }
-        }
-        plan->pack_wg_start.push_back((int)tot);
-    }
-    int *d_pre = sbits_prefix_ptr(plan, ws, 2);
-    SBITS_HIP(ctx, hipMemcpyAsync(d_pre, plan->pack_wg_start.data(), plan->pack_wg_start.size() * 4,
-                                  hipMemcpyHostToDevice, ctx->stream));
+    if (plan->pack_wg_start.empty()) return SBITS_ERR_BAD_SHAPE;
     a.descs = sbits_desc_ptr(ws);
-    a.wg_start = d_pre;
+    a.wg_start = sbits_prefix_ptr(plan, ws, SLOT_PACK_WGS);
     a.n_mats = plan->n_mats;
     a.total_wg = plan->pack_wg_start.back();
     a.W = static_cast<const uint16_t *>(w_re);

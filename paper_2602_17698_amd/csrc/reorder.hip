@@ -747,9 +747,7 @@ int sbits_launch_reorder_all(sbits_plan *plan, int32_t *row_perm, int32_t *col_p
     ReorderWs w;
     reorder_ws_layout(sbits_scratch(plan, ws), plan->sum_rows + plan->sum_cols, plan->sum_rowpart,
                       plan->sum_colpart, &w);
-    int *d_pre = sbits_prefix_ptr(plan, ws, 1);
-    SBITS_HIP(ctx, hipMemcpyAsync(d_pre, plan->score_wg_start.data(), plan->score_wg_start.size() * 4,
-                                  hipMemcpyHostToDevice, ctx->stream));
+    const int *d_pre = sbits_prefix_ptr(plan, ws, SLOT_SCORE_WGS);
     MatDesc none;
     memset(&none, 0, sizeof none);
     int rc = run_scores(ctx, sbits_desc_ptr(ws), none, d_pre, plan->n_mats, plan->score_wg_start.back(),
@@ -765,8 +763,7 @@ int sbits_launch_reorder_all(sbits_plan *plan, int32_t *row_perm, int32_t *col_p
 // (seg), the next member of its group (next) and, for non-leaders, the group's first member (leader).
 int sbits_coupling_tables(const sbits_plan *plan, const int32_t *row_group, const int32_t *col_group, int n_groups,
                           const int32_t *group_segment, const int32_t *row_repeat, const int32_t *col_repeat,
-                          std::vector<int> *mode_, std::vector<int> *seg_, std::vector<int> *next_,
-                          std::vector<int> *leader_, std::vector<int> *rep_)
+                          sbits_coupling *out)
 {
     const int nm = plan->n_mats, na = 2 * nm;
     std::vector<int> mode(na), seg(na, 0), next(na, -1), leader(na, -1), rep(na, 1);
@@ -802,40 +799,25 @@ int sbits_coupling_tables(const sbits_plan *plan, const int32_t *row_group, cons
             last[g] = a;
         }
     }
-    if (mode_) { *mode_ = mode; *seg_ = seg; *next_ = next; *leader_ = leader; *rep_ = rep; }
+    *out = sbits_coupling{mode, seg, next, leader, rep};
     return SBITS_OK;
 }
 
 // Coupled reordering of all matrices.  group[a] for every array a (rows of matrix a, or columns of
 // matrix a - n_mats): SBITS_DIM_INDEPENDENT, SBITS_DIM_FIXED or a group id; segment[g]: 0 or the
-// piece length for group g; repeat: pieces of the member per piece of the group.  Tables go to
-// slots 6..10 of the workspace head.
-int sbits_launch_reorder_coupled_all(sbits_plan *plan, const int32_t *row_group, const int32_t *col_group,
-                                     int n_groups, const int32_t *group_segment, const int32_t *row_repeat,
-                                     const int32_t *col_repeat, int32_t *row_perm, int32_t *col_perm, void *ws)
+// piece length for group g; repeat: pieces of the member per piece of the group.  The tables made of
+// them are in the workspace head.
+int sbits_launch_reorder_coupled_all(sbits_plan *plan, const sbits_coupling &cpl, int32_t *row_perm, int32_t *col_perm, void *ws)
 {
     sbits_ctx *ctx = plan->ctx;
     const int nm = plan->n_mats, na = 2 * nm;
-    std::vector<int> mode, seg, next, leader, rep;
-    int rcv = sbits_coupling_tables(plan, row_group, col_group, n_groups, group_segment, row_repeat, col_repeat,
-                                    &mode, &seg, &next, &leader, &rep);
-    if (rcv) return rcv;
-    int *d_mode = sbits_prefix_ptr(plan, ws, 6), *d_seg = sbits_prefix_ptr(plan, ws, 7);
-    int *d_next = sbits_prefix_ptr(plan, ws, 8), *d_leader = sbits_prefix_ptr(plan, ws, 9);
-    int *d_rep = sbits_prefix_ptr(plan, ws, 10);
-    SBITS_HIP(ctx, hipMemcpyAsync(d_mode, mode.data(), (size_t)na * 4, hipMemcpyHostToDevice, ctx->stream));
-    SBITS_HIP(ctx, hipMemcpyAsync(d_seg, seg.data(), (size_t)na * 4, hipMemcpyHostToDevice, ctx->stream));
-    SBITS_HIP(ctx, hipMemcpyAsync(d_next, next.data(), (size_t)na * 4, hipMemcpyHostToDevice, ctx->stream));
-    SBITS_HIP(ctx, hipMemcpyAsync(d_leader, leader.data(), (size_t)na * 4, hipMemcpyHostToDevice, ctx->stream));
-    SBITS_HIP(ctx, hipMemcpyAsync(d_rep, rep.data(), (size_t)na * 4, hipMemcpyHostToDevice, ctx->stream));
-    SBITS_HIP(ctx, hipStreamSynchronize(ctx->stream));           // the host vectors go away on return
-
+    const int *d_mode = sbits_prefix_ptr(plan, ws, SLOT_ARR_MODE), *d_seg = sbits_prefix_ptr(plan, ws, SLOT_ARR_SEG);
+    const int *d_next = sbits_prefix_ptr(plan, ws, SLOT_ARR_NEXT), *d_leader = sbits_prefix_ptr(plan, ws, SLOT_ARR_LEADER);
+    const int *d_rep = sbits_prefix_ptr(plan, ws, SLOT_ARR_REP);
     ReorderWs w;
     reorder_ws_layout(sbits_scratch(plan, ws), plan->sum_rows + plan->sum_cols, plan->sum_rowpart,
                       plan->sum_colpart, &w);
-    int *d_pre = sbits_prefix_ptr(plan, ws, 1);
-    SBITS_HIP(ctx, hipMemcpyAsync(d_pre, plan->score_wg_start.data(), plan->score_wg_start.size() * 4,
-                                  hipMemcpyHostToDevice, ctx->stream));
+    const int *d_pre = sbits_prefix_ptr(plan, ws, SLOT_SCORE_WGS);
     MatDesc none;
     memset(&none, 0, sizeof none);
     const MatDesc *descs = sbits_desc_ptr(ws);
@@ -844,69 +826,66 @@ int sbits_launch_reorder_coupled_all(sbits_plan *plan, const int32_t *row_group,
     const int64_t maxlen = plan->max_rows > plan->max_cols ? plan->max_rows : plan->max_cols;
     const dim3 g2((unsigned)((maxlen + 255) / 256), (unsigned)na);
     hipLaunchKernelGGL(group_sum_kernel, g2, dim3(256), 0, ctx->stream, descs, nm, plan->sum_rows, w.scores,
-                       (const int *)d_mode, (const int *)d_next, (const int *)d_seg, (const int *)d_rep);
+                       d_mode, d_next, d_seg, d_rep);
     int64_t max_piece = 1;
     for (int a = 0; a < na; ++a) {
-        const int64_t len = mode[a] != ARR_SORT ? 1 : seg[a] > 0 ? seg[a] : a < nm ? plan->rows[a] : plan->cols[a - nm];
+        const int64_t len = cpl.mode[a] != ARR_SORT ? 1 : cpl.seg[a] > 0 ? cpl.seg[a] : a < nm ? plan->rows[a] : plan->cols[a - nm];
         if (len > max_piece) max_piece = len;
     }
     rc = run_argsort(ctx, SortArrays{descs, none, nm, 1, plan->sum_rows, d_mode, d_seg, row_perm, col_perm}, maxlen, max_piece, w);
     if (rc) return rc;
     hipLaunchKernelGGL(replicate_perm_kernel, g2, dim3(256), 0, ctx->stream, descs, nm, row_perm, col_perm,
-                       (const int *)d_mode, (const int *)d_leader, (const int *)d_seg, (const int *)d_rep);
+                       d_mode, d_leader, d_seg, d_rep);
     SBITS_HIP(ctx, hipGetLastError());
     return SBITS_OK;
 }
 
+// Matrices grouped by column count: members and workgroup prefixes of the weights' and the sensitivities' launches,
+// class after class (each class has n_k + 1 prefix entries).
+void sbits_gather_tables(sbits_plan *plan)
+{
+    std::vector<int64_t> classes;
+    for (int i = 0; i < plan->n_mats; ++i) {
+        bool seen = false;
+        for (int64_t c : classes) seen = seen || c == plan->cols[i];
+        if (!seen) classes.push_back(plan->cols[i]);
+    }
+    for (int64_t c : classes) {
+        sbits_plan::GatherClass gc;
+        gc.cols = c;
+        gc.first = (int)plan->gather_members.size();
+        gc.pre_first = (int)plan->gather_pre_w.size();
+        gc.rpw_w = gather_rows_per_wg(c, 2);
+        gc.rpw_s = gather_rows_per_wg(c, 4);
+        int64_t tw = 0, ts = 0;
+        gc.n = 0;
+        for (int i = 0; i < plan->n_mats; ++i) {
+            if (plan->cols[i] != c) continue;
+            plan->gather_members.push_back(i);
+            plan->gather_pre_w.push_back((int)tw);
+            plan->gather_pre_s.push_back((int)ts);
+            tw += (plan->rows[i] + gc.rpw_w - 1) / gc.rpw_w;
+            ts += (plan->rows[i] + gc.rpw_s - 1) / gc.rpw_s;
+            ++gc.n;
+        }
+        if (tw > 0x7fffffff || ts > 0x7fffffff) {
+            plan->gather_members.clear(); plan->gather_pre_w.clear(); plan->gather_pre_s.clear(); plan->gather_classes.clear();
+            return;
+        }
+        plan->gather_pre_w.push_back((int)tw);
+        plan->gather_pre_s.push_back((int)ts);
+        plan->gather_classes.push_back(gc);
+    }
+}
+
 // One launch per class of matrices with equal column count (equal LDS need) and element type.
-// The class tables depend on shapes only: built once, kept in the plan, copied per call.
-//   slot 3 of the workspace head: members of all classes, class after class
-//   slot 4: workgroup prefixes (W), slot 5: workgroup prefixes (S); each class has n_k + 1 entries
 int sbits_launch_gather_all(sbits_plan *plan, const int32_t *row_perm, const int32_t *col_perm,
                             void *w_re, float *s_re, void *ws)
 {
     sbits_ctx *ctx = plan->ctx;
-    if ((size_t)plan->max_cols * 4 > 160 * 1024) return SBITS_ERR_BAD_SHAPE;
-    if (plan->gather_members.empty()) {
-        std::vector<int64_t> classes;
-        for (int i = 0; i < plan->n_mats; ++i) {
-            bool seen = false;
-            for (int64_t c : classes) seen = seen || c == plan->cols[i];
-            if (!seen) classes.push_back(plan->cols[i]);
-        }
-        for (int64_t c : classes) {
-            sbits_plan::GatherClass gc;
-            gc.cols = c;
-            gc.first = (int)plan->gather_members.size();
-            gc.pre_first = (int)plan->gather_pre_w.size();
-            gc.rpw_w = gather_rows_per_wg(c, 2);
-            gc.rpw_s = gather_rows_per_wg(c, 4);
-            int64_t tw = 0, ts = 0;
-            gc.n = 0;
-            for (int i = 0; i < plan->n_mats; ++i) {
-                if (plan->cols[i] != c) continue;
-                plan->gather_members.push_back(i);
-                plan->gather_pre_w.push_back((int)tw);
-                plan->gather_pre_s.push_back((int)ts);
-                tw += (plan->rows[i] + gc.rpw_w - 1) / gc.rpw_w;
-                ts += (plan->rows[i] + gc.rpw_s - 1) / gc.rpw_s;
-                ++gc.n;
-            }
-            if (tw > 0x7fffffff || ts > 0x7fffffff) { plan->gather_members.clear(); return SBITS_ERR_BAD_SHAPE; }
-            plan->gather_pre_w.push_back((int)tw);
-            plan->gather_pre_s.push_back((int)ts);
-            plan->gather_classes.push_back(gc);
-        }
-    }
-    int *d_mem = sbits_prefix_ptr(plan, ws, 3);
-    int *d_pw = sbits_prefix_ptr(plan, ws, 4);
-    int *d_ps = sbits_prefix_ptr(plan, ws, 5);
-    SBITS_HIP(ctx, hipMemcpyAsync(d_mem, plan->gather_members.data(), plan->gather_members.size() * 4,
-                                  hipMemcpyHostToDevice, ctx->stream));
-    SBITS_HIP(ctx, hipMemcpyAsync(d_pw, plan->gather_pre_w.data(), plan->gather_pre_w.size() * 4,
-                                  hipMemcpyHostToDevice, ctx->stream));
-    SBITS_HIP(ctx, hipMemcpyAsync(d_ps, plan->gather_pre_s.data(), plan->gather_pre_s.size() * 4,
-                                  hipMemcpyHostToDevice, ctx->stream));
+    if ((size_t)plan->max_cols * 4 > 160 * 1024 || plan->gather_classes.empty()) return SBITS_ERR_BAD_SHAPE;
+    const int *d_mem = sbits_prefix_ptr(plan, ws, SLOT_GATHER_MEMBERS);
+    const int *d_pw = sbits_prefix_ptr(plan, ws, SLOT_GATHER_WGS_W), *d_ps = sbits_prefix_ptr(plan, ws, SLOT_GATHER_WGS_S);
     MatDesc none;
     memset(&none, 0, sizeof none);
     const MatDesc *descs = sbits_desc_ptr(ws);

@@ -15,7 +15,7 @@ struct sbits_ctx {
     int device;            // -1: host-only context
     hipStream_t stream;
     int last_hip;
-    void *pinned;          // small page-locked host buffer for state read-backs (allocated on first use)
+    void *pinned;          // small page-locked host buffer that the device writes results to (allocated on first use)
     int cus;               // compute units of the device (0: host-only)
     bool d16_zero_fill;    // 16-bit loads into a register half write zeros to the other half (target id "sramecc+")
 };
@@ -45,15 +45,21 @@ struct sbits_plan {
     size_t head_bytes;                       // workspace head: descriptor table + workgroup prefixes
     size_t ws_bytes;
     size_t ws_given;                         // size of the caller's workspace if declared, else SIZE_MAX
-    void *desc_pinned;                       // two page-locked images of the descriptor table (allocated on first upload)
+    void *desc_pinned;                       // two page-locked images of the workspace head (allocated on first upload)
     hipEvent_t desc_done[2];                 // recorded behind the upload that read image i
     bool desc_used[2];
     int desc_turn;
 };
 
 // The workspace head holds the per-matrix descriptor table and the small integer tables (workgroup
-// prefixes, class members, coupling tables) of the batched launches; stage scratch starts at sbits_scratch(plan, ws).
-constexpr int SBITS_N_PREFIX = 11;
+// prefixes, class members, coupling tables) of the batched launches, one slot each; a call sends it whole, in one copy.
+// Stage scratch starts at sbits_scratch(plan, ws).
+enum {
+    SLOT_COST_UNITS, SLOT_SCORE_WGS, SLOT_PACK_WGS, SLOT_FUSED_MEMBERS, SLOT_FUSED_WGS, SLOT_GATHER_MEMBERS, SLOT_GATHER_WGS_W,
+    SLOT_GATHER_WGS_S, SLOT_ARR_MODE, SLOT_ARR_SEG, SLOT_ARR_NEXT, SLOT_ARR_LEADER, SLOT_ARR_REP, SBITS_N_PREFIX
+};
+// what a coupled reordering does with every array (see sbits_coupling_tables)
+struct sbits_coupling { std::vector<int> mode, seg, next, leader, rep; };
 static inline size_t sbits_desc_bytes(int n_mats) { return (size_t)((n_mats * sizeof(sbits::MatDesc) + 255) / 256 * 256); }
 static inline size_t sbits_prefix_bytes(int n_mats) { return (size_t)((2 * (n_mats + 1) * 4 + 255) / 256 * 256); }
 static inline sbits::MatDesc *sbits_desc_ptr(void *ws) { return static_cast<sbits::MatDesc *>(ws); }
@@ -89,11 +95,8 @@ int sbits_launch_reorder(sbits_ctx *ctx, const float *S, int64_t R, int64_t C, i
 int sbits_launch_reorder_all(sbits_plan *plan, int32_t *row_perm, int32_t *col_perm, void *ws);
 int sbits_coupling_tables(const sbits_plan *plan, const int32_t *row_group, const int32_t *col_group, int n_groups,
                           const int32_t *group_segment, const int32_t *row_repeat, const int32_t *col_repeat,
-                          std::vector<int> *mode, std::vector<int> *seg, std::vector<int> *next,
-                          std::vector<int> *leader, std::vector<int> *rep);
-int sbits_launch_reorder_coupled_all(sbits_plan *plan, const int32_t *row_group, const int32_t *col_group,
-                                     int n_groups, const int32_t *group_segment, const int32_t *row_repeat,
-                                     const int32_t *col_repeat, int32_t *row_perm, int32_t *col_perm, void *ws);
+                          sbits_coupling *out);
+int sbits_launch_reorder_coupled_all(sbits_plan *plan, const sbits_coupling &cpl, int32_t *row_perm, int32_t *col_perm, void *ws);
 int sbits_launch_gather_all(sbits_plan *plan, const int32_t *row_perm, const int32_t *col_perm,
                             void *w_re, float *s_re, void *ws);
 int sbits_launch_pack_all(sbits_plan *plan, const void *w_re, const uint8_t *level, const int64_t *byte_off,
@@ -103,8 +106,13 @@ int sbits_launch_gather(sbits_ctx *ctx, const void *W, const float *S, int64_t R
                         void *w_out, float *s_out);
 int sbits_launch_cost(sbits_ctx *ctx, const void *Wp, const float *Sp, int64_t R, int64_t C,
                       int m, int n, const int32_t *bits, int K, float *cost_rows);
-// batched over all matrices of the plan (descriptor table already in the workspace head)
-int sbits_upload_descs(sbits_plan *plan, const sbits_matrix *mats, void *ws);
+// batched over all matrices of the plan (workspace head already there)
+int sbits_upload_head(sbits_plan *plan, const sbits_matrix *mats, const sbits_coupling *cpl, void *ws);
+// the tables of the head that follow from the plan's shapes (each left empty if it would not fit 32 bits)
+void sbits_cost_tables(sbits_plan *plan);
+void sbits_pack_tables(sbits_plan *plan);
+void sbits_fused_tables(sbits_plan *plan);
+void sbits_gather_tables(sbits_plan *plan);
 int sbits_launch_cost_all(sbits_plan *plan, const void *w_re, const float *s_re, float *cost, void *ws);
 // gather fused with the cost table (reads the original matrices once; writes w_re and cost)
 bool sbits_fused_shapes_ok(const sbits_plan *plan);
@@ -131,9 +139,10 @@ int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t 
                          const float *zero, float *y, void *scratch);
 int sbits_run_propose(sbits_plan *plan, const float *s_up, const float *s_down, const uint8_t *level_in,
                       double avg_bits, int64_t k, uint8_t *level_out, sbits_proposal *host_out, void *ws);
-int sbits_run_allocate(sbits_plan *plan, const float *cost, double avg_bits,
-                       const sbits_params *prm, uint8_t *level, sbits_stats *host_stats,
-                       sbits_trace *host_trace, int64_t trace_cap, void *ws);
+// allocation: everything enqueued, without a wait; then, after the caller has waited for the stream, its result.  In between
+// the scratch may be used again (a trace is lost then), the context's page-locked buffer may not.
+int sbits_enqueue_allocate(sbits_plan *plan, const float *cost, double avg_bits, const sbits_params *prm, uint8_t *level, void *ws);
+int sbits_finish_allocate(sbits_plan *plan, sbits_stats *host_stats, sbits_trace *host_trace, int64_t trace_cap, void *ws);
 int sbits_launch_offsets(sbits_ctx *ctx, const uint8_t *level, int64_t N, int m, int n,
                          const int32_t *bits, int K, int64_t *byte_off, void *ws);
 int sbits_offsets_static_setup(sbits_ctx *ctx);
