@@ -6,8 +6,8 @@ Variants (compile-time switches of the arithmetic, one library each):
 For the tests only (--tests):
   "impatient" -> libscalebits_impatient.so   the search's workgroups give up waiting for each other at once, so that
                                              the single-workgroup search behind it is reached
-  "late31", "late32" -> ...                  the search's count of arrivals starts where 31 or 32 bits end, and a search
-                                             that was given up is not repeated
+  "late31", "late32" -> ...                  a search that was given up is not repeated: what they find, the resident
+                                             workgroups have found
 """
 from __future__ import annotations
 
@@ -23,8 +23,8 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 VARIANTS = {"": [], "l1": ["-DSBITS_COST_POWER=1"]}
 TEST_VARIANTS = {"impatient": ["-DSBITS_SPIN_LIMIT=0"],
-                 "late31": ["-DSBITS_FIRST_ARRIVALS=0x7ffffff0u", "-DSBITS_SECOND_TRY=0"],
-                 "late32": ["-DSBITS_FIRST_ARRIVALS=0xfffffff0u", "-DSBITS_SECOND_TRY=0"]}
+                 "late31": ["-DSBITS_SECOND_TRY=0"],
+                 "late32": ["-DSBITS_SECOND_TRY=0"]}
 ONLY = {v: ["alloc.hip"] for v in TEST_VARIANTS}       # sources a variant compiles anew; the rest are the default build's objects
 SOURCES = ["api.hip", "reorder.hip", "cost.hip", "fused.hip", "alloc.hip", "pack.hip", "mpgemm.hip", "dequant.hip"]
 

@@ -4,7 +4,7 @@
 // Per iteration:
 //   keys    : marginal cost change per bit of raising / lowering every block,
 //             read off the table at the current levels (Alg. 2 line 5), encoded
-//             as 64-bit keys  [ordered value : 32][N-1-index : IB][step bits : 8]
+//             as an ordered 32-bit word with the place of the block, [word : 32][N-1-index : 32],
 //             so that "larger key" = "earlier in (value, lower index first)".
 //             After the first iteration only the blocks that moved get new ones.
 //   select  : the longest prefix of the descending key order that keeps
@@ -21,16 +21,17 @@
 // order in which atomics land.
 //
 // What bounds it: the chain of rounds (two to three per selection, one or two selections per
-// iteration), not bytes.  With a launch per round an empty one cost 2 us and one with work 5 to 16 us
-// (state re-read from memory, ticket, the last workgroup's serial scan), and an iteration took up to
-// 20 of them and the host's answer.  Here G workgroups own a slice of the blocks each, in registers where it
+// iteration), not bytes: the latency of barriers, LDS and exchanges, of scalar state in between, and the vector instructions on the
+// keys.  G workgroups own a slice of the blocks each, in registers where it
 // fits, and stay for the whole search; what they exchange (histograms, sums) goes through device-scope atomics
-// into one of three rotating buffers, followed by a counter that all of them wait for, and every
-// workgroup draws the same conclusions from the same sums.  No fence: nothing else is shared, so no cache has to be
-// written back or invalidated.  A round takes 4 to 6 us that way, 2 us within one workgroup (512 threads: a
-// wave's share of the scan is repeated per wave; 1024 threads spill and 256 leave the LDS atomics too few waves).
-// Whole searches, launch per round before -> now: 107 k blocks, 24 iterations 2.72 -> 0.75 ms; 430 k blocks, 22 iterations
-// 2.27 -> 0.79 ms; 4.2 M blocks 4.9 -> 3.6 ms; one proposal on 430 k blocks 157 -> 72 us.
+// into one of three rotating buffers, and every workgroup draws the same conclusions from the same sums.  An exchange shows by
+// its values that it is complete, so nothing waits for the acknowledgement of what it added (see sel_rounds, team_sum).
+// No fence: nothing else is shared, so no cache has to be written back or invalidated.  A round takes 1.7 us within
+// one workgroup, 3 to 4 us with 7 to 26, 5 with 104, whose additions to the same bins take longer than the rest (512
+// threads: 1024 spill and 256 leave the LDS atomics too few waves).
+// Measured, whole searches (with a count of arrivals, 64-bit keys, one selection after the other, keys computed by the search's own
+// workgroups -> now): 13 k blocks, 15 iterations 207 -> 183 us; 27 k, 15 iterations 346 -> 266; 107 k, 15 iterations 465 -> 355;
+// 426 k, 15 iterations 428 -> 396; 336 blocks 87 -> 85; one proposal on 426 k blocks 67 -> 57, on 13 k 45 -> 37.
 #include <math.h>
 #include <string.h>
 
@@ -46,13 +47,17 @@ constexpr int SEL_DB = 10;                    // digit bits of a selection round
 constexpr int SEL_BINS = 1 << SEL_DB;
 constexpr int AL_KPT = 8;                     // blocks a thread holds in registers, or has in flight from memory
 constexpr int AL_BPT = SEL_BINS / AL_THREADS;       // bins per thread
-constexpr int AL_SUMS = 8;                    // values of one reduction
+constexpr int AL_SUMS = 5;                    // values of one reduction, at most
+constexpr int PREP_THREADS = 256, PREP_WGS = 512;
+static_assert(PREP_WGS <= AL_THREADS, "a thread of the search reads what one workgroup of the preparation found");
+constexpr int SEL_SETS = 2;                   // selections that go side by side
+enum { UP, DOWN };                            // among the blocks that can be raised, among those that can be lowered
 
 enum { MODE_NONE = 0, MODE_EXPAND = 1, MODE_ACCEPT = 2 };
 
 struct AllocHead {
     long long N, T, k, kmin, used;
-    int K, IB, l0, max_iters, done, mode;
+    int K, l0, max_iters, done, mode, min_step;
     int ceil_log2_n;
     int bits[MAX_CAND];
     unsigned long long tauE, tauU, tauD, tauU2;   // the single step on caller-supplied estimates: what it raises and lowers
@@ -66,31 +71,17 @@ struct AllocResult {
     long long prop_up, prop_dn, prop_after;
     int shift, status, iters, expansions, swaps_ok, swaps_rej, mode, valid;
 };
-// One exchange between the workgroups; three of them take turns (see grid_sync).
+// One exchange between the workgroups; three of them take turns (see end_turn).
 struct AllocXchg {
-    unsigned long long hist[SEL_BINS];        // per bin: (sum of step widths << 32) | number of keys
-    unsigned long long sum[AL_SUMS];
+    unsigned long long hist[SEL_SETS][SEL_BINS];   // per bin: (sum of step widths << 32) | number of keys
+    unsigned long long mark;                  // (workgroups that took part << 32) + the keys that they put into bins (see sel_rounds)
+    unsigned long long part[2 * AL_SUMS];     // halves of sums, each with the number of workgroups that added theirs (see team_sum)
 };
 struct AllocState {
     AllocHead head;
-    unsigned int arrived;                     // workgroups that reached the current exchange, counted on (past 32 bits: from 0 again)
-    unsigned int pad_[63];
     AllocXchg x[3];
+    unsigned long long range[PREP_WGS][AL_SUMS];   // what each workgroup of the preparation found among its blocks
 };
-
-// What the count of arrivals starts from.
-#ifndef SBITS_FIRST_ARRIVALS
-#define SBITS_FIRST_ARRIVALS 0u
-#endif
-
-// The start state from a kernel argument: no host buffer has to outlive the call, so nothing waits.
-__global__ __launch_bounds__(AL_THREADS)
-void set_state_kernel(AllocState *st, AllocHead head)
-{
-    if (threadIdx.x == 0) { st->head = head; st->arrived = SBITS_FIRST_ARRIVALS; }
-    unsigned long long *j = reinterpret_cast<unsigned long long *>(st->x);
-    for (unsigned i = threadIdx.x; i < sizeof(st->x) / 8; i += AL_THREADS) j[i] = 0ull;
-}
 
 __device__ __forceinline__ unsigned int ord_f32(float f)
 {
@@ -118,164 +109,234 @@ struct Team {
     AllocState *st;
     int G, g;                     // workgroups, this one
     long long n0, n1;             // its blocks
-    unsigned int turn;            // exchanges so far
+    int turn;                     // the exchange buffer in use
     int spin_limit;
     bool ok;                      // false: a wait was given up, leave
 };
 
+struct Sel { u64 tau; int n_sel, w_sel; };           // selected <=> key >= tau
+
+// One selection: the longest prefix of the descending order of its keys with at most cnt_max keys and at most w_max step
+// bits (neither negative).  The interval that the prefix ends in is one of words; when it has come down to a single word
+// that several keys share, it is one of places among those (tie).  The same in every thread, in scalar registers: read from LDS
+// it costs a round several hundred clocks.
+struct Pick {
+    unsigned from, last;                             // the interval, both ends in it
+    unsigned base;                                   // bin of x: (x - base) >> shift; what is outside of the bins: the next one
+    int shift;
+    unsigned tie;                                    // the shared word, or 0
+    int cnt_max, w_max;
+    Sel r;                                           // keys and step bits above the interval; the threshold, once it has ended
+};
+
+constexpr int WS_SET = 16;                           // a wave's sums of set s: entry WS_SET * s + wave
 struct AllocShared {
-    u64 hist[SEL_BINS];
-    alignas(16) int wave_c[AL_WAVES], wave_w[AL_WAVES];
-    u64 sum[AL_SUMS];
-    int above_c, above_w, at_cnt, boundary;
-    int ok;
+    alignas(16) u64 hist[SEL_SETS][SEL_BINS];
+    u64 wave[2][64];                                 // sums of the waves (see sel_rounds)
+    u64 mark;
+    int live;
+    int4 found[SEL_SETS];
+    u64 sum[AL_SUMS], part[2][2 * AL_SUMS];
     int bits[MAX_CAND];
 };
 
-__device__ __forceinline__ AllocXchg *xchg(const Team &t) { return &t.st->x[t.turn % 3u]; }
+__device__ __forceinline__ AllocXchg *xchg(const Team &t) { return &t.st->x[t.turn]; }
 
-// All workgroups have added their part to the exchange buffer of this turn; afterwards its sums are
-// complete for everybody.  The atomics are performed at the point of coherence: waiting for their
-// acknowledgement (vmcnt) orders them before the arrival.
-// The wait is bounded: if a workgroup gets no place on the device, the others leave, each after its own wait, at this
-// exchange or the next one; so do those that start later, at their first exchange that somebody is missing from.
-__device__ __forceinline__ void grid_sync(Team &t, AllocShared &sh)
+// A wait between workgroups: how long one goes on polling.  Every wait is bounded: if a workgroup gets no place on the
+// device, the others leave, each after its own wait, at this exchange or the next one; so do those that start later, at their
+// first exchange that somebody is missing from.
+__device__ __forceinline__ void give_up(Team &t)
 {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const unsigned int target = SBITS_FIRST_ARRIVALS + (unsigned int)t.G * (t.turn + 1u);
-        (void)__hip_atomic_fetch_add(&t.st->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        unsigned int seen;
-        int left = t.spin_limit;
-        // (the count is less than 2 G away from the target: the difference has a sign wherever 32 bits end)
-        while ((int)((seen = __hip_atomic_load(&t.st->arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) - target) < 0 && left-- > 0)
-            __builtin_amdgcn_s_sleep(1);
-        const bool ok = (int)(seen - target) >= 0;
-        if (!ok) (void)__hip_atomic_fetch_add(&t.st->head.aborted, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        sh.ok = ok;
-    }
-    __syncthreads();
-    t.ok = uni(sh.ok) != 0;
+    if (threadIdx.x == 0) (void)__hip_atomic_fetch_add(&t.st->head.aborted, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    t.ok = false;
 }
 
-// The end of a turn, after the sums were read.  The buffer of the turn before was read by everybody before
-// they arrived at this one: it is cleared, and is in use again two turns later.
+// The end of a turn, after its values were read complete.  Whoever took part in it had read the buffer of the turn before: that one
+// is cleared, and is in use again two turns later.  (Before a workgroup takes part in the next turn it waits for its clearing
+// stores, so whoever finds the next turn complete finds that buffer clear.)
 __device__ __forceinline__ void end_turn(Team &t)
 {
-    AllocXchg *old = &t.st->x[(t.turn + 2u) % 3u];
-    const int per = (SEL_BINS + t.G - 1) / t.G;
-    for (int b = t.g * per + (int)threadIdx.x; b < min((t.g + 1) * per, SEL_BINS); b += AL_THREADS) dev_store(&old->hist[b], 0ull);
-    if (t.g == 0 && threadIdx.x < AL_SUMS) dev_store(&old->sum[threadIdx.x], 0ull);
-    ++t.turn;
+    u64 *old = reinterpret_cast<u64 *>(&t.st->x[t.turn ? t.turn - 1 : 2]);
+    constexpr int WORDS = (int)(sizeof(AllocXchg) / 8);
+    const int per = (WORDS + t.G - 1) / t.G;
+    for (int b = t.g * per + (int)threadIdx.x; b < min((t.g + 1) * per, WORDS); b += AL_THREADS) dev_store(&old[b], 0ull);
+    t.turn = t.turn < 2 ? t.turn + 1 : 0;
 }
 
-// Maxima of the first NMAX and sums of the other values over all threads of all workgroups; the same in every thread.
+// maximum or sum over the lanes of a wave, in lane 63 (the others hold parts of it)
+template <bool MAX>
+__device__ __forceinline__ u64 wave_reduce(u64 v)
+{
+    auto step = [&](auto ctrl, auto rows) {
+        const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)v, decltype(ctrl)::value, decltype(rows)::value, 0xf, false);
+        const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(v >> 32), decltype(ctrl)::value, decltype(rows)::value, 0xf, false);
+        const u64 o = (u64)hi << 32 | lo;            // (0 where there is no lane to take it from)
+        v = MAX ? (o > v ? o : v) : v + o;
+    };
+    step(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xf>{});   // row_shr:1, 2, 4, 8
+    step(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xf>{});
+    step(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xf>{});
+    step(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xf>{});
+    step(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});   // row_bcast:15 into rows 1, 3
+    step(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});   // row_bcast:31 into rows 2, 3
+    return v;
+}
+
+// v[] of the whole workgroup to sum[] (LDS): maxima of the first NMAX, sums of the others
 template <int NMAX, int NV>
-__device__ __forceinline__ void team_reduce(Team &t, AllocShared &sh, u64 (&v)[NV])
+__device__ __forceinline__ void block_reduce(u64 *sum, u64 (&v)[NV])
 {
     static_assert(NV <= AL_SUMS, "slots");
-#pragma unroll
-    for (int q = 0; q < NV; ++q)
-        for (int off = 32; off; off >>= 1) {
-            const u64 o = __shfl_xor(v[q], off);
-            v[q] = q < NMAX ? (v[q] > o ? v[q] : o) : v[q] + o;
-        }
+    if (threadIdx.x < NV) sum[threadIdx.x] = 0ull;
     __syncthreads();
-    if (threadIdx.x < NV) sh.sum[threadIdx.x] = 0ull;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) {
 #pragma unroll
-        for (int q = 0; q < NV; ++q) {
-            if (q < NMAX) atomicMax(&sh.sum[q], v[q]);
-            else atomicAdd(&sh.sum[q], v[q]);
+    for (int q = 0; q < NV; ++q) {
+        const u64 o = q < NMAX ? wave_reduce<true>(v[q]) : wave_reduce<false>(v[q]);
+        if ((threadIdx.x & 63) == 63 && o) {
+            if (q < NMAX) atomicMax(&sum[q], o);
+            else atomicAdd(&sum[q], o);
         }
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // (the clearing stores of the turn before, see end_turn)
     __syncthreads();
-    if (t.G > 1) {
-        AllocXchg *x = xchg(t);
-        if (threadIdx.x < NV) {
-            const u64 o = sh.sum[threadIdx.x];
-            if ((int)threadIdx.x < NMAX) atomicMax(&x->sum[threadIdx.x], o);
-            else atomicAdd(&x->sum[threadIdx.x], o);
-        }
-        grid_sync(t, sh);
-        if (threadIdx.x < NV) sh.sum[threadIdx.x] = dev_load(&x->sum[threadIdx.x]);
-        end_turn(t);
+}
+
+// Sums over all threads of all workgroups (mod 2^64); the same in every thread.  A sum travels in two halves of 32 bits, each
+// in 48 bits below the number of workgroups (at most 256) that have added theirs: complete when that is all of them.
+template <int NV>
+__device__ __forceinline__ void team_sum(Team &t, AllocShared &sh, u64 (&v)[NV])
+{
+    __syncthreads();                                          // (the sums of the last time were read)
+    block_reduce<0>(sh.sum, v);
+    const int q = (int)threadIdx.x;
+    if (t.G == 1) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) v[i] = uni(sh.sum[i]);
+        return;
+    }
+    AllocXchg *x = xchg(t);
+    if (q < 2 * NV) (void)__hip_atomic_fetch_add(&x->part[q], 1ull << 48 | (sh.sum[q >> 1] >> (q & 1 ? 32 : 0) & 0xffffffffull),
+                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int left = t.spin_limit;
+    for (int turn = 0;; turn ^= 1) {                          // (the buffers take turns: one barrier a poll)
+        if (q < 2 * NV) sh.part[turn][q] = dev_load(&x->part[q]);
         __syncthreads();
-    }
+        bool all = true;
+        u64 h[2 * NV];
 #pragma unroll
-    for (int q = 0; q < NV; ++q) v[q] = uni(sh.sum[q]);
+        for (int i = 0; i < 2 * NV; ++i) {
+            h[i] = uni(sh.part[turn][i]);
+            all = all && (int)(h[i] >> 48) == t.G;
+        }
+        if (all) {
+#pragma unroll
+            for (int i = 0; i < NV; ++i) v[i] = (h[2 * i] & 0xffffffffffffull) + (h[2 * i + 1] << 32);
+            break;
+        }
+        if (left-- <= 0) { give_up(t); return; }
+    }
+    end_turn(t);
 }
 
 // the smallest s with span >> s < SEL_BINS
-__device__ __forceinline__ int bin_shift(u64 span)
+__device__ __forceinline__ int bin_shift(unsigned span)
 {
-    const int len = 64 - __clzll((long long)(span | 1ull));
+    const int len = 32 - __clz((int)(span | 1u));
     return len > SEL_DB ? len - SEL_DB : 0;
 }
 
-struct Sel { u64 tau; int n_sel, w_sel; };           // selected <=> key >= tau
+// Where a first round's bins are: they cover the words of the values above zero, where nearly all keys lie; the outermost bins
+// hold what is below and above.  none: no value is above zero.
+struct Bins { unsigned lo, hi, base; int shift; };
+__device__ __forceinline__ Bins bins_over(unsigned lo, unsigned hi)
+{
+    const unsigned span = hi > lo ? hi - lo : 0u, wide = span + 2 * (span >> (SEL_DB - 1)) + 2u;    // (two bins are the outermost)
+    Bins b;
+    b.lo = lo; b.hi = hi;
+    b.shift = bin_shift(wide < span ? ~0u : wide);
+    b.base = lo > 1u << b.shift ? lo - (1u << b.shift) : 0u;
+    return b;
+}
+struct Ranges { Bins up, down; };                     // of keyU, of keyD
 
-// A workgroup's blocks: their two keys (0: cannot be raised / lowered) and levels.  A thread owns blocks n0 + tid,
+// A workgroup's blocks: the words of their two keys (0: cannot be raised / lowered; in 32 bits, because a round is bound by
+// the vector instructions on them: with 64-bit keys a round of one workgroup took 3 us, 2 of them here), the widths of the two steps, four bits each, and
+// their levels.  A thread owns blocks n0 + tid,
 // n0 + tid + AL_THREADS, ... and nobody else touches what belongs to them.  RES: it holds all of them (at most
 // AL_KPT) in registers; otherwise they live in memory and come in AL_KPT at a time.
-struct Batch { u64 ku[AL_KPT], kd[AL_KPT]; int lv[AL_KPT]; };
+struct Batch { unsigned ku[AL_KPT], kd[AL_KPT], su, sd; int lv[AL_KPT]; };
+__device__ __forceinline__ unsigned width_of(unsigned packed, int q) { return packed >> (4 * q) & 15u; }
+__device__ __forceinline__ void set_width(unsigned &packed, int q, unsigned w) { packed = (packed & ~(15u << (4 * q))) | w << (4 * q); }
 template <bool RES>
 struct Slice {
     Batch reg;                    // RES
-    u64 *mu, *md;                 // [N] in the workspace
+    u64 *mu, *md;                 // [N] in the workspace: word << 32 | width
     uint8_t *level;
-    long long n0, n1;
+    int n0, n1;
+    int used;                     // RES: slots of a thread that hold blocks
 
-    // f(first block of the batch, batch): block u of it is first + u * AL_THREADS, there if < n1 (else its keys are 0).
-    // What f changes is kept (WR) in all three arrays.  need_kd: f looks at keyD (from memory it is half of the bytes).
+    // f(first block of the batch, batch, slots): block u of it is first + u * AL_THREADS, there if < n1 (else its keys are 0).
+    // What f changes is kept (WR) in all arrays.  need_kd: f looks at keyD (from memory it is half of the bytes).
     template <bool LV, bool WR, class F>
     __device__ __forceinline__ void visit(F &&f, bool need_kd = true)
     {
         if constexpr (RES) {
-            f(n0 + (int)threadIdx.x, reg);
+            f(n0 + (int)threadIdx.x, reg, used);
         } else {
-            for (long long i0 = n0 + (int)threadIdx.x; i0 < n1; i0 += (long long)AL_KPT * AL_THREADS) {
+            for (int i0 = n0 + (int)threadIdx.x; i0 < n1; i0 += AL_KPT * AL_THREADS) {
                 Batch b;
+                b.su = b.sd = 0u;
+                u64 w[AL_KPT];
 #pragma unroll
                 for (int u = 0; u < AL_KPT; ++u) {
-                    const long long i = i0 + (long long)u * AL_THREADS;
-                    b.ku[u] = i < n1 ? mu[i] : 0ull;
-                    b.kd[u] = 0ull;
+                    const int i = i0 + u * AL_THREADS;
+                    w[u] = i < n1 ? mu[i] : 0ull;
                     b.lv[u] = LV && i < n1 ? (int)level[i] : 0;
                 }
+#pragma unroll
+                for (int u = 0; u < AL_KPT; ++u) { b.ku[u] = (unsigned)(w[u] >> 32); set_width(b.su, u, (unsigned)w[u]); b.kd[u] = 0u; }
                 if (need_kd) {
 #pragma unroll
                     for (int u = 0; u < AL_KPT; ++u) {
-                        const long long i = i0 + (long long)u * AL_THREADS;
-                        b.kd[u] = i < n1 ? md[i] : 0ull;
+                        const int i = i0 + u * AL_THREADS;
+                        w[u] = i < n1 ? md[i] : 0ull;
                     }
+#pragma unroll
+                    for (int u = 0; u < AL_KPT; ++u) { b.kd[u] = (unsigned)(w[u] >> 32); set_width(b.sd, u, (unsigned)w[u]); }
                 }
-                f(i0, b);
+                f(i0, b, AL_KPT);
                 if constexpr (WR) store(i0, b);
             }
         }
     }
-    __device__ __forceinline__ void store(long long i0, const Batch &b)
+    __device__ __forceinline__ void store(int i0, const Batch &b)
     {
 #pragma unroll
         for (int u = 0; u < AL_KPT; ++u) {
-            const long long i = i0 + (long long)u * AL_THREADS;
-            if (i < n1) { mu[i] = b.ku[u]; md[i] = b.kd[u]; level[i] = (uint8_t)b.lv[u]; }
+            const int i = i0 + u * AL_THREADS;
+            if (i < n1) {
+                mu[i] = (u64)b.ku[u] << 32 | width_of(b.su, u);
+                md[i] = (u64)b.kd[u] << 32 | width_of(b.sd, u);
+                level[i] = (uint8_t)b.lv[u];
+            }
         }
     }
-    // the blocks for the first time
-    template <class F>
-    __device__ __forceinline__ void start(F &&f)
+    // the blocks for the first time, from memory
+    __device__ __forceinline__ void load(int lv)
     {
-        for (long long i0 = n0 + (int)threadIdx.x; i0 < n1; i0 += (long long)AL_KPT * AL_THREADS) {
-            Batch b;
+        u64 a[AL_KPT], b[AL_KPT];
 #pragma unroll
-            for (int u = 0; u < AL_KPT; ++u) { b.ku[u] = b.kd[u] = 0ull; b.lv[u] = 0; }
-            f(i0, b);
-            if constexpr (RES) reg = b;
-            else store(i0, b);
+        for (int u = 0; u < AL_KPT; ++u) {
+            const int i = n0 + (int)threadIdx.x + u * AL_THREADS;
+            a[u] = i < n1 ? mu[i] : 0ull;
+            b[u] = i < n1 ? md[i] : 0ull;
+        }
+        reg.su = reg.sd = 0u;
+#pragma unroll
+        for (int u = 0; u < AL_KPT; ++u) {
+            reg.ku[u] = (unsigned)(a[u] >> 32); reg.kd[u] = (unsigned)(b[u] >> 32); reg.lv[u] = lv;
+            set_width(reg.su, u, (unsigned)a[u]);
+            set_width(reg.sd, u, (unsigned)b[u]);
         }
     }
 };
@@ -295,119 +356,186 @@ __device__ __forceinline__ unsigned int wave_prefix(unsigned int v)
     return v;
 }
 
-// The longest prefix of the descending order of the blocks' keys >= key_min with at most cnt_max keys and at
-// most w_max step bits: of the keyU, or (down) of the keyD of the blocks outside the set keyU >= excl_tau.
-// v = key >> 8 is compared; the first round's bins cover [lo, hi), where nearly all values lie, and its
-// outermost bins everything below and above, so values outside are found as well, a round later.
-// Neither limit is negative.  sh.hist is all zero before and after.
-template <bool RES>
-__device__ __forceinline__ Sel select(Team &t, AllocShared &sh, Slice<RES> &own, bool down, u64 excl_tau, u64 key_min,
-                                      int cnt_max, int w_max, u64 lo, u64 hi, int TB)
+// A selection at its start: among the keys of words from and above (from >= 1: no key that says that there is no step).
+__device__ __forceinline__ Pick pick(unsigned from, const Bins &b, int cnt_max, int w_max)
 {
-    const int tid = (int)threadIdx.x;
-    Sel r;
-    int c0 = 0, w0 = 0;                              // totals of the keys above the current interval
-    u64 from = 0, to = 0;                            // the interval after the first round
-    int sh_bin = 0;
-    bool first = true;
-    sh_bin = bin_shift(hi > lo ? hi - lo + 2 * ((hi - lo) >> (SEL_DB - 1)) : 0);   // (two bins are the outermost)
-    for (;;) {
-        own.template visit<false, false>([&](long long, const Batch &bt) {
+    return Pick{from, ~0u, b.base, b.shift, 0u, cnt_max, w_max, {~0ull, 0, 0}};
+}
+
+// The selection after the round in which its prefix ended in bin b (-1: every key fitted), with ac keys of aw step bits above
+// and n keys in it.  Returns whether it has ended.
+__device__ __forceinline__ bool narrow(Pick &p, int b, int n, int ac, int aw, int N)
+{
+    p.r.n_sel = ac;
+    p.r.w_sel = aw;
+    if (b < 0) {
+        p.r.tau = p.tie ? (u64)p.tie << 32 | p.from : (u64)p.from << 32;
+        return true;
+    }
+    const unsigned begin = p.base + ((unsigned)b << p.shift), end = begin + ((1u << p.shift) - 1u);    // (it holds a key: only its end may be past 32 bits)
+    if (b < SEL_BINS - 1 && end >= begin && end < p.last) p.last = end;
+    if (b > 0 && begin > p.from) p.from = begin;
+    if (n == 1 || (p.tie && p.from == p.last)) {     // one key that does not fit: the prefix ends above it
+        p.r.tau = p.tie ? (u64)p.tie << 32 | (p.last + 1u) : p.last == ~0u ? ~0ull : (u64)(p.last + 1u) << 32;
+        return true;
+    }
+    if (p.from == p.last) {                          // several keys of one word: their places decide
+        p.tie = p.from;
+        p.from = 0u;
+        p.last = (unsigned)(N - 1);
+    }
+    p.base = p.from;
+    p.shift = bin_shift(p.last - p.from);
+    return false;
+}
+
+__device__ __forceinline__ u64 key_at(unsigned word, int place) { return (u64)word << 32 | (unsigned)place; }
+
+// The selections p of `open` (a bit each), side by side: UP among the keyU, DOWN among the keyD of the blocks outside the set
+// keyU >= excl.  Each round splits a selection's interval into bins and goes on with the bin in which the prefix ends,
+// until that bin holds one key.  sh.hist is all zero before and after.
+//
+// The exchange.  Every workgroup adds its bins and, without waiting for that, to `mark` how many keys they hold.  One thread polls `mark`
+// until all workgroups have said so; then the bins are read until they hold as many as it says.  (All threads polling the bins, or
+// a mark from every wave, are in the way of the additions: 104 workgroups 775 us against 425.)
+template <bool RES>
+__device__ __forceinline__ void sel_rounds(Team &t, AllocShared &sh, Slice<RES> &own, Pick (&p)[SEL_SETS], unsigned open, u64 excl, int N)
+{
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
+#pragma unroll 1
+    while (open) {
+        int live = 0;                                // keys put into bins (of this wave: the first lane's)
+        own.template visit<false, false>([&](int i0, const Batch &bt, int slots) {
+            static_for<0, SEL_SETS>([&](auto is) {
+                constexpr int s = decltype(is)::value;
+                if (!(open & 1u << s)) return;
+                const unsigned span = p[s].last - p[s].from;
 #pragma unroll
-            for (int q = 0; q < AL_KPT; ++q) {
-                const u64 key = down ? bt.kd[q] : bt.ku[q];
-                if (key < key_min) continue;                         // also drops what is past the end (key 0)
-                if (down && bt.ku[q] >= excl_tau) continue;
-                const u64 v = key >> 8;
-                int bin;
-                if (first) {
-                    const u64 n = ((v - lo) >> sh_bin) + 1ull;
-                    bin = v < lo ? 0 : (n < (u64)(SEL_BINS - 1) ? (int)n : SEL_BINS - 1);
-                } else {
-                    if (v < from || v >= to) continue;
-                    bin = (int)((v - from) >> sh_bin);
+                for (int q = 0; q < AL_KPT; ++q) {
+                    if (q >= slots) break;
+                    const int place = N - 1 - (i0 + q * AL_THREADS);
+                    unsigned x = s == DOWN ? bt.kd[q] : bt.ku[q];
+                    if (s == DOWN && excl != ~0ull && key_at(bt.ku[q], place) >= excl) x = 0u;
+                    bool in = x - p[s].from <= span;
+                    if (p[s].tie) {
+                        in = x == p[s].tie && (unsigned)place - p[s].from <= span;
+                        x = (unsigned)place;
+                    }
+                    live += __popcll(__ballot(in));
+                    if (in) {
+                        const unsigned n = __builtin_elementwise_sub_sat(x, p[s].base) >> p[s].shift;
+                        const int b = (int)(n < SEL_BINS ? n : SEL_BINS - 1);
+                        atomicAdd(&sh.hist[s][SEL_BINS - 1 - b], (u64)width_of(s == DOWN ? bt.sd : bt.su, q) << 32 | 1ull);   // descending: the top bin first
+                    }
                 }
-                atomicAdd(&sh.hist[SEL_BINS - 1 - bin], ((key & 255ull) << 32) | 1ull);   // descending: the top bin first
-            }
-        }, down);
-        __syncthreads();
+            });
+        }, open & 1u << DOWN);
+        AllocXchg *const x = xchg(t);
         if (t.G > 1) {
-            AllocXchg *x = xchg(t);
+            if (lane == 0 && live) atomicAdd(&sh.live, live);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // (the clearing stores of the turn before)
+        }
+        __syncthreads();
+        u64 v[SEL_SETS][AL_BPT];                     // a thread has AL_BPT consecutive bins
+        static_for<0, SEL_SETS>([&](auto is) {
+            constexpr int s = decltype(is)::value;
+            if (!(open & 1u << s)) return;
 #pragma unroll
             for (int q = 0; q < AL_BPT; ++q) {
-                const u64 v = sh.hist[tid + q * AL_THREADS];
-                if (v) (void)__hip_atomic_fetch_add(&x->hist[tid + q * AL_THREADS], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                u64 &b = sh.hist[s][tid * AL_BPT + q];
+                v[s][q] = b;
+                b = 0ull;
+                if (t.G > 1 && v[s][q])
+                    (void)__hip_atomic_fetch_add(&x->hist[s][tid * AL_BPT + q], v[s][q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
-            grid_sync(t, sh);
-            u64 v[AL_BPT];
-#pragma unroll
-            for (int q = 0; q < AL_BPT; ++q) v[q] = dev_load(&x->hist[tid + q * AL_THREADS]);
-#pragma unroll
-            for (int q = 0; q < AL_BPT; ++q) sh.hist[tid + q * AL_THREADS] = v[q];
-            end_turn(t);
-            if (!t.ok) { r.tau = ~0ull; r.n_sel = r.w_sel = 0; return r; }
+        });
+        int pc[SEL_SETS], pw[SEL_SETS];              // sums over the bins above (at most 2^24 keys of width <= 8: below 2^31)
+        int left = t.spin_limit, all = 0;
+        if (t.G > 1) {
+            if (tid == 0) {
+                (void)__hip_atomic_fetch_add(&x->mark, 1ull << 32 | (u64)(unsigned)sh.live, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                sh.live = 0;
+                u64 m;
+                while ((int)((m = dev_load(&x->mark)) >> 32) != t.G && left-- > 0) __builtin_amdgcn_s_sleep(1);
+                sh.mark = m;
+            }
             __syncthreads();
+            const u64 m = uni(sh.mark);
+            if ((int)(m >> 32) != t.G) { give_up(t); return; }
+            all = (int)(unsigned)m;
+            left = t.spin_limit;
         }
-        // Sums over the bins above each bin (at most 2^24 keys of width <= 8: neither can reach 2^31); a thread has
-        // AL_BPT consecutive bins.
-        int mc[AL_BPT], mw[AL_BPT], tc = 0, tw = 0;
+#pragma unroll 1
+        for (int turn = 0;; turn ^= 1) {             // (the waves' sums take turns in two buffers: one barrier a read)
+            if (t.G > 1) {
+                static_for<0, SEL_SETS>([&](auto is) {
+                    constexpr int s = decltype(is)::value;
+                    if (!(open & 1u << s)) return;
 #pragma unroll
-        for (int q = 0; q < AL_BPT; ++q) {
-            const u64 v = sh.hist[tid * AL_BPT + q];
-            mc[q] = (int)v; mw[q] = (int)(v >> 32);
-            tc += mc[q]; tw += mw[q];
-        }
+                    for (int q = 0; q < AL_BPT; ++q) v[s][q] = dev_load(&x->hist[s][tid * AL_BPT + q]);
+                });
+            }
+            static_for<0, SEL_SETS>([&](auto is) {
+                constexpr int s = decltype(is)::value;
+                if (!(open & 1u << s)) return;
+                int c = 0, w = 0;
 #pragma unroll
-        for (int q = 0; q < AL_BPT; ++q) sh.hist[tid * AL_BPT + q] = 0ull;
-        int pc = (int)wave_prefix((unsigned)tc), pw = (int)wave_prefix((unsigned)tw);
-        if ((tid & 63) == 63) { sh.wave_c[tid >> 6] = pc; sh.wave_w[tid >> 6] = pw; }
-        __syncthreads();
-#pragma unroll
-        for (int w = 0; w < AL_WAVES - 1; ++w) {
-            const bool before = w < (tid >> 6);
-            pc += before ? sh.wave_c[w] : 0;
-            pw += before ? sh.wave_w[w] : 0;
+                for (int q = 0; q < AL_BPT; ++q) { c += (int)v[s][q]; w += (int)(v[s][q] >> 32); }
+                const int ic = (int)wave_prefix((unsigned)c), iw = (int)wave_prefix((unsigned)w);
+                pc[s] = ic - c;
+                pw[s] = iw - w;
+                if (lane == 63) sh.wave[turn][WS_SET * s + wave] = (u64)(unsigned)iw << 32 | (unsigned)ic;
+            });
+            __syncthreads();
+            // lanes 0 .. 7 of a row of 16 have the sums of set (row); a prefix over them
+            const u64 e = sh.wave[turn][lane];
+            const int ec = (int)e, ew = (int)(e >> 32);
+            int sc = ec, sw = ew;
+            auto step = [&](auto ctrl) {
+                sc += __builtin_amdgcn_update_dpp(0, sc, decltype(ctrl)::value, 0xf, 0xf, true);
+                sw += __builtin_amdgcn_update_dpp(0, sw, decltype(ctrl)::value, 0xf, 0xf, true);
+            };
+            step(std::integral_constant<int, 0x111>{});               // row_shr:1, 2, 4
+            step(std::integral_constant<int, 0x112>{});
+            step(std::integral_constant<int, 0x114>{});
+            int sum = 0;
+            static_for<0, SEL_SETS>([&](auto is) {
+                constexpr int s = decltype(is)::value;
+                if (!(open & 1u << s)) return;
+                pc[s] += __builtin_amdgcn_readlane(sc - ec, WS_SET * s + wave);
+                pw[s] += __builtin_amdgcn_readlane(sw - ew, WS_SET * s + wave);
+                sum += __builtin_amdgcn_readlane(sc, WS_SET * s + AL_WAVES - 1);
+            });
+            if (t.G == 1 || sum == all) break;
+            if (left-- <= 0) { give_up(t); return; }
         }
         // The sums only grow downwards, so the first bin that does not fit whole is the one that does not fit while
         // everything above it does; it ends the prefix.
-        int ac = c0 + pc - tc, aw = w0 + pw - tw;
+        static_for<0, SEL_SETS>([&](auto is) {
+            constexpr int s = decltype(is)::value;
+            if (!(open & 1u << s)) return;
+            int ac = p[s].r.n_sel + pc[s], aw = p[s].r.w_sel + pw[s];
 #pragma unroll
-        for (int q = 0; q < AL_BPT; ++q) {
-            const int ic = ac + mc[q], iw = aw + mw[q];
-            const bool fits = ic <= cnt_max && iw <= w_max;
-            if (mc[q] && !fits && ac <= cnt_max && aw <= w_max) {
-                sh.boundary = SEL_BINS - 1 - (tid * AL_BPT + q); sh.above_c = ac; sh.above_w = aw; sh.at_cnt = mc[q];
-            } else if (q == AL_BPT - 1 && tid == AL_THREADS - 1 && fits) {
-                sh.boundary = -1; sh.above_c = ic; sh.above_w = iw; sh.at_cnt = 0;
+            for (int q = 0; q < AL_BPT; ++q) {
+                const int n = (int)v[s][q], ic = ac + n, iw = aw + (int)(v[s][q] >> 32);
+                const bool fits = ic <= p[s].cnt_max && iw <= p[s].w_max;
+                if (n && !fits && ac <= p[s].cnt_max && aw <= p[s].w_max) sh.found[s] = make_int4(SEL_BINS - 1 - (tid * AL_BPT + q), n, ac, aw);
+                else if (q == AL_BPT - 1 && tid == AL_THREADS - 1 && fits) sh.found[s] = make_int4(-1, 0, ic, iw);
+                ac = ic; aw = iw;
             }
-            ac = ic; aw = iw;
-        }
+        });
         __syncthreads();
-        const int b = uni(sh.boundary), at = uni(sh.at_cnt);
-        c0 = uni(sh.above_c); w0 = uni(sh.above_w);
-        if (b < 0) {                                 // every key of the interval fits
-            const u64 edge = first ? 0ull : from << 8;
-            r.tau = edge > key_min ? edge : key_min;
-            break;
-        }
-        if (first) {
-            if (b == 0) { from = 0; to = lo; }
-            else if (b == SEL_BINS - 1) { from = lo + ((u64)(SEL_BINS - 2) << sh_bin); to = 1ull << TB; }
-            else { from = lo + ((u64)(b - 1) << sh_bin); to = from + (1ull << sh_bin); }
-            first = false;
-        } else {
-            from += (u64)b << sh_bin;
-            const u64 end = from + (1ull << sh_bin);
-            to = end < to ? end : to;
-        }
-        if (at == 1 || to - from <= 1) {             // one key that does not fit: the prefix ends above it
-            r.tau = to >> 56 ? ~0ull : to << 8;
-            break;
-        }
-        sh_bin = bin_shift(to - from - 1);
+        int4 f[SEL_SETS];
+        static_for<0, SEL_SETS>([&](auto is) {
+            constexpr int s = decltype(is)::value;
+            if (open & 1u << s) f[s] = sh.found[s];
+        });
+        if (t.G > 1) end_turn(t);
+        static_for<0, SEL_SETS>([&](auto is) {
+            constexpr int s = decltype(is)::value;
+            if (open & 1u << s && narrow(p[s], uni(f[s].x), uni(f[s].y), uni(f[s].z), uni(f[s].w), N)) open &= ~(1u << s);
+        });
     }
-    r.n_sel = c0; r.w_sel = w0;
-    return r;
 }
 
 __device__ __forceinline__ void trace_write(sbits_trace *tr, int it, int kind, long long k, long long n_up, long long n_dn,
@@ -419,74 +547,153 @@ __device__ __forceinline__ void trace_write(sbits_trace *tr, int it, int kind, l
     t.bits_before = before; t.bits_after = after; t.delta_fixed = delta;
 }
 
-// keys of block i at level l, whose table entries there, a level below and a level above are cl, cm and cp
-__device__ __forceinline__ void table_keys(float cm, float cl, float cp, int l, int K, const int *bits, long long N, int IB,
-                                           long long i, u64 &ku, u64 &kd)
-{
-    const u64 low = (u64)(N - 1 - i) << 8;
-    ku = kd = 0;
-    if (l < K - 1) {
-        const int step = bits[l + 1] - bits[l];
-        ku = ((u64)ord_f32((cl - cp) / (float)step) << (IB + 8)) | low | (unsigned)step;
-    }
-    if (l > 0) {
-        const int step = bits[l] - bits[l - 1];
-        kd = ((u64)(~ord_f32((cm - cl) / (float)step)) << (IB + 8)) | low | (unsigned)step;
-    }
-}
-
-struct Ranges { u64 loU, hiU, loD, hiD; int TB, IB; };
+// 0 is no word of a key: it says that there is no step
+__device__ __forceinline__ unsigned some(unsigned word) { return word ? word : 1u; }
 
 // The sets of one iteration of Algorithm 2.  e: the expansion (not tried without slack): the first k blocks by
 // keyU with a value above zero that fit the slack.  If it is empty, the balanced swap: u = the first h by keyU,
 // d = the first h by keyD outside u, u2 = the longest prefix of u whose step bits fit the slack plus the bits d
-// frees.  (One loop around one copy of the selection: inlined four times it spills.)  STEP: the levels are the caller's and
-// may be over budget; the search's own never are.
+// frees.
+// u and d go side by side, d as if u took none of its blocks: what a raise gains the least is what a lowering costs the
+// least, so the two hardly ever meet.  The caller counts the blocks that are in both and, if there are any, asks again with
+// apart = u's threshold.
+// STEP: the levels are the caller's and may be over budget; the search's own never are.
+struct Sets { Sel e, u, d, u2; };
 template <bool STEP, bool RES>
-__device__ __forceinline__ void choose_sets(Team &t, AllocShared &sh, Slice<RES> &own, long long k, long long slack,
-                                            const Ranges &rg, Sel &e, Sel &u, Sel &d, Sel &u2)
+__device__ __forceinline__ void choose_sets(Team &t, AllocShared &sh, Slice<RES> &own, long long k, long long slack, int min_step,
+                                            const Ranges &rg, int N, u64 apart, Sets &o)
 {
-    enum { EXPAND, UP, DOWN, UP2 };
     const int INF = 0x7fffffff;
     auto clip = [](long long v) { return (int)(v < -1 ? -1 : v > INF ? INF : v); };
-    const u64 key_pos = (u64)0x80000001u << (rg.IB + 8);             // value > +0
-    const int kc = clip(k), h = k / 2 < 1 ? 1 : clip(k / 2);
-    e = u = d = u2 = Sel{~0ull, 0, 0};
-    int phase = slack > 0 ? EXPAND : UP;
-    for (;;) {
-        const bool down = phase == DOWN;
-        const Sel r = select(t, sh, own, down, u.tau, phase == EXPAND ? key_pos : 1ull, phase == EXPAND ? kc : h,
-                             phase == EXPAND ? clip(slack) : phase == UP2 ? clip(slack + d.w_sel) : INF, down ? rg.loD : rg.loU,
-                             down ? rg.hiD : rg.hiU, rg.TB);
+    const int h = k / 2 < 1 ? 1 : clip(k / 2);
+    Pick p[SEL_SETS];
+    p[UP] = pick(1u, rg.up, h, INF);
+    p[DOWN] = pick(1u, rg.down, h, INF);
+    enum { EXPAND, BOTH, AGAIN, FIT };
+    int phase = BOTH;
+    unsigned open = 1u << UP | 1u << DOWN;
+    if (apart != ~0ull) {
+        phase = AGAIN;
+        open = 1u << DOWN;
+    } else {
+        o.e = o.u = o.d = o.u2 = Sel{~0ull, 0, 0};
+        if (slack >= min_step && rg.up.hi) {         // (else no step fits, or none is worth taking)
+            phase = EXPAND;
+            open = 1u << UP;
+            p[UP] = pick(0x80000001u, rg.up, clip(k), clip(slack));  // (values above +0)
+        }
+    }
+#pragma unroll 1
+    for (;;) {                                       // (one copy of the rounds: inlined several times they spill)
+        sel_rounds(t, sh, own, p, open, apart, N);
         if (!t.ok) return;
         if (phase == EXPAND) {
-            e = r;
-            if (e.n_sel > 0) return;
-            phase = UP;
-        } else if (phase == UP) {
-            u = r;
-            phase = DOWN;
-        } else if (phase == DOWN) {
-            d = r;
-            u2 = u;
-            if (u.w_sel <= slack + d.w_sel) return;                  // all of u fits
-            if constexpr (STEP)
-                if (slack + d.w_sel < 0) { u2 = Sel{~0ull, 0, 0}; return; }   // over by more than d frees: nothing of u does
-            phase = UP2;
-        } else {
-            u2 = r;
-            return;
+            o.e = p[UP].r;
+            if (o.e.n_sel > 0) return;
+            phase = BOTH;
+            open = 1u << UP | 1u << DOWN;
+            p[UP] = pick(1u, rg.up, h, INF);
+            continue;
         }
+        if (phase == FIT) { o.u2 = p[UP].r; return; }
+        if (phase == BOTH) o.u = p[UP].r;
+        o.d = p[DOWN].r;
+        o.u2 = o.u;
+        if (o.u.w_sel <= slack + o.d.w_sel) return;                  // all of u fits
+        if constexpr (STEP)
+            if (slack + o.d.w_sel < 0) { o.u2 = Sel{~0ull, 0, 0}; return; }   // over by more than d frees: nothing of u does
+        phase = FIT;
+        open = 1u << UP;
+        const unsigned from = (unsigned)(o.u.tau >> 32);              // u has no keys below these words
+        p[UP] = pick(from, bins_over(from > rg.up.lo ? from : rg.up.lo, rg.up.hi), h, clip(slack + o.d.w_sel));
     }
 }
 
-// The range of the values above zero, from its largest (as an ordered 32-bit word) and the complement of its
-// smallest: for the values themselves (keyU) and for their complements (keyD).  0 to 0 if there is none.
-__device__ __forceinline__ void value_range(u64 omax, u64 omin_inv, int IB, u64 &loU, u64 &hiU, u64 &loD, u64 &hiD)
+// The words of the values above zero, from the largest one and the complement of the smallest one: of keyU, and of keyD, which
+// are complements.  0 to 0 if there is none.
+__device__ __forceinline__ Ranges value_ranges(u64 omax, u64 omin_inv)
 {
-    const u64 omin = (u64)~(unsigned int)omin_inv;
-    loU = omax ? omin << IB : 0; hiU = omax ? (omax + 1) << IB : 0;
-    loD = omax ? (u64)~(unsigned int)omax << IB : 0; hiD = omax ? (omin_inv + 1) << IB : 0;
+    return Ranges{bins_over(omax ? ~(unsigned)omin_inv : 0u, (unsigned)omax), bins_over(omax ? ~(unsigned)omax : 0u, (unsigned)omin_inv)};
+}
+
+// Where a search begins, with every CU at work (computed by the search's few workgroups themselves it took 20 us for 107 k blocks):
+// keys of blocks first, first + stride, ... at level l0, and of all gains in their rows of the table the largest and the
+// smallest inverted above zero, and the largest entry.
+__device__ __forceinline__ void table_keys(const float *__restrict__ cost, int N, int K, const int *bits, int l0, int first, int stride,
+                                           uint8_t *level, u64 *__restrict__ keyU, u64 *__restrict__ keyD, u64 (&red)[3])
+{
+    for (int i = first; i < N; i += stride) {
+        float c[MAX_CAND];
+#pragma unroll
+        for (int l = 0; l < MAX_CAND; ++l) c[l] = l < K ? cost[(int64_t)i * K + l] : 0.0f;
+        u64 ku = 0ull, kd = 0ull;
+#pragma unroll
+        for (int l = 0; l < MAX_CAND; ++l) {
+            if (l >= K) continue;
+            if (c[l] > 0.0f) red[2] = max(red[2], (u64)__float_as_uint(c[l]));
+            if (l) {
+                const unsigned step = (unsigned)(bits[l] - bits[l - 1]), o = ord_f32((c[l - 1] - c[l]) / (float)step);
+                if (o > 0x80000000u) { red[0] = max(red[0], (u64)o); red[1] = max(red[1], (u64)~o); }
+                if (l == l0 + 1) ku = (u64)some(o) << 32 | step;
+                if (l == l0) kd = (u64)some(~o) << 32 | step;
+            }
+        }
+        keyU[i] = ku;
+        keyD[i] = kd;
+        level[i] = (uint8_t)l0;
+    }
+}
+// The same for a step on the caller's estimates at the caller's levels: largest and smallest inverted of s_up above zero, of
+// s_down, and the bits in use.
+__device__ __forceinline__ void step_keys(const float *__restrict__ s_up, const float *__restrict__ s_down, const uint8_t *level, int N, int K,
+                                          const int *bits, int first, int stride, u64 *__restrict__ keyU, u64 *__restrict__ keyD, u64 (&red)[5])
+{
+#pragma unroll 4
+    for (int i = first; i < N; i += stride) {
+        const int l = min((int)level[i], K - 1);
+        const float up = s_up[i], dn = s_down[i];
+        red[4] += (u64)bits[l];
+        u64 ku = 0, kd = 0;
+        if (l < K - 1) {
+            const unsigned int o = ord_f32(up);
+            ku = (u64)some(o) << 32 | (unsigned)(bits[l + 1] - bits[l]);
+            if (o > 0x80000000u) { red[0] = max(red[0], (u64)o); red[1] = max(red[1], (u64)~o); }
+        }
+        if (l > 0) {
+            const unsigned int o = ord_f32(dn);
+            kd = (u64)some(~o) << 32 | (unsigned)(bits[l] - bits[l - 1]);
+            if (o > 0x80000000u) { red[2] = max(red[2], (u64)o); red[3] = max(red[3], (u64)~o); }
+        }
+        keyU[i] = ku;
+        keyD[i] = kd;
+    }
+}
+
+// Ahead of the search: its start state (from a kernel argument: no host buffer has to outlive the call), clear exchange
+// buffers, keys and their ranges.
+template <bool STEP>
+__global__ __launch_bounds__(PREP_THREADS)
+void prepare_kernel(AllocState *st, AllocHead head, const float *__restrict__ cost, const float *__restrict__ s_up,
+                    const float *__restrict__ s_down, uint8_t *level, u64 *__restrict__ keyU, u64 *__restrict__ keyD)
+{
+    __shared__ u64 sum[AL_SUMS];
+    __shared__ int bits[MAX_CAND];
+    const int tid = (int)threadIdx.x, at = (int)blockIdx.x * PREP_THREADS + tid, all = (int)gridDim.x * PREP_THREADS;
+    if (at == 0) st->head = head;
+    u64 *j = reinterpret_cast<u64 *>(st->x);
+    for (int i = at; i < (int)(sizeof(st->x) / 8); i += all) j[i] = 0ull;
+    if (tid < MAX_CAND) bits[tid] = head.bits[tid];
+    __syncthreads();
+    if constexpr (STEP) {
+        u64 red[5] = {0, 0, 0, 0, 0};
+        step_keys(s_up, s_down, level, (int)head.N, head.K, bits, at, all, keyU, keyD, red);
+        block_reduce<4>(sum, red);
+    } else {
+        u64 red[3] = {0, 0, 0};
+        table_keys(cost, (int)head.N, head.K, bits, head.l0, at, all, level, keyU, keyD, red);
+        block_reduce<3>(sum, red);
+    }
+    if (tid < (STEP ? 5 : 3)) st->range[blockIdx.x][tid] = sum[tid];
 }
 
 // The whole search (STEP = false), or one step of it on caller-supplied estimates s_up / s_down at level[]
@@ -498,80 +705,68 @@ template <bool STEP, bool RES>
 __global__ __launch_bounds__(AL_THREADS)
 void search_kernel(AllocState *st, const float *__restrict__ cost, const float *__restrict__ s_up,
                    const float *__restrict__ s_down, uint8_t *level, u64 *__restrict__ keyU, u64 *__restrict__ keyD,
-                   sbits_trace *tr, AllocResult *result, int spin_limit, int only_if_aborted)
+                   sbits_trace *tr, AllocResult *result, int n_ranges, int spin_limit, int only_if_aborted)
 {
     __shared__ AllocShared sh;
     const int tid = (int)threadIdx.x;
     if (only_if_aborted && !st->head.aborted) return;
     Team t;
     t.st = st; t.G = (int)gridDim.x; t.g = (int)blockIdx.x; t.turn = 0; t.spin_limit = spin_limit; t.ok = true;
-    const long long N = st->head.N, T = st->head.T;
-    const int K = st->head.K, IB = st->head.IB;
-    const long long per = (N + t.G - 1) / t.G;
+    const int N = uni((int)st->head.N), K = uni(st->head.K), per = (N + t.G - 1) / t.G;      // (N <= 2^24)
+    const long long T = st->head.T;
+    for (int b = tid; b < SEL_SETS * SEL_BINS; b += AL_THREADS) sh.hist[0][b] = 0ull;
+    if (tid == 0) sh.live = 0;
+    if (tid < MAX_CAND) sh.bits[tid] = st->head.bits[tid];
+    constexpr int NRED = STEP ? 5 : 3, NMAX = STEP ? 4 : 3;
+    u64 red[NRED] = {};
+    if (tid < n_ranges) {
+#pragma unroll
+        for (int q = 0; q < NRED; ++q) red[q] = st->range[tid][q];
+    }
+    block_reduce<NMAX>(sh.sum, red);
+#pragma unroll
+    for (int q = 0; q < NRED; ++q) red[q] = uni(sh.sum[q]);
+    const int *bits = sh.bits;
+    const bool lead = blockIdx.x == 0 && tid == AL_THREADS - 64;     // (of the last wave: it is waited for the least)
+    const int min_step = uni(st->head.min_step), l0 = uni(st->head.l0);
+    long long used = st->head.used, k = st->head.k;
+    if constexpr (!STEP) {
+        if (only_if_aborted) {                       // keys and levels as they were before the first try
+            u64 again[3] = {0, 0, 0};
+            table_keys(cost, N, K, bits, l0, tid, AL_THREADS, level, keyU, keyD, again);
+            __syncthreads();
+        }
+    }
     Slice<RES> own;
     own.mu = keyU; own.md = keyD; own.level = level;
     own.n0 = min(N, per * t.g);
     own.n1 = min(N, own.n0 + per);
-    if constexpr (RES) {
-#pragma unroll
-        for (int u = 0; u < AL_KPT; ++u) { own.reg.ku[u] = own.reg.kd[u] = 0ull; own.reg.lv[u] = 0; }
-    }
-    for (int b = tid; b < SEL_BINS; b += AL_THREADS) sh.hist[b] = 0ull;
-    if (tid < MAX_CAND) sh.bits[tid] = st->head.bits[tid];
-    __syncthreads();
-    const int *bits = sh.bits;
-    const bool lead = blockIdx.x == 0 && tid == 0;
-    long long used = st->head.used, k = st->head.k;
+    own.used = (own.n1 - own.n0 + AL_THREADS - 1) / AL_THREADS;
+    if constexpr (RES) own.load(l0);
     Ranges rg;
-    rg.TB = 32 + IB; rg.IB = IB;
-
     if constexpr (STEP) {
-        u64 red[5] = {0, 0, 0, 0, 0};                // s_up: largest, smallest inverted; s_down: the same; bits in use
-        // (The keys go to memory in either form: the kernel that applies the step reads them.  All loads of a batch are
-        // requested before any is used, the estimates whether the level needs them or not: one level after the other, each
-        // followed by its estimates, an expansion over 16.7 M blocks takes 100 us longer.)
-        for (long long i0 = own.n0 + tid; i0 < own.n1; i0 += (long long)AL_KPT * AL_THREADS) {
-            int lv[AL_KPT];
-            float up[AL_KPT], dn[AL_KPT];
-#pragma unroll
-            for (int q = 0; q < AL_KPT; ++q) {
-                const long long i = i0 + (long long)q * AL_THREADS;
-                lv[q] = i < own.n1 ? (int)level[i] : 0;
-                up[q] = i < own.n1 ? s_up[i] : 0.0f;
-                dn[q] = i < own.n1 ? s_down[i] : 0.0f;
-            }
-#pragma unroll
-            for (int q = 0; q < AL_KPT; ++q) {
-                const long long i = i0 + (long long)q * AL_THREADS;
-                if (i >= own.n1) continue;
-                const int l = min(lv[q], K - 1);
-                red[4] += (u64)bits[l];
-                const u64 low = (u64)(N - 1 - i) << 8;
-                u64 ku = 0, kd = 0;
-                if (l < K - 1) {
-                    const unsigned int o = ord_f32(up[q]);
-                    ku = ((u64)o << (IB + 8)) | low | (unsigned)(bits[l + 1] - bits[l]);
-                    if (o > 0x80000000u) { red[0] = max(red[0], (u64)o); red[1] = max(red[1], (u64)~o); }
-                }
-                if (l > 0) {
-                    const unsigned int o = ord_f32(dn[q]);
-                    kd = ((u64)(~o) << (IB + 8)) | low | (unsigned)(bits[l] - bits[l - 1]);
-                    if (o > 0x80000000u) { red[2] = max(red[2], (u64)o); red[3] = max(red[3], (u64)~o); }
-                }
-                keyU[i] = ku;
-                keyD[i] = kd;
-                if constexpr (RES) { own.reg.ku[q] = ku; own.reg.kd[q] = kd; }
-            }
-        }
-        team_reduce<4>(t, sh, red);
-        if (!t.ok) return;
-        u64 q0, q1;
-        value_range(red[0], red[1], IB, rg.loU, rg.hiU, q0, q1);
-        value_range(red[2], red[3], IB, q0, q1, rg.loD, rg.hiD);
+        rg.up = value_ranges(red[0], red[1]).up;
+        rg.down = value_ranges(red[2], red[3]).down;
         used = (long long)red[4];
-        Sel e, u, d, u2;
-        choose_sets<STEP>(t, sh, own, k, T - used, rg, e, u, d, u2);
-        if (!t.ok) return;
+        Sets o;
+        const Sel &e = o.e, &u = o.u, &d = o.d, &u2 = o.u2;
+        for (u64 apart = ~0ull;;) {
+            choose_sets<STEP>(t, sh, own, k, T - used, min_step, rg, N, apart, o);
+            if (!t.ok) return;
+            if (e.n_sel > 0 || apart != ~0ull) break;
+            u64 both[1] = {0};
+            own.template visit<false, false>([&](int i0, const Batch &bt, int) {
+#pragma unroll
+                for (int q = 0; q < AL_KPT; ++q) {
+                    const int place = N - 1 - (i0 + q * AL_THREADS);
+                    both[0] += key_at(bt.kd[q], place) >= d.tau && key_at(bt.ku[q], place) >= u.tau;
+                }
+            });
+            team_sum(t, sh, both);
+            if (!t.ok) return;
+            if (!both[0]) break;
+            apart = u.tau;
+        }
         // (a swap is a proposal: the caller accepts or rejects it)
         const int mode = e.n_sel > 0 ? MODE_EXPAND : u2.n_sel > 0 && d.n_sel > 0 ? MODE_ACCEPT : MODE_NONE;
         if (lead) {
@@ -590,33 +785,6 @@ void search_kernel(AllocState *st, const float *__restrict__ cost, const float *
             }
         }
     } else {
-        const int l0 = st->head.l0;
-        u64 red[3] = {0, 0, 0};                      // gains: largest, smallest inverted; the largest cost
-        own.start([&](long long i0, Batch &bt) {
-#pragma unroll
-            for (int q = 0; q < AL_KPT; ++q) {
-                const long long i = i0 + (long long)q * AL_THREADS;
-                if (i >= own.n1) continue;
-                const float *c = cost + i * K;
-                float prev = 0.0f, cm = 0.0f, cl = 0.0f, cp = 0.0f;
-                for (int l = 0; l < K; ++l) {
-                    const float v = c[l];
-                    if (v > 0.0f) red[2] = max(red[2], (u64)__float_as_uint(v));
-                    if (l) {
-                        const unsigned int o = ord_f32((prev - v) / (float)(bits[l] - bits[l - 1]));
-                        if (o > 0x80000000u) { red[0] = max(red[0], (u64)o); red[1] = max(red[1], (u64)~o); }
-                    }
-                    if (l == l0 - 1) cm = v;
-                    if (l == l0) cl = v;
-                    if (l == l0 + 1) cp = v;
-                    prev = v;
-                }
-                table_keys(cm, cl, cp, l0, K, bits, N, IB, i, bt.ku[q], bt.kd[q]);
-                bt.lv[q] = l0;
-            }
-        });
-        team_reduce<3>(t, sh, red);
-        if (!t.ok) return;
         int shift = 0;
         if (red[2]) {
             const unsigned int b = (unsigned int)red[2];
@@ -624,41 +792,63 @@ void search_kernel(AllocState *st, const float *__restrict__ cost, const float *
             const int ilog = e ? e - 127 : (31 - __clz((int)(b & 0x7fffffu))) - 149;
             shift = 61 - st->head.ceil_log2_n - (ilog + 1);
         }
-        value_range(red[0], red[1], IB, rg.loU, rg.hiU, rg.loD, rg.hiD);
+        rg = value_ranges(red[0], red[1]);
         const long long kmin = st->head.kmin;
         const int max_iters = st->head.max_iters;
         int iters = 0, expansions = 0, swaps_ok = 0, swaps_rej = 0, status = SBITS_OK;
         bool done = st->head.done != 0;
-        // The blocks that way(keyU, keyD) moves by +1 or -1 get their new level and keys.  (All loads of a batch are
+        // The blocks that way(keyU, keyD) moves by +1 or -1 get their new level and keys.  What it cost to leave the old level
+        // is, complemented, the key of the way back; the other key is read off the table.  (All loads of a batch are
         // requested before any is used.)
-        auto move = [&](auto way) {
-            own.template visit<true, true>([&](long long i0, Batch &bt) {
-                int by[AL_KPT];
-                float cm[AL_KPT], cl[AL_KPT], cp[AL_KPT];
+        struct Moves { int by[AL_KPT]; float a[AL_KPT], b[AL_KPT]; };
+        auto ask = [&](int i0, const Batch &bt, Moves &m, auto way) {
 #pragma unroll
-                for (int q = 0; q < AL_KPT; ++q) {
-                    const long long i = i0 + (long long)q * AL_THREADS;
-                    by[q] = i < own.n1 ? way(bt.ku[q], bt.kd[q]) : 0;
-                    cm[q] = cl[q] = cp[q] = 0.0f;
-                    if (by[q]) {
-                        const int l = bt.lv[q] + by[q];
-                        const float *c = cost + i * K;
-                        cl[q] = c[l];
-                        cm[q] = c[max(l - 1, 0)];
-                        cp[q] = c[min(l + 1, K - 1)];
+            for (int q = 0; q < AL_KPT; ++q) {
+                const int i = i0 + q * AL_THREADS;
+                m.by[q] = i < own.n1 ? way(key_at(bt.ku[q], N - 1 - i), key_at(bt.kd[q], N - 1 - i)) : 0;
+                m.a[q] = m.b[q] = 0.0f;
+                if (m.by[q]) {
+                    const int from = bt.lv[q] + (m.by[q] > 0 ? 1 : -2);              // the next step from there
+                    if (from >= 0 && from < K - 1) {
+                        const float *c = cost + (int64_t)i * K + from;
+                        m.a[q] = c[0];
+                        m.b[q] = c[1];
                     }
                 }
+            }
+        };
+        auto apply = [&](Batch &bt, const Moves &m) {
 #pragma unroll
-                for (int q = 0; q < AL_KPT; ++q)
-                    if (by[q]) {
-                        bt.lv[q] += by[q];
-                        table_keys(cm[q], cl[q], cp[q], bt.lv[q], K, bits, N, IB, i0 + (long long)q * AL_THREADS, bt.ku[q], bt.kd[q]);
+            for (int q = 0; q < AL_KPT; ++q)
+                if (m.by[q]) {
+                    const bool up = m.by[q] > 0;
+                    const int from = bt.lv[q] + (up ? 1 : -2);
+                    unsigned word = 0u, step = 0u;
+                    if (from >= 0 && from < K - 1) {
+                        step = (unsigned)(bits[from + 1] - bits[from]);
+                        const unsigned o = ord_f32((m.a[q] - m.b[q]) / (float)step);
+                        word = some(up ? o : ~o);
                     }
+                    const unsigned back = some(~(up ? bt.ku[q] : bt.kd[q])), wide = width_of(up ? bt.su : bt.sd, q);
+                    bt.ku[q] = up ? word : back;
+                    bt.kd[q] = up ? back : word;
+                    set_width(bt.su, q, up ? step : wide);
+                    set_width(bt.sd, q, up ? wide : step);
+                    bt.lv[q] += m.by[q];
+                }
+        };
+        auto move = [&](auto way) {
+            own.template visit<true, true>([&](int i0, Batch &bt, int) {
+                Moves m;
+                ask(i0, bt, m, way);
+                apply(bt, m);
             });
         };
+        Sets o;
+        const Sel &e = o.e, &u = o.u, &d = o.d, &u2 = o.u2;
+        u64 apart = ~0ull;
         while (!done) {
-            Sel e, u, d, u2;
-            choose_sets<STEP>(t, sh, own, k, T - used, rg, e, u, d, u2);
+            choose_sets<STEP>(t, sh, own, k, T - used, min_step, rg, N, apart, o);
             if (!t.ok) return;
             if (e.n_sel > 0) {
                 move([&](u64 ku, u64) { return ku >= e.tau ? 1 : 0; });
@@ -666,18 +856,20 @@ void search_kernel(AllocState *st, const float *__restrict__ cost, const float *
                 used += e.w_sel;
                 ++expansions;
             } else {
-                u64 lg[2] = {0, 0};                  // the swap's loss and gain
+                u64 lg[3] = {0, 0, 0};               // the swap's loss and gain; blocks that both sets hold
                 auto way = [&](u64 ku, u64 kd) { return ku >= u2.tau ? 1 : (kd >= d.tau && !(ku >= u.tau)) ? -1 : 0; };
-                own.template visit<true, false>([&](long long i0, const Batch &bt) {
+                own.template visit<true, false>([&](int i0, const Batch &bt, int) {
                     int by[AL_KPT];
                     float hi[AL_KPT], lo[AL_KPT];    // the table entries below and above the step
 #pragma unroll
                     for (int q = 0; q < AL_KPT; ++q) {
-                        const long long i = i0 + (long long)q * AL_THREADS;
-                        by[q] = i < own.n1 ? way(bt.ku[q], bt.kd[q]) : 0;
+                        const int i = i0 + q * AL_THREADS;
+                        const u64 ku = key_at(bt.ku[q], N - 1 - i), kd = key_at(bt.kd[q], N - 1 - i);
+                        by[q] = i < own.n1 ? way(ku, kd) : 0;
+                        lg[2] += i < own.n1 && kd >= d.tau && ku >= u.tau;
                         hi[q] = lo[q] = 0.0f;
                         if (by[q]) {
-                            const float *c = cost + i * K + bt.lv[q] + (by[q] > 0 ? 0 : -1);
+                            const float *c = cost + (int64_t)i * K + bt.lv[q] + (by[q] > 0 ? 0 : -1);
                             hi[q] = c[0];
                             lo[q] = c[1];
                         }
@@ -686,11 +878,19 @@ void search_kernel(AllocState *st, const float *__restrict__ cost, const float *
                     for (int q = 0; q < AL_KPT; ++q)
                         if (by[q]) lg[by[q] > 0] += (u64)fx(hi[q] - lo[q], shift);
                 });
-                team_reduce<0>(t, sh, lg);
+                Moves m;                             // (what the swap will need of the table if it is accepted, asked for in good time)
+                if constexpr (RES) ask(own.n0 + tid, own.reg, m, way);
+                team_sum(t, sh, lg);
                 if (!t.ok) return;
+                if (lg[2] && apart == ~0ull) {       // d has blocks of u: it is chosen again, outside u
+                    apart = u.tau;
+                    continue;
+                }
+                apart = ~0ull;
                 const long long delta = (long long)(lg[0] - lg[1]);
                 if (u2.n_sel > 0 && d.n_sel > 0 && delta < 0) {
-                    move(way);
+                    if constexpr (RES) apply(own.reg, m);
+                    else move(way);
                     if (lead)
                         trace_write(tr, iters, 1, k, u2.n_sel, d.n_sel, u2.n_sel, d.n_sel, used, used + u2.w_sel - d.w_sel, delta);
                     used += u2.w_sel - d.w_sel;
@@ -706,25 +906,25 @@ void search_kernel(AllocState *st, const float *__restrict__ cost, const float *
             else if (iters >= max_iters) { done = true; status = SBITS_ERR_MAX_ITERS; }
         }
         u64 fin[2] = {0, 0};                         // cost and bits of the final levels
-        own.template visit<true, false>([&](long long i0, const Batch &bt) {
+        own.template visit<true, false>([&](int i0, const Batch &bt, int) {
             float c[AL_KPT];
 #pragma unroll
             for (int q = 0; q < AL_KPT; ++q) {
-                const long long i = i0 + (long long)q * AL_THREADS;
+                const int i = i0 + q * AL_THREADS;
                 c[q] = 0.0f;
                 if (i < own.n1) {
-                    c[q] = cost[i * K + bt.lv[q]];
+                    c[q] = cost[(int64_t)i * K + bt.lv[q]];
                     if constexpr (RES) level[i] = (uint8_t)bt.lv[q];
                 }
             }
 #pragma unroll
             for (int q = 0; q < AL_KPT; ++q)
-                if (i0 + (long long)q * AL_THREADS < own.n1) {
+                if (i0 + q * AL_THREADS < own.n1) {
                     fin[0] += (u64)fx(c[q], shift);
                     fin[1] += (u64)bits[bt.lv[q]];
                 }
         });
-        team_reduce<0>(t, sh, fin);
+        team_sum(t, sh, fin);
         if (!t.ok) return;
         if (lead) {
             AllocResult r = {};
@@ -745,9 +945,9 @@ void step_apply_kernel(const AllocState *st, const u64 *__restrict__ keyU, const
     const AllocHead &hd = st->head;
     const int mode = hd.mode;
     const u64 tauE = hd.tauE, tauU = hd.tauU, tauD = hd.tauD, tauU2 = hd.tauU2;
-    const long long N = hd.N;
+    const long long N = hd.N;          // (the widths that the keys end in in memory make way for the blocks' places)
     for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (long long)gridDim.x * blockDim.x) {
-        const u64 ku = keyU[i], kd = keyD[i];
+        const u64 ku = key_at((unsigned)(keyU[i] >> 32), (int)(N - 1 - i)), kd = key_at((unsigned)(keyD[i] >> 32), (int)(N - 1 - i));
         int l = level_in[i];
         if (mode == MODE_EXPAND) {
             if (ku >= tauE) ++l;
@@ -798,13 +998,15 @@ static AllocWs alloc_ws(void *ws, int64_t N)
     return w;
 }
 
+static int prep_wgs(int64_t N) { return (int)((N + PREP_THREADS - 1) / PREP_THREADS < PREP_WGS ? (N + PREP_THREADS - 1) / PREP_THREADS : PREP_WGS); }
+
 template <bool STEP>
 static void launch_search(hipStream_t sm, unsigned G, const AllocWs &w, int64_t N, const float *cost, const float *s_up,
                           const float *s_down, uint8_t *level, AllocResult *result, int only_if_aborted)
 {
     auto *fn = (N + G - 1) / G <= (int64_t)AL_KPT * AL_THREADS ? &search_kernel<STEP, true> : &search_kernel<STEP, false>;
-    hipLaunchKernelGGL(fn, dim3(G), dim3(AL_THREADS), 0, sm, w.st, cost, s_up, s_down, level, w.keyU, w.keyD, w.tr, result, SBITS_SPIN_LIMIT,
-                       only_if_aborted);
+    hipLaunchKernelGGL(fn, dim3(G), dim3(AL_THREADS), 0, sm, w.st, cost, s_up, s_down, level, w.keyU, w.keyD, w.tr, result, prep_wgs(N),
+                       SBITS_SPIN_LIMIT, only_if_aborted);
 }
 
 static AllocHead start_head(const sbits_plan *plan, double avg_bits)
@@ -815,7 +1017,8 @@ static AllocHead start_head(const sbits_plan *plan, double avg_bits)
     h.T = (long long)floor(avg_bits * (double)plan->N);
     h.K = plan->K;
     h.ceil_log2_n = ceil_log2_ll(plan->N);
-    h.IB = h.ceil_log2_n > 0 ? h.ceil_log2_n : 1;
+    h.min_step = 0x7fffffff;
+    for (int c = 1; c < plan->K; ++c) if (plan->bits[c] - plan->bits[c - 1] < h.min_step) h.min_step = plan->bits[c] - plan->bits[c - 1];
     for (int c = 0; c < MAX_CAND; ++c) h.bits[c] = c < plan->K ? plan->bits[c] : plan->bits[plan->K - 1];
     return h;
 }
@@ -868,9 +1071,9 @@ int sbits_enqueue_allocate(sbits_plan *plan, const float *cost, double avg_bits,
     if (all_max) h0.done = 1;
 
     // The workgroups wait for each other.  Should the device be so full that they never run together, they
-    // give up (see grid_sync) and one workgroup, which waits for nobody, does the search.
+    // give up (see give_up) and one workgroup, which waits for nobody, does the search.
     const unsigned G = search_wgs(N, false, ctx->cus);
-    hipLaunchKernelGGL(set_state_kernel, dim3(1), dim3(AL_THREADS), 0, sm, w.st, h0);
+    hipLaunchKernelGGL(prepare_kernel<false>, dim3(prep_wgs(N)), dim3(PREP_THREADS), 0, sm, w.st, h0, cost, nullptr, nullptr, level, w.keyU, w.keyD);
     launch_search<false>(sm, G, w, N, cost, nullptr, nullptr, level, result, 0);
     if (G > 1 && SBITS_SECOND_TRY) launch_search<false>(sm, 1, w, N, cost, nullptr, nullptr, level, result, 1);   // returns at once unless the first gave up
     SBITS_HIP(ctx, hipGetLastError());
@@ -912,9 +1115,9 @@ int sbits_run_propose(sbits_plan *plan, const float *s_up, const float *s_down, 
     AllocHead h = start_head(plan, avg_bits);
     h.k = k;
     // the start state travels as a kernel argument: nothing to keep alive, nothing to wait for
-    hipLaunchKernelGGL(set_state_kernel, dim3(1), dim3(AL_THREADS), 0, sm, w.st, h);
     const unsigned G = search_wgs(N, true, ctx->cus);
     uint8_t *const lv = const_cast<uint8_t *>(level_in);             // (only read by the step)
+    hipLaunchKernelGGL(prepare_kernel<true>, dim3(prep_wgs(N)), dim3(PREP_THREADS), 0, sm, w.st, h, nullptr, s_up, s_down, lv, w.keyU, w.keyD);
     launch_search<true>(sm, G, w, N, nullptr, s_up, s_down, lv, result, 0);
     if (G > 1 && SBITS_SECOND_TRY) launch_search<true>(sm, 1, w, N, nullptr, s_up, s_down, lv, result, 1);   // returns at once unless the first gave up
     const unsigned grid = (unsigned)((N + 255) / 256 < 1024 ? (N + 255) / 256 : 1024);

@@ -6,8 +6,9 @@
 namespace sbits {
 
 // Workgroups of a search over N blocks on a device (or partition) of `cus` CUs: 2048 blocks each (four to a thread) up to 32
-// workgroups, beyond that 4096, the most their registers hold (14 k blocks, 23 iterations: 360 us with 7 workgroups, 401
-// with 4; 430 k blocks, 22 iterations: 788 us with 105, 837 with 128).  At most half of the CUs, one of them takes one
+// workgroups, beyond that 4096, the most their registers hold (13 k blocks, 15 iterations: 181 us with 7 workgroups, 199
+// with 4, 176 with 13; 27 k: 271 with 13, 300 with 7, 266 with 26; 107 k: 355 with 26, 457 with 64; below 4096 blocks one would
+// do, 210 us for 4096, but two take 230 only).  At most half of the CUs, one of them takes one
 // workgroup, so that two searches fit side by side: workgroups that have no place at the same time wait for each other in
 // vain, and one of them does it all.  Larger tables live in memory then (4.2 M blocks: 3.6 ms; 4.9 ms with a launch per round).
 // A single step over a table in memory is a pass or two over it and needs a third of the registers, so beyond 2 M blocks it
