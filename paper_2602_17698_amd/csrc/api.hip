@@ -395,7 +395,7 @@ int sbits_gather_cost_all(sbits_plan *plan, const sbits_matrix *mats, const int3
     if ((rc = need_device(plan))) return rc;
     if ((rc = sbits_upload_head(plan, mats, nullptr, ws))) return rc;
     if (!sbits_fused_layout_ok(plan, true)) return SBITS_ERR_UNIMPLEMENTED;
-    return sbits_launch_gather_cost_all(plan, row_perm, col_perm, w_re_bf16, cost, ws);
+    return sbits_launch_gather_cost_all(plan, row_perm, col_perm, w_re_bf16, nullptr, cost, ws);
 }
 
 int sbits_surrogates_all(sbits_plan *plan, const sbits_matrix *mats, const int32_t *row_perm,
@@ -579,10 +579,14 @@ static int search_impl(sbits_plan *plan, const sbits_matrix *mats, const Couplin
     if (rc) return rc;
     const bool one_pass = sbits_fused_shapes_ok(plan) && sbits_fused_layout_ok(plan, true);
     if (one_pass) {
-        if ((rc = sbits_launch_gather_cost_all(plan, out->row_perm, out->col_perm, out->w_re_bf16, out->cost, ws)))
+        if ((rc = sbits_launch_gather_cost_all(plan, out->row_perm, out->col_perm, out->w_re_bf16, nullptr, out->cost, ws)))
+            return rc;
+    } else if (!out->s_re || !out->w_re_bf16) {
+        return SBITS_ERR_INVALID_ARG;
+    } else if (sbits_copies_shapes_ok(plan) && sbits_fused_layout_ok(plan, true)) {
+        if ((rc = sbits_launch_gather_cost_all(plan, out->row_perm, out->col_perm, out->w_re_bf16, out->s_re, out->cost, ws)))
             return rc;
     } else {
-        if (!out->s_re || !out->w_re_bf16) return SBITS_ERR_INVALID_ARG;
         if ((rc = sbits_launch_gather_all(plan, out->row_perm, out->col_perm, out->w_re_bf16, out->s_re, ws)))
             return rc;
         if ((rc = sbits_launch_cost_all(plan, out->w_re_bf16, out->s_re, out->cost, ws))) return rc;

@@ -18,15 +18,19 @@ constexpr int COST_MAX_ROUND = 4;                     // rows that may share one
 #endif
 static_assert(SBITS_COST_POWER == 1 || SBITS_COST_POWER == 2, "cost power is 1 or 2");
 
-// value held by lane j*SP + SLOT of the caller's lane group, j in [0, LPG/SP)
-template <int LPG, int SP, int SLOT>
+// Lanes that share a round of divisions: a lane group, but no more than a row of 16 lanes, in which a broadcast is a move
+// (256-column blocks: both rows of a group divide the same; a broadcast over 32 lanes goes through LDS).
+constexpr int div_lanes(int lpg) { return lpg < 16 ? lpg : 16; }
+
+// value held by lane j*SP + SLOT of the caller's LD lanes, j in [0, LD/SP)
+template <int LD, int SP, int SLOT>
 __device__ __forceinline__ float bcast_row(float v, int j)
 {
-    constexpr int RPG = LPG / SP;
-    if (RPG <= 1 || j == 0) return group_bcast<LPG, SLOT>(v);
-    if (RPG >= 2 && j == 1) return group_bcast<LPG, (1 * SP + SLOT) % LPG>(v);
-    if (RPG >= 4 && j == 2) return group_bcast<LPG, (2 * SP + SLOT) % LPG>(v);
-    return group_bcast<LPG, (3 * SP + SLOT) % LPG>(v);
+    constexpr int RPG = LD / SP;
+    if (RPG <= 1 || j == 0) return group_bcast<LD, SLOT>(v);
+    if (RPG >= 2 && j == 1) return group_bcast<LD, (1 * SP + SLOT) % LD>(v);
+    if (RPG >= 4 && j == 2) return group_bcast<LD, (2 * SP + SLOT) % LD>(v);
+    return group_bcast<LD, (3 * SP + SLOT) % LD>(v);
 }
 
 // Per-lane constants of the distributed grid divisions.  The 2K quotients of a
@@ -36,9 +40,10 @@ __device__ __forceinline__ float bcast_row(float v, int j)
 template <int LPG, int K>
 struct DivPlan {
     static constexpr int SP = (2 * K <= 2) ? 2 : (2 * K <= 4) ? 4 : (2 * K <= 8) ? 8 : 16;   // slots per row
-    static constexpr int RP0 = (LPG >= SP) ? (LPG / SP) : 1;
+    static constexpr int LD = div_lanes(LPG);
+    static constexpr int RP0 = (LD >= SP) ? (LD / SP) : 1;
     static constexpr int RP = RP0 < COST_MAX_ROUND ? RP0 : COST_MAX_ROUND;                                         // rows per round
-    static constexpr int NS = (LPG >= SP) ? 1 : (2 * K + LPG - 1) / LPG;                       // divisions per lane
+    static constexpr int NS = (LD >= SP) ? 1 : (2 * K + LD - 1) / LD;                       // divisions per lane
     float qf[NS], thr[NS];
     bool is_scale[NS];
     int my_row;
@@ -47,7 +52,7 @@ struct DivPlan {
     {
 #pragma unroll
         for (int t = 0; t < NS; ++t) {
-            const int slot = (LPG >= SP) ? (lig % SP) : (lig + t * LPG);
+            const int slot = (LD >= SP) ? (lig % SP) : (lig + t * LD);
             int c = slot >> 1;
             c = c < K ? c : K - 1;
             float q = gc.qmaxf[0], th = gc.thr[0];
@@ -58,7 +63,7 @@ struct DivPlan {
             thr[t] = th;
             is_scale[t] = (slot & 1) != 0;
         }
-        my_row = (LPG >= SP) ? (lig / SP) : 0;
+        my_row = (LD >= SP) ? (lig % LD / SP) : 0;
     }
 };
 
@@ -140,8 +145,8 @@ __device__ __forceinline__ void quant_cost_finish(const float (&w)[NI][8], const
                                                   const float (&s)[NI][8], float (&out)[NI][K])
 {
     using DP = DivPlan<LPG, K - Z0>;
-    constexpr int SP = DP::SP;
-    constexpr bool RIDE = RIDE_OK && LPG == 16 && LPG >= SP;   // the reciprocal's broadcast rides on the multiply
+    constexpr int SP = DP::SP, LD = DP::LD;
+    constexpr bool RIDE = RIDE_OK && LD == 16 && LD >= SP;     // the reciprocal's broadcast rides on the multiply
     float v0 = val[0];
     if constexpr (RIDE) dpp_settle(v0);
     static_for<0, NI>([&](auto ij) {
@@ -157,19 +162,19 @@ __device__ __forceinline__ void quant_cost_finish(const float (&w)[NI][8], const
             constexpr int c = decltype(ic)::value;
             float inv = 0.0f, scl;
             if constexpr (RIDE) {
-                scl = bcast_row<LPG, SP, 2 * c + 1>(v0, j);
-            } else if constexpr (LPG >= SP) {
-                inv = bcast_row<LPG, SP, 2 * c>(val[0], j);
-                scl = bcast_row<LPG, SP, 2 * c + 1>(val[0], j);
+                scl = bcast_row<LD, SP, 2 * c + 1>(v0, j);
+            } else if constexpr (LD >= SP) {
+                inv = bcast_row<LD, SP, 2 * c>(val[0], j);
+                scl = bcast_row<LD, SP, 2 * c + 1>(val[0], j);
             } else {
-                inv = group_bcast<LPG, (2 * c) % LPG>(val[(2 * c) / LPG]);
-                scl = group_bcast<LPG, (2 * c + 1) % LPG>(val[(2 * c + 1) / LPG]);
+                inv = group_bcast<LD, (2 * c) % LD>(val[(2 * c) / LD]);
+                scl = group_bcast<LD, (2 * c + 1) % LD>(val[(2 * c + 1) / LD]);
             }
             float acc = 0.0f;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 float t;
-                if constexpr (RIDE) t = mul_bcast16<((LPG / SP > 1 ? j : 0) * SP + 2 * c) % 16>(v0, x[j][e]);
+                if constexpr (RIDE) t = mul_bcast16<((LD / SP > 1 ? j : 0) * SP + 2 * c) % 16>(v0, x[j][e]);
                 else t = x[j][e] * inv;
                 const float q = rintf(t);
                 const float d = fmaf(-q, scl, x[j][e]);

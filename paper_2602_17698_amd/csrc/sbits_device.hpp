@@ -43,6 +43,10 @@ constexpr int DPP_BCAST0 = 0x150;       // row_newbcast:0 (+n for lane n of the 
 // an adjacent-pair tree (lanes 2j,2j+1, then pairs of pairs, ...): after the
 // quad steps all lanes of a quad agree, so the mirror steps pair quads and
 // halves exactly as xor 4 / xor 8 would.  Every lane ends with the same bits.
+// (the swap of a value with itself leaves one operand of each pair of rows, or of halves, in one register and the other in the
+// other; the operations are commutative)
+template <class Op, class Pair>
+__device__ __forceinline__ float op_halves(float, Op op, Pair p) { return op(__uint_as_float(p[0]), __uint_as_float(p[1])); }
 template <int LPG, class Op>
 __device__ __forceinline__ float group_allreduce(float v, Op op)
 {
@@ -50,8 +54,8 @@ __device__ __forceinline__ float group_allreduce(float v, Op op)
     if (LPG >= 4)  v = op(v, dpp_mov<DPP_XOR2>(v));
     if (LPG >= 8)  v = op(v, dpp_mov<DPP_HALF_MIRROR>(v));
     if (LPG >= 16) v = op(v, dpp_mov<DPP_MIRROR>(v));
-    if (LPG >= 32) v = op(v, __shfl_xor(v, 16));
-    if (LPG >= 64) v = op(v, __shfl_xor(v, 32));
+    if (LPG >= 32) v = op_halves(v, op, __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false));
+    if (LPG >= 64) v = op_halves(v, op, __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false));
     return v;
 }
 
@@ -64,6 +68,8 @@ template <int LPG, int J>
 __device__ __forceinline__ float group_bcast(float v)
 {
     if (LPG == 1) return v;
+    if (LPG == 2) return dpp_mov<(J & 1) * 0x55 + 0xA0>(v);                  // quad_perm [J, J, 2 + J, 2 + J]
+    if (LPG == 4) return dpp_mov<(J & 3) * 0x55>(v);                // quad_perm [J, J, J, J]
     if (LPG == 16) return dpp_mov<DPP_BCAST0 + (J & 15)>(v);
     const int lane = (int)(threadIdx.x & 63);
     return __shfl(v, (lane & ~(LPG - 1)) + J);

@@ -120,7 +120,8 @@ bool sbits_fused_all_staged(const sbits_plan *plan);
 bool sbits_fused_layout_ok(const sbits_plan *plan, bool need_s);
 size_t sbits_fused_ws_bytes(const sbits_plan *plan);
 int sbits_launch_gather_cost_all(sbits_plan *plan, const int32_t *row_perm, const int32_t *col_perm,
-                                 void *w_re, float *cost, void *ws);
+                                 void *w_re, float *s_re, float *cost, void *ws);
+bool sbits_copies_shapes_ok(const sbits_plan *plan);
 int sbits_launch_surrogates_all(sbits_plan *plan, const int32_t *row_perm, const int32_t *col_perm,
                                 const uint8_t *level, float *s_up, float *s_down, void *ws);
 int sbits_launch_gather_pack_all(sbits_plan *plan, const int32_t *row_perm, const int32_t *col_perm,
