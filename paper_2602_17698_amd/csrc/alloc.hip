@@ -71,6 +71,8 @@ struct AllocResult {
     long long prop_up, prop_dn, prop_after;
     int shift, status, iters, expansions, swaps_ok, swaps_rej, mode, valid;
 };
+// gave_up: a word of its own, which the leader does not write: a workgroup may give up at the very last exchange.
+struct AllocReport { AllocResult result; int pad_[16]; unsigned int gave_up; };
 // One exchange between the workgroups; three of them take turns (see end_turn).
 struct AllocXchg {
     unsigned long long hist[SEL_SETS][SEL_BINS];   // per bin: (sum of step widths << 32) | number of keys
@@ -111,6 +113,7 @@ struct Team {
     long long n0, n1;             // its blocks
     int turn;                     // the exchange buffer in use
     int spin_limit;
+    AllocReport *report;          // page-locked host memory, or null
     bool ok;                      // false: a wait was given up, leave
 };
 
@@ -147,7 +150,10 @@ __device__ __forceinline__ AllocXchg *xchg(const Team &t) { return &t.st->x[t.tu
 // first exchange that somebody is missing from.
 __device__ __forceinline__ void give_up(Team &t)
 {
-    if (threadIdx.x == 0) (void)__hip_atomic_fetch_add(&t.st->head.aborted, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x == 0) {
+        (void)__hip_atomic_fetch_add(&t.st->head.aborted, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (t.report) t.report->gave_up = 1u;
+    }
     t.ok = false;
 }
 
@@ -705,13 +711,13 @@ template <bool STEP, bool RES>
 __global__ __launch_bounds__(AL_THREADS)
 void search_kernel(AllocState *st, const float *__restrict__ cost, const float *__restrict__ s_up,
                    const float *__restrict__ s_down, uint8_t *level, u64 *__restrict__ keyU, u64 *__restrict__ keyD,
-                   sbits_trace *tr, AllocResult *result, int n_ranges, int spin_limit, int only_if_aborted)
+                   sbits_trace *tr, AllocReport *report, int n_ranges, int spin_limit, int only_if_aborted)
 {
     __shared__ AllocShared sh;
     const int tid = (int)threadIdx.x;
     if (only_if_aborted && !st->head.aborted) return;
     Team t;
-    t.st = st; t.G = (int)gridDim.x; t.g = (int)blockIdx.x; t.turn = 0; t.spin_limit = spin_limit; t.ok = true;
+    t.st = st; t.G = (int)gridDim.x; t.g = (int)blockIdx.x; t.turn = 0; t.spin_limit = spin_limit; t.report = report; t.ok = true;
     const int N = uni((int)st->head.N), K = uni(st->head.K), per = (N + t.G - 1) / t.G;      // (N <= 2^24)
     const long long T = st->head.T;
     for (int b = tid; b < SEL_SETS * SEL_BINS; b += AL_THREADS) sh.hist[0][b] = 0ull;
@@ -773,7 +779,7 @@ void search_kernel(AllocState *st, const float *__restrict__ cost, const float *
             AllocHead &hd = st->head;
             hd.mode = mode;
             hd.tauE = e.tau; hd.tauU = u.tau; hd.tauD = d.tau; hd.tauU2 = u2.tau;
-            if (result) {
+            if (report) {
                 AllocResult r = {};
                 r.used = used; r.budget = T;
                 r.mode = mode;
@@ -781,7 +787,7 @@ void search_kernel(AllocState *st, const float *__restrict__ cost, const float *
                 r.prop_dn = mode == MODE_ACCEPT ? d.n_sel : 0;
                 r.prop_after = used + (mode == MODE_EXPAND ? e.w_sel : mode == MODE_ACCEPT ? u2.w_sel - d.w_sel : 0);
                 r.valid = 1;
-                *result = r;
+                report->result = r;
             }
         }
     } else {
@@ -932,7 +938,7 @@ void search_kernel(AllocState *st, const float *__restrict__ cost, const float *
             r.iters = iters; r.expansions = expansions; r.swaps_ok = swaps_ok; r.swaps_rej = swaps_rej;
             r.cost_fixed = (long long)fin[0]; r.bits_check = (long long)fin[1];
             r.valid = 1;
-            *result = r;
+            report->result = r;
         }
     }
 }
@@ -1002,10 +1008,10 @@ static int prep_wgs(int64_t N) { return (int)((N + PREP_THREADS - 1) / PREP_THRE
 
 template <bool STEP>
 static void launch_search(hipStream_t sm, unsigned G, const AllocWs &w, int64_t N, const float *cost, const float *s_up,
-                          const float *s_down, uint8_t *level, AllocResult *result, int only_if_aborted)
+                          const float *s_down, uint8_t *level, AllocReport *report, int only_if_aborted)
 {
     auto *fn = (N + G - 1) / G <= (int64_t)AL_KPT * AL_THREADS ? &search_kernel<STEP, true> : &search_kernel<STEP, false>;
-    hipLaunchKernelGGL(fn, dim3(G), dim3(AL_THREADS), 0, sm, w.st, cost, s_up, s_down, level, w.keyU, w.keyD, w.tr, result, prep_wgs(N),
+    hipLaunchKernelGGL(fn, dim3(G), dim3(AL_THREADS), 0, sm, w.st, cost, s_up, s_down, level, w.keyU, w.keyD, w.tr, report, prep_wgs(N),
                        SBITS_SPIN_LIMIT, only_if_aborted);
 }
 
@@ -1024,12 +1030,13 @@ static AllocHead start_head(const sbits_plan *plan, double avg_bits)
 }
 
 // The context's page-locked buffer, ready for the next result.
-static int result_buffer(sbits_ctx *ctx, AllocResult **out)
+static int report_buffer(sbits_ctx *ctx, AllocReport **out)
 {
-    static_assert(sizeof(AllocResult) <= SBITS_PINNED_BYTES, "a result must fit the pinned buffer");
+    static_assert(sizeof(AllocReport) <= SBITS_PINNED_BYTES, "a result must fit the pinned buffer");
     if (!ctx->pinned) SBITS_HIP(ctx, hipHostMalloc(&ctx->pinned, SBITS_PINNED_BYTES, hipHostMallocDefault));
-    *out = static_cast<AllocResult *>(ctx->pinned);
-    (*out)->valid = 0;
+    *out = static_cast<AllocReport *>(ctx->pinned);
+    (*out)->result.valid = 0;
+    (*out)->gave_up = 0u;
     return SBITS_OK;
 }
 
@@ -1050,8 +1057,8 @@ int sbits_enqueue_allocate(sbits_plan *plan, const float *cost, double avg_bits,
     const int K = plan->K;
     if (avg_bits < (double)plan->bits[0]) return SBITS_ERR_INFEASIBLE_BUDGET;
     const AllocWs w = alloc_ws(ws, N);
-    AllocResult *result;
-    const int rc = result_buffer(ctx, &result);
+    AllocReport *report;
+    const int rc = report_buffer(ctx, &report);
     if (rc) return rc;
 
     AllocHead h0 = start_head(plan, avg_bits);
@@ -1074,17 +1081,40 @@ int sbits_enqueue_allocate(sbits_plan *plan, const float *cost, double avg_bits,
     // give up (see give_up) and one workgroup, which waits for nobody, does the search.
     const unsigned G = search_wgs(N, false, ctx->cus);
     hipLaunchKernelGGL(prepare_kernel<false>, dim3(prep_wgs(N)), dim3(PREP_THREADS), 0, sm, w.st, h0, cost, nullptr, nullptr, level, w.keyU, w.keyD);
-    launch_search<false>(sm, G, w, N, cost, nullptr, nullptr, level, result, 0);
-    if (G > 1 && SBITS_SECOND_TRY) launch_search<false>(sm, 1, w, N, cost, nullptr, nullptr, level, result, 1);   // returns at once unless the first gave up
+    launch_search<false>(sm, G, w, N, cost, nullptr, nullptr, level, report, 0);
     SBITS_HIP(ctx, hipGetLastError());
     return SBITS_SECOND_TRY ? SBITS_OK : stop_if_aborted(ctx, w.st);
+}
+
+bool sbits_allocation_failed(const sbits_plan *plan)
+{
+    const AllocReport *r = static_cast<const AllocReport *>(plan->ctx->pinned);
+    return !r->result.valid || r->gave_up;
+}
+
+int sbits_repeat_allocate(sbits_plan *plan, const float *cost, uint8_t *level, void *ws)
+{
+    sbits_ctx *ctx = plan->ctx;
+    const AllocWs w = alloc_ws(ws, plan->N);
+    AllocReport *report;
+    const int rc = report_buffer(ctx, &report);
+    if (rc) return rc;
+    launch_search<false>(ctx->stream, 1, w, plan->N, cost, nullptr, nullptr, level, report, 1);
+    SBITS_HIP(ctx, hipGetLastError());
+    return SBITS_OK;
+}
+
+sbits_alloc_after sbits_after_allocate(const sbits_plan *plan, void *ws)
+{
+    const AllocWs w = alloc_ws(ws, plan->N);
+    return sbits_alloc_after{&w.st->head.aborted, w.keyU};
 }
 
 int sbits_finish_allocate(sbits_plan *plan, sbits_stats *host_stats, sbits_trace *host_trace, int64_t trace_cap, void *ws)
 {
     sbits_ctx *ctx = plan->ctx;
-    const AllocResult h = *static_cast<const AllocResult *>(ctx->pinned);
-    if (!h.valid) return SBITS_ERR_INTERNAL;
+    const AllocResult h = static_cast<const AllocReport *>(ctx->pinned)->result;
+    if (sbits_allocation_failed(plan)) return SBITS_ERR_INTERNAL;
     if (host_stats) {
         host_stats->iters = h.iters; host_stats->expansions = h.expansions;
         host_stats->swaps_ok = h.swaps_ok; host_stats->swaps_rej = h.swaps_rej;
@@ -1101,7 +1131,7 @@ int sbits_finish_allocate(sbits_plan *plan, sbits_stats *host_stats, sbits_trace
     return h.status;
 }
 
-// One step of Algorithm 2 on caller-supplied estimates.  Workspace as sbits_run_allocate.
+// One step of Algorithm 2 on caller-supplied estimates.  Workspace as the allocation's.
 int sbits_run_propose(sbits_plan *plan, const float *s_up, const float *s_down, const uint8_t *level_in,
                       double avg_bits, int64_t k, uint8_t *level_out, sbits_proposal *host_out, void *ws)
 {
@@ -1109,8 +1139,8 @@ int sbits_run_propose(sbits_plan *plan, const float *s_up, const float *s_down, 
     hipStream_t sm = ctx->stream;
     const int64_t N = plan->N;
     const AllocWs w = alloc_ws(ws, N);
-    AllocResult *result = nullptr;                                   // (without a host output nothing is waited for)
-    const int rc = host_out ? result_buffer(ctx, &result) : SBITS_OK;
+    AllocReport *report = nullptr;                                   // (without a host output nothing is waited for)
+    const int rc = host_out ? report_buffer(ctx, &report) : SBITS_OK;
     if (rc) return rc;
     AllocHead h = start_head(plan, avg_bits);
     h.k = k;
@@ -1118,15 +1148,15 @@ int sbits_run_propose(sbits_plan *plan, const float *s_up, const float *s_down, 
     const unsigned G = search_wgs(N, true, ctx->cus);
     uint8_t *const lv = const_cast<uint8_t *>(level_in);             // (only read by the step)
     hipLaunchKernelGGL(prepare_kernel<true>, dim3(prep_wgs(N)), dim3(PREP_THREADS), 0, sm, w.st, h, nullptr, s_up, s_down, lv, w.keyU, w.keyD);
-    launch_search<true>(sm, G, w, N, nullptr, s_up, s_down, lv, result, 0);
-    if (G > 1 && SBITS_SECOND_TRY) launch_search<true>(sm, 1, w, N, nullptr, s_up, s_down, lv, result, 1);   // returns at once unless the first gave up
+    launch_search<true>(sm, G, w, N, nullptr, s_up, s_down, lv, report, 0);
+    if (G > 1 && SBITS_SECOND_TRY) launch_search<true>(sm, 1, w, N, nullptr, s_up, s_down, lv, report, 1);   // returns at once unless the first gave up
     const unsigned grid = (unsigned)((N + 255) / 256 < 1024 ? (N + 255) / 256 : 1024);
     hipLaunchKernelGGL(step_apply_kernel, dim3(grid), dim3(256), 0, sm, (const AllocState *)w.st,
                        (const u64 *)w.keyU, (const u64 *)w.keyD, level_in, level_out);
     SBITS_HIP(ctx, hipGetLastError());
     if (host_out) {
         SBITS_HIP(ctx, hipStreamSynchronize(sm));
-        const AllocResult r = *result;
+        const AllocResult r = report->result;            // (of the second launch, if the first gave up)
         if (!r.valid) return SBITS_ERR_INTERNAL;
         host_out->kind = r.mode == MODE_EXPAND ? 1 : r.mode == MODE_ACCEPT ? 2 : 0;
         host_out->pad_ = 0;

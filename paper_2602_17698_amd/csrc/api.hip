@@ -198,8 +198,9 @@ static int need_device(const sbits_plan *plan)
 // matrix 20 us between its kernels.
 // The image a copy reads must not change while the copy is pending: the head is built in one of two
 // page-locked buffers of the plan, taken in turns; before a buffer is rewritten the host waits for the
-// event recorded behind the copy that last read it (two uploads back: as good as always complete).
-int sbits_upload_head(sbits_plan *plan, const sbits_matrix *mats, const sbits_coupling *cpl, void *ws)
+// event recorded behind the copy that last read it (two uploads back: as good as always complete).  guard = false: no event, which
+// takes the device 5 us; the caller waits for the stream before it returns.
+int sbits_upload_head(sbits_plan *plan, const sbits_matrix *mats, const sbits_coupling *cpl, void *ws, bool guard)
 {
     sbits_ctx *ctx = plan->ctx;
     const size_t bytes = plan->head_bytes;
@@ -253,8 +254,8 @@ int sbits_upload_head(sbits_plan *plan, const sbits_matrix *mats, const sbits_co
         table(head, SLOT_ARR_REP, cpl->rep);
     }
     SBITS_HIP(ctx, hipMemcpyAsync(ws, head, bytes, hipMemcpyHostToDevice, ctx->stream));
-    SBITS_HIP(ctx, hipEventRecord(plan->desc_done[t], ctx->stream));
-    plan->desc_used[t] = true;
+    plan->desc_used[t] = guard;
+    if (guard) SBITS_HIP(ctx, hipEventRecord(plan->desc_done[t], ctx->stream));
     return SBITS_OK;
 }
 
@@ -447,6 +448,10 @@ int sbits_allocate(sbits_plan *plan, const float *cost, double avg_bits, const s
     if (rc) return rc;
     if ((rc = sbits_enqueue_allocate(plan, cost, avg_bits, params, level, sbits_scratch(plan, ws)))) return rc;
     SBITS_HIP(plan->ctx, hipStreamSynchronize(plan->ctx->stream));
+    if (sbits_allocation_failed(plan)) {
+        if ((rc = sbits_repeat_allocate(plan, cost, level, sbits_scratch(plan, ws)))) return rc;
+        SBITS_HIP(plan->ctx, hipStreamSynchronize(plan->ctx->stream));
+    }
     return sbits_finish_allocate(plan, host_stats, host_trace, trace_cap, sbits_scratch(plan, ws));
 }
 
@@ -551,6 +556,52 @@ struct Coupling {
     int n_groups;
 };
 
+// the stages one after the other, on checked arguments; waits for the stream at the end
+static int run_search(sbits_plan *plan, const sbits_matrix *mats, const sbits_coupling *tables, bool one_pass, double avg_bits,
+                      const sbits_params *params, const sbits_outputs *out, sbits_stats *host_stats, void *ws)
+{
+    int rc;
+    if ((rc = sbits_upload_head(plan, mats, tables, ws, false))) return rc;
+    if (tables)
+        rc = sbits_launch_reorder_coupled_all(plan, *tables, out->row_perm, out->col_perm, ws);
+    else
+        rc = sbits_launch_reorder_all(plan, out->row_perm, out->col_perm, ws);
+    if (rc) return rc;
+    if (one_pass) {
+        if ((rc = sbits_launch_gather_cost_all(plan, out->row_perm, out->col_perm, out->w_re_bf16, nullptr, out->cost, ws)))
+            return rc;
+    } else if (sbits_copies_shapes_ok(plan) && sbits_fused_layout_ok(plan, true)) {
+        if ((rc = sbits_launch_gather_cost_all(plan, out->row_perm, out->col_perm, out->w_re_bf16, out->s_re, out->cost, ws)))
+            return rc;
+    } else {
+        if ((rc = sbits_launch_gather_all(plan, out->row_perm, out->col_perm, out->w_re_bf16, out->s_re, ws)))
+            return rc;
+        if ((rc = sbits_launch_cost_all(plan, out->w_re_bf16, out->s_re, out->cost, ws))) return rc;
+    }
+    // Nothing of what follows waits for the host: the search's result is read at the end (a wait in between left the device idle
+    // for 40 us while the host woke up and enqueued the rest).  Should its workgroups have given up, the kernels behind it do
+    // nothing, and both are repeated.
+    void *const scratch = sbits_scratch(plan, ws);
+    if ((rc = sbits_enqueue_allocate(plan, out->cost, avg_bits, params, out->level, scratch))) return rc;
+    for (int attempt = 0;; ++attempt) {
+        const sbits_alloc_after after = sbits_after_allocate(plan, scratch);
+        const unsigned *aborted = attempt ? nullptr : after.aborted;
+        if ((rc = sbits_launch_offsets(plan->ctx, out->level, plan->N, plan->m, plan->n, plan->bits, plan->K, out->byte_off, after.spare,
+                                       aborted)))
+            return rc;
+        if (one_pass)
+            rc = sbits_launch_gather_pack_all(plan, out->row_perm, out->col_perm, out->level, out->byte_off, out->codes,
+                                              out->scale, out->zero, ws, aborted);
+        else
+            rc = sbits_launch_pack_all(plan, out->w_re_bf16, out->level, out->byte_off, out->codes, out->scale,
+                                       out->zero, ws, aborted);
+        if (rc) return rc;
+        SBITS_HIP(plan->ctx, hipStreamSynchronize(plan->ctx->stream));
+        if (attempt || !sbits_allocation_failed(plan)) return sbits_finish_allocate(plan, host_stats, nullptr, 0, scratch);
+        if ((rc = sbits_repeat_allocate(plan, out->cost, out->level, scratch))) return rc;
+    }
+}
+
 static int search_impl(sbits_plan *plan, const sbits_matrix *mats, const Coupling &cpl, double avg_bits,
                        const sbits_params *params, const sbits_outputs *out, sbits_stats *host_stats, void *ws)
 {
@@ -571,43 +622,13 @@ static int search_impl(sbits_plan *plan, const sbits_matrix *mats, const Couplin
                                     cpl.col_repeat, &tables)))
         return rc;
     if (!params_ok(params, avg_bits)) return SBITS_ERR_INVALID_ARG;
-    if ((rc = sbits_upload_head(plan, mats, cpl.row_group ? &tables : nullptr, ws))) return rc;
-    if (cpl.row_group)
-        rc = sbits_launch_reorder_coupled_all(plan, tables, out->row_perm, out->col_perm, ws);
-    else
-        rc = sbits_launch_reorder_all(plan, out->row_perm, out->col_perm, ws);
-    if (rc) return rc;
     const bool one_pass = sbits_fused_shapes_ok(plan) && sbits_fused_layout_ok(plan, true);
-    if (one_pass) {
-        if ((rc = sbits_launch_gather_cost_all(plan, out->row_perm, out->col_perm, out->w_re_bf16, nullptr, out->cost, ws)))
-            return rc;
-    } else if (!out->s_re || !out->w_re_bf16) {
-        return SBITS_ERR_INVALID_ARG;
-    } else if (sbits_copies_shapes_ok(plan) && sbits_fused_layout_ok(plan, true)) {
-        if ((rc = sbits_launch_gather_cost_all(plan, out->row_perm, out->col_perm, out->w_re_bf16, out->s_re, out->cost, ws)))
-            return rc;
-    } else {
-        if ((rc = sbits_launch_gather_all(plan, out->row_perm, out->col_perm, out->w_re_bf16, out->s_re, ws)))
-            return rc;
-        if ((rc = sbits_launch_cost_all(plan, out->w_re_bf16, out->s_re, out->cost, ws))) return rc;
-    }
-    // Nothing of what follows waits for the host: the levels are valid whatever the search ends with, and its result is read
-    // at the end (a wait in between left the device idle for 40 us while the host woke up and enqueued the rest).
-    void *const scratch = sbits_scratch(plan, ws);
-    if ((rc = sbits_enqueue_allocate(plan, out->cost, avg_bits, params, out->level, scratch))) return rc;
-    if ((rc = sbits_launch_offsets(plan->ctx, out->level, plan->N, plan->m, plan->n, plan->bits, plan->K, out->byte_off, scratch)))
-        return rc;
-    if (one_pass)
-        rc = sbits_launch_gather_pack_all(plan, out->row_perm, out->col_perm, out->level, out->byte_off, out->codes,
-                                          out->scale, out->zero, ws);
-    else
-        rc = sbits_launch_pack_all(plan, out->w_re_bf16, out->level, out->byte_off, out->codes, out->scale,
-                                   out->zero, ws);
-    if (rc) return rc;
-    SBITS_HIP(plan->ctx, hipStreamSynchronize(plan->ctx->stream));
-    return sbits_finish_allocate(plan, host_stats, nullptr, 0, scratch);
+    if (!one_pass && (!out->s_re || !out->w_re_bf16)) return SBITS_ERR_INVALID_ARG;
+    rc = run_search(plan, mats, cpl.row_group ? &tables : nullptr, one_pass, avg_bits, params, out, host_stats, ws);
+    // (what is enqueued may still read the head's image: nothing else guards it)
+    if (rc) (void)hipStreamSynchronize(plan->ctx->stream);
+    return rc;
 }
-
 extern "C" {
 
 int sbits_search(sbits_plan *plan, const sbits_matrix *mats, double avg_bits, const sbits_params *params,

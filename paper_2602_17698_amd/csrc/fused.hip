@@ -107,8 +107,9 @@ void gather_pack_kernel(const MatDesc *__restrict__ descs, const int *__restrict
                         const int32_t *__restrict__ row_perm, const int32_t *__restrict__ col_perm, int m,
                         const uint8_t *__restrict__ level, const int64_t *__restrict__ byte_off,
                         uint8_t *__restrict__ codes, float *__restrict__ scale, float *__restrict__ zero,
-                        GridConsts gc, int cmax, int opu)
+                        GridConsts gc, int cmax, int opu, const unsigned *__restrict__ aborted)
 {
+    const unsigned stop = aborted ? *aborted : 0u;   // the levels are those of a search that gave up: not used
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int rowsrc[FU_OPU * 8];
     constexpr int NIT = RS * CPL;
@@ -193,6 +194,7 @@ void gather_pack_kernel(const MatDesc *__restrict__ descs, const int *__restrict
     const int nsteps = noct * (8 / RS);
 
     prefetch(0);
+    if (stop) return;
     for (int st = 0; st < nsteps; ++st) {
         stage();
         lds_barrier();
@@ -353,6 +355,7 @@ struct FusedPackLaunch {
     int cmax;
     int64_t cols;
     int opu;
+    const unsigned *aborted;
 };
 
 template <int LPG, int CPL, int RS, int TMAX>
@@ -365,7 +368,7 @@ static int launch_gpack_g(sbits_ctx *ctx, const FusedPackLaunch &a)
     const size_t lds = (size_t)RS * a.cols * 2 + (size_t)(CPL * T / LPG) * ((size_t)RS * LPG * a.cmax + 8);
     hipLaunchKernelGGL(fn, dim3((unsigned)a.total_wg), dim3(T), lds, ctx->stream, a.descs, a.members,
                        a.wg_start, a.n_members, a.row_perm, a.col_perm, a.m, a.level, a.byte_off, a.codes, a.scale,
-                       a.zero, a.gc, a.cmax, a.opu);
+                       a.zero, a.gc, a.cmax, a.opu, a.aborted);
     SBITS_HIP(ctx, hipGetLastError());
     return SBITS_OK;
 }
@@ -449,6 +452,7 @@ void sbits_fused_tables(sbits_plan *plan)
         fc.n = 0;
         // octets per workgroup: FU_OPU, halved while the class would not even give every CU a few
         // workgroups (one decoder layer of a streamed model is such a plan)
+        // (the last halving, to one octet, only while there is less than one per CU: 512 x 512 cost 18.7 -> 10.7 us, packing 8.4 -> 5.7)
         int opu = FU_OPU;
         auto class_wgs = [&](int o) {
             int64_t t = 0;
@@ -456,7 +460,7 @@ void sbits_fused_tables(sbits_plan *plan)
                 if (plan->cols[i] == c) t += (plan->rows[i] / 8 + o - 1) / o;
             return t;
         };
-        while (opu > 2 && class_wgs(opu) < 2048) opu >>= 1;
+        while (opu > 1 && class_wgs(opu) < (opu > 2 ? 2048 : 256)) opu >>= 1;
         fc.opu = opu;
         int64_t t = 0;
         for (int i = 0; i < plan->n_mats; ++i) {
@@ -547,7 +551,7 @@ int sbits_launch_gather_cost_all(sbits_plan *plan, const int32_t *row_perm, cons
 // the packing stage on the original weights, one launch per class
 int sbits_launch_gather_pack_all(sbits_plan *plan, const int32_t *row_perm, const int32_t *col_perm,
                                  const uint8_t *level, const int64_t *byte_off, uint8_t *codes, float *scale,
-                                 float *zero, void *ws)
+                                 float *zero, void *ws, const unsigned *aborted)
 {
     sbits_ctx *ctx = plan->ctx;
     if (!sbits_fused_shapes_ok(plan) || !sbits_fused_layout_ok(plan, false)) return SBITS_ERR_BAD_SHAPE;
@@ -563,6 +567,7 @@ int sbits_launch_gather_pack_all(sbits_plan *plan, const int32_t *row_perm, cons
     a.m = plan->m;
     a.level = level; a.byte_off = byte_off; a.codes = codes; a.scale = scale; a.zero = zero;
     a.cmax = plan->bits[plan->K - 1];
+    a.aborted = aborted;
     for (const sbits_plan::FusedClass &fc : plan->fused_classes) {
         a.members = d_mem + fc.first;
         a.wg_start = d_pre + fc.pre_first;

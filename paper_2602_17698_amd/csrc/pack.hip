@@ -25,6 +25,7 @@ constexpr int OF_THREADS = 256;
 constexpr int OF_ITEMS = 8;
 constexpr int OF_TILE = OF_THREADS * OF_ITEMS;
 
+typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 struct BitsTab { int bits[MAX_CAND]; };
 // (a level beyond the table, which no valid input holds, reads its last entry)
 __device__ __forceinline__ int tab_bits(const BitsTab &bt, int lv) { return bt.bits[lv < MAX_CAND ? lv : MAX_CAND - 1]; }
@@ -52,8 +53,9 @@ __device__ __forceinline__ long long block_exclusive_scan(long long v, long long
 
 __global__ __launch_bounds__(OF_THREADS)
 void tile_sum_kernel(const uint8_t *__restrict__ level, long long N, long long Mdiv8, BitsTab bt,
-                     long long *__restrict__ tilesum)
+                     long long *__restrict__ tilesum, const unsigned *aborted)
 {
+    if (aborted && *aborted) return;                 // the levels are those of a search that gave up and is repeated
     const long long i0 = (long long)blockIdx.x * OF_TILE + (long long)threadIdx.x * OF_ITEMS;
     long long s = 0;
     for (int e = 0; e < OF_ITEMS; ++e)
@@ -80,8 +82,10 @@ void scan_tiles_kernel(long long *tilesum, long long ntiles)
 
 __global__ __launch_bounds__(OF_THREADS)
 void tile_scan_kernel(const uint8_t *__restrict__ level, long long N, long long Mdiv8, BitsTab bt,
-                      const long long *__restrict__ tilebase, int64_t *__restrict__ byte_off)
+                      const long long *__restrict__ tilebase, int64_t *__restrict__ byte_off,
+                      const unsigned *aborted)
 {
+    if (aborted && *aborted) return;
     const long long i0 = (long long)blockIdx.x * OF_TILE + (long long)threadIdx.x * OF_ITEMS;
     long long v[OF_ITEMS], s = 0;
     for (int e = 0; e < OF_ITEMS; ++e) {
@@ -93,6 +97,82 @@ void tile_scan_kernel(const uint8_t *__restrict__ level, long long N, long long 
     for (int e = 0; e < OF_ITEMS; ++e) {
         if (i0 + e < N) byte_off[i0 + e] = acc;
         acc += v[e];
+        if (i0 + e == N - 1) byte_off[N] = acc;
+    }
+}
+
+// All in one launch, because a launch costs 4.6 us: a workgroup adds up all levels before its tile by itself, 16 a load, four at a
+// time through a byte permute that looks their bitwidths up.  Three launches take 14 us up to 107 k blocks, this one 4.5
+// for a few, 9 for 52 k.  The line is where the last workgroup reads half a megabyte.
+constexpr int OO_THREADS = 1024, OO_TILE = OO_THREADS * OF_ITEMS;
+constexpr int64_t OO_MAX_BLOCKS = 1 << 19;
+__global__ __launch_bounds__(OO_THREADS)
+void offsets_kernel(const uint8_t *__restrict__ level, int N, long long Mdiv8, BitsTab bt, int64_t *__restrict__ byte_off,
+                    const unsigned *aborted)
+{
+    __shared__ unsigned bits_before;
+    __shared__ int wave_bits[OO_THREADS / 64];
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6, t0 = (int)blockIdx.x * OO_TILE;
+    const unsigned stop = aborted ? *aborted : 0u;   // nonzero: the levels are those of a search that gave up and is repeated
+    if (tid == 0) bits_before = 0u;
+    unsigned lo = 0u, hi = 0u;                       // bitwidths of levels 0 .. 3, 4 .. 7
+#pragma unroll
+    for (int l = 0; l < 4; ++l) { lo |= (unsigned)bt.bits[l] << (8 * l); hi |= (unsigned)bt.bits[l + 4] << (8 * l); }
+    unsigned before = 0u;                            // (at most 2^19 blocks of 8 bits)
+    const int i0 = t0 + tid * OF_ITEMS;
+    u32x2_t own = {0u, 0u};
+    if (i0 + OF_ITEMS <= N) __builtin_memcpy(&own, level + i0, 8);
+    for (int j0 = tid * 16; j0 < t0; j0 += 4 * OO_THREADS * 16) {    // (t0 is a multiple of 16; all loads of a turn before any use)
+        u32x4_t v[4];
+        unsigned any = 0u;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int j = j0 + b * OO_THREADS * 16;
+            v[b] = u32x4_t{0u, 0u, 0u, 0u};
+            if (j < t0) __builtin_memcpy(&v[b], level + j, 16);
+        }
+#pragma unroll
+        for (int b = 0; b < 4; ++b) any |= v[b].x | v[b].y | v[b].z | v[b].w;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            if (j0 + b * OO_THREADS * 16 >= t0) continue;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                if ((any & 0xf8f8f8f8u) == 0u) {
+                    before = __builtin_amdgcn_sad_u8(__builtin_amdgcn_perm(hi, lo, v[b][w]), 0u, before);
+                } else {
+                    for (int e = 0; e < 4; ++e) before += (unsigned)tab_bits(bt, (int)(v[b][w] >> (8 * e) & 255u));
+                }
+            }
+        }
+    }
+    int v[OF_ITEMS], s = 0;
+#pragma unroll
+    for (int e = 0; e < OF_ITEMS; ++e) {
+        int lv = (int)((e < 4 ? own.x : own.y) >> (8 * (e & 3)) & 255u);
+        if (i0 + OF_ITEMS > N && i0 + e < N) lv = level[i0 + e];     // (the last blocks)
+        v[e] = i0 + e < N ? tab_bits(bt, lv) : 0;
+        s += v[e];
+    }
+    int inc = s;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int t = __shfl_up(inc, off);
+        if (lane >= off) inc += t;
+    }
+    if (lane == 63) wave_bits[wave] = inc;
+    for (int off = 32; off; off >>= 1) before += __shfl_xor(before, off);
+    __syncthreads();
+    if (stop) return;
+    if (lane == 0 && before) atomicAdd(&bits_before, before);
+    __syncthreads();
+    int base = inc - s;
+#pragma unroll
+    for (int w = 0; w < OO_THREADS / 64; ++w) base += w < wave ? wave_bits[w] : 0;
+    long long acc = Mdiv8 * ((long long)bits_before + base);
+#pragma unroll
+    for (int e = 0; e < OF_ITEMS; ++e) {
+        if (i0 + e < N) byte_off[i0 + e] = acc;
+        acc += Mdiv8 * v[e];
         if (i0 + e == N - 1) byte_off[N] = acc;
     }
 }
@@ -119,8 +199,9 @@ __global__ __launch_bounds__(PK_THREADS)
 void pack_kernel(const MatDesc *__restrict__ descs, MatDesc one, const int *__restrict__ wg_start, int n_mats,
                  const uint16_t *__restrict__ W, int m, const uint8_t *__restrict__ level,
                  const int64_t *__restrict__ byte_off, uint8_t *__restrict__ codes, float *__restrict__ scale,
-                 float *__restrict__ zero, GridConsts gc)
+                 float *__restrict__ zero, GridConsts gc, const unsigned *aborted)
 {
+    if (aborted && *aborted) return;                 // the levels are those of a search that gave up and is repeated
     using G = PackGeom<LPG>;
     constexpr int BX = G::BX, OS = G::OS, NG = PK_THREADS / LPG;
     __shared__ __align__(16) uint8_t stage[NG][8 * LPG * 8];     // per group: 8 rows x LPG*c bytes (c <= 8)
@@ -194,6 +275,7 @@ struct PackLaunch {
     uint8_t *codes;
     float *scale, *zero;
     GridConsts gc;
+    const unsigned *aborted;
 };
 
 template <int LPG>
@@ -203,7 +285,7 @@ static int launch_pack_l(sbits_ctx *ctx, const PackLaunch &a)
     if (a.total_wg == 0) return SBITS_OK;
     hipLaunchKernelGGL((pack_kernel<LPG>), dim3((unsigned)a.total_wg), dim3(PK_THREADS), 0, ctx->stream,
                        a.descs, a.one, a.wg_start, a.n_mats, a.W, a.m, a.level, a.byte_off, a.codes, a.scale,
-                       a.zero, a.gc);
+                       a.zero, a.gc, a.aborted);
     SBITS_HIP(ctx, hipGetLastError());
     return SBITS_OK;
 }
@@ -288,18 +370,24 @@ int sbits_launch_offsets_static(sbits_ctx *ctx, const uint8_t *level, int64_t N,
 }
 
 int sbits_launch_offsets(sbits_ctx *ctx, const uint8_t *level, int64_t N, int m, int n,
-                         const int32_t *bits, int K, int64_t *byte_off, void *ws)
+                         const int32_t *bits, int K, int64_t *byte_off, void *ws, const unsigned *aborted)
 {
     BitsTab bt;
     for (int c = 0; c < sbits::MAX_CAND; ++c) bt.bits[c] = c < K ? bits[c] : bits[K - 1];
     const long long Mdiv8 = (long long)m * n / 8;
+    if (N <= OO_MAX_BLOCKS) {
+        hipLaunchKernelGGL(offsets_kernel, dim3((unsigned)((N + OO_TILE - 1) / OO_TILE)), dim3(OO_THREADS), 0, ctx->stream, level, (int)N,
+                           Mdiv8, bt, byte_off, aborted);
+        SBITS_HIP(ctx, hipGetLastError());
+        return SBITS_OK;
+    }
     const int64_t ntiles = (N + OF_TILE - 1) / OF_TILE;
     long long *tiles = static_cast<long long *>(ws);
     hipLaunchKernelGGL(tile_sum_kernel, dim3((unsigned)ntiles), dim3(OF_THREADS), 0, ctx->stream,
-                       level, (long long)N, Mdiv8, bt, tiles);
+                       level, (long long)N, Mdiv8, bt, tiles, aborted);
     hipLaunchKernelGGL(scan_tiles_kernel, dim3(1), dim3(OF_THREADS), 0, ctx->stream, tiles, (long long)ntiles);
     hipLaunchKernelGGL(tile_scan_kernel, dim3((unsigned)ntiles), dim3(OF_THREADS), 0, ctx->stream,
-                       level, (long long)N, Mdiv8, bt, tiles, byte_off);
+                       level, (long long)N, Mdiv8, bt, tiles, byte_off, aborted);
     SBITS_HIP(ctx, hipGetLastError());
     return SBITS_OK;
 }
@@ -335,11 +423,12 @@ void sbits_pack_tables(sbits_plan *plan)
 
 // all matrices of the plan in one launch; the descriptor table is already in the workspace head
 int sbits_launch_pack_all(sbits_plan *plan, const void *w_re, const uint8_t *level, const int64_t *byte_off,
-                          uint8_t *codes, float *scale, float *zero, void *ws)
+                          uint8_t *codes, float *scale, float *zero, void *ws, const unsigned *aborted)
 {
     sbits_ctx *ctx = plan->ctx;
     PackLaunch a;
     memset(&a, 0, sizeof a);
+    a.aborted = aborted;
     sbits_fill_grid_consts(plan->bits, plan->K, &a.gc);
     if (plan->pack_wg_start.empty()) return SBITS_ERR_BAD_SHAPE;
     a.descs = sbits_desc_ptr(ws);

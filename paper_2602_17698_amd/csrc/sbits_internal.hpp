@@ -100,14 +100,14 @@ int sbits_launch_reorder_coupled_all(sbits_plan *plan, const sbits_coupling &cpl
 int sbits_launch_gather_all(sbits_plan *plan, const int32_t *row_perm, const int32_t *col_perm,
                             void *w_re, float *s_re, void *ws);
 int sbits_launch_pack_all(sbits_plan *plan, const void *w_re, const uint8_t *level, const int64_t *byte_off,
-                          uint8_t *codes, float *scale, float *zero, void *ws);
+                          uint8_t *codes, float *scale, float *zero, void *ws, const unsigned *aborted = nullptr);
 int sbits_launch_gather(sbits_ctx *ctx, const void *W, const float *S, int64_t R, int64_t C,
                         int64_t ld_w, int64_t ld_s, const int32_t *rp, const int32_t *cp,
                         void *w_out, float *s_out);
 int sbits_launch_cost(sbits_ctx *ctx, const void *Wp, const float *Sp, int64_t R, int64_t C,
                       int m, int n, const int32_t *bits, int K, float *cost_rows);
 // batched over all matrices of the plan (workspace head already there)
-int sbits_upload_head(sbits_plan *plan, const sbits_matrix *mats, const sbits_coupling *cpl, void *ws);
+int sbits_upload_head(sbits_plan *plan, const sbits_matrix *mats, const sbits_coupling *cpl, void *ws, bool guard = true);
 // the tables of the head that follow from the plan's shapes (each left empty if it would not fit 32 bits)
 void sbits_cost_tables(sbits_plan *plan);
 void sbits_pack_tables(sbits_plan *plan);
@@ -126,7 +126,7 @@ int sbits_launch_surrogates_all(sbits_plan *plan, const int32_t *row_perm, const
                                 const uint8_t *level, float *s_up, float *s_down, void *ws);
 int sbits_launch_gather_pack_all(sbits_plan *plan, const int32_t *row_perm, const int32_t *col_perm,
                                  const uint8_t *level, const int64_t *byte_off, uint8_t *codes, float *scale,
-                                 float *zero, void *ws);
+                                 float *zero, void *ws, const unsigned *aborted = nullptr);
 // dequant.hip
 int sbits_launch_dequant(sbits_plan *plan, int mat, const uint8_t *level, const int64_t *byte_off,
                          const uint8_t *codes, const float *scale, const float *zero, void *out, int64_t ld_out,
@@ -141,11 +141,17 @@ int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t 
 int sbits_run_propose(sbits_plan *plan, const float *s_up, const float *s_down, const uint8_t *level_in,
                       double avg_bits, int64_t k, uint8_t *level_out, sbits_proposal *host_out, void *ws);
 // allocation: everything enqueued, without a wait; then, after the caller has waited for the stream, its result.  In between
-// the scratch may be used again (a trace is lost then), the context's page-locked buffer may not.
+// neither the scratch nor the context's page-locked buffer may be used for anything else.
 int sbits_enqueue_allocate(sbits_plan *plan, const float *cost, double avg_bits, const sbits_params *prm, uint8_t *level, void *ws);
+// if a workgroup gave up, which the host finds after its wait: once more, by one workgroup, on the same scratch
+bool sbits_allocation_failed(const sbits_plan *plan);
+int sbits_repeat_allocate(sbits_plan *plan, const float *cost, uint8_t *level, void *ws);
+// for kernels behind it: a word on the device that is not 0 if it was given up (they do nothing then); scratch that it needs no more
+struct sbits_alloc_after { const unsigned *aborted; void *spare; };
+sbits_alloc_after sbits_after_allocate(const sbits_plan *plan, void *ws);
 int sbits_finish_allocate(sbits_plan *plan, sbits_stats *host_stats, sbits_trace *host_trace, int64_t trace_cap, void *ws);
 int sbits_launch_offsets(sbits_ctx *ctx, const uint8_t *level, int64_t N, int m, int n,
-                         const int32_t *bits, int K, int64_t *byte_off, void *ws);
+                         const int32_t *bits, int K, int64_t *byte_off, void *ws, const unsigned *aborted = nullptr);
 int sbits_offsets_static_setup(sbits_ctx *ctx);
 int sbits_launch_offsets_static(sbits_ctx *ctx, const uint8_t *level, int64_t N, int m, int n,
                                 const int32_t *bits, int K, int64_t *byte_off);
