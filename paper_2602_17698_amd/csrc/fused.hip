@@ -100,7 +100,10 @@ void octet_finish_kernel(const float *__restrict__ part, const MatDesc *__restri
 // (written and read by lanes of one wave only) and leave as 32-bit words.
 // T threads per workgroup; launch bounds ask for 4 waves per SIMD (two workgroups of 512 or one
 // of 1024 per CU), which the kernel's ~120 registers allow.
-template <int LPG, int CPL, int RS, int TMAX>
+// PARTS = 2 (rows of more than 16384 elements): two workgroups stage the same rows and pack half of the columns each, two chunks
+// per lane as for shorter rows; they are eight apart in the grid, so that they share an L2.  (All columns in one workgroup are
+// four chunks a lane, one row a step, 33 registers spilled: 8192 x 28672 in 382 us, 202 this way.)
+template <int LPG, int CPL, int RS, int TMAX, int PARTS = 1>
 __global__ __launch_bounds__(TMAX, 4)
 void gather_pack_kernel(const MatDesc *__restrict__ descs, const int *__restrict__ members,
                         const int *__restrict__ wg_start, int n_members,
@@ -118,12 +121,14 @@ void gather_pack_kernel(const MatDesc *__restrict__ descs, const int *__restrict
     const int tid = (int)threadIdx.x;
     const int T = (int)blockDim.x;                   // a multiple of 64, at most TMAX
     const int lig = tid % LPG;
-    const int mem = funi(find_matrix(wg_start, n_members, (int)blockIdx.x));
+    const int unit = PARTS == 1 ? (int)blockIdx.x : (int)(blockIdx.x >> 4 << 3 | (blockIdx.x & 7));
+    if (PARTS > 1 && unit >= wg_start[n_members]) return;
+    const int mem = funi(find_matrix(wg_start, n_members, unit));
     const MatDesc &d = descs[funi(members[mem])];
     const int R = funi((int)d.rows), C = funi((int)d.cols) & ~7;
     const int nbc = funi(d.nbc);
     const int opb = m >> 3;
-    const int oct0 = ((int)blockIdx.x - funi(wg_start[mem])) * opu;
+    const int oct0 = (unit - funi(wg_start[mem])) * opu;
     const int noct = min(opu, (R >> 3) - oct0);
     const int32_t *__restrict__ rp = row_perm + d.row_off;
     const int32_t *__restrict__ cp = col_perm + d.col_off;
@@ -146,11 +151,12 @@ void gather_pack_kernel(const MatDesc *__restrict__ descs, const int *__restrict
         rowsrc[i] = sr < 0 ? 0 : (sr >= R ? R - 1 : sr);
     }
     const int nchunk = C >> 3;
+    const int chunk0 = PARTS == 1 ? 0 : (int)(blockIdx.x >> 3 & 1) * CPL * T;    // this workgroup's chunks: CPL * T from here (whole groups)
     int ci[CPL][8];
     bool valid[CPL];
 #pragma unroll
     for (int c = 0; c < CPL; ++c) {
-        const int chunk = tid + T * c;
+        const int chunk = chunk0 + tid + T * c;
         valid[c] = chunk < nchunk;
         const int cb = valid[c] ? chunk * 8 : 0;
         const int4 a = *reinterpret_cast<const int4 *>(cp + cb);
@@ -161,19 +167,20 @@ void gather_pack_kernel(const MatDesc *__restrict__ descs, const int *__restrict
     }
     __syncthreads();
 
-    uint32_t offw[CPL];
+    constexpr int STG = CPL * PARTS;                 // chunks that a lane stages of a row
+    uint32_t offw[STG];
 #pragma unroll
-    for (int c = 0; c < CPL; ++c) offw[c] = (uint32_t)min(tid + T * c, nchunk - 1) * 16u;
-    uint4 pw[RS][CPL];
+    for (int c = 0; c < STG; ++c) offw[c] = (uint32_t)min(tid + T * c, nchunk - 1) * 16u;
+    uint4 pw[RS][STG];
     auto prefetch = [&](int row) {
 #pragma unroll
         for (int rs = 0; rs < RS; ++rs) {
             const int sr = funi(rowsrc[row + rs]);
             const char *wrow = Wg + (int64_t)sr * pitch_w;
 #pragma unroll
-            for (int c = 0; c < CPL; ++c) {
-                const u32x4_t v = __builtin_nontemporal_load(
-                    (const __attribute__((address_space(1))) u32x4_t *)(wrow + offw[c]));
+            for (int c = 0; c < STG; ++c) {
+                const __attribute__((address_space(1))) u32x4_t *p = (const __attribute__((address_space(1))) u32x4_t *)(wrow + offw[c]);
+                const u32x4_t v = PARTS == 1 ? __builtin_nontemporal_load(p) : *p;           // (the other workgroup reads it too)
                 pw[rs][c] = make_uint4(v.x, v.y, v.z, v.w);
             }
         }
@@ -182,7 +189,7 @@ void gather_pack_kernel(const MatDesc *__restrict__ descs, const int *__restrict
 #pragma unroll
         for (int rs = 0; rs < RS; ++rs)
 #pragma unroll
-            for (int c = 0; c < CPL; ++c)
+            for (int c = 0; c < STG; ++c)
                 *reinterpret_cast<uint4 *>(smem + (size_t)rs * C * 2 + offw[c]) = pw[rs][c];
     };
 
@@ -208,7 +215,7 @@ void gather_pack_kernel(const MatDesc *__restrict__ descs, const int *__restrict
             curI = I;
 #pragma unroll
             for (int c = 0; c < CPL; ++c) {
-                const int J = min((tid + T * c) / LPG, nbc - 1);
+                const int J = min((chunk0 + tid + T * c) / LPG, nbc - 1);
                 gb[c] = block_base + (int64_t)I * nbc + J;
                 lk[c] = level_consts(gc, level[gb[c]]);
                 dst[c] = codes + byte_off[gb[c]];
@@ -358,15 +365,18 @@ struct FusedPackLaunch {
     const unsigned *aborted;
 };
 
-template <int LPG, int CPL, int RS, int TMAX>
+template <int LPG, int CPL, int RS, int TMAX, int PARTS = 1>
 static int launch_gpack_g(sbits_ctx *ctx, const FusedPackLaunch &a)
 {
-    const int T = fused_threads(a.cols, CPL, TMAX);
-    auto *fn = &gather_pack_kernel<LPG, CPL, RS, TMAX>;
+    const int T = fused_threads(a.cols, CPL * PARTS, TMAX);
+    auto *fn = &gather_pack_kernel<LPG, CPL, RS, TMAX, PARTS>;
     SBITS_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, 159 * 1024));
     const size_t lds = (size_t)RS * a.cols * 2 + (size_t)(CPL * T / LPG) * ((size_t)RS * LPG * a.cmax + 8);
-    hipLaunchKernelGGL(fn, dim3((unsigned)a.total_wg), dim3(T), lds, ctx->stream, a.descs, a.members,
+    if constexpr (PARTS > 1 && RS > 1)
+        if (lds > 159 * 1024) return launch_gpack_g<LPG, CPL, 1, TMAX, PARTS>(ctx, a);     // (more than 30000 columns at 8 bits)
+    const unsigned grid = PARTS == 1 ? (unsigned)a.total_wg : ((unsigned)a.total_wg + 7u) / 8u * 16u;
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(T), lds, ctx->stream, a.descs, a.members,
                        a.wg_start, a.n_members, a.row_perm, a.col_perm, a.m, a.level, a.byte_off, a.codes, a.scale,
                        a.zero, a.gc, a.cmax, a.opu, a.aborted);
     SBITS_HIP(ctx, hipGetLastError());
@@ -380,7 +390,7 @@ static int launch_gpack_l(sbits_ctx *ctx, const FusedPackLaunch &a)
     if (chunks <= 512) return launch_gpack_g<LPG, 1, 4, 512>(ctx, a);
     if (chunks <= 1024) return launch_gpack_g<LPG, 2, 2, 512>(ctx, a);
     if (chunks <= 2048) return launch_gpack_g<LPG, 2, 2, 1024>(ctx, a);
-    if (chunks <= 4096) return launch_gpack_g<LPG, 4, 1, 1024>(ctx, a);
+    if (chunks <= 4096) return launch_gpack_g<LPG, 2, 2, 1024, 2>(ctx, a);
     return SBITS_ERR_BAD_SHAPE;
 }
 
