@@ -95,22 +95,22 @@ void octet_finish_kernel(const float *__restrict__ part, const MatDesc *__restri
 // ================================================================ gather + pack
 // The packing stage on the ORIGINAL weights: a workgroup owns a run of octets of one matrix,
 // stages RS source rows per step in LDS like the kernel above (weights only), and every lane
-// re-quantizes its chunks at the bitwidth chosen for their block.  The codes of a lane group's
-// RS rows are consecutive in the block's stream: they are collected in a per-group LDS strip
-// (written and read by lanes of one wave only) and leave as 32-bit words.
+// re-quantizes its chunks at the bitwidth chosen for their block.  The codes of four rows of a lane
+// group, from one step or from two, are consecutive in the block's stream and leave as whole words
+// (store_codes4).  WIDE: a candidate has more than 4 bits.
 // T threads per workgroup; launch bounds ask for 4 waves per SIMD (two workgroups of 512 or one
 // of 1024 per CU), which the kernel's ~120 registers allow.
 // PARTS = 2 (rows of more than 16384 elements): two workgroups stage the same rows and pack half of the columns each, two chunks
 // per lane as for shorter rows; they are eight apart in the grid, so that they share an L2.  (All columns in one workgroup are
 // four chunks a lane, one row a step, 33 registers spilled: 8192 x 28672 in 382 us, 202 this way.)
-template <int LPG, int CPL, int RS, int TMAX, int PARTS = 1>
+template <int LPG, int CPL, int RS, int TMAX, bool WIDE, int PARTS = 1>
 __global__ __launch_bounds__(TMAX, 4)
 void gather_pack_kernel(const MatDesc *__restrict__ descs, const int *__restrict__ members,
                         const int *__restrict__ wg_start, int n_members,
                         const int32_t *__restrict__ row_perm, const int32_t *__restrict__ col_perm, int m,
                         const uint8_t *__restrict__ level, const int64_t *__restrict__ byte_off,
                         uint8_t *__restrict__ codes, float *__restrict__ scale, float *__restrict__ zero,
-                        GridConsts gc, int cmax, int opu, const unsigned *__restrict__ aborted)
+                        GridConsts gc, int opu, const unsigned *__restrict__ aborted)
 {
     const unsigned stop = aborted ? *aborted : 0u;   // the levels are those of a search that gave up: not used
     extern __shared__ __align__(16) unsigned char smem[];
@@ -136,16 +136,7 @@ void gather_pack_kernel(const MatDesc *__restrict__ descs, const int *__restrict
     const int64_t pitch_w = d.ld_w * 2;
     const int64_t block_base = d.block_base;
 
-    // LDS: weights [RS][C] bf16, then one strip of RS * LPG * cmax bytes per (lane group, chunk)
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
-    // (+8: a lane's third word may lie past its row; it is zero there, but has to be addressable)
-    const int strip = RS * LPG * cmax + 8;
-    const uint32_t strips = lds0 + (uint32_t)RS * (uint32_t)C * 2u;
-    for (int c = 0; c < CPL; ++c) {                  // every group zeroes its own strips
-        const uint32_t s0 = strips + (uint32_t)((tid / LPG) + (T / LPG) * c) * (uint32_t)strip;
-        for (int k = lig; k < strip / 4; k += LPG) *(lds_u32 *)(s0 + 4u * (uint32_t)k) = 0u;
-    }
-
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;    // weights [RS][C] bf16
     for (int i = tid; i < noct * 8; i += T) {
         int sr = rp[oct0 * 8 + i];
         rowsrc[i] = sr < 0 ? 0 : (sr >= R ? R - 1 : sr);
@@ -200,6 +191,7 @@ void gather_pack_kernel(const MatDesc *__restrict__ descs, const int *__restrict
     uint8_t *dst[CPL];
     const int nsteps = noct * (8 / RS);
 
+    uint32_t held_lo[RS == 4 ? 1 : CPL][4], held_hi[RS == 4 ? 1 : CPL][4];     // rows that wait for the rest of their four
     prefetch(0);
     if (stop) return;
     for (int st = 0; st < nsteps; ++st) {
@@ -238,17 +230,24 @@ void gather_pack_kernel(const MatDesc *__restrict__ descs, const int *__restrict
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
             const int cb = lk[c].c;
-            const int row_bytes = LPG * cb;
-            const uint32_t strip0 = strips + (uint32_t)((tid / LPG) + (T / LPG) * c) * (uint32_t)strip;
             uint4 raw[RS];
 #pragma unroll
             for (int rs = 0; rs < RS; ++rs) raw[rs] = gw[rs * CPL + c];
-            unsigned long long word[RS];
+            uint32_t half[RS][2];
             float scl[RS], mn[RS];
-            quant_pack_rows<LPG, RS>(raw, lk[c], lig, word, scl, mn);
+            quant_pack_rows<LPG, RS>(raw, lk[c], lig, half, scl, mn);
+            uint32_t lo[RS], hi[RS];
 #pragma unroll
-            for (int rs = 0; rs < RS; ++rs)
-                or_code_bytes(strip0 + (uint32_t)(rs * row_bytes), lig * cb, word[rs], cmax > 4);
+            for (int rs = 0; rs < RS; ++rs) {
+                if constexpr (WIDE) {
+                    const uint64_t w = (uint64_t)half[rs][1] << (4 * cb) | half[rs][0];
+                    lo[rs] = (uint32_t)w;
+                    hi[rs] = (uint32_t)(w >> 32);
+                } else {
+                    lo[rs] = half[rs][1] << (4 * cb) | half[rs][0];
+                    hi[rs] = 0u;
+                }
+            }
             if (valid[c] && lig == 0) {
                 // RS consecutive rows of one block: one vector store each (rib is a multiple of RS)
                 const int64_t ri = gb[c] * m + rib;
@@ -266,23 +265,18 @@ void gather_pack_kernel(const MatDesc *__restrict__ descs, const int *__restrict
                     for (int rs = 0; rs < RS; ++rs) { scale[ri + rs] = scl[rs]; zero[ri + rs] = zr[rs]; }
                 }
             }
-            // the strip is private to this lane group (one wave): LDS keeps a wave's operations in order
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            if (valid[c]) {
-                const int nwords = RS * row_bytes / 4;           // row_bytes is a multiple of 8
-                uint32_t *d32 = reinterpret_cast<uint32_t *>(dst[c] + (int64_t)rib * row_bytes);
-                for (int k = lig; k < nwords; k += LPG) {
-                    lds_u32 *sp = (lds_u32 *)(strip0 + 4u * (uint32_t)k);
-                    d32[k] = *sp;
-                    *sp = 0u;                                    // zero again for the next step's ORs
-                }
+            // the rows of this step, behind those of the steps before it in the same group of four
+            uint8_t *const out = dst[c] + (int64_t)(rib & ~3) * (LPG * cb);
+            if constexpr (RS == 4) {
+                if (valid[c]) store_codes4<LPG, WIDE>(out, cb, lo, hi, lig);
             } else {
-                for (int k = lig; k < RS * row_bytes / 4; k += LPG) *(lds_u32 *)(strip0 + 4u * (uint32_t)k) = 0u;
+#pragma unroll
+                for (int rs = 0; rs < RS; ++rs)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if (q % RS == rs && (rib & 3) == q - rs) { held_lo[c][q] = lo[rs]; held_hi[c][q] = hi[rs]; }
+                if ((rib & 3) == 4 - RS && valid[c]) store_codes4<LPG, WIDE>(out, cb, held_lo[c], held_hi[c], lig);
             }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
         }
     }
 }
@@ -359,7 +353,7 @@ struct FusedPackLaunch {
     uint8_t *codes;
     float *scale, *zero;
     GridConsts gc;
-    int cmax;
+    bool wide;                // a candidate has more than 4 bits
     int64_t cols;
     int opu;
     const unsigned *aborted;
@@ -369,16 +363,14 @@ template <int LPG, int CPL, int RS, int TMAX, int PARTS = 1>
 static int launch_gpack_g(sbits_ctx *ctx, const FusedPackLaunch &a)
 {
     const int T = fused_threads(a.cols, CPL * PARTS, TMAX);
-    auto *fn = &gather_pack_kernel<LPG, CPL, RS, TMAX, PARTS>;
+    auto *fn = a.wide ? &gather_pack_kernel<LPG, CPL, RS, TMAX, true, PARTS> : &gather_pack_kernel<LPG, CPL, RS, TMAX, false, PARTS>;
     SBITS_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, 159 * 1024));
-    const size_t lds = (size_t)RS * a.cols * 2 + (size_t)(CPL * T / LPG) * ((size_t)RS * LPG * a.cmax + 8);
-    if constexpr (PARTS > 1 && RS > 1)
-        if (lds > 159 * 1024) return launch_gpack_g<LPG, CPL, 1, TMAX, PARTS>(ctx, a);     // (more than 30000 columns at 8 bits)
+    const size_t lds = (size_t)RS * a.cols * 2;
     const unsigned grid = PARTS == 1 ? (unsigned)a.total_wg : ((unsigned)a.total_wg + 7u) / 8u * 16u;
     hipLaunchKernelGGL(fn, dim3(grid), dim3(T), lds, ctx->stream, a.descs, a.members,
                        a.wg_start, a.n_members, a.row_perm, a.col_perm, a.m, a.level, a.byte_off, a.codes, a.scale,
-                       a.zero, a.gc, a.cmax, a.opu, a.aborted);
+                       a.zero, a.gc, a.opu, a.aborted);
     SBITS_HIP(ctx, hipGetLastError());
     return SBITS_OK;
 }
@@ -576,7 +568,7 @@ int sbits_launch_gather_pack_all(sbits_plan *plan, const int32_t *row_perm, cons
     a.col_perm = col_perm;
     a.m = plan->m;
     a.level = level; a.byte_off = byte_off; a.codes = codes; a.scale = scale; a.zero = zero;
-    a.cmax = plan->bits[plan->K - 1];
+    a.wide = plan->bits[plan->K - 1] > 4;
     a.aborted = aborted;
     for (const sbits_plan::FusedClass &fc : plan->fused_classes) {
         a.members = d_mem + fc.first;

@@ -79,10 +79,10 @@ __device__ __forceinline__ unsigned long long quant_pack_row(const uint4 &raw, c
 // RS rows of one lane group at once (raw[rs] = the lane's 8 weights of row rs), LPG >= 2 * RS: the
 // 2 * RS grid quotients are spread over the lanes of the group (lane 2*rs: qmax / R of row rs,
 // lane 2*rs + 1: R / qmax), so the rows share ONE division sequence instead of paying one each.
-// Same results as quant_pack_row row by row.
+// Same results as quant_pack_row row by row, the codes in two halves: code 4 h + e in bits [e*c, (e+1)*c) of half[.][h].
 template <int LPG, int RS>
 __device__ __forceinline__ void quant_pack_rows(const uint4 (&raw)[RS], const LevelConsts &k, int lig,
-                                                unsigned long long (&word)[RS], float (&scl)[RS], float (&mn)[RS])
+                                                uint32_t (&half)[RS][2], float (&scl)[RS], float (&mn)[RS])
 {
     static_assert(LPG >= 2 * RS, "one lane per quotient");
     float w[RS][8], R[RS];
@@ -110,7 +110,6 @@ __device__ __forceinline__ void quant_pack_rows(const uint4 (&raw)[RS], const Le
         constexpr int rs = decltype(irs)::value;
         const float inv = group_bcast<LPG, 2 * rs>(v);
         scl[rs] = group_bcast<LPG, 2 * rs + 1>(v);
-        uint32_t half[2];
 #pragma unroll
         for (int hq = 0; hq < 2; ++hq) {
             uint32_t acc = 0;
@@ -120,26 +119,70 @@ __device__ __forceinline__ void quant_pack_rows(const uint4 (&raw)[RS], const Le
                 const uint32_t q = __float_as_uint(y + 12582912.0f) & k.qmax;   // see quant_pack_row
                 acc |= q << (e * k.c);
             }
-            half[hq] = acc;
+            half[rs][hq] = acc;
         }
-        word[rs] = (unsigned long long)half[0] | ((unsigned long long)half[1] << (4 * k.c));
     });
 }
 
-// ORs the lane's c bytes (c <= 8, held in `word`) into a zeroed LDS strip at byte offset `off` of
-// the row that starts at LDS address `row` (4-byte aligned): at most three 32-bit words, the third
-// only when c > 4 (`wide`).  No byte-wise stores, no branches.
-typedef __attribute__((address_space(3))) uint32_t lds_u32;
-__device__ __forceinline__ void or_code_bytes(uint32_t row, int off, unsigned long long word, bool wide)
+// Transposes a 4 x 4 matrix over the lanes of a quad: on return a[i] is what lane i of the quad held in a[own lane].
+__device__ __forceinline__ void quad_transpose(uint32_t (&a)[4], int lane)
 {
-    const int sh = (off & 3) * 8;
-    const uint32_t a = row + (uint32_t)(off & ~3);
-    const unsigned long long t = word << sh;
-    __hip_atomic_fetch_or((lds_u32 *)a, (uint32_t)t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    __hip_atomic_fetch_or((lds_u32 *)(a + 4u), (uint32_t)(t >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    if (wide) {
-        const uint32_t top = sh ? (uint32_t)(word >> (64 - sh)) : 0u;
-        __hip_atomic_fetch_or((lds_u32 *)(a + 8u), top, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    auto swap = [&](uint32_t &lo, uint32_t &hi, bool odd, auto ctrl) {
+        const uint32_t got = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(odd ? lo : hi), decltype(ctrl)::value, 0xf, 0xf, true);
+        lo = odd ? got : lo;
+        hi = odd ? hi : got;
+    };
+    const bool b0 = (lane & 1) != 0, b1 = (lane & 2) != 0;
+    swap(a[0], a[1], b0, std::integral_constant<int, DPP_XOR1>{});
+    swap(a[2], a[3], b0, std::integral_constant<int, DPP_XOR1>{});
+    swap(a[0], a[2], b1, std::integral_constant<int, DPP_XOR2>{});
+    swap(a[1], a[3], b1, std::integral_constant<int, DPP_XOR2>{});
+}
+
+// Codes of four consecutive rows of a block (lo / hi: the low and high words of the 8 c bits that this lane has of each row) to
+// the stream.  Four lanes have 32 codes of a row, which are c whole words: after a transposition lane j of a quad has
+// those of row j, puts them together and stores them at once; the rows' bytes are consecutive, so a lane group's stores cover one
+// run.  dst: the first row's bytes.  WIDE: c may be more than 4 (else hi is not used).
+// (Collecting a group's bytes in LDS took two or three atomic ORs a lane and row, which with the column gather filled the LDS
+// pipe: 2.7 ms for the 4096-column rows of the 8B-shaped model, PACK4096 this way.)
+template <int LPG, bool WIDE>
+__device__ __forceinline__ void store_codes4(uint8_t *dst, int c, uint32_t (&lo)[4], uint32_t (&hi)[4], int lig)
+{
+    quad_transpose(lo, lig);
+    if constexpr (WIDE) quad_transpose(hi, lig);
+    typedef __attribute__((address_space(1))) uint32_t *gp;
+    typedef unsigned int u2_t __attribute__((ext_vector_type(2), aligned(4)));
+    typedef unsigned int u3_t __attribute__((ext_vector_type(3), aligned(4)));
+    typedef unsigned int u4_t __attribute__((ext_vector_type(4), aligned(4)));
+    const gp p = (gp)(dst + (lig & 3) * (LPG * c) + (lig >> 2) * 4 * c);
+    auto put2 = [&](int at, uint32_t a, uint32_t b) { *(__attribute__((address_space(1))) u2_t *)(p + at) = u2_t{a, b}; };
+    auto put3 = [&](int at, uint32_t a, uint32_t b, uint32_t d) { *(__attribute__((address_space(1))) u3_t *)(p + at) = u3_t{a, b, d}; };
+    auto put4 = [&](int at, uint32_t a, uint32_t b, uint32_t d, uint32_t e) { *(__attribute__((address_space(1))) u4_t *)(p + at) = u4_t{a, b, d, e}; };
+    switch (c) {                                     // (a wave has up to eight blocks, of different bitwidths)
+    case 0: break;
+    case 1: p[0] = lo[0] | lo[1] << 8 | lo[2] << 16 | lo[3] << 24; break;
+    case 2: put2(0, lo[0] | lo[1] << 16, lo[2] | lo[3] << 16); break;
+    case 3: put3(0, lo[0] | lo[1] << 24, lo[1] >> 8 | lo[2] << 16, lo[2] >> 16 | lo[3] << 8); break;
+    case 4: put4(0, lo[0], lo[1], lo[2], lo[3]); break;
+    default:
+        if constexpr (WIDE) switch (c) {
+        case 5:
+            put4(0, lo[0], hi[0] | lo[1] << 8, lo[1] >> 24 | hi[1] << 8 | lo[2] << 16, lo[2] >> 16 | hi[2] << 16 | lo[3] << 24);
+            p[4] = lo[3] >> 8 | hi[3] << 24;
+            break;
+        case 6:
+            put4(0, lo[0], hi[0] | lo[1] << 16, lo[1] >> 16 | hi[1] << 16, lo[2]);
+            put2(4, hi[2] | lo[3] << 16, lo[3] >> 16 | hi[3] << 16);
+            break;
+        case 7:
+            put4(0, lo[0], hi[0] | lo[1] << 24, lo[1] >> 8 | hi[1] << 24, hi[1] >> 8 | lo[2] << 16);
+            put3(4, lo[2] >> 16 | hi[2] << 16, hi[2] >> 16 | lo[3] << 8, lo[3] >> 24 | hi[3] << 8);
+            break;
+        default:
+            put4(0, lo[0], hi[0], lo[1], hi[1]);
+            put4(4, lo[2], hi[2], lo[3], hi[3]);
+            break;
+        }
     }
 }
 
