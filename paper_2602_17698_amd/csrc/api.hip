@@ -395,7 +395,7 @@ int sbits_gather_cost_all(sbits_plan *plan, const sbits_matrix *mats, const int3
     if (!sbits_fused_shapes_ok(plan)) return SBITS_ERR_UNIMPLEMENTED;
     if ((rc = need_device(plan))) return rc;
     if ((rc = sbits_upload_head(plan, mats, nullptr, ws))) return rc;
-    if (!sbits_fused_layout_ok(plan, true)) return SBITS_ERR_UNIMPLEMENTED;
+    if (!sbits_fused_layout_ok(plan)) return SBITS_ERR_UNIMPLEMENTED;
     return sbits_launch_gather_cost_all(plan, row_perm, col_perm, w_re_bf16, nullptr, cost, ws);
 }
 
@@ -410,7 +410,7 @@ int sbits_surrogates_all(sbits_plan *plan, const sbits_matrix *mats, const int32
     if (!sbits_fused_all_staged(plan)) return SBITS_ERR_UNIMPLEMENTED;
     if ((rc = need_device(plan))) return rc;
     if ((rc = sbits_upload_head(plan, mats, nullptr, ws))) return rc;
-    if (!sbits_fused_layout_ok(plan, true)) return SBITS_ERR_UNIMPLEMENTED;
+    if (!sbits_fused_layout_ok(plan)) return SBITS_ERR_UNIMPLEMENTED;
     return sbits_launch_surrogates_all(plan, row_perm, col_perm, level, s_up, s_down, ws);
 }
 
@@ -427,7 +427,7 @@ int sbits_gather_pack_all(sbits_plan *plan, const sbits_matrix *mats, const int3
     if (!sbits_fused_shapes_ok(plan)) return SBITS_ERR_UNIMPLEMENTED;
     if ((rc = need_device(plan))) return rc;
     if ((rc = sbits_upload_head(plan, mats, nullptr, ws))) return rc;
-    if (!sbits_fused_layout_ok(plan, false)) return SBITS_ERR_UNIMPLEMENTED;
+    if (!sbits_fused_layout_ok(plan)) return SBITS_ERR_UNIMPLEMENTED;
     return sbits_launch_gather_pack_all(plan, row_perm, col_perm, level, byte_off, codes, scale, zero, ws);
 }
 
@@ -570,7 +570,7 @@ static int run_search(sbits_plan *plan, const sbits_matrix *mats, const sbits_co
     if (one_pass) {
         if ((rc = sbits_launch_gather_cost_all(plan, out->row_perm, out->col_perm, out->w_re_bf16, nullptr, out->cost, ws)))
             return rc;
-    } else if (sbits_copies_shapes_ok(plan) && sbits_fused_layout_ok(plan, true)) {
+    } else if (sbits_copies_shapes_ok(plan) && sbits_fused_layout_ok(plan)) {
         if ((rc = sbits_launch_gather_cost_all(plan, out->row_perm, out->col_perm, out->w_re_bf16, out->s_re, out->cost, ws)))
             return rc;
     } else {
@@ -622,7 +622,7 @@ static int search_impl(sbits_plan *plan, const sbits_matrix *mats, const Couplin
                                     cpl.col_repeat, &tables)))
         return rc;
     if (!params_ok(params, avg_bits)) return SBITS_ERR_INVALID_ARG;
-    const bool one_pass = sbits_fused_shapes_ok(plan) && sbits_fused_layout_ok(plan, true);
+    const bool one_pass = sbits_fused_shapes_ok(plan) && sbits_fused_layout_ok(plan);
     if (!one_pass && (!out->s_re || !out->w_re_bf16)) return SBITS_ERR_INVALID_ARG;
     rc = run_search(plan, mats, cpl.row_group ? &tables : nullptr, one_pass, avg_bits, params, out, host_stats, ws);
     // (what is enqueued may still read the head's image: nothing else guards it)

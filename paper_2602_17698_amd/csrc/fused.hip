@@ -98,6 +98,9 @@ void octet_finish_kernel(const float *__restrict__ part, const MatDesc *__restri
 // re-quantizes its chunks at the bitwidth chosen for their block.  The codes of four rows of a lane
 // group, from one step or from two, are consecutive in the block's stream and leave as whole words
 // (store_codes4).  WIDE: a candidate has more than 4 bits.
+// Rows go through registers into one of two LDS buffers, in the cost kernel's layout, and a lane takes its elements out as floats (upper
+// halves): one barrier a step, no packing and unpacking.  (Awaiting the next rows before a step's stores, or less rows a step for
+// more waves: 3 to 7 % slower.)
 // T threads per workgroup; launch bounds ask for 4 waves per SIMD (two workgroups of 512 or one
 // of 1024 per CU), which the kernel's ~120 registers allow.
 // PARTS = 2 (rows of more than 16384 elements): two workgroups stage the same rows and pack half of the columns each, two chunks
@@ -143,7 +146,7 @@ void gather_pack_kernel(const MatDesc *__restrict__ descs, const int *__restrict
     }
     const int nchunk = C >> 3;
     const int chunk0 = PARTS == 1 ? 0 : (int)(blockIdx.x >> 3 & 1) * CPL * T;    // this workgroup's chunks: CPL * T from here (whole groups)
-    int ci[CPL][8];
+    uint32_t ci[CPL][8];                             // LDS addresses of the source columns, row 0 of a step in the first buffer
     bool valid[CPL];
 #pragma unroll
     for (int c = 0; c < CPL; ++c) {
@@ -154,7 +157,10 @@ void gather_pack_kernel(const MatDesc *__restrict__ descs, const int *__restrict
         const int4 b = *reinterpret_cast<const int4 *>(cp + cb + 4);
         const int t[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) ci[c][e] = 2 * (t[e] < 0 ? 0 : (t[e] >= C ? C - 1 : t[e]));
+        for (int e = 0; e < 8; ++e) {
+            const uint32_t sc = (uint32_t)(t[e] < 0 ? 0 : (t[e] >= C ? C - 1 : t[e]));
+            ci[c][e] = lds0 + (((sc >> 9) * (uint32_t)RS) << 10) + ((sc & 511u) << 1);
+        }
     }
     __syncthreads();
 
@@ -176,12 +182,15 @@ void gather_pack_kernel(const MatDesc *__restrict__ descs, const int *__restrict
             }
         }
     };
-    auto stage = [&]() {
+    // Rows lie piece by piece (1 KiB), the rows of a step interleaved, as in the cost kernel; two buffers where they fit.
+    constexpr bool TWO = PARTS == 1;
+    const uint32_t buffer = (uint32_t)((2 * C + 1023) >> 10) * (uint32_t)RS << 10;
+    auto stage = [&](uint32_t buf) {
 #pragma unroll
         for (int rs = 0; rs < RS; ++rs)
 #pragma unroll
             for (int c = 0; c < STG; ++c)
-                *reinterpret_cast<uint4 *>(smem + (size_t)rs * C * 2 + offw[c]) = pw[rs][c];
+                *reinterpret_cast<uint4 *>(smem + buf + (((offw[c] >> 10) * RS + rs) << 10) + (offw[c] & 1023u)) = pw[rs][c];
     };
 
     // per chunk: the block it falls in (fixed column, block row changes every opb octets)
@@ -194,10 +203,21 @@ void gather_pack_kernel(const MatDesc *__restrict__ descs, const int *__restrict
     uint32_t held_lo[RS == 4 ? 1 : CPL][4], held_hi[RS == 4 ? 1 : CPL][4];     // rows that wait for the rest of their four
     prefetch(0);
     if (stop) return;
+    if constexpr (TWO) {
+        stage(0u);
+        if (nsteps > 1) prefetch(RS);
+    }
+    uint32_t buf = 0u;
     for (int st = 0; st < nsteps; ++st) {
-        stage();
-        lds_barrier();
-        if (st + 1 < nsteps) prefetch((st + 1) * RS);
+        if constexpr (TWO) {
+            lds_barrier();                           // this step's rows are there, the other buffer has been read
+            if (st + 1 < nsteps) stage(buffer - buf);
+            if (st + 2 < nsteps) prefetch((st + 2) * RS);
+        } else {
+            stage(0u);
+            lds_barrier();
+            if (st + 1 < nsteps) prefetch((st + 1) * RS);
+        }
 
         const int row = st * RS;
         const int og = oct0 + (row >> 3);
@@ -214,28 +234,36 @@ void gather_pack_kernel(const MatDesc *__restrict__ descs, const int *__restrict
             }
         }
 
-        uint4 gw[NIT];
+        float gw[TWO ? RS : NIT][8];
+        auto gather = [&](auto ic) {                 // the lane's elements of chunk c, rows of the step
+            constexpr int c = decltype(ic)::value, at = TWO ? 0 : c * RS;
+            static_for<0, RS>([&](auto irs) {
+                constexpr int rs = decltype(irs)::value;
 #pragma unroll
-        for (int it = 0; it < NIT; ++it) {
-            const int rs = it / CPL, c = it % CPL;
-            uint32_t wbase = lds0 + (uint32_t)rs * (uint32_t)C * 2u;
-            asm volatile("" : "+s"(wbase));          // keeps the 8 sums below out of loop-invariant registers
-            uint32_t h[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) h[e] = *(const lds_u16 *)(wbase + (uint32_t)ci[c][e]);
-            gw[it] = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
+                for (int e = 0; e < 8; ++e) lds_w_hi<rs * 1024>(gw[at + rs][e], ci[c][e] + buf);
+            });
+        };
+        if constexpr (!TWO) {
+            static_for<0, CPL>([&](auto ic) { gather(ic); });
+            static_for<0, NIT>([&](auto iit) { lds_gather_wait(gw[decltype(iit)::value]); });
+            asm volatile("s_barrier" ::: "memory");  // the rows may be overwritten from here on
         }
-        lds_barrier();                               // the rows may be overwritten from here on
 
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) {
+        static_for<0, CPL>([&](auto ic) {
+            constexpr int c = decltype(ic)::value;
+            if constexpr (TWO) {
+                gather(ic);
+                static_for<0, RS>([&](auto irs) { lds_gather_wait(gw[decltype(irs)::value]); });
+            }
             const int cb = lk[c].c;
-            uint4 raw[RS];
+            float w[RS][8];
 #pragma unroll
-            for (int rs = 0; rs < RS; ++rs) raw[rs] = gw[rs * CPL + c];
+            for (int rs = 0; rs < RS; ++rs)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) w[rs][e] = gw[(TWO ? 0 : c * RS) + rs][e];
             uint32_t half[RS][2];
             float scl[RS], mn[RS];
-            quant_pack_rows<LPG, RS>(raw, lk[c], lig, half, scl, mn);
+            quant_pack_rows<LPG, RS>(w, lk[c], lig, half, scl, mn);
             uint32_t lo[RS], hi[RS];
 #pragma unroll
             for (int rs = 0; rs < RS; ++rs) {
@@ -277,7 +305,8 @@ void gather_pack_kernel(const MatDesc *__restrict__ descs, const int *__restrict
                         if (q % RS == rs && (rib & 3) == q - rs) { held_lo[c][q] = lo[rs]; held_hi[c][q] = hi[rs]; }
                 if ((rib & 3) == 4 - RS && valid[c]) store_codes4<LPG, WIDE>(out, cb, held_lo[c], held_hi[c], lig);
             }
-        }
+        });
+        if constexpr (TWO) buf = buffer - buf;
     }
 }
 
@@ -366,7 +395,7 @@ static int launch_gpack_g(sbits_ctx *ctx, const FusedPackLaunch &a)
     auto *fn = a.wide ? &gather_pack_kernel<LPG, CPL, RS, TMAX, true, PARTS> : &gather_pack_kernel<LPG, CPL, RS, TMAX, false, PARTS>;
     SBITS_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, 159 * 1024));
-    const size_t lds = (size_t)RS * a.cols * 2;
+    const size_t lds = (PARTS == 1 ? 2 : 1) * staged_step_bytes(a.cols, RS, false);
     const unsigned grid = PARTS == 1 ? (unsigned)a.total_wg : ((unsigned)a.total_wg + 7u) / 8u * 16u;
     hipLaunchKernelGGL(fn, dim3(grid), dim3(T), lds, ctx->stream, a.descs, a.members,
                        a.wg_start, a.n_members, a.row_perm, a.col_perm, a.m, a.level, a.byte_off, a.codes, a.scale,
@@ -429,12 +458,12 @@ size_t sbits_fused_ws_bytes(const sbits_plan *plan)
     return octet_partial_bytes(plan) + spill;
 }
 
-// The kernels that read sensitivities rely on 16-bit register-half loads filling the other half with
+// The kernels rely on 16-bit register-half loads filling the other half with
 // zeros (the device's target id says "sramecc+").  (That every source row starts on a 16-byte boundary,
 // which the row loads need, is a rule of every entry point that takes matrices: checked there.)
-bool sbits_fused_layout_ok(const sbits_plan *plan, bool need_s)
+bool sbits_fused_layout_ok(const sbits_plan *plan)
 {
-    return !need_s || plan->ctx->d16_zero_fill;
+    return plan->ctx->d16_zero_fill;
 }
 
 // matrices grouped by column count: members and workgroup prefixes, class after class
@@ -495,7 +524,7 @@ int sbits_launch_gather_cost_all(sbits_plan *plan, const int32_t *row_perm, cons
 {
     sbits_ctx *ctx = plan->ctx;
     const bool copies = sbits_copies_shapes_ok(plan);
-    if ((!copies && !sbits_fused_shapes_ok(plan)) || !sbits_fused_layout_ok(plan, true)) return SBITS_ERR_BAD_SHAPE;
+    if ((!copies && !sbits_fused_shapes_ok(plan)) || !sbits_fused_layout_ok(plan)) return SBITS_ERR_BAD_SHAPE;
     if (copies ? !w_re || !s_re : s_re != nullptr) return SBITS_ERR_INVALID_ARG;
     const int *d_mem, *d_pre;
     int rc0 = fused_classes(plan, ws, &d_mem, &d_pre);
@@ -556,7 +585,7 @@ int sbits_launch_gather_pack_all(sbits_plan *plan, const int32_t *row_perm, cons
                                  float *zero, void *ws, const unsigned *aborted)
 {
     sbits_ctx *ctx = plan->ctx;
-    if (!sbits_fused_shapes_ok(plan) || !sbits_fused_layout_ok(plan, false)) return SBITS_ERR_BAD_SHAPE;
+    if (!sbits_fused_shapes_ok(plan) || !sbits_fused_layout_ok(plan)) return SBITS_ERR_BAD_SHAPE;
     const int *d_mem, *d_pre;
     int rc0 = fused_classes(plan, ws, &d_mem, &d_pre);
     if (rc0) return rc0;
@@ -590,7 +619,7 @@ int sbits_launch_surrogates_all(sbits_plan *plan, const int32_t *row_perm, const
                                 const uint8_t *level, float *s_up, float *s_down, void *ws)
 {
     sbits_ctx *ctx = plan->ctx;
-    if (!sbits_fused_all_staged(plan) || !sbits_fused_layout_ok(plan, true)) return SBITS_ERR_BAD_SHAPE;
+    if (!sbits_fused_all_staged(plan) || !sbits_fused_layout_ok(plan)) return SBITS_ERR_BAD_SHAPE;
     const int *d_mem, *d_pre;
     int rc0 = fused_classes(plan, ws, &d_mem, &d_pre);
     if (rc0) return rc0;

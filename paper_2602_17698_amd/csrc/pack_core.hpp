@@ -76,19 +76,18 @@ __device__ __forceinline__ unsigned long long quant_pack_row(const uint4 &raw, c
     return word;
 }
 
-// RS rows of one lane group at once (raw[rs] = the lane's 8 weights of row rs), LPG >= 2 * RS: the
+// RS rows of one lane group at once (w[rs] = the lane's 8 weights of row rs), LPG >= 2 * RS: the
 // 2 * RS grid quotients are spread over the lanes of the group (lane 2*rs: qmax / R of row rs,
 // lane 2*rs + 1: R / qmax), so the rows share ONE division sequence instead of paying one each.
 // Same results as quant_pack_row row by row, the codes in two halves: code 4 h + e in bits [e*c, (e+1)*c) of half[.][h].
 template <int LPG, int RS>
-__device__ __forceinline__ void quant_pack_rows(const uint4 (&raw)[RS], const LevelConsts &k, int lig,
+__device__ __forceinline__ void quant_pack_rows(const float (&w)[RS][8], const LevelConsts &k, int lig,
                                                 uint32_t (&half)[RS][2], float (&scl)[RS], float (&mn)[RS])
 {
     static_assert(LPG >= 2 * RS, "one lane per quotient");
-    float w[RS][8], R[RS];
+    float R[RS];
 #pragma unroll
     for (int rs = 0; rs < RS; ++rs) {
-        unpack8(raw[rs], w[rs]);
         float lo = fminf(fminf(fminf(w[rs][0], w[rs][1]), fminf(w[rs][2], w[rs][3])),
                          fminf(fminf(w[rs][4], w[rs][5]), fminf(w[rs][6], w[rs][7])));
         float hi = fmaxf(fmaxf(fmaxf(w[rs][0], w[rs][1]), fmaxf(w[rs][2], w[rs][3])),
@@ -144,7 +143,9 @@ __device__ __forceinline__ void quad_transpose(uint32_t (&a)[4], int lane)
 // those of row j, puts them together and stores them at once; the rows' bytes are consecutive, so a lane group's stores cover one
 // run.  dst: the first row's bytes.  WIDE: c may be more than 4 (else hi is not used).
 // (Collecting a group's bytes in LDS took two or three atomic ORs a lane and row, which with the column gather filled the LDS
-// pipe: 2.7 ms for the 4096-column rows of the 8B-shaped model, PACK4096 this way.)
+// pipe: two 8B-shaped layers in 64-column blocks at 1 to 8 bits 303 us, 269 this way; the 8192-column rows of the 70B-shaped layer 366,
+// with two row buffers besides 298; the 14336-column rows of the 8B-shaped model 1137, 1056; its 4096-column rows, whose stream of weights is the
+// slower part, 2.7 ms both.)
 template <int LPG, bool WIDE>
 __device__ __forceinline__ void store_codes4(uint8_t *dst, int c, uint32_t (&lo)[4], uint32_t (&hi)[4], int lig)
 {

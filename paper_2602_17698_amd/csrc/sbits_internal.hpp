@@ -117,7 +117,7 @@ int sbits_launch_cost_all(sbits_plan *plan, const void *w_re, const float *s_re,
 // gather fused with the cost table (reads the original matrices once; writes w_re and cost)
 bool sbits_fused_shapes_ok(const sbits_plan *plan);
 bool sbits_fused_all_staged(const sbits_plan *plan);
-bool sbits_fused_layout_ok(const sbits_plan *plan, bool need_s);
+bool sbits_fused_layout_ok(const sbits_plan *plan);
 size_t sbits_fused_ws_bytes(const sbits_plan *plan);
 int sbits_launch_gather_cost_all(sbits_plan *plan, const int32_t *row_perm, const int32_t *col_perm,
                                  void *w_re, float *s_re, float *cost, void *ws);
