@@ -496,7 +496,7 @@ int sbits_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t ld_x, i
     // launches share the scratch in stream order
     for (int b0 = 0, nb; b0 < batch; b0 += nb) {
         nb = sbits_mp_gemm_rows(plan, mat, ld_x, batch - b0);
-        rc = sbits_launch_mp_gemm(plan, mat, static_cast<const uint16_t *>(x_bf16) + (int64_t)b0 * ld_x, ld_x, nb, level,
+        rc = sbits_launch_mp_gemm(plan, mat, static_cast<const uint16_t *>(x_bf16) + (int64_t)b0 * ld_x, ld_x, nb, batch > 32, level,
                                   byte_off, codes, scale, zero, y + (int64_t)b0 * plan->rows[mat],
                                   sbits_scratch(plan, ws));
         if (rc) return rc;

@@ -17,10 +17,15 @@
 // Mapping (v_mfma_f32_16x16x32_bf16: A = x, 16 batch rows; B = What^T, 16 output channels; K = 32):
 //   lane l supplies channel i = l % 16 and the K-quarter g = l / 16 of a block row: its n / 4 codes
 //   are n * c / 32 consecutive bytes of the stream; the wave's 16 rows x n codes are one contiguous
-//   run.  A workgroup of 16 waves covers 128 rows (4 row groups of 32 = 2 channel tiles each) x 16
-//   block columns (4 waves per row group, 4 blocks per wave, two or three of them in flight in a ring
-//   of register slots); the x slice of those columns sits in LDS.  Block columns beyond the first 16
+//   run.  A workgroup covers 1, 2 or 4 row groups of 32 rows (2 channel tiles each; by the size of the
+//   product) x 16 block columns (4 waves per row group, 4 blocks per wave, two or three of them in flight
+//   in a ring of register slots); the x slice of those columns sits in LDS.  Block columns beyond the first 16
 //   go to further workgroups (grid.y), whose partial sums a second kernel adds in a fixed order.
+//   Workgroups of 4 row groups leave no room for a second one on the CU, so nothing ran while one started
+//   or ended: with 2 of 512 threads 9344 x 9344 at 5 rows took 18.5 us instead of 22.2.  Codes come by two
+//   loads whatever the bitwidth (load_quarter): with one path per bitwidth the ring was copied at the paths'
+//   end, behind a wait for it, 5824 x 6144 at 23 rows 17.7 -> 15.6 us; 64-column blocks, before two bytes
+//   at a time, 960 x 23872 at 13 rows 31.8 -> 16.5.
 // More than 32 batch rows, and most products of up to 16 (few_rows), take the kernels further down.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -32,10 +37,7 @@ namespace sbits {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4v_t __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
-typedef unsigned int u32x3_t __attribute__((ext_vector_type(3)));
 
-constexpr int MG_WAVES = 16, MG_THREADS = MG_WAVES * 64;
-constexpr int MG_RG = 4;                 // row groups (32 rows) per workgroup
 constexpr int MG_JL = 4;                 // waves per row group, each on its own block columns
 constexpr int MG_NBLK = 4;               // blocks per wave
 constexpr int MG_SPAN = MG_JL * MG_NBLK; // block columns per workgroup
@@ -59,27 +61,6 @@ __device__ __forceinline__ bf16x8_t as_bf16x8(uint32_t a, uint32_t b, uint32_t c
     return __builtin_bit_cast(bf16x8_t, v);
 }
 
-// The lane's codes of one block row quarter: C dwords (C = 0: an absent block, nothing needed).
-// Always exactly two load instructions, whatever C is: the first brings min(C, 4) dwords, the second
-// the rest or, if there is no rest, dword 0 once more into r[7] (kept alive by the consumer).  With
-// the same number of loads on every path the compiler can count the loads still in flight, and a
-// block's product waits for its own codes only, not for those of the blocks behind it.
-template <int C>
-__device__ __forceinline__ void load_codes(const uint8_t *p, uint32_t (&r)[8])
-{
-    const __attribute__((address_space(1))) uint32_t *q = (const __attribute__((address_space(1))) uint32_t *)p;
-    constexpr int A = C == 0 ? 1 : (C < 4 ? C : 4);
-    if constexpr (A == 1) r[0] = q[0];
-    else if constexpr (A == 2) { const u32x2_t v = *(const __attribute__((address_space(1))) u32x2_t *)q; r[0] = v.x; r[1] = v.y; }
-    else if constexpr (A == 3) { const u32x3_t v = *(const __attribute__((address_space(1))) u32x3_t *)q; r[0] = v.x; r[1] = v.y; r[2] = v.z; }
-    else { const u32x4_t v = *(const __attribute__((address_space(1))) u32x4_t *)q; r[0] = v.x; r[1] = v.y; r[2] = v.z; r[3] = v.w; }
-    if constexpr (C <= 4) { r[7] = __builtin_nontemporal_load(q); }
-    else if constexpr (C == 5) r[4] = q[4];
-    else if constexpr (C == 6) { const u32x2_t v = *(const __attribute__((address_space(1))) u32x2_t *)(q + 4); r[4] = v.x; r[5] = v.y; }
-    else if constexpr (C == 7) { const u32x3_t v = *(const __attribute__((address_space(1))) u32x3_t *)(q + 4); r[4] = v.x; r[5] = v.y; r[6] = v.z; }
-    else { const u32x4_t v = *(const __attribute__((address_space(1))) u32x4_t *)(q + 4); r[4] = v.x; r[5] = v.y; r[6] = v.z; r[7] = v.w; }
-}
-
 // code e (0 .. 8 * words - 1) of the lane's LSB-first stream, C bits
 template <int C>
 __device__ __forceinline__ uint32_t code_at(const uint32_t (&r)[8], int e)
@@ -90,14 +71,53 @@ __device__ __forceinline__ uint32_t code_at(const uint32_t (&r)[8], int e)
     return v & ((1u << C) - 1u);
 }
 
-// B operand of step `st`: the lane's codes 8 * st .. 8 * st + 7 as bf16, in stream order.
-// C < 8: 128 + q (the code in the mantissa of 128.0);  C == 8: q itself (converted).
+// Operands of the products of more than 32 rows, two codes in three instructions whatever the bitwidth c <= 7: field
+// extraction, spread to the two halves, mask and exponent.  c <= 5: B = 1 + q / 2^c (the code at the top of the
+// mantissa: the offset taken out again is no larger than the codes' range), c = 6, 7: B = 128 + q, c = 8: B = q.
+// the exponents of a pair (in a vector register) and the codes' places (in a scalar one): held in registers the last two
+// operations are one instruction, which takes no literals
+template <int C> struct PairConst {
+    static constexpr uint32_t one = C <= 5 ? 0x3f803f80u : 0x43004300u;
+    static constexpr uint32_t field = C <= 5 ? ((1u << C) - 1u) << (7 - C) : (1u << C) - 1u;
+};
 template <int C>
+__device__ __forceinline__ uint32_t code_pair(const uint32_t *r, int e, uint32_t one, uint32_t mask)   // codes e, e + 1 (e even) as two bf16
+{
+    if constexpr (C == 8) {
+        const uint32_t w = r[e >> 2];
+        const uint32_t f0 = __float_as_uint((float)((w >> (8 * (e & 3))) & 255u)), f1 = __float_as_uint((float)((w >> (8 * (e & 3) + 8)) & 255u));
+        return __builtin_amdgcn_perm(f1, f0, 0x07060302u);
+    } else {
+        const int bit = e * C, idx = bit >> 5, sh = bit & 31;
+        const uint32_t x = sh + 2 * C <= 32 ? __builtin_amdgcn_ubfe(r[idx], sh, 2 * C)
+                                            : __builtin_amdgcn_alignbit(r[idx + 1], r[idx], sh) & ((1u << (2 * C)) - 1u);
+        // C <= 5: the copies of the two codes do not overlap where the mask looks, nor carry into it
+        const uint32_t y = C <= 5 ? __umul24(x, (1u << (7 - C)) + (1u << (23 - 2 * C))) : x | x << (16 - C);
+        return (y & mask) | one;
+    }
+}
+
+// the block's scale and zero as they apply to sum B x (ONE_BIT_PLAIN and 1 bit: to sum q x) and sum x
+template <int C, bool ONE_BIT_PLAIN>
+__device__ __forceinline__ void term_factors(float sc, float ze, float &f, float &z)
+{
+    if constexpr (C == 1 && ONE_BIT_PLAIN) { f = sc; z = ze; return; }
+    f = C <= 5 ? sc * (float)(1 << C) : sc;
+    z = C <= 5 ? fmaf(-(float)(1 << C), sc, ze) : C < 8 ? fmaf(-128.0f, sc, ze) : ze;
+}
+
+// B operand of step `st`: the lane's codes 8 * st .. 8 * st + 7 as bf16, in stream order.
+// C < 8: 128 + q (the code in the mantissa of 128.0);  C == 8: q itself (converted).  FINE: as code_pair().
+template <int C, bool FINE>
 __device__ __forceinline__ bf16x8_t operand(const uint32_t (&r)[8], int st)
 {
     uint32_t w[4];
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
+        if constexpr (FINE) {
+            w[p] = code_pair<C>(r, 8 * st + 2 * p, PairConst<C>::one, PairConst<C>::field * 0x10001u);
+            continue;
+        }
         const uint32_t q0 = code_at<C>(r, 8 * st + 2 * p), q1 = code_at<C>(r, 8 * st + 2 * p + 1);
         if constexpr (C < 8) {
             w[p] = 0x43004300u | q0 | (q1 << 16);
@@ -121,17 +141,50 @@ struct PairOrder {
     static constexpr bool value = C == 4 || C == 2 || (C == 1 && KL == 32);
 };
 
-template <int C>
+template <int C, bool FINE>
 __device__ __forceinline__ bf16x8_t operand_pairs(const uint32_t (&r)[8], int st)
 {
     uint32_t w[4];
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
-        if constexpr (C == 4) w[p] = ((r[st] >> (4 * p)) & 0x000f000fu) | 0x43004300u;
+        if constexpr (FINE) {                                 // (the codes to the mantissa's top)
+            const uint32_t word = C == 4 ? r[st] : C == 2 ? r[st >> 1] : r[0];
+            const int sh = (C == 4 ? 4 * p : C == 2 ? 2 * (4 * (st & 1) + p) : 4 * st + p) - (7 - C);
+            w[p] = ((sh < 0 ? word << -sh : word >> (sh < 0 ? 0 : sh)) & PairConst<C>::field * 0x10001u) | PairConst<C>::one;
+        } else if constexpr (C == 4) w[p] = ((r[st] >> (4 * p)) & 0x000f000fu) | 0x43004300u;
         else if constexpr (C == 2) w[p] = ((r[st >> 1] >> (2 * (4 * (st & 1) + p))) & 0x00030003u) | 0x43004300u;
         else w[p] = ((r[0] >> (4 * st + p)) & 0x00010001u) | 0x43004300u;
     }
     return as_bf16x8(w[0], w[1], w[2], w[3]);
+}
+
+// The lane's codes of one block row quarter, `at` bytes into the block, as raw as they come: always the same two loads
+// into the same registers, whatever the bitwidth (a choice by bitwidth ends in copies, and a copy waits for its load).
+// They go through a descriptor of exactly the block's bytes: what lies past its end reads as zero and is not fetched.
+// 128 columns: up to 8 dwords from a multiple of 4 bytes on.  64 columns: up to 16 bytes from a multiple of 2 on, so the
+// 5 aligned dwords around them, which align_quarter() shifts into place.
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+template <int N_COLS>
+struct Quarter { uint32_t r[N_COLS == 128 ? 8 : 5]; };
+template <int N_COLS>
+__device__ __forceinline__ void load_quarter(rsrc_t rs, uint32_t at, Quarter<N_COLS> &o)
+{
+    const int off = (int)(N_COLS == 128 ? at : at & ~3u);
+    const u32x4_t v = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
+    o.r[0] = v.x; o.r[1] = v.y; o.r[2] = v.z; o.r[3] = v.w;
+    if constexpr (N_COLS == 128) {
+        const u32x4_t h = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16, 0, 0));
+        o.r[4] = h.x; o.r[5] = h.y; o.r[6] = h.z; o.r[7] = h.w;
+    } else {
+        o.r[4] = __builtin_amdgcn_raw_buffer_load_b32(rs, off + 16, 0, 0);
+    }
+}
+template <int N_COLS>
+__device__ __forceinline__ void align_quarter(const Quarter<N_COLS> &q, uint32_t at, uint32_t (&r)[N_COLS / 16])
+{
+#pragma unroll
+    for (int i = 0; i < N_COLS / 16; ++i)
+        r[i] = N_COLS == 128 ? q.r[i] : __builtin_amdgcn_alignbit(q.r[i + 1 < 5 ? i + 1 : 4], q.r[i], (at & 2u) * 8u);
 }
 
 // x operand of step st, read from the lane's 2 * KL bytes of the staged slice (natural order in LDS).
@@ -161,13 +214,12 @@ __device__ __forceinline__ bf16x8_t x_operand(const unsigned char *xl, int st)
 }
 
 // One block: loads were issued before (cw, sc, ze); multiply and add into acc.
-template <int C, int N_COLS, int NB>
+template <int C, int N_COLS, int NB, bool FINE>
 __device__ __forceinline__ void block_product(const uint32_t (&cw)[2][8], const float (&sc)[2], const float (&ze)[2],
                                               const unsigned char *const (&xl)[NB], f32x4v_t (&acc)[2][NB])
 {
     constexpr int STEPS = N_COLS / 32;
     constexpr bool PAIRS = PairOrder<C, N_COLS / 4>::value;
-    if constexpr (C <= 4 && N_COLS == 128) asm volatile("" :: "v"(cw[0][7]), "v"(cw[1][7]));   // the second load of load_codes
     const bf16x8_t ones = as_bf16x8(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
     f32x4v_t d[2][NB], d1[NB];
 #pragma unroll
@@ -179,8 +231,8 @@ __device__ __forceinline__ void block_product(const uint32_t (&cw)[2][8], const 
 #pragma unroll
     for (int st = 0; st < STEPS; ++st) {
         bf16x8_t b0, b1;
-        if constexpr (PAIRS) { b0 = operand_pairs<C>(cw[0], st); b1 = operand_pairs<C>(cw[1], st); }
-        else { b0 = operand<C>(cw[0], st); b1 = operand<C>(cw[1], st); }
+        if constexpr (PAIRS) { b0 = operand_pairs<C, FINE>(cw[0], st); b1 = operand_pairs<C, FINE>(cw[1], st); }
+        else { b0 = operand<C, FINE>(cw[0], st); b1 = operand<C, FINE>(cw[1], st); }
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
             const bf16x8_t xa = x_operand<C, PAIRS>(xl[nb], st);
@@ -191,70 +243,51 @@ __device__ __forceinline__ void block_product(const uint32_t (&cw)[2][8], const 
     }
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-        const float zz = C < 8 ? fmaf(-128.0f, sc[t], ze[t]) : ze[t];
+        float f = sc[t], zz = C < 8 ? fmaf(-128.0f, sc[t], ze[t]) : ze[t];
+        if constexpr (FINE) term_factors<C, false>(sc[t], ze[t], f, zz);
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                acc[t][nb][r] = fmaf(sc[t], d[t][nb][r], fmaf(zz, d1[nb][r], acc[t][nb][r]));
+                acc[t][nb][r] = fmaf(f, d[t][nb][r], fmaf(zz, d1[nb][r], acc[t][nb][r]));
     }
 }
 
 // Codes, scales and zeros of block T of a wave -> register slot S; the same number of load
 // instructions whatever the block.  c = 0: a block column beyond the matrix, or a pruned block (0 bits:
-// no codes, contributes nothing); its dummy loads read the first dword of the scales, which always
-// exists, and the clamped block's scales.  (A macro: through a function the slots end up in scratch memory.)
+// an empty descriptor, nothing fetched; the clamped block's scales).  (A macro: through a function the slots end up in
+// scratch memory.)
 #define MG_REQUEST(T, S)                                                                                          \
     do {                                                                                                          \
-        const int c_ = cbits[T];                                                                                  \
-        const uint8_t *pb_ = c_ ? a.codes + (int64_t)(((uint64_t)off_hi[T] << 32) | off_lo[T])                    \
-                                : reinterpret_cast<const uint8_t *>(a.scale);                                     \
+        const uint64_t at_ = ((uint64_t)off_hi[T] << 32) | off_lo[T];                                             \
+        const rsrc_t rs_ = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(a.codes) + at_, 0,             \
+            (int)((uint32_t)(a.m * (N_COLS / 8)) * (uint32_t)cbits[T]), 0x00027000);                              \
         const float *ps_ = a.scale + blk[T] * a.m + rin, *pz_ = a.zero + blk[T] * a.m + rin;                      \
         _Pragma("unroll") for (int tl = 0; tl < 2; ++tl) {                                                        \
-            const uint8_t *p_ = pb_ + (lane_units + (uint32_t)(tl * 16 * (N_COLS / 8))) * (uint32_t)c_;           \
             sc[S][tl] = ps_[16 * tl + li];                                                                        \
             ze[S][tl] = pz_[16 * tl + li];                                                                        \
-            if constexpr (KL == 32) {                                                                             \
-                switch (c_) {                                                                                     \
-                case 0: load_codes<0>(p_, cw[S][tl]); break;                                                      \
-                case 1: load_codes<1>(p_, cw[S][tl]); break;                                                      \
-                case 2: load_codes<2>(p_, cw[S][tl]); break;                                                      \
-                case 3: load_codes<3>(p_, cw[S][tl]); break;                                                      \
-                case 4: load_codes<4>(p_, cw[S][tl]); break;                                                      \
-                case 5: load_codes<5>(p_, cw[S][tl]); break;                                                      \
-                case 6: load_codes<6>(p_, cw[S][tl]); break;                                                      \
-                case 7: load_codes<7>(p_, cw[S][tl]); break;                                                      \
-                default: load_codes<8>(p_, cw[S][tl]); break;                                                     \
-                }                                                                                                 \
-            } else {                                                                                              \
-                /* 2 * c bytes: 16-bit halves (the stream is only 2-byte aligned here) */                         \
-                const __attribute__((address_space(1))) uint16_t *h_ =                                            \
-                    (const __attribute__((address_space(1))) uint16_t *)p_;                                       \
-                _Pragma("unroll") for (int i = 0; i < 8; ++i)                                                     \
-                    if (i < c_)                                                                                   \
-                        cw[S][tl][i >> 1] = (i & 1) ? (cw[S][tl][i >> 1] | ((uint32_t)h_[i] << 16)) : (uint32_t)h_[i]; \
-            }                                                                                                     \
+            load_quarter<N_COLS>(rs_, (lane_units + (uint32_t)(tl * 16 * (N_COLS / 8))) * (uint32_t)cbits[T], cq[S][tl]); \
         }                                                                                                         \
     } while (0)
 
-template <int N_COLS, int NB>
-__global__ __launch_bounds__(MG_THREADS)
+template <int N_COLS, int NB, int RG, bool FINE>
+__global__ __launch_bounds__((64 * MG_JL * RG), 4)
 void mp_gemm_kernel(MpArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    constexpr int KL = N_COLS / 4, STEPS = N_COLS / 32;
+    constexpr int KL = N_COLS / 4, THREADS = 64 * MG_JL * RG;
     constexpr int SLICE = MG_SPAN * N_COLS;                    // x columns per workgroup
     constexpr int PITCH = SLICE * 2 + 16;                      // bytes per batch row in LDS (+16: spreads the rows over the banks)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: the bookkeeping below stays scalar
-    const int rg = wave & (MG_RG - 1), jl = wave >> 2;
+    const int rg = wave & (RG - 1), jl = wave / RG;
     const int li = lane & 15, g = lane >> 4;
     const int col0 = blockIdx.y * SLICE;                       // first x column of the slice
     const int J0 = blockIdx.y * MG_SPAN;
 
     // ---- this wave's blocks: all metadata loads first (they head the longest dependency chain);
     // a block column beyond the matrix reads the last one's metadata and is skipped later
-    const int row0 = blockIdx.x * (MG_RG * 32) + rg * 32;      // first of the wave's 32 rows
+    const int row0 = blockIdx.x * (RG * 32) + rg * 32;      // first of the wave's 32 rows
     const bool rows_ok = row0 < a.R;                           // (R is a multiple of 32)
     const int I = rows_ok ? row0 / a.m : 0, rin = rows_ok ? row0 - I * a.m : 0;
     // PF blocks of codes are in flight at a time (a ring of PF register slots, refilled after each
@@ -262,7 +295,7 @@ void mp_gemm_kernel(MpArgs a)
     // requested at once, whose first block then arrives late), two with two batch tiles (registers)
     constexpr int PF = NB == 1 ? 3 : 2;
     int cbits[MG_NBLK];
-    uint32_t cw[PF][2][8];
+    Quarter<N_COLS> cq[PF][2];
     float sc[PF][2], ze[PF][2];
     int64_t blk[MG_NBLK];
     uint32_t lvl_v[MG_NBLK];
@@ -276,12 +309,12 @@ void mp_gemm_kernel(MpArgs a)
     }
     // ---- x slice: requested together with the metadata (rows beyond the batch and columns beyond C read
     // as zero) and in LDS by the time the metadata has arrived
-    constexpr int XCH = 16 * NB * (SLICE / 8) / MG_THREADS;    // 16-byte pieces per thread
-    static_assert(16 * NB * (SLICE / 8) % MG_THREADS == 0, "whole pieces per thread");
+    constexpr int XCH = 16 * NB * (SLICE / 8) / THREADS;    // 16-byte pieces per thread
+    static_assert(16 * NB * (SLICE / 8) % THREADS == 0, "whole pieces per thread");
     u32x4_t xs[XCH];
 #pragma unroll
     for (int i = 0; i < XCH; ++i) {
-        const int q = tid + i * MG_THREADS;
+        const int q = tid + i * THREADS;
         const int b = q / (SLICE / 8), ch = q - b * (SLICE / 8);
         const int bc = b < a.batch ? b : a.batch - 1;                               // in bounds; zeroed below
         const int cc = col0 + ch * 8 < a.C ? col0 + ch * 8 : 0;
@@ -290,7 +323,7 @@ void mp_gemm_kernel(MpArgs a)
 
 #pragma unroll
     for (int i = 0; i < XCH; ++i) {
-        const int q = tid + i * MG_THREADS;
+        const int q = tid + i * THREADS;
         const int b = q / (SLICE / 8), ch = q - b * (SLICE / 8);
         const bool ok = b < a.batch && col0 + ch * 8 < a.C;
         u32x4_t v = xs[i];
@@ -330,15 +363,23 @@ void mp_gemm_kernel(MpArgs a)
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
             xa[nb] = smem + (size_t)(16 * nb + li) * PITCH + (size_t)(Jl * N_COLS + g * KL) * 2;
+        uint32_t cw[2][8];
+#pragma unroll
+        for (int tl = 0; tl < 2; ++tl) {
+            uint32_t w[N_COLS / 16];
+            align_quarter<N_COLS>(cq[t % PF][tl], (lane_units + (uint32_t)(tl * 16 * (N_COLS / 8))) * (uint32_t)c, w);
+#pragma unroll
+            for (int i = 0; i < N_COLS / 16; ++i) cw[tl][i] = w[i];
+        }
         if (c != 0) switch (c) {                               // (0: no such block column, or a pruned block)
-        case 1: block_product<1, N_COLS, NB>(cw[t % PF], sc[t % PF], ze[t % PF], xa, acc); break;
-        case 2: block_product<2, N_COLS, NB>(cw[t % PF], sc[t % PF], ze[t % PF], xa, acc); break;
-        case 3: block_product<3, N_COLS, NB>(cw[t % PF], sc[t % PF], ze[t % PF], xa, acc); break;
-        case 4: block_product<4, N_COLS, NB>(cw[t % PF], sc[t % PF], ze[t % PF], xa, acc); break;
-        case 5: block_product<5, N_COLS, NB>(cw[t % PF], sc[t % PF], ze[t % PF], xa, acc); break;
-        case 6: block_product<6, N_COLS, NB>(cw[t % PF], sc[t % PF], ze[t % PF], xa, acc); break;
-        case 7: block_product<7, N_COLS, NB>(cw[t % PF], sc[t % PF], ze[t % PF], xa, acc); break;
-        default: block_product<8, N_COLS, NB>(cw[t % PF], sc[t % PF], ze[t % PF], xa, acc); break;
+        case 1: block_product<1, N_COLS, NB, FINE>(cw, sc[t % PF], ze[t % PF], xa, acc); break;
+        case 2: block_product<2, N_COLS, NB, FINE>(cw, sc[t % PF], ze[t % PF], xa, acc); break;
+        case 3: block_product<3, N_COLS, NB, FINE>(cw, sc[t % PF], ze[t % PF], xa, acc); break;
+        case 4: block_product<4, N_COLS, NB, FINE>(cw, sc[t % PF], ze[t % PF], xa, acc); break;
+        case 5: block_product<5, N_COLS, NB, FINE>(cw, sc[t % PF], ze[t % PF], xa, acc); break;
+        case 6: block_product<6, N_COLS, NB, FINE>(cw, sc[t % PF], ze[t % PF], xa, acc); break;
+        case 7: block_product<7, N_COLS, NB, FINE>(cw, sc[t % PF], ze[t % PF], xa, acc); break;
+        default: block_product<8, N_COLS, NB, FINE>(cw, sc[t % PF], ze[t % PF], xa, acc); break;
         }
         if (t + PF < MG_NBLK) MG_REQUEST((t + PF) % MG_NBLK, t % PF);   // the slot is free again
     }
@@ -365,7 +406,7 @@ void mp_gemm_kernel(MpArgs a)
                 float v = acc[t][nb][r];
 #pragma unroll
                 for (int j = 1; j < MG_JL; ++j)
-                    v = v + red[((((rg + MG_RG * j) * 2 + t) * NB + nb) * 4 + r) * 64 + lane];
+                    v = v + red[((((rg + RG * j) * 2 + t) * NB + nb) * 4 + r) * 64 + lane];
                 const int b = 16 * nb + 4 * g + r;             // D layout: row 4 * (lane / 16) + r, column lane % 16
                 if (b < a.batch) dst[(int64_t)b * a.R + row0 + 16 * t + li] = v;
             }
@@ -396,67 +437,6 @@ void mp_gemm_kernel(MpArgs a)
 // block product of its own.
 constexpr int WG_WAVES = 8, WG_THREADS = WG_WAVES * 64;
 constexpr int WG_LDS = 144 * 1024;                            // for the stages of x
-
-// the exponents of a pair (in a vector register) and the codes' places (in a scalar one): held in registers the last two
-// operations are one instruction, which takes no literals
-template <int C> struct PairConst {
-    static constexpr uint32_t one = C <= 5 ? 0x3f803f80u : 0x43004300u;
-    static constexpr uint32_t field = C <= 5 ? ((1u << C) - 1u) << (7 - C) : (1u << C) - 1u;
-};
-template <int C>
-__device__ __forceinline__ uint32_t code_pair(const uint32_t *r, int e, uint32_t one, uint32_t mask)   // codes e, e + 1 (e even) as two bf16
-{
-    if constexpr (C == 8) {
-        const uint32_t w = r[e >> 2];
-        const uint32_t f0 = __float_as_uint((float)((w >> (8 * (e & 3))) & 255u)), f1 = __float_as_uint((float)((w >> (8 * (e & 3) + 8)) & 255u));
-        return __builtin_amdgcn_perm(f1, f0, 0x07060302u);
-    } else {
-        const int bit = e * C, idx = bit >> 5, sh = bit & 31;
-        const uint32_t x = sh + 2 * C <= 32 ? __builtin_amdgcn_ubfe(r[idx], sh, 2 * C)
-                                            : __builtin_amdgcn_alignbit(r[idx + 1], r[idx], sh) & ((1u << (2 * C)) - 1u);
-        // C <= 5: the copies of the two codes do not overlap where the mask looks, nor carry into it
-        const uint32_t y = C <= 5 ? __umul24(x, (1u << (7 - C)) + (1u << (23 - 2 * C))) : x | x << (16 - C);
-        return (y & mask) | one;
-    }
-}
-
-// the block's scale and zero as they apply to sum B x (1 bit: to sum q x) and sum x
-template <int C>
-__device__ __forceinline__ void term_factors(float sc, float ze, float &f, float &z)
-{
-    if constexpr (C == 1) { f = sc; z = ze; return; }
-    f = C <= 5 ? sc * (float)(1 << C) : sc;
-    z = C <= 5 ? fmaf(-(float)(1 << C), sc, ze) : C < 8 ? fmaf(-128.0f, sc, ze) : ze;
-}
-
-// The lane's codes of one block row quarter, `at` bytes into the block, as raw as they come: always the same two loads
-// into the same registers, whatever the bitwidth (a choice by bitwidth ends in copies, and a copy waits for its load).
-// They go through a descriptor of exactly the block's bytes: what lies past its end reads as zero and is not fetched.
-// 128 columns: up to 8 dwords from a multiple of 4 bytes on.  64 columns: up to 16 bytes from a multiple of 2 on, so the
-// 5 aligned dwords around them, which align_quarter() shifts into place.
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
-template <int N_COLS>
-struct Quarter { uint32_t r[N_COLS == 128 ? 8 : 5]; };
-template <int N_COLS>
-__device__ __forceinline__ void load_quarter(rsrc_t rs, uint32_t at, Quarter<N_COLS> &o)
-{
-    const int off = (int)(N_COLS == 128 ? at : at & ~3u);
-    const u32x4_t v = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
-    o.r[0] = v.x; o.r[1] = v.y; o.r[2] = v.z; o.r[3] = v.w;
-    if constexpr (N_COLS == 128) {
-        const u32x4_t h = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16, 0, 0));
-        o.r[4] = h.x; o.r[5] = h.y; o.r[6] = h.z; o.r[7] = h.w;
-    } else {
-        o.r[4] = __builtin_amdgcn_raw_buffer_load_b32(rs, off + 16, 0, 0);
-    }
-}
-template <int N_COLS>
-__device__ __forceinline__ void align_quarter(const Quarter<N_COLS> &q, uint32_t at, uint32_t (&r)[N_COLS / 16])
-{
-#pragma unroll
-    for (int i = 0; i < N_COLS / 16; ++i)
-        r[i] = N_COLS == 128 ? q.r[i] : __builtin_amdgcn_alignbit(q.r[i + 1 < 5 ? i + 1 : 4], q.r[i], (at & 2u) * 8u);
-}
 
 template <int NB, int SUMS>
 struct WideState {
@@ -741,7 +721,7 @@ void mp_gemm_wide_kernel(MpArgs a, int cols_per_split)
     auto apply = [&](const float (&sc)[2], const float (&ze)[2], int c, int u) {
         if (c == 0) return;
         float f[2], z[2];
-#define WG_TERM(C) term_factors<C>(sc[0], ze[0], f[0], z[0]); term_factors<C>(sc[1], ze[1], f[1], z[1])
+#define WG_TERM(C) term_factors<C, true>(sc[0], ze[0], f[0], z[0]); term_factors<C, true>(sc[1], ze[1], f[1], z[1])
         f[0] = f[1] = z[0] = z[1] = 0.0f;
         WG_SWITCH(c, WG_TERM)
 #undef WG_TERM
@@ -874,16 +854,16 @@ void mp_gemm_wide_kernel(MpArgs a, int cols_per_split)
     }
 }
 
-// ================================================================ up to 16 batch rows
+// ================================================================ few batch rows
 // Few rows of x are small next to the codes, so nothing is staged and no columns are split off: a workgroup takes 32
-// channels and all columns, its 16 waves every 16th block column each, with x straight from the caches into the operand
-// registers, two blocks in flight, and one exchange through LDS at the end.  Against the first kernel this takes the
-// second launch, the partial sums in memory and the wait for x out, and four times as many CUs share a small matrix; the
-// price is x read once per 32 channels instead of once per 128.  Products as there, in its column order.  Latency bounds
-// it: level and offset, then codes, then the exchange.
-// 1024 x 4096, bitwidths 1 .. 4, one row: 11.3 -> 5.8 us; 4096 x 4096, 4 bits: 11.2 -> 5.9, 16 rows 11.5 -> 8.3; 14336 x 4096,
-// one row: 12.5 -> 10.7; 64-column blocks (whose codes the first kernel reads two bytes at a time): 11008 x 4096 44 -> 17.
-constexpr int ND_WAVES = 16, ND_THREADS = ND_WAVES * 64;
+// channels, 16 rows of x and all columns, its 8 or 16 waves every 8th or 16th block column each, with x straight from the
+// caches into the operand registers, two blocks in flight, and one exchange through LDS at the end.  Against the first kernel
+// this takes the second launch, the partial sums in memory and the wait for x out, and a small matrix has more CUs; the price is x read
+// once per 32 channels, and codes once per 16 rows.  Products as there, in its column order; a wave of 8 keeps two sums, so
+// that there are the same sixteen partial sums either way.  Latency bounds it: level and offset, then codes, then the
+// exchange; with many rows and turns, x from L2.
+// 1024 x 4096, bitwidths 1 .. 4, one row: 11.3 -> 5.8 us; 4096 x 4096, 4 bits: 11.2 -> 5.9.  17 .. 32 rows, which all took
+// the first kernel before: 1984 x 3328 at 26 rows 16.1 -> 8.2 us, 2112 x 1856 in 64-column blocks at 23 rows 14.9 -> 6.2.
 
 // x operand of step st from the lane's KL values in registers: natural or, for the bitwidths of PairOrder, pair order
 template <int C, int KL>
@@ -899,7 +879,7 @@ __device__ __forceinline__ bf16x8_t x_held(const u32x4_t (&x)[KL / 8], int st)
     }
 }
 
-template <int C, int N_COLS>
+template <int C, int N_COLS, bool FINE>
 __device__ __forceinline__ void narrow_block(const uint32_t (&cw)[2][8], const float (&sc)[2], const float (&ze)[2],
                                              const u32x4_t (&x)[N_COLS / 32], f32x4v_t (&acc)[2])
 {
@@ -912,44 +892,48 @@ __device__ __forceinline__ void narrow_block(const uint32_t (&cw)[2][8], const f
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             bf16x8_t b;
-            if constexpr (PairOrder<C, KL>::value) b = operand_pairs<C>(cw[t], st);
-            else b = operand<C>(cw[t], st);
+            if constexpr (PairOrder<C, KL>::value) b = operand_pairs<C, FINE>(cw[t], st);
+            else b = operand<C, FINE>(cw[t], st);
             d[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, b, d[t], 0, 0, 0);
         }
         d1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, ones, d1, 0, 0, 0);
     }
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-        const float zz = C < 8 ? fmaf(-128.0f, sc[t], ze[t]) : ze[t];
+        float f = sc[t], zz = C < 8 ? fmaf(-128.0f, sc[t], ze[t]) : ze[t];
+        if constexpr (FINE) term_factors<C, false>(sc[t], ze[t], f, zz);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[t][r] = fmaf(sc[t], d[t][r], fmaf(zz, d1[r], acc[t][r]));
+        for (int r = 0; r < 4; ++r) acc[t][r] = fmaf(f, d[t][r], fmaf(zz, d1[r], acc[t][r]));
     }
 }
 
-template <int N_COLS>
-__global__ __launch_bounds__(ND_THREADS)
+template <int N_COLS, int WAVES, bool FINE>
+__global__ __launch_bounds__((64 * WAVES), 4)
 void mp_gemm_narrow_kernel(MpArgs a)
 {
-    __shared__ float red[ND_WAVES][2][4][64];
+    static_assert(WAVES == 8 || WAVES == 16, "sixteen partial sums");
+    constexpr int SUMS = 16 / WAVES;                          // of a wave: the columns wave + WAVES s + 16 i
+    __shared__ float red[16][2][4][64];
     constexpr int KL = N_COLS / 4, XL = KL / 8;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, g = lane >> 4;
     const int row0 = (int)blockIdx.x * 32;                    // (R is a multiple of 32)
+    const int batch0 = (int)blockIdx.y * 16, batch = a.batch - batch0;
     const int I = row0 / a.m, rin = row0 - I * a.m;
     const int64_t blk0 = a.block_base + (int64_t)I * a.nbc;
-    // level and offset of this wave's t-th block column, wave + 16 t, in lane t (at most 512 block columns)
-    const int mine = min(wave + ND_WAVES * lane, a.nbc - 1);
+    // level and offset of this wave's t-th block column, wave + WAVES t, in lane t (512 block columns at most: 64 a wave)
+    const int mine = min(wave + WAVES * lane, a.nbc - 1);
     const int lvl = a.level[blk0 + mine];
     const int64_t off = a.byte_off[blk0 + mine];
-    const int nt = (a.nbc - wave + ND_WAVES - 1) / ND_WAVES;  // 0 or less: none
-    const uint16_t *const xrow = a.x + (int64_t)min(li, a.batch - 1) * a.ld_x + g * KL;   // (rows past the batch: not stored)
+    const int nt = (a.nbc - wave + WAVES - 1) / WAVES;  // 0 or less: none
+    const uint16_t *const xrow = a.x + (int64_t)(batch0 + min(li, batch - 1)) * a.ld_x + g * KL;   // (rows past the batch: not stored)
     const uint32_t lane_units = (uint32_t)((rin + li) * (N_COLS / 8) + g * (KL / 8));   // x c = the lane's byte offset in the block
     const uint32_t block_bytes_per_bit = (uint32_t)a.m * (N_COLS / 8);
 
     struct Slot { Quarter<N_COLS> q[2]; float sc[2], ze[2]; u32x4_t x[XL]; int c; };
     auto request = [&](Slot &o, int t) {
-        const int tt = min(t, nt - 1), J = wave + ND_WAVES * tt;
+        const int tt = min(t, nt - 1), J = wave + WAVES * tt;
         const int lv = __builtin_amdgcn_readlane(lvl, tt);
         int c = a.bits[0];
 #pragma unroll
@@ -969,8 +953,12 @@ void mp_gemm_narrow_kernel(MpArgs a)
             o.ze[tl] = pz[16 * tl + li];
         }
     };
-    f32x4v_t acc[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
-    auto add = [&](const Slot &o) {
+    f32x4v_t sums[SUMS][2];
+#pragma unroll
+    for (int s = 0; s < SUMS; ++s)
+#pragma unroll
+        for (int tl = 0; tl < 2; ++tl) sums[s][tl] = f32x4v_t{0.0f, 0.0f, 0.0f, 0.0f};
+    auto add = [&](const Slot &o, f32x4v_t (&acc)[2]) {
         if (o.c == 0) return;                                 // no such block column, or a pruned block
         uint32_t cw[2][8];
 #pragma unroll
@@ -980,7 +968,7 @@ void mp_gemm_narrow_kernel(MpArgs a)
 #pragma unroll
             for (int i = 0; i < N_COLS / 16; ++i) cw[tl][i] = r[i];
         }
-#define ND_BLOCK(C) narrow_block<C, N_COLS>(cw, o.sc, o.ze, o.x, acc)
+#define ND_BLOCK(C) narrow_block<C, N_COLS, FINE>(cw, o.sc, o.ze, o.x, acc)
         WG_SWITCH(o.c, ND_BLOCK)
 #undef ND_BLOCK
     };
@@ -989,24 +977,26 @@ void mp_gemm_narrow_kernel(MpArgs a)
         request(s0, 0);
         request(s1, 1);
         for (int t = 0; t < nt; t += 2) {
-            add(s0);
+            add(s0, sums[0]);
             if (t + 2 < nt) request(s0, t + 2);
-            add(s1);
+            add(s1, sums[SUMS - 1]);
             if (t + 2 < nt) request(s1, t + 3);
         }
     }
 #pragma unroll
-    for (int tl = 0; tl < 2; ++tl)
+    for (int s = 0; s < SUMS; ++s)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) red[wave][tl][r][lane] = acc[tl][r];
+        for (int tl = 0; tl < 2; ++tl)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) red[wave + WAVES * s][tl][r][lane] = sums[s][tl][r];
     __syncthreads();
     // D layout: batch row 4 (lane / 16) + r, channel lane % 16
     const int ch = tid & 31, b = tid >> 5;                    // 32 channels x 16 batch rows in the first 512 threads
-    if (b < a.batch && b < 16) {
+    if (b < batch && b < 16) {
         float v = red[0][ch >> 4][b & 3][(b >> 2) * 16 + (ch & 15)];
 #pragma unroll
-        for (int w = 1; w < ND_WAVES; ++w) v = v + red[w][ch >> 4][b & 3][(b >> 2) * 16 + (ch & 15)];
-        a.out[(int64_t)b * a.R + row0 + ch] = v;
+        for (int w = 1; w < 16; ++w) v = v + red[w][ch >> 4][b & 3][(b >> 2) * 16 + (ch & 15)];
+        a.out[(int64_t)(batch0 + b) * a.R + row0 + ch] = v;
     }
 }
 
@@ -1087,16 +1077,26 @@ size_t sbits_mp_gemm_ws_bytes(const sbits_plan *plan)
     return sbits_align_up(mx, 256);
 }
 
-template <int N_COLS, int NB>
-static int launch_mp(sbits_ctx *ctx, const MpArgs &a, dim3 grid)
+template <int N_COLS, int NB, int RG, bool FINE>
+static int launch_mp(sbits_ctx *ctx, const MpArgs &a)
 {
     constexpr size_t x_bytes = (size_t)16 * NB * (MG_SPAN * N_COLS * 2 + 16);
-    constexpr size_t red_bytes = (size_t)MG_WAVES * 2 * NB * 4 * 64 * 4;
+    constexpr size_t red_bytes = (size_t)MG_JL * RG * 2 * NB * 4 * 64 * 4;
     constexpr size_t lds = x_bytes > red_bytes ? x_bytes : red_bytes;
-    auto *fn = &mp_gemm_kernel<N_COLS, NB>;
+    auto *fn = &mp_gemm_kernel<N_COLS, NB, RG, FINE>;
     SBITS_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)lds));
-    hipLaunchKernelGGL(fn, grid, dim3(MG_THREADS), lds, ctx->stream, a);
+    const dim3 grid((unsigned)((a.R + RG * 32 - 1) / (RG * 32)), (unsigned)a.n_split);
+    hipLaunchKernelGGL(fn, grid, dim3(64 * MG_JL * RG), lds, ctx->stream, a);
+    SBITS_HIP(ctx, hipGetLastError());
+    return SBITS_OK;
+}
+
+template <int N_COLS, int WAVES, bool FINE>
+static int launch_narrow(sbits_ctx *ctx, const MpArgs &a)
+{
+    const dim3 grid((unsigned)(a.R / 32), (unsigned)((a.batch + 15) / 16));
+    hipLaunchKernelGGL((mp_gemm_narrow_kernel<N_COLS, WAVES, FINE>), grid, dim3(64 * WAVES), 0, ctx->stream, a);
     SBITS_HIP(ctx, hipGetLastError());
     return SBITS_OK;
 }
@@ -1123,52 +1123,63 @@ static int launch_wide_rg(sbits_ctx *ctx, int n, const MpArgs &a, dim3 grid, int
     return a.batch <= 48 ? launch_wide<128, 3, RG>(ctx, a, grid, cols_per_split) : launch_wide<128, 4, RG>(ctx, a, grid, cols_per_split);
 }
 
-// What a product of up to 16 rows takes in the first kernel and in the narrow one, in hundredths of a microsecond, from 3500
-// products of 32 .. 32768 x 256 .. 28672 at 1 .. 16 rows of x: the kernel that these name takes 0.1 % longer than the
-// better one on average.
-// First: one workgroup per 128 channels and 16 block columns, 256 at a time.  One column split: by the blocks of a wave
-// (24576 x 2048: 10 us at 1 and 16 rows); more: the second launch, and a turn of the CUs per 256 workgroups, less where the
-// last one is light (16384 x 4096 13 us, x 8192 23).  64-column blocks: codes come in two bytes at a time, so a turn takes
-// 7.6, 8.8, 11, 19 and 33 us at 1, 2, 3, 4 and 8 bits.
-// Narrow: one workgroup per 32 channels, 256 at a time; its first turn is a chain of latencies, by the blocks of a wave
-// beyond two; every further one costs its blocks, and x once more (1024 x 4096 5.9 and 8.0 us at 1 and 16 rows, 24576 x 2048 12 and
-// 20, 14336 x 4096 11 and 15).
-struct FewRows { int64_t first, narrow; };
-static FewRows few_rows(const sbits_plan *plan, int64_t R, int nbc, int b)
+// What a product takes in the first kernel (up to 32 rows) and in the narrow one (up to 64), in microseconds, fitted to 2600
+// products of 256 .. 28672 x 256 .. 28672, 1 .. 64 rows of x, bitwidths up to 8: with the choice made by these the products
+// take 0.4 % longer than with the better kernel each time (always the first 10 %, always the narrow one 18 %); no product
+// takes less than a launch, 5.2.
+// First: by the turns of the CUs (32 channels and 16 block columns each, 256 at a time) and their bytes; with several column
+// splits, their number, the partial sums and the second launch (1024 x 17216 in 64-column blocks, 17 splits, 12.5 us).
+// Narrow: by turns of 256 workgroups and block columns in each, x once more per turn; with 17 rows or more a workgroup per
+// 16 of them (26368 x 1024 at 29 rows: 10.8 us in the first kernel and 19.9 in this one; 256 .. 8192 x 2048 5.5 .. 8 in this one and 9 .. 12
+// in the first).
+struct FewRows { double first, narrow; };
+static FewRows few_rows(const sbits_plan *plan, int64_t R, int nbc, int batch)
 {
-    const int waves = (nbc + ND_WAVES - 1) / ND_WAVES;         // blocks of a wave of the narrow kernel; column splits of the first
-    const int64_t turns = (R / 32 + 255) / 256, tiles = (R + 127) / 128, wgs = tiles * waves;
     const bool wide = plan->n == 128;
-    int64_t t64 = 0, bits = 0;                                // a turn of the first kernel in 64-column blocks; candidates on average
-    for (int l = 0; l < plan->K; ++l) {
-        const int c = plan->bits[l];
-        t64 += c == 0 ? 900 : c < 3 ? 640 + 120 * c : c == 3 ? 1140 : 460 + 355 * c;
-        bits += c;
-    }
-    t64 /= plan->K;
+    const int groups = (batch + 15) / 16, b = batch < 16 ? batch : 16, splits = (nbc + MG_SPAN - 1) / MG_SPAN;
+    const double turns = (double)((R / 32 * groups + 255) / 256 - 1);         // beyond the first
+    const double load = (double)(R / 32 * splits) / 256, over = load > 1 ? load - 1 : 0;
+    double bits = 0;                                          // of the candidates, on average
+    for (int l = 0; l < plan->K; ++l) bits += plan->bits[l];
+    bits /= plan->K;
     FewRows o;
-    if (waves == 1) {
-        o.first = wide ? 610 + 61 * nbc / 2 : 640 + (t64 - 640) * nbc / 16;
-        const int64_t turn = wide ? 105 + nbc * (159 + 9 * b) / 10 : 115 + nbc * (224 + 11 * b) / 20;
-        o.narrow = (wide ? 180 : 110) + turns * turn;
-        if (o.narrow < 560) o.narrow = 560;
+    if (splits == 1) {
+        if (wide) {
+            o.narrow = 5.55 + 0.01 * nbc + turns * (0.06 + nbc * (0.0103 * b + 0.022 * bits - 0.045));
+            o.first = batch <= 16 ? 5.62 + 0.032 * nbc + over * (0.28 + nbc * (0.048 + 0.020 * bits))
+                                  : 6.45 + 0.15 * nbc + over * (0.67 + nbc * (0.044 * bits - 0.071));
+        } else {
+            o.narrow = 5.43 + 0.015 * nbc + turns * (0.16 + nbc * (0.0079 * b + 0.0076 * bits - 0.033));
+            o.first = batch <= 16 ? 5.68 + 0.003 * nbc + over * (nbc * (0.045 + 0.0079 * bits) - 0.23)
+                                  : 5.45 + 0.058 * nbc + over * (0.55 + nbc * (0.055 + 0.0087 * bits));
+        }
     } else {
-        const int64_t full = 100 * ((wgs + 255) / 256 - 1), light = tiles * nbc * 160 / 4096 - 85;
-        const int64_t more = light < 0 ? 0 : light < full ? light : full;
-        o.first = wide ? 1220 + 10 * more : 300 + t64 + t64 * more / 100;
-        const int half = nbc % 32 < 16 ? nbc % 32 : 16;                       // (a wave's blocks come in pairs)
-        const int64_t turn = (nbc / 32 * 16 + half) * (wide ? 288 + 19 * b : 297 + 11 * b) / 16;
-        const int64_t blocks = (waves - 2) * (wide ? 135 + 6 * b : 122 + 4 * b) + (turns - 1) * turn;
-        o.narrow = 570 + (wide ? 15 : 6) * b + (wide ? blocks : blocks * (7 * plan->K + bits) / (10 * plan->K));
+        const double part = (double)batch * (double)R * splits * 1e-6;        // partial sums, millions
+        if (wide) {
+            o.narrow = 3.44 + 0.0143 * b + nbc * (0.092 + 0.0046 * b) + turns * (0.61 + nbc * (0.054 + 0.0033 * b + 0.0116 * bits));
+            o.first = batch <= 16 ? 7.75 + 0.236 * splits + 1.98 * over + load * (0.155 * bits - 0.77) + 3.79 * part
+                                  : 10.6 + 0.249 * splits + 2.75 * over + load * (0.244 * bits - 1.26) + 1.89 * part;
+        } else {
+            o.narrow = 3.19 + 0.0204 * b + nbc * (0.076 + 0.0021 * b) + turns * (0.38 + nbc * (0.045 + 0.0016 * b + 0.0099 * bits));
+            o.first = batch <= 16 ? 7.51 + 0.217 * splits + 1.90 * over + load * (0.082 * bits - 0.91) + 2.01 * part
+                                  : 7.69 + 0.254 * splits + 1.61 * over + load * (0.072 * bits - 0.43) + 2.15 * part;
+        }
     }
+    if (o.first < 5.2) o.first = 5.2;
+    if (o.narrow < 5.2) o.narrow = 5.2;
     return o;
 }
 
-static bool takes_narrow(const sbits_plan *plan, const MpArgs &a)
+// Up to 16 block columns and two turns of the narrow kernel, where both take hardly more than a launch, it is the better one (up to
+// 16 rows by 3 .. 8 % on average and at most 3 % slower, up to 32 by 5 .. 26 %).
+// Above 32 rows the alternative is the wide kernel, whose estimate is above the launch: 2 us fit best in 128-column blocks, 2.5 in
+// 64 (of 1 .. 5; the better kernel each time is 0.1 % faster, always the wide one 18 % slower).
+static bool takes_narrow(const sbits_plan *plan, const MpArgs &a, const WideSplit &ws)
 {
-    if (a.batch > 16) return false;
+    if (a.batch > 64) return false;
+    if (a.batch <= 32 && a.nbc <= MG_SPAN && a.R / 32 * ((a.batch + 15) / 16) <= 512) return true;
     const FewRows t = few_rows(plan, a.R, a.nbc, a.batch);
-    return t.narrow < t.first;
+    return a.batch > 32 ? t.narrow * 100 < (double)(ws.cost + (plan->n == 128 ? 200 : 250)) : t.narrow <= t.first;
 }
 
 // Rows of x the next launch takes of those that are left: 128 (two batch groups) while a group's byte offsets fit the 32 bits
@@ -1181,14 +1192,15 @@ int sbits_mp_gemm_rows(const sbits_plan *plan, int mat, int64_t ld_x, int left)
     if (left > 64 && left <= 96) {
         const int64_t R = plan->rows[mat];
         const int n = plan->n, nbc = (int)(plan->cols[mat] / n);
-        const FewRows t = few_rows(plan, R, nbc, left - 64 < 16 ? left - 64 : 16);
-        const int64_t rest = left - 64 > 16 ? t.first * 5 / 4 : t.narrow < t.first ? t.narrow : t.first;
+        const FewRows t = few_rows(plan, R, nbc, left - 64);
+        const int64_t rest = (int64_t)((t.narrow < t.first ? t.narrow : t.first) * 100);
         if (wide_split(R, nbc, n, 64).cost + rest + 300 <= wide_split(R, nbc, n, left).cost) return 64;
     }
     return left < 128 ? left : 128;
 }
 
-int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t ld_x, int batch,
+// fine: rows of a product of more than 32, whose codes enter with the smaller offset in every kernel
+int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t ld_x, int batch, bool fine,
                          const uint8_t *level, const int64_t *byte_off, const uint8_t *codes, const float *scale,
                          const float *zero, float *y, void *scratch)
 {
@@ -1201,25 +1213,44 @@ int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t 
     a.batch = batch;
     const bool wide = batch > 32;
     const WideSplit ws = wide ? wide_split(a.R, a.nbc, plan->n, batch) : WideSplit{0, 0, 0, 0};
-    if (takes_narrow(plan, a)) {
+    for (int c = 0; c < sbits::MAX_CAND; ++c) a.bits[c] = c < plan->K ? plan->bits[c] : plan->bits[plan->K - 1];
+    if (takes_narrow(plan, a, ws)) {
         a.n_split = 1;
         a.out = y;
-        for (int c = 0; c < sbits::MAX_CAND; ++c) a.bits[c] = c < plan->K ? plan->bits[c] : plan->bits[plan->K - 1];
-        auto *fn = plan->n == 128 ? &mp_gemm_narrow_kernel<128> : &mp_gemm_narrow_kernel<64>;
-        hipLaunchKernelGGL(fn, dim3((unsigned)(a.R / 32)), dim3(ND_THREADS), 0, ctx->stream, a);
-        SBITS_HIP(ctx, hipGetLastError());
-        return SBITS_OK;
+        // One turn of the CUs and up to 8 rows: the wait for codes bounds it, and 16 waves ask for more of them at a time
+        // (5504 x 17664 in 64-column blocks, one row: 24.9 us, 30.8 with 8 waves); so too, at any number of rows, where all blocks
+        // of 16 waves are requested at once and of 8 waves only half (25 .. 32 block columns: 2 .. 8 %).  Else workgroups of 8 waves:
+        // 2 .. 8 % with more rows, whose exchange is smaller, and 9 .. 40 % with two turns or more, as one computes while the other on
+        // its CU starts or ends.  The same sums.
+        const bool deep = a.R / 32 * ((batch + 15) / 16) <= 256 && (batch <= 8 || (a.nbc > 24 && a.nbc <= 32));
+        if (fine) return plan->n == 128 ? launch_narrow<128, 8, true>(ctx, a) : launch_narrow<64, 8, true>(ctx, a);
+        if (plan->n == 128) return deep ? launch_narrow<128, 16, false>(ctx, a) : launch_narrow<128, 8, false>(ctx, a);
+        return deep ? launch_narrow<64, 16, false>(ctx, a) : launch_narrow<64, 8, false>(ctx, a);
     }
     a.n_split = wide ? ws.n_split : sbits_mp_gemm_splits(a.C, plan->n);
-    for (int c = 0; c < sbits::MAX_CAND; ++c) a.bits[c] = c < plan->K ? plan->bits[c] : plan->bits[plan->K - 1];
     a.out = a.n_split > 1 ? static_cast<float *>(scratch) : y;
-    const int rows = wide ? ws.rg * 32 : MG_RG * 32;
-    const dim3 grid((unsigned)((a.R + rows - 1) / rows), (unsigned)a.n_split, (unsigned)(wide ? (batch + 63) / 64 : 1));
-    const int nb = batch <= 16 ? 1 : 2;
     int rc;
-    if (wide) rc = ws.rg == 4 ? launch_wide_rg<4>(ctx, plan->n, a, grid, ws.per_split) : launch_wide_rg<2>(ctx, plan->n, a, grid, ws.per_split);
-    else if (plan->n == 128) rc = nb == 1 ? launch_mp<128, 1>(ctx, a, grid) : launch_mp<128, 2>(ctx, a, grid);
-    else rc = nb == 1 ? launch_mp<64, 1>(ctx, a, grid) : launch_mp<64, 2>(ctx, a, grid);
+    if (wide) {
+        const int rows = ws.rg * 32;
+        const dim3 grid((unsigned)((a.R + rows - 1) / rows), (unsigned)a.n_split, (unsigned)((batch + 63) / 64));
+        rc = ws.rg == 4 ? launch_wide_rg<4>(ctx, plan->n, a, grid, ws.per_split) : launch_wide_rg<2>(ctx, plan->n, a, grid, ws.per_split);
+    } else {
+        // Channels of a workgroup: x takes 32 .. 128 KiB of LDS, and as many waves as the registers allow (16) should be on a
+        // CU.  64-column blocks up to 16 rows: four workgroups of 32 channels.  Else 64 (128 with 128 KiB of x), and half as
+        // many where all workgroups are on the chip at once even so: 15872 x 2048 at 18 rows 11.5 -> 9.1 us with 64, 19584 x 896 at
+        // 21 rows 9.4 -> 13.6; 2560 x 6784 at 2 rows 10.1 -> 9.3 with 32, 8096 x 7552 11.6 -> 14.1.  The same sums.
+        const int64_t wgs32 = (int64_t)(a.R / 32) * a.n_split, wgs64 = (int64_t)((a.R + 63) / 64) * a.n_split;
+        if (fine) {                                           // (the last rows of a large product: many workgroups)
+            if (plan->n == 128) rc = batch <= 16 ? launch_mp<128, 1, 2, true>(ctx, a) : launch_mp<128, 2, 4, true>(ctx, a);
+            else rc = batch <= 16 ? launch_mp<64, 1, 1, true>(ctx, a) : launch_mp<64, 2, 2, true>(ctx, a);
+        } else if (plan->n == 128) {
+            if (batch <= 16) rc = wgs32 <= 512 ? launch_mp<128, 1, 1, false>(ctx, a) : launch_mp<128, 1, 2, false>(ctx, a);
+            else rc = wgs64 <= 256 ? launch_mp<128, 2, 2, false>(ctx, a) : launch_mp<128, 2, 4, false>(ctx, a);
+        } else {
+            if (batch <= 16) rc = launch_mp<64, 1, 1, false>(ctx, a);
+            else rc = wgs32 <= 256 ? launch_mp<64, 2, 1, false>(ctx, a) : launch_mp<64, 2, 2, false>(ctx, a);
+        }
+    }
     if (rc) return rc;
     if (a.n_split > 1) {
         const int64_t n = (int64_t)batch * a.R;

@@ -135,7 +135,7 @@ int sbits_launch_dequant(sbits_plan *plan, int mat, const uint8_t *level, const 
 bool sbits_mp_gemm_shapes_ok(const sbits_plan *plan);
 size_t sbits_mp_gemm_ws_bytes(const sbits_plan *plan);
 int sbits_mp_gemm_rows(const sbits_plan *plan, int mat, int64_t ld_x, int left);
-int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t ld_x, int batch,
+int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t ld_x, int batch, bool fine,
                          const uint8_t *level, const int64_t *byte_off, const uint8_t *codes, const float *scale,
                          const float *zero, float *y, void *scratch);
 int sbits_run_propose(sbits_plan *plan, const float *s_up, const float *s_down, const uint8_t *level_in,
