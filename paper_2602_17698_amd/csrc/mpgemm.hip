@@ -856,12 +856,14 @@ void mp_gemm_wide_kernel(MpArgs a, int cols_per_split)
 
 // ================================================================ few batch rows
 // Few rows of x are small next to the codes, so nothing is staged and no columns are split off: a workgroup takes 32
-// channels, 16 rows of x and all columns, its 8 or 16 waves every 8th or 16th block column each, with x straight from the
-// caches into the operand registers, two blocks in flight, and one exchange through LDS at the end.  Against the first kernel
-// this takes the second launch, the partial sums in memory and the wait for x out, and a small matrix has more CUs; the price is x read
-// once per 32 channels, and codes once per 16 rows.  Products as there, in its column order; a wave of 8 keeps two sums, so
-// that there are the same sixteen partial sums either way.  Latency bounds it: level and offset, then codes, then the
-// exchange; with many rows and turns, x from L2.
+// channels, 16 rows of x and all columns, its 8 or 16 waves every 8th or 16th block column each, codes of two blocks in flight,
+// and one exchange through LDS at the end.  Against the first kernel this takes the second launch, the partial sums in memory
+// and the wait for x out, and a small matrix has more CUs; the price is x read once per 32 channels, and codes once per 16 rows.
+// Products as there, in its column order; a wave of 8 keeps two sums, so that there are the same sixteen partial sums either way.
+// Up to 4 rows the operands of x come straight from the caches.  With more, a lane's operand is 16 bytes of a row of its own:
+// 64 lanes, 64 lines, and the L1 takes a line a clock.  There whole rows are read (16 lanes 256 bytes) and change lanes in LDS,
+// private to the wave: 8192 x 8192 at 16 rows 15.7 -> 12.6 us.  Latency bounds it: level and offset, then codes, then
+// the exchange; with several turns, vector issue (unpacking) and L2.
 // 1024 x 4096, bitwidths 1 .. 4, one row: 11.3 -> 5.8 us; 4096 x 4096, 4 bits: 11.2 -> 5.9.  17 .. 32 rows, which all took
 // the first kernel before: 1984 x 3328 at 26 rows 16.1 -> 8.2 us, 2112 x 1856 in 64-column blocks at 23 rows 14.9 -> 6.2.
 
@@ -879,16 +881,31 @@ __device__ __forceinline__ bf16x8_t x_held(const u32x4_t (&x)[KL / 8], int st)
     }
 }
 
-template <int C, int N_COLS, bool FINE>
+// the same from LDS: piece st of the lane's row lies at base ^ 16 st
+template <int C, int KL>
+__device__ __forceinline__ bf16x8_t x_in_lds(const unsigned char *lds, uint32_t base, int st)
+{
+    if constexpr (!PairOrder<C, KL>::value) {
+        return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t *>(lds + (base ^ (uint32_t)(16 * st))));
+    } else {
+        const int ea = C == 4 ? 8 * st : C == 2 ? 16 * (st >> 1) + 4 * (st & 1) : 4 * st, eb = ea + 16 / C;
+        const u32x2_t wa = *reinterpret_cast<const u32x2_t *>(lds + (base ^ (uint32_t)(2 * ea)));
+        const u32x2_t wb = *reinterpret_cast<const u32x2_t *>(lds + (base ^ (uint32_t)(2 * eb)));
+        return as_bf16x8(__builtin_amdgcn_perm(wb.x, wa.x, 0x05040100u), __builtin_amdgcn_perm(wb.x, wa.x, 0x07060302u),
+                         __builtin_amdgcn_perm(wb.y, wa.y, 0x05040100u), __builtin_amdgcn_perm(wb.y, wa.y, 0x07060302u));
+    }
+}
+
+template <int C, int N_COLS, bool FINE, typename X>
 __device__ __forceinline__ void narrow_block(const uint32_t (&cw)[2][8], const float (&sc)[2], const float (&ze)[2],
-                                             const u32x4_t (&x)[N_COLS / 32], f32x4v_t (&acc)[2])
+                                             const X &x, f32x4v_t (&acc)[2])
 {
     constexpr int KL = N_COLS / 4;
     const bf16x8_t ones = as_bf16x8(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
     f32x4v_t d[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}}, d1 = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int st = 0; st < N_COLS / 32; ++st) {
-        const bf16x8_t xa = x_held<C, KL>(x, st);
+        const bf16x8_t xa = x.template operand<C>(st);
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             bf16x8_t b;
@@ -907,14 +924,29 @@ __device__ __forceinline__ void narrow_block(const uint32_t (&cw)[2][8], const f
     }
 }
 
-template <int N_COLS, int WAVES, bool FINE>
+template <int KL>
+struct HeldX {
+    const u32x4_t (&x)[KL / 8];
+    template <int C> __device__ __forceinline__ bf16x8_t operand(int st) const { return x_held<C, KL>(x, st); }
+};
+template <int KL>
+struct StagedX {
+    const unsigned char *lds;
+    uint32_t base;
+    template <int C> __device__ __forceinline__ bf16x8_t operand(int st) const { return x_in_lds<C, KL>(lds, base, st); }
+};
+
+template <int N_COLS, int WAVES, bool FINE, bool STAGED>
 __global__ __launch_bounds__((64 * WAVES), 4)
 void mp_gemm_narrow_kernel(MpArgs a)
 {
     static_assert(WAVES == 8 || WAVES == 16, "sixteen partial sums");
     constexpr int SUMS = 16 / WAVES;                          // of a wave: the columns wave + WAVES s + 16 i
-    __shared__ float red[16][2][4][64];
     constexpr int KL = N_COLS / 4, XL = KL / 8;
+    constexpr int ROW = N_COLS / 8;                           // 16-byte pieces of a row of x in a block column
+    constexpr int X_BYTES = STAGED ? WAVES * 16 * ROW * 16 : 0, RED_BYTES = 16 * 2 * 4 * 64 * 4;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[X_BYTES > RED_BYTES ? X_BYTES : RED_BYTES];
+    float (*const red)[2][4][64] = reinterpret_cast<float (*)[2][4][64]>(smem);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, g = lane >> 4;
@@ -927,11 +959,19 @@ void mp_gemm_narrow_kernel(MpArgs a)
     const int lvl = a.level[blk0 + mine];
     const int64_t off = a.byte_off[blk0 + mine];
     const int nt = (a.nbc - wave + WAVES - 1) / WAVES;  // 0 or less: none
-    const uint16_t *const xrow = a.x + (int64_t)(batch0 + min(li, batch - 1)) * a.ld_x + g * KL;   // (rows past the batch: not stored)
+    // x: a lane's own operand (rows past the batch as the last one: not stored), or (STAGED) pieces of whole rows, by way of the
+    // wave's LDS: piece c of row b at position c ^ b (64 columns: c ^ b / 2), so that 16 rows' same pieces lie in 16 different
+    // quarters of the banks
+    const uint16_t *const x0 = a.x + (int64_t)batch0 * a.ld_x, *const xrow = x0 + (int64_t)min(li, batch - 1) * a.ld_x + g * KL;
+    const uint32_t x_at = 2u * (uint32_t)(lane / ROW) * (uint32_t)a.ld_x + 16u * (uint32_t)(lane % ROW);      // bytes
+    const uint32_t x_step = 2u * (64 / ROW) * (uint32_t)a.ld_x, x_end = 2u * ((uint32_t)(min(batch, 16) - 1) * (uint32_t)a.ld_x + (uint32_t)a.C);
+    unsigned char *const xl = smem + (STAGED ? wave * 16 * ROW * 16 : 0);
+    const uint32_t x_to = (uint32_t)(lane * 16) ^ (uint32_t)((lane >> 4) * 16);
+    const uint32_t x_from = (uint32_t)(li * ROW + ((g * XL) ^ (N_COLS == 128 ? li : li >> 1))) * 16;
     const uint32_t lane_units = (uint32_t)((rin + li) * (N_COLS / 8) + g * (KL / 8));   // x c = the lane's byte offset in the block
     const uint32_t block_bytes_per_bit = (uint32_t)a.m * (N_COLS / 8);
 
-    struct Slot { Quarter<N_COLS> q[2]; float sc[2], ze[2]; u32x4_t x[XL]; int c; };
+    struct Slot { Quarter<N_COLS> q[2]; float sc[2], ze[2]; u32x4_t x[STAGED ? 1 : XL]; int c; };
     auto request = [&](Slot &o, int t) {
         const int tt = min(t, nt - 1), J = wave + WAVES * tt;
         const int lv = __builtin_amdgcn_readlane(lvl, tt);
@@ -945,12 +985,37 @@ void mp_gemm_narrow_kernel(MpArgs a)
         const float *ps = a.scale + (blk0 + J) * a.m + rin, *pz = a.zero + (blk0 + J) * a.m + rin;
 #pragma unroll
         for (int tl = 0; tl < 2; ++tl) load_quarter<N_COLS>(rs, (lane_units + (uint32_t)(tl * 16 * (N_COLS / 8))) * (uint32_t)o.c, o.q[tl]);
+        if constexpr (!STAGED) {
 #pragma unroll
-        for (int i = 0; i < XL; ++i) o.x[i] = *(const __attribute__((address_space(1))) u32x4_t *)(xrow + J * N_COLS + 8 * i);
+            for (int i = 0; i < XL; ++i) o.x[i] = *(const __attribute__((address_space(1))) u32x4_t *)(xrow + J * N_COLS + 8 * i);
+        }
 #pragma unroll
         for (int tl = 0; tl < 2; ++tl) {
             o.sc[tl] = ps[16 * tl + li];
             o.ze[tl] = pz[16 * tl + li];
+        }
+    };
+    // STAGED: x of one block at a time on the way (it comes from the caches); what lies past the rows reads as zero
+    u32x4_t xr[STAGED ? XL : 1];
+    auto request_x = [&](int t) {
+        if constexpr (STAGED) {
+            const int J = wave + WAVES * min(t, nt - 1);
+            const rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(x0 + J * N_COLS), 0, (int)(x_end - 2u * (uint32_t)(J * N_COLS)), 0x00027000);
+#pragma unroll
+            for (int i = 0; i < XL; ++i) xr[i] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(x_at + (uint32_t)i * x_step), 0, 0));
+        }
+    };
+    auto stage_x = [&]() {
+        if constexpr (STAGED) {
+            // (a wave's LDS accesses are done in order: the fences keep the compiler to it)
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            uint32_t to = x_to;                               // (addresses made here, not kept for all blocks)
+            asm volatile("" : "+v"(to));
+#pragma unroll
+            for (int i = 0; i < XL; ++i) *reinterpret_cast<u32x4_t *>(xl + (to ^ (uint32_t)(i * (1024 + 64)))) = xr[i];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
         }
     };
     f32x4v_t sums[SUMS][2];
@@ -968,21 +1033,35 @@ void mp_gemm_narrow_kernel(MpArgs a)
 #pragma unroll
             for (int i = 0; i < N_COLS / 16; ++i) cw[tl][i] = r[i];
         }
-#define ND_BLOCK(C) narrow_block<C, N_COLS, FINE>(cw, o.sc, o.ze, o.x, acc)
-        WG_SWITCH(o.c, ND_BLOCK)
+        if constexpr (STAGED) {
+            uint32_t from = x_from;                           // (addresses made here, not kept for all blocks)
+            asm volatile("" : "+v"(from));
+            const StagedX<KL> x{xl, from};
+#define ND_BLOCK(C) narrow_block<C, N_COLS, FINE>(cw, o.sc, o.ze, x, acc)
+            WG_SWITCH(o.c, ND_BLOCK)
+        } else {
+            const HeldX<KL> x{o.x};
+            WG_SWITCH(o.c, ND_BLOCK)
 #undef ND_BLOCK
+        }
     };
     if (nt > 0) {
         Slot s0, s1;
         request(s0, 0);
+        request_x(0);
         request(s1, 1);
         for (int t = 0; t < nt; t += 2) {
+            stage_x();
+            request_x(t + 1);
             add(s0, sums[0]);
             if (t + 2 < nt) request(s0, t + 2);
+            stage_x();
+            if (t + 2 < nt) request_x(t + 2);
             add(s1, sums[SUMS - 1]);
             if (t + 2 < nt) request(s1, t + 3);
         }
     }
+    if constexpr (STAGED) __syncthreads();                    // every wave is done with its x
 #pragma unroll
     for (int s = 0; s < SUMS; ++s)
 #pragma unroll
@@ -1092,11 +1171,11 @@ static int launch_mp(sbits_ctx *ctx, const MpArgs &a)
     return SBITS_OK;
 }
 
-template <int N_COLS, int WAVES, bool FINE>
+template <int N_COLS, int WAVES, bool FINE, bool STAGED>
 static int launch_narrow(sbits_ctx *ctx, const MpArgs &a)
 {
     const dim3 grid((unsigned)(a.R / 32), (unsigned)((a.batch + 15) / 16));
-    hipLaunchKernelGGL((mp_gemm_narrow_kernel<N_COLS, WAVES, FINE>), grid, dim3(64 * WAVES), 0, ctx->stream, a);
+    hipLaunchKernelGGL((mp_gemm_narrow_kernel<N_COLS, WAVES, FINE, STAGED>), grid, dim3(64 * WAVES), 0, ctx->stream, a);
     SBITS_HIP(ctx, hipGetLastError());
     return SBITS_OK;
 }
@@ -1145,22 +1224,22 @@ static FewRows few_rows(const sbits_plan *plan, int64_t R, int nbc, int batch)
     FewRows o;
     if (splits == 1) {
         if (wide) {
-            o.narrow = 5.55 + 0.01 * nbc + turns * (0.06 + nbc * (0.0103 * b + 0.022 * bits - 0.045));
+            o.narrow = 5.27 + 0.0325 * nbc + turns * (0.364 + nbc * (0.0065 * b + 0.0105 * bits - 0.0152));
             o.first = batch <= 16 ? 5.62 + 0.032 * nbc + over * (0.28 + nbc * (0.048 + 0.020 * bits))
                                   : 6.45 + 0.15 * nbc + over * (0.67 + nbc * (0.044 * bits - 0.071));
         } else {
-            o.narrow = 5.43 + 0.015 * nbc + turns * (0.16 + nbc * (0.0079 * b + 0.0076 * bits - 0.033));
+            o.narrow = 5.53 + 0.0064 * nbc + turns * (0.353 + nbc * (0.0044 * b + 0.0034 * bits - 0.0085));
             o.first = batch <= 16 ? 5.68 + 0.003 * nbc + over * (nbc * (0.045 + 0.0079 * bits) - 0.23)
                                   : 5.45 + 0.058 * nbc + over * (0.55 + nbc * (0.055 + 0.0087 * bits));
         }
     } else {
         const double part = (double)batch * (double)R * splits * 1e-6;        // partial sums, millions
         if (wide) {
-            o.narrow = 3.44 + 0.0143 * b + nbc * (0.092 + 0.0046 * b) + turns * (0.61 + nbc * (0.054 + 0.0033 * b + 0.0116 * bits));
+            o.narrow = 3.34 + 0.0333 * b + nbc * (0.101 + 0.0006 * b) + turns * (0.73 + nbc * (0.0503 + 0.0011 * b + 0.011 * bits));
             o.first = batch <= 16 ? 7.75 + 0.236 * splits + 1.98 * over + load * (0.155 * bits - 0.77) + 3.79 * part
                                   : 10.6 + 0.249 * splits + 2.75 * over + load * (0.244 * bits - 1.26) + 1.89 * part;
         } else {
-            o.narrow = 3.19 + 0.0204 * b + nbc * (0.076 + 0.0021 * b) + turns * (0.38 + nbc * (0.045 + 0.0016 * b + 0.0099 * bits));
+            o.narrow = 3.32 + 0.033 * b + nbc * 0.0775 + turns * (0.40 + nbc * (0.0448 + 0.0005 * b + 0.0101 * bits));
             o.first = batch <= 16 ? 7.51 + 0.217 * splits + 1.90 * over + load * (0.082 * bits - 0.91) + 2.01 * part
                                   : 7.69 + 0.254 * splits + 1.61 * over + load * (0.072 * bits - 0.43) + 2.15 * part;
         }
@@ -1172,14 +1251,14 @@ static FewRows few_rows(const sbits_plan *plan, int64_t R, int nbc, int batch)
 
 // Up to 16 block columns and two turns of the narrow kernel, where both take hardly more than a launch, it is the better one (up to
 // 16 rows by 3 .. 8 % on average and at most 3 % slower, up to 32 by 5 .. 26 %).
-// Above 32 rows the alternative is the wide kernel, whose estimate is above the launch: 2 us fit best in 128-column blocks, 2.5 in
-// 64 (of 1 .. 5; the better kernel each time is 0.1 % faster, always the wide one 18 % slower).
+// Above 32 rows the alternative is the wide kernel, whose estimate is above the launch: 2.5 us fit best (of 1 .. 5; always the wide one:
+// 18 % slower).  A pitch of x past the 32-bit offsets of the narrow kernel: the first.
 static bool takes_narrow(const sbits_plan *plan, const MpArgs &a, const WideSplit &ws)
 {
-    if (a.batch > 64) return false;
+    if (a.batch > 64 || a.ld_x > 1 << 25) return false;
     if (a.batch <= 32 && a.nbc <= MG_SPAN && a.R / 32 * ((a.batch + 15) / 16) <= 512) return true;
     const FewRows t = few_rows(plan, a.R, a.nbc, a.batch);
-    return a.batch > 32 ? t.narrow * 100 < (double)(ws.cost + (plan->n == 128 ? 200 : 250)) : t.narrow <= t.first;
+    return a.batch > 32 ? t.narrow * 100 < (double)(ws.cost + 250) : t.narrow <= t.first;
 }
 
 // Rows of x the next launch takes of those that are left: 128 (two batch groups) while a group's byte offsets fit the 32 bits
@@ -1217,15 +1296,21 @@ int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t 
     if (takes_narrow(plan, a, ws)) {
         a.n_split = 1;
         a.out = y;
-        // One turn of the CUs and up to 8 rows: the wait for codes bounds it, and 16 waves ask for more of them at a time
-        // (5504 x 17664 in 64-column blocks, one row: 24.9 us, 30.8 with 8 waves); so too, at any number of rows, where all blocks
-        // of 16 waves are requested at once and of 8 waves only half (25 .. 32 block columns: 2 .. 8 %).  Else workgroups of 8 waves:
-        // 2 .. 8 % with more rows, whose exchange is smaller, and 9 .. 40 % with two turns or more, as one computes while the other on
-        // its CU starts or ends.  The same sums.
-        const bool deep = a.R / 32 * ((batch + 15) / 16) <= 256 && (batch <= 8 || (a.nbc > 24 && a.nbc <= 32));
-        if (fine) return plan->n == 128 ? launch_narrow<128, 8, true>(ctx, a) : launch_narrow<64, 8, true>(ctx, a);
-        if (plan->n == 128) return deep ? launch_narrow<128, 16, false>(ctx, a) : launch_narrow<128, 8, false>(ctx, a);
-        return deep ? launch_narrow<64, 16, false>(ctx, a) : launch_narrow<64, 8, false>(ctx, a);
+        // Workgroups of 16 waves while all of them are on the chip at once, one a CU (against 8 waves 2 .. 14 % faster): more codes
+        // on their way; beyond that two workgroups of 8 waves, one of which computes while the other starts or ends (up to 25 %
+        // faster).  x by way of LDS from 5 rows on: at 1 and 2 rows it costs 2 .. 6 %, at 3 and 4 it gives -2 .. 3, at 9 .. 16 3 .. 19, at 17
+        // and more 3 .. 22 %.  The same sums all ways.
+        const bool deep = a.R / 32 * ((batch + 15) / 16) <= 256;
+        if (fine) {
+            if (plan->n == 128) return deep ? launch_narrow<128, 16, true, true>(ctx, a) : launch_narrow<128, 8, true, true>(ctx, a);
+            return deep ? launch_narrow<64, 16, true, true>(ctx, a) : launch_narrow<64, 8, true, true>(ctx, a);
+        }
+        if (batch > 4) {
+            if (plan->n == 128) return deep ? launch_narrow<128, 16, false, true>(ctx, a) : launch_narrow<128, 8, false, true>(ctx, a);
+            return deep ? launch_narrow<64, 16, false, true>(ctx, a) : launch_narrow<64, 8, false, true>(ctx, a);
+        }
+        if (plan->n == 128) return deep ? launch_narrow<128, 16, false, false>(ctx, a) : launch_narrow<128, 8, false, false>(ctx, a);
+        return deep ? launch_narrow<64, 16, false, false>(ctx, a) : launch_narrow<64, 8, false, false>(ctx, a);
     }
     a.n_split = wide ? ws.n_split : sbits_mp_gemm_splits(a.C, plan->n);
     a.out = a.n_split > 1 ? static_cast<float *>(scratch) : y;

@@ -1,6 +1,6 @@
-"""The kernels for few rows at the edges of their choices: 16 and 8 waves a workgroup (one turn of the chip, up to 8 rows or
-25 .. 32 block columns), one to four groups of 16 rows with a ragged last one, 32, 64 and 128 channels a workgroup of the
-kernel with column splits, a pitch, pruned blocks, every bitwidth.  Bound as for the other products: terms of size
+"""The kernels for few rows at the edges of their choices: 16 and 8 waves a workgroup (one turn of the chip), x straight from
+memory (up to 4 rows) and by way of LDS, one to four groups of 16 rows with a ragged last one, 32, 64 and 128 channels a
+workgroup of the kernel with column splits, a pitch, pruned blocks, every bitwidth.  Bound as for the other products: terms of size
 |B| scale |x| and |zero| |x| in fp32, where the codes' offset is 128 (up to 32 rows) or 2^c (more rows, bitwidths up to 5):
 2^-22 of their sum for the largest error, 2^-24 for the root mean square."""
 import numpy as np
@@ -16,13 +16,17 @@ ALL = [1, 2, 3, 4, 5, 6, 7, 8]
 
 
 @pytest.mark.parametrize("R,C,m,n,bits,batch,pad", [
-    (8192, 128 * 17, 128, 128, ALL, 8, 0),                # 256 workgroups: 16 waves
-    (8224, 128 * 17, 32, 128, [2, 5], 8, 8),              # 257: 8 waves
-    (64, 128 * 17, 32, 128, [0] + ALL, 9, 0),             # 9 rows: 8 waves
-    (64, 128 * 24, 32, 128, ALL, 16, 0),                  # three blocks a wave of 8
-    (64, 128 * 25, 32, 128, ALL, 16, 8),                  # two of 16
+    (8192, 128 * 17, 128, 128, ALL, 4, 0),                # 256 workgroups: 16 waves, x from memory
+    (8192, 128 * 17, 128, 128, [1, 2, 4, 7], 5, 8),       # by way of LDS
+    (8224, 128 * 17, 32, 128, [2, 5], 4, 8),              # 257: 8 waves
+    (8224, 128 * 17, 32, 128, [0] + ALL, 5, 0),
+    (8224, 64 * 20, 32, 64, ALL, 4, 0),
+    (8224, 64 * 20, 32, 64, [0] + ALL, 13, 24),
+    (64, 128 * 17, 32, 128, [0] + ALL, 9, 0),
+    (64, 128 * 24, 32, 128, ALL, 16, 0),
     (64, 128 * 33, 32, 128, ALL, 15, 0),
     (96, 64 * 25, 32, 64, [0] + ALL, 16, 0),
+    (96, 64 * 25, 32, 64, ALL, 3, 8),
     (32, 64 * 512, 32, 64, [1, 3], 16, 0),                # the widest row: 64 blocks a wave
     (96, 64 * 7, 32, 64, ALL, 17, 8),                     # a second group of one row
     (64, 128 * 9, 32, 128, [0] + ALL, 31, 0),
@@ -30,6 +34,8 @@ ALL = [1, 2, 3, 4, 5, 6, 7, 8]
     (64, 128 * 5, 32, 128, ALL, 33, 8),                   # three groups: more than 32 rows
     (96, 64 * 40, 32, 64, [0] + ALL, 47, 0),
     (64, 64 * 3, 64, 64, [1, 2, 4], 64, 0),
+    (4128, 128 * 4, 32, 128, ALL, 33, 0),                 # three groups, two turns
+    (4128, 64 * 5, 32, 64, ALL, 48, 8),
     (16416, 128 * 3, 32, 128, [3, 8], 16, 0),             # 513 workgroups of 32 channels: 64 each
     (4128, 128 * 65, 32, 128, [1, 2], 16, 0),             # column splits, ragged last workgroup
     (8192, 128 * 10, 64, 128, ALL, 32, 0),                # two groups, two turns
