@@ -1202,15 +1202,14 @@ static int launch_wide_rg(sbits_ctx *ctx, int n, const MpArgs &a, dim3 grid, int
     return a.batch <= 48 ? launch_wide<128, 3, RG>(ctx, a, grid, cols_per_split) : launch_wide<128, 4, RG>(ctx, a, grid, cols_per_split);
 }
 
-// What a product takes in the first kernel (up to 32 rows) and in the narrow one (up to 64), in microseconds, fitted to 2600
-// products of 256 .. 28672 x 256 .. 28672, 1 .. 64 rows of x, bitwidths up to 8: with the choice made by these the products
-// take 0.4 % longer than with the better kernel each time (always the first 10 %, always the narrow one 18 %); no product
+// What a product takes in the first kernel (up to 32 rows) and in the narrow one (up to 64), in microseconds, fitted to 2600 and
+// 900 products of 256 .. 28672 x 256 .. 28672, 1 .. 64 rows of x, bitwidths up to 8: with the choice made by these the products
+// take 0.3 .. 2 % longer than with the better kernel each time (always the first 10 %, always the narrow one 18 %); no product
 // takes less than a launch, 5.2.
 // First: by the turns of the CUs (32 channels and 16 block columns each, 256 at a time) and their bytes; with several column
 // splits, their number, the partial sums and the second launch (1024 x 17216 in 64-column blocks, 17 splits, 12.5 us).
 // Narrow: by turns of 256 workgroups and block columns in each, x once more per turn; with 17 rows or more a workgroup per
-// 16 of them (26368 x 1024 at 29 rows: 10.8 us in the first kernel and 19.9 in this one; 256 .. 8192 x 2048 5.5 .. 8 in this one and 9 .. 12
-// in the first).
+// 16 of them (4096 x 4096 at 32 rows: 11.5 us in the first kernel and 6.9 in this one; 14336 x 4096 15.5 and 17.8).
 struct FewRows { double first, narrow; };
 static FewRows few_rows(const sbits_plan *plan, int64_t R, int nbc, int batch)
 {
@@ -1238,6 +1237,9 @@ static FewRows few_rows(const sbits_plan *plan, int64_t R, int nbc, int batch)
             o.narrow = 3.34 + 0.0333 * b + nbc * (0.101 + 0.0006 * b) + turns * (0.73 + nbc * (0.0503 + 0.0011 * b + 0.011 * bits));
             o.first = batch <= 16 ? 7.75 + 0.236 * splits + 1.98 * over + load * (0.155 * bits - 0.77) + 3.79 * part
                                   : 10.6 + 0.249 * splits + 2.75 * over + load * (0.244 * bits - 1.26) + 1.89 * part;
+            // at a draw the first: full turns and whole column splits make it faster than fitted (8192 x 8192 at 32 rows 17.5 us, 19
+            // to 21 in the narrow one; with the margin 0.6 % behind the better kernel, 1.4 % without)
+            if (batch > 16 && turns > 0) o.narrow *= 1.12;
         } else {
             o.narrow = 3.32 + 0.033 * b + nbc * 0.0775 + turns * (0.40 + nbc * (0.0448 + 0.0005 * b + 0.0101 * bits));
             o.first = batch <= 16 ? 7.51 + 0.217 * splits + 1.90 * over + load * (0.082 * bits - 0.91) + 2.01 * part
