@@ -120,6 +120,10 @@ int sbits_plan_create(sbits_ctx *ctx, const int64_t *rows, const int64_t *cols, 
     }
     if (p->N > (1ll << 24) || score_wgs > 0x7fffffff) { delete p; return SBITS_ERR_BAD_SHAPE; }   // index field of the selection keys
     p->score_wg_start.push_back((int)score_wgs);
+    sbits_cost_tables(p);
+    sbits_pack_tables(p);
+    sbits_fused_tables(p);
+    sbits_gather_tables(p);
     size_t ws = sbits_reorder_ws_bytes(p->sum_rows + p->sum_cols, p->sum_rowpart, p->sum_colpart);
     const size_t a = sbits_alloc_ws_bytes(p->N), o = sbits_offsets_ws_bytes(p->N);
     if (a > ws) ws = a;
@@ -207,14 +211,19 @@ int sbits_upload_head(sbits_plan *plan, const sbits_matrix *mats, const sbits_co
     auto table = [&](char *img, int slot, const std::vector<int> &t) {
         if (!t.empty()) memcpy(sbits_prefix_ptr(plan, img, slot), t.data(), t.size() * 4);
     };
-    if (!plan->desc_pinned) {
-        sbits_cost_tables(plan);
-        sbits_pack_tables(plan);
-        sbits_fused_tables(plan);
-        sbits_gather_tables(plan);
-        SBITS_HIP(ctx, hipHostMalloc(&plan->desc_pinned, 2 * bytes, hipHostMallocDefault));
+    if (!plan->desc_pinned) {                        // (whole, or as if it had not been tried)
+        void *images;
+        SBITS_HIP(ctx, hipHostMalloc(&images, 2 * bytes, hipHostMallocDefault));
         for (int i = 0; i < 2; ++i) {
-            char *img = static_cast<char *>(plan->desc_pinned) + (size_t)i * bytes;
+            const hipError_t e = hipEventCreateWithFlags(&plan->desc_done[i], hipEventDisableTiming);
+            if (e == hipSuccess) continue;
+            if (i) (void)hipEventDestroy(plan->desc_done[0]);
+            (void)hipHostFree(images);
+            ctx->last_hip = (int)e;
+            return SBITS_ERR_HIP;
+        }
+        for (int i = 0; i < 2; ++i) {
+            char *img = static_cast<char *>(images) + (size_t)i * bytes;
             memset(img, 0, bytes);
             table(img, SLOT_COST_UNITS, plan->cost_unit_start);
             table(img, SLOT_SCORE_WGS, plan->score_wg_start);
@@ -225,9 +234,9 @@ int sbits_upload_head(sbits_plan *plan, const sbits_matrix *mats, const sbits_co
             table(img, SLOT_GATHER_WGS_W, plan->gather_pre_w);
             table(img, SLOT_GATHER_WGS_S, plan->gather_pre_s);
         }
-        for (int i = 0; i < 2; ++i) SBITS_HIP(ctx, hipEventCreateWithFlags(&plan->desc_done[i], hipEventDisableTiming));
         plan->desc_turn = 0;
         plan->desc_used[0] = plan->desc_used[1] = false;
+        plan->desc_pinned = images;
     }
     const int t = plan->desc_turn;
     plan->desc_turn ^= 1;

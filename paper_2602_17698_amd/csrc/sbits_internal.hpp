@@ -108,7 +108,7 @@ int sbits_launch_cost(sbits_ctx *ctx, const void *Wp, const float *Sp, int64_t R
                       int m, int n, const int32_t *bits, int K, float *cost_rows);
 // batched over all matrices of the plan (workspace head already there)
 int sbits_upload_head(sbits_plan *plan, const sbits_matrix *mats, const sbits_coupling *cpl, void *ws, bool guard = true);
-// the tables of the head that follow from the plan's shapes (each left empty if it would not fit 32 bits)
+// the tables of the head that follow from the plan's shapes (each left empty if it would not fit 32 bits); made once, with the plan
 void sbits_cost_tables(sbits_plan *plan);
 void sbits_pack_tables(sbits_plan *plan);
 void sbits_fused_tables(sbits_plan *plan);
