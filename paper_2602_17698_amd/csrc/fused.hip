@@ -106,7 +106,9 @@ void octet_finish_kernel(const float *__restrict__ part, const MatDesc *__restri
 // PARTS = 2 (rows of more than 16384 elements): two workgroups stage the same rows and pack half of the columns each, two chunks
 // per lane as for shorter rows; they are eight apart in the grid, so that they share an L2.  (All columns in one workgroup are
 // four chunks a lane, one row a step, 33 registers spilled: 8192 x 28672 in 382 us, 202 this way.)
-template <int LPG, int CPL, int RS, int TMAX, bool WIDE, int PARTS = 1>
+// MASK: for a device whose 16-bit loads leave the other half of the register as it was (see lds_w_hi); not for the others, because it
+// costs an AND per weight.
+template <int LPG, int CPL, int RS, int TMAX, bool WIDE, int PARTS = 1, bool MASK = false>
 __global__ __launch_bounds__(TMAX, 4)
 void gather_pack_kernel(const MatDesc *__restrict__ descs, const int *__restrict__ members,
                         const int *__restrict__ wg_start, int n_members,
@@ -260,7 +262,10 @@ void gather_pack_kernel(const MatDesc *__restrict__ descs, const int *__restrict
 #pragma unroll
             for (int rs = 0; rs < RS; ++rs)
 #pragma unroll
-                for (int e = 0; e < 8; ++e) w[rs][e] = gw[(TWO ? 0 : c * RS) + rs][e];
+                for (int e = 0; e < 8; ++e) {
+                    w[rs][e] = gw[(TWO ? 0 : c * RS) + rs][e];
+                    if constexpr (MASK) w[rs][e] = __uint_as_float(__float_as_uint(w[rs][e]) & 0xffff0000u);
+                }
             uint32_t half[RS][2];
             float scl[RS], mn[RS];
             quant_pack_rows<LPG, RS>(w, lk[c], lig, half, scl, mn);
@@ -383,6 +388,7 @@ struct FusedPackLaunch {
     float *scale, *zero;
     GridConsts gc;
     bool wide;                // a candidate has more than 4 bits
+    bool mask;                // 16-bit loads into a register half leave the other one as it was
     int64_t cols;
     int opu;
     const unsigned *aborted;
@@ -392,7 +398,8 @@ template <int LPG, int CPL, int RS, int TMAX, int PARTS = 1>
 static int launch_gpack_g(sbits_ctx *ctx, const FusedPackLaunch &a)
 {
     const int T = fused_threads(a.cols, CPL * PARTS, TMAX);
-    auto *fn = a.wide ? &gather_pack_kernel<LPG, CPL, RS, TMAX, true, PARTS> : &gather_pack_kernel<LPG, CPL, RS, TMAX, false, PARTS>;
+    auto *fn = a.mask ? &gather_pack_kernel<LPG, CPL, RS, TMAX, true, PARTS, true>
+             : a.wide ? &gather_pack_kernel<LPG, CPL, RS, TMAX, true, PARTS> : &gather_pack_kernel<LPG, CPL, RS, TMAX, false, PARTS>;
     SBITS_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, 159 * 1024));
     const size_t lds = (PARTS == 1 ? 2 : 1) * staged_step_bytes(a.cols, RS, false);
@@ -458,8 +465,8 @@ size_t sbits_fused_ws_bytes(const sbits_plan *plan)
     return octet_partial_bytes(plan) + spill;
 }
 
-// The kernels rely on 16-bit register-half loads filling the other half with
-// zeros (the device's target id says "sramecc+").  (That every source row starts on a 16-byte boundary,
+// The cost and surrogate kernels rely on 16-bit register-half loads filling the other half with
+// zeros (the device's target id says "sramecc+"); packing has instances that do not.  (That every source row starts on a 16-byte boundary,
 // which the row loads need, is a rule of every entry point that takes matrices: checked there.)
 bool sbits_fused_layout_ok(const sbits_plan *plan)
 {
@@ -585,7 +592,7 @@ int sbits_launch_gather_pack_all(sbits_plan *plan, const int32_t *row_perm, cons
                                  float *zero, void *ws, const unsigned *aborted)
 {
     sbits_ctx *ctx = plan->ctx;
-    if (!sbits_fused_shapes_ok(plan) || !sbits_fused_layout_ok(plan)) return SBITS_ERR_BAD_SHAPE;
+    if (!sbits_fused_shapes_ok(plan)) return SBITS_ERR_BAD_SHAPE;
     const int *d_mem, *d_pre;
     int rc0 = fused_classes(plan, ws, &d_mem, &d_pre);
     if (rc0) return rc0;
@@ -598,6 +605,7 @@ int sbits_launch_gather_pack_all(sbits_plan *plan, const int32_t *row_perm, cons
     a.m = plan->m;
     a.level = level; a.byte_off = byte_off; a.codes = codes; a.scale = scale; a.zero = zero;
     a.wide = plan->bits[plan->K - 1] > 4;
+    a.mask = !ctx->d16_zero_fill;
     a.aborted = aborted;
     for (const sbits_plan::FusedClass &fc : plan->fused_classes) {
         a.members = d_mem + fc.first;

@@ -70,7 +70,7 @@ static inline size_t staged_step_bytes(int64_t cols, int rs, bool with_s)
 // (d16_hi).  On a GPU whose memories run with error correction (the target id says "sramecc+"; every
 // MI355X does) such a load writes the whole register, zeros below: the register then holds the weight
 // as a float, no conversion instruction needed.  (Without error correction the lower half would keep
-// its old contents: the library refuses the one-pass route on such a device.)  The compiler does not
+// its old contents: the library refuses the one-pass route on such a device, and the packing kernel masks it.)  The compiler does not
 // see these loads' completion: lds_gather_wait() below stands between them and the first use.
 template <int OFF>
 __device__ __forceinline__ void lds_w_hi(float &w, uint32_t addr)

@@ -1,0 +1,33 @@
+"""Choices that the host makes by the device, on devices that need not be there."""
+from recording_runtime import record
+
+PACK = r"""
+ctx_of = lambda ecc: (device(256, ecc), sb.Context(0, 0))[1]
+out = {}
+for ecc in (1, 0):
+    for n, cols in ((64, 4096), (64, 8192), (128, 16384), (128, 28672)):
+        ctx = ctx_of(ecc)
+        plan = sb.Plan(ctx, [(64, cols)], 32, n, [1, 2, 4])
+        mats = [sb.Matrix(fake(128 * cols), fake(256 * cols), 64, cols, cols, cols)]
+        a = [fake(1 << 24) for _ in range(8)]
+        log()
+        plan.gather_pack_all(mats, a[0], a[1], a[2], a[3], a[4], a[5], a[6], a[7])
+        pack = [line.split()[1] for line in log() if line.startswith("launch")]
+        try:
+            rc = plan.gather_cost_all(mats, a[0], a[1], None, a[2], a[7])
+        except sb.SbitsError as e:
+            rc = e.status
+        out["%d %d %d" % (ecc, n, cols)] = [pack, rc]
+        plan.close()
+        ctx.close()
+answer(out)
+"""
+
+
+def test_packing_of_original_weights_is_for_any_device(tmp_path):
+    """Where 16-bit loads leave half of a register as it was, packing takes the instances that mask it; scoring is refused there."""
+    for key, (pack, cost) in record(tmp_path, PACK).items():
+        ecc = key[0] == "1"
+        assert len(pack) == 1 and "gather_pack_kernel" in pack[0], key
+        assert pack[0].count("Lb1E") == (0 if ecc else 2), key                  # (WIDE and MASK)
+        assert cost == (0 if ecc else -8), key                                  # SBITS_ERR_UNIMPLEMENTED
