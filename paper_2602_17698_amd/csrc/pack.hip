@@ -102,10 +102,11 @@ void tile_scan_kernel(const uint8_t *__restrict__ level, long long N, long long 
 }
 
 // All in one launch, because a launch costs 4.6 us: a workgroup adds up all levels before its tile by itself, 16 a load, four at a
-// time through a byte permute that looks their bitwidths up.  Three launches take 14 us up to 107 k blocks, this one 4.5
-// for a few, 9 for 52 k.  The line is where the last workgroup reads half a megabyte.
+// time through a byte permute that looks their bitwidths up.  One launch against three, calls one behind the other: 1 k blocks
+// 3.7 and 8.5 us, 33 k 7.4 and 9.7, 106 k 8.8 and 9.8, 197 k 9.9 and 10.2, 262 k 10.8 and 10.4, 426 k 13.3 and 11.1, 1 M 22.4 and
+// 15.5: the last workgroup reads all levels, so the line is where that takes what two launches do.
 constexpr int OO_THREADS = 1024, OO_TILE = OO_THREADS * OF_ITEMS;
-constexpr int64_t OO_MAX_BLOCKS = 1 << 19;
+constexpr int64_t OO_MAX_BLOCKS = 3 << 16;
 __global__ __launch_bounds__(OO_THREADS)
 void offsets_kernel(const uint8_t *__restrict__ level, int N, long long Mdiv8, BitsTab bt, int64_t *__restrict__ byte_off,
                     const unsigned *aborted)
@@ -118,7 +119,7 @@ void offsets_kernel(const uint8_t *__restrict__ level, int N, long long Mdiv8, B
     unsigned lo = 0u, hi = 0u;                       // bitwidths of levels 0 .. 3, 4 .. 7
 #pragma unroll
     for (int l = 0; l < 4; ++l) { lo |= (unsigned)bt.bits[l] << (8 * l); hi |= (unsigned)bt.bits[l + 4] << (8 * l); }
-    unsigned before = 0u;                            // (at most 2^19 blocks of 8 bits)
+    unsigned before = 0u;                            // (OO_MAX_BLOCKS blocks of at most 8 bits: far below 2^32)
     const int i0 = t0 + tid * OF_ITEMS;
     u32x2_t own = {0u, 0u};
     if (i0 + OF_ITEMS <= N) __builtin_memcpy(&own, level + i0, 8);

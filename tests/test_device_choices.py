@@ -1,4 +1,4 @@
-"""Choices that the host makes by the device, on devices that need not be there."""
+"""Choices that the host makes by size and by device, on devices that need not be there."""
 from recording_runtime import record
 
 PACK = r"""
@@ -31,3 +31,21 @@ def test_packing_of_original_weights_is_for_any_device(tmp_path):
         assert len(pack) == 1 and "gather_pack_kernel" in pack[0], key
         assert pack[0].count("Lb1E") == (0 if ecc else 2), key                  # (WIDE and MASK)
         assert cost == (0 if ecc else -8), key                                  # SBITS_ERR_UNIMPLEMENTED
+
+
+OFFSETS = r"""
+ctx = sb.Context(0, 0)
+out = {}
+for rows, cols in ((8, 8), (24576, 512), (24584, 512), (26624, 1024), (8192, 4096)):
+    plan = sb.Plan(ctx, [(rows, cols)], 8, 8, [1, 2, 4])
+    log()
+    plan.offsets(fake(1 << 20), fake(1 << 23), fake(1 << 23))
+    out[plan.num_blocks()] = len(log())
+    plan.close()
+answer(out)
+"""
+
+
+def test_offsets_in_one_launch_where_that_is_faster(tmp_path):
+    for n, launches in record(tmp_path, OFFSETS).items():
+        assert launches == (1 if int(n) <= 196608 else 3), n

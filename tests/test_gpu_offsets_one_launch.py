@@ -10,7 +10,7 @@ from paper_2602_17698_amd import binding as sb
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("N", [1, 15, 8191, 8192, 8193, 16384 + 24, 131072, 524288 - 8, 524288, 524288 + 8])
+@pytest.mark.parametrize("N", [1, 15, 8191, 8192, 8193, 16384 + 24, 131072, 196608 - 8, 196608, 196608 + 8, 524288 - 8, 524288, 524288 + 8])
 @pytest.mark.parametrize("bits", [[3], [1, 2, 4, 8], [0, 1, 2, 3, 4, 5, 6, 7, 8]])
 def test_offsets(N, bits):
     print("[case] offsets", N, bits, flush=True)
