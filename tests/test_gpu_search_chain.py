@@ -1,5 +1,8 @@
 """A search is enqueued whole and its result read at the end: it equals the stages called one by one, also when it is stopped by
-max_iters, when it takes several workgroups or the two-pass route, and when another plan of the context had its turn in between."""
+max_iters, when it takes several workgroups or the two-pass route, and when another plan of the context had its turn in between.
+And where its workgroups give up waiting for each other: what was enqueued behind them does nothing, and both are done again."""
+import os
+
 import numpy as np
 import pytest
 
@@ -56,3 +59,39 @@ def test_search_equals_its_stages(m, n, max_iters):
     for p in plans:
         p.close()
     ctx.close()
+
+
+# one pass with rows that two workgroups share, two passes, copies in one pass; offsets in one launch and in three; tables in
+# registers and in memory
+@pytest.mark.parametrize("shapes,m,n", [([(256, 8192), (128, 20480), (192, 4096)], 8, 64), ([(512, 4096), (256, 2048)], 8, 16),
+                                        ([(512, 4096), (64, 1024)], 8, 32), ([(4096, 4096)], 8, 8), ([(8192, 4096 + 64)], 8, 8)])
+def test_search_whose_workgroups_give_up(shapes, m, n):
+    dev = torch.device("cuda:0")
+    bits, avg = [1, 2, 4, 8], 2.9
+    path = sb.variant_path("impatient")
+    assert os.path.exists(path), "build the variant first: python -m paper_2602_17698_amd.build --tests"
+    data = [synth.make_matrix("student_t", r, c, seed=11, tid=2 * i, device=dev) for i, (r, c) in enumerate(shapes)]
+    mats = [sb.matrix(w, s) for w, s in data]
+    prev, got = sb.LIB_PATH, []
+    try:
+        for lib in (prev, path, path):
+            print("[case] search gives up", shapes, n, os.path.basename(lib), flush=True)
+            sb.use_library(lib)
+            ctx = sb.Context(0, torch.cuda.current_stream().cuda_stream)
+            plan = sb.Plan(ctx, shapes, m, n, bits)
+            assert plan.num_blocks() > 2048                  # more than one workgroup
+            ws = torch.empty(plan.workspace_bytes(), dtype=torch.uint8, device=dev)
+            o = outputs(plan, shapes, m, avg, dev)
+            p = {k: t.data_ptr() for k, t in o.items()}
+            out = sb.Outputs(p["rp"], p["cp"], p["w"], p["s"], p["cost"], p["level"], p["off"], p["codes"], o["codes"].numel(),
+                             p["scale"], p["zero"])
+            rc, st = plan.search(mats, avg, out, ws)
+            got.append((rc, st, {k: t.cpu().numpy() for k, t in o.items() if k not in ("w", "s")}))
+            plan.close()
+            ctx.close()
+    finally:
+        sb.use_library(prev)
+    for rc, st, o in got[1:]:
+        assert (rc, st) == got[0][:2]
+        for k, t in o.items():
+            np.testing.assert_array_equal(t, got[0][2][k], err_msg=k)
