@@ -7,7 +7,7 @@ For the tests only (--tests):
   "impatient" -> libscalebits_impatient.so   the search's workgroups give up waiting for each other at once, so that
                                              the single-workgroup search behind it is reached
   "masked" -> libscalebits_masked.so         takes the device for one whose 16-bit loads leave half of a register as it was
-  "late31", "late32" -> ...                  a search that was given up is not repeated: what they find, the resident
+  "noretry" -> libscalebits_noretry.so       a search that was given up is not repeated: what it finds, the resident
                                              workgroups have found
 """
 from __future__ import annotations
@@ -25,8 +25,7 @@ INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 VARIANTS = {"": [], "l1": ["-DSBITS_COST_POWER=1"]}
 TEST_VARIANTS = {"impatient": ["-DSBITS_SPIN_LIMIT=0"],
                  "masked": ["-DSBITS_D16_ZERO_FILL=0"],
-                 "late31": ["-DSBITS_SECOND_TRY=0"],
-                 "late32": ["-DSBITS_SECOND_TRY=0"]}
+                 "noretry": ["-DSBITS_SECOND_TRY=0"]}
 ONLY = {v: ["api.hip" if v == "masked" else "alloc.hip"] for v in TEST_VARIANTS}       # sources a variant compiles anew; the rest are the default build's objects
 SOURCES = ["api.hip", "reorder.hip", "cost.hip", "fused.hip", "fused_copies.hip", "alloc.hip", "pack.hip", "mpgemm.hip", "dequant.hip"]
 

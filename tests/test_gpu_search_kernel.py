@@ -156,33 +156,59 @@ def test_propose_on_levels_over_budget(orc, ctx, dev, N):
     plan.close()
 
 
-@pytest.mark.parametrize("bits_end", [31, 32])
-def test_the_count_of_arrivals_goes_on(orc, dev, bits_end):
-    """A library whose count starts just below 2^31 or 2^32, as after some million exchanges, and that does not repeat a search."""
-    prev, path = sb.LIB_PATH, sb.variant_path("late%d" % bits_end)
+@pytest.fixture
+def unaided(dev):
+    """A context of a library that does not repeat a search that was given up."""
+    prev, path = sb.LIB_PATH, sb.variant_path("noretry")
     assert os.path.exists(path), "build the variant first: python -m paper_2602_17698_amd.build --tests"
     sb.use_library(path)
     try:
-        ctx = sb.Context(device=0, stream=torch.cuda.current_stream().cuda_stream)
-        for N in (6000, 524304):
-            say("late", bits_end, N)
-            bits = [1, 2, 3, 4]
-            cost = table(N, bits, N)
-            plan, ws = plan_with_blocks(ctx, N, bits, dev)
-            level = torch.full((N,), 255, dtype=torch.uint8, device=dev)
-            rc, st, tr = plan.allocate(torch.from_numpy(cost).to(dev), 2.5, level, ws, trace_cap=500)
-            rc_o, level_o, st_o, tr_o = orc.allocate(cost, bits, 2.5, want_trace=True)
-            assert (rc, st, tr) == (rc_o, st_o, tr_o)
-            np.testing.assert_array_equal(level.cpu().numpy(), level_o)
-            s_up, s_dn = (np.ascontiguousarray(cost[:, i]) for i in (0, 2))
-            kind, want, winfo = orc.propose(s_up, s_dn, level_o, bits, 2.6, N // 20)
-            info = plan.propose(torch.from_numpy(s_up).to(dev), torch.from_numpy(s_dn).to(dev), level, 2.6, N // 20, level, ws)
-            assert info["kind"] == kind and all(info[f] == winfo[f] for f in winfo)
-            np.testing.assert_array_equal(level.cpu().numpy(), want)
-            plan.close()
-        ctx.close()
+        c = sb.Context(device=0, stream=torch.cuda.current_stream().cuda_stream)
+        yield c
+        c.close()
     finally:
         sb.use_library(prev)
+
+
+# 3, 128 and 128 workgroups; "both signs": entries that fall and rise, whose changes have sums with all upper bits set, added up
+# as two halves: the lower ones carry, the upper ones wrap
+@pytest.mark.parametrize("N", [6000, 524288, 524304])
+@pytest.mark.parametrize("kind", ["falling", "both signs"])
+def test_the_resident_workgroups_finish_by_themselves(orc, unaided, dev, N, kind):
+    say("no second try", N, kind)
+    bits = [1, 2, 3, 4]
+    cost = table(N, bits, N) if kind == "falling" else np.random.default_rng(N).random((N, 4), dtype=np.float32)
+    plan, ws = plan_with_blocks(unaided, N, bits, dev)
+    level = torch.full((N,), 255, dtype=torch.uint8, device=dev)
+    rc, st, tr = plan.allocate(torch.from_numpy(cost).to(dev), 2.5, level, ws, trace_cap=500)
+    rc_o, level_o, st_o, tr_o = orc.allocate(cost, bits, 2.5, want_trace=True)
+    assert (rc, st, tr) == (rc_o, st_o, tr_o)
+    assert any(t["delta_fixed"] < 0 for t in tr)
+    np.testing.assert_array_equal(level.cpu().numpy(), level_o)
+    s_up, s_dn = (np.ascontiguousarray(cost[:, i]) for i in (0, 2))
+    kind, want, winfo = orc.propose(s_up, s_dn, level_o, bits, 2.6, N // 20)
+    info = plan.propose(torch.from_numpy(s_up).to(dev), torch.from_numpy(s_dn).to(dev), level, 2.6, N // 20, level, ws)
+    assert info["kind"] == kind and all(info[f] == winfo[f] for f in winfo)
+    np.testing.assert_array_equal(level.cpu().numpy(), want)
+    plan.close()
+
+
+def test_propose_with_the_most_workgroups(orc, unaided, dev):
+    """256 of them, the largest number of parts that a sum has, in a swap whose two sets meet in many blocks."""
+    N, bits = 1 << 22, [1, 2, 3, 4]
+    say("no second try", N)
+    plan, ws = plan_with_blocks(unaided, N, bits, dev)
+    rng = np.random.default_rng(2)
+    level = rng.integers(0, 4, N).astype(np.uint8)
+    s_up = rng.random(N, dtype=np.float32)
+    s_dn = np.ascontiguousarray(1 - s_up)
+    avg, k = int(np.asarray(bits)[level].sum()) / N + 1e-9, N // 3
+    kind, want, winfo = orc.propose(s_up, s_dn, level, bits, avg, k)
+    out = torch.full((N,), 77, dtype=torch.uint8, device=dev)
+    info = plan.propose(torch.from_numpy(s_up).to(dev), torch.from_numpy(s_dn).to(dev), torch.from_numpy(level).to(dev), avg, k, out, ws)
+    assert kind == 2 and info["kind"] == kind and all(info[f] == winfo[f] for f in winfo)
+    np.testing.assert_array_equal(out.cpu().numpy(), want)
+    plan.close()
 
 
 def test_propose_replays_from_a_captured_graph(orc, dev):
