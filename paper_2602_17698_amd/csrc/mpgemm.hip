@@ -26,7 +26,7 @@
 //   loads whatever the bitwidth (load_quarter): with one path per bitwidth the ring was copied at the paths'
 //   end, behind a wait for it, 5824 x 6144 at 23 rows 17.7 -> 15.6 us; 64-column blocks, before two bytes
 //   at a time, 960 x 23872 at 13 rows 31.8 -> 16.5.
-// More than 32 batch rows, and most products of up to 16 (few_rows), take the kernels further down.
+// More than 32 batch rows, and products of up to 64 where few_rows says so (most of up to 16), take the kernels further down.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -490,8 +490,10 @@ __device__ __forceinline__ void read_halves(uint32_t at, uint32_t bt, u32x2_t (&
 
 // A block of 1 bit: the same products as in the kernel above, 128 + q and columns in its order (pair order for 128
 // columns), with sums of x of its own.  d = sum q x then has the rounding of that kernel, which for 1 bit is the largest
-// there is (128 against codes of 0 and 1), and what a row of x gives differs little between batches of 32 and 33 rows:
-// 14336 x 4096, bitwidths 1 .. 8: by 1.3e-4 of the root mean square at most, 4.3e-4 with 1 + q / 2.
+// there is (128 against codes of 0 and 1), and what a row of x gives differs less between that kernel and this one:
+// 14336 x 4096, bitwidths 1 .. 8: by 1.3e-4 of the root mean square at most, 4.3e-4 with 1 + q / 2.  (The narrow kernel has 1 + q / 2 from 33 to
+// 64 rows: what it gives is nearer to the exact sum, 1e-6 .. 3e-5 at most, and so differs from either by their error, 1e-4 at most with
+// ordinary weights and 3e-4 .. 1e-3 with outliers.)
 template <int N_COLS, int NB, int SUMS>
 __device__ __forceinline__ void wide_block_1bit(const uint32_t (&cw)[2][N_COLS / 16], const uint32_t (&at)[N_COLS / 32], uint32_t sum_tile,
                                                 WideState<NB, SUMS> &w)
@@ -1280,7 +1282,8 @@ int sbits_mp_gemm_rows(const sbits_plan *plan, int mat, int64_t ld_x, int left)
     return left < 128 ? left : 128;
 }
 
-// fine: rows of a product of more than 32, whose codes enter with the smaller offset in every kernel
+// fine: rows of a product of more than 32, whose codes enter with the smaller offset in every kernel (1 bit not in the wide one, see
+// wide_block_1bit)
 int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t ld_x, int batch, bool fine,
                          const uint8_t *level, const int64_t *byte_off, const uint8_t *codes, const float *scale,
                          const float *zero, float *y, void *scratch)
