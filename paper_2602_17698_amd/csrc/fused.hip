@@ -491,6 +491,7 @@ void sbits_fused_tables(sbits_plan *plan)
         // octets per workgroup: FU_OPU, halved while the class would not even give every CU a few
         // workgroups (one decoder layer of a streamed model is such a plan)
         // (the last halving, to one octet, only while there is less than one per CU: 512 x 512 cost 18.7 -> 10.7 us, packing 8.4 -> 5.7)
+        const int cus = sbits_cus(plan->ctx);
         int opu = FU_OPU;
         auto class_wgs = [&](int o) {
             int64_t t = 0;
@@ -498,7 +499,7 @@ void sbits_fused_tables(sbits_plan *plan)
                 if (plan->cols[i] == c) t += (plan->rows[i] / 8 + o - 1) / o;
             return t;
         };
-        while (opu > 1 && class_wgs(opu) < (opu > 2 ? 2048 : 256)) opu >>= 1;
+        while (opu > 1 && class_wgs(opu) < (opu > 2 ? 8 * cus : cus)) opu >>= 1;
         fc.opu = opu;
         int64_t t = 0;
         for (int i = 0; i < plan->n_mats; ++i) {

@@ -1207,7 +1207,8 @@ static int launch_wide_rg(sbits_ctx *ctx, int n, const MpArgs &a, dim3 grid, int
 // What a product takes in the first kernel (up to 32 rows) and in the narrow one (up to 64), in microseconds, fitted to 2600 and
 // 900 products of 256 .. 28672 x 256 .. 28672, 1 .. 64 rows of x, bitwidths up to 8: with the choice made by these the products
 // take 0.3 .. 2 % longer than with the better kernel each time (always the first 10 %, always the narrow one 18 %); no product
-// takes less than a launch, 5.2.
+// takes less than a launch, 5.2.  (The turns are those of a whole device also on a partition of one, here and in wide_split: the choice decides the
+// order of the sums, and a product gives the same bits on either.)
 // First: by the turns of the CUs (32 channels and 16 block columns each, 256 at a time) and their bytes; with several column
 // splits, their number, the partial sums and the second launch (1024 x 17216 in 64-column blocks, 17 splits, 12.5 us).
 // Narrow: by turns of 256 workgroups and block columns in each, x once more per turn; with 17 rows or more a workgroup per
@@ -1305,7 +1306,7 @@ int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t 
         // on their way; beyond that two workgroups of 8 waves, one of which computes while the other starts or ends (up to 25 %
         // faster).  x by way of LDS from 5 rows on: at 1 and 2 rows it costs 2 .. 6 %, at 3 and 4 it gives -2 .. 3, at 9 .. 16 3 .. 19, at 17
         // and more 3 .. 22 %.  The same sums all ways.
-        const bool deep = a.R / 32 * ((batch + 15) / 16) <= 256;
+        const bool deep = a.R / 32 * ((batch + 15) / 16) <= sbits_cus(ctx);
         if (fine) {
             if (plan->n == 128) return deep ? launch_narrow<128, 16, true, true>(ctx, a) : launch_narrow<128, 8, true, true>(ctx, a);
             return deep ? launch_narrow<64, 16, true, true>(ctx, a) : launch_narrow<64, 8, true, true>(ctx, a);
@@ -1329,16 +1330,17 @@ int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t 
         // CU.  64-column blocks up to 16 rows: four workgroups of 32 channels.  Else 64 (128 with 128 KiB of x), and half as
         // many where all workgroups are on the chip at once even so: 15872 x 2048 at 18 rows 11.5 -> 9.1 us with 64, 19584 x 896 at
         // 21 rows 9.4 -> 13.6; 2560 x 6784 at 2 rows 10.1 -> 9.3 with 32, 8096 x 7552 11.6 -> 14.1.  The same sums.
+        const int cus = sbits_cus(ctx);
         const int64_t wgs32 = (int64_t)(a.R / 32) * a.n_split, wgs64 = (int64_t)((a.R + 63) / 64) * a.n_split;
         if (fine) {                                           // (the last rows of a large product: many workgroups)
             if (plan->n == 128) rc = batch <= 16 ? launch_mp<128, 1, 2, true>(ctx, a) : launch_mp<128, 2, 4, true>(ctx, a);
             else rc = batch <= 16 ? launch_mp<64, 1, 1, true>(ctx, a) : launch_mp<64, 2, 2, true>(ctx, a);
         } else if (plan->n == 128) {
-            if (batch <= 16) rc = wgs32 <= 512 ? launch_mp<128, 1, 1, false>(ctx, a) : launch_mp<128, 1, 2, false>(ctx, a);
-            else rc = wgs64 <= 256 ? launch_mp<128, 2, 2, false>(ctx, a) : launch_mp<128, 2, 4, false>(ctx, a);
+            if (batch <= 16) rc = wgs32 <= 2 * cus ? launch_mp<128, 1, 1, false>(ctx, a) : launch_mp<128, 1, 2, false>(ctx, a);
+            else rc = wgs64 <= cus ? launch_mp<128, 2, 2, false>(ctx, a) : launch_mp<128, 2, 4, false>(ctx, a);
         } else {
             if (batch <= 16) rc = launch_mp<64, 1, 1, false>(ctx, a);
-            else rc = wgs32 <= 256 ? launch_mp<64, 2, 1, false>(ctx, a) : launch_mp<64, 2, 2, false>(ctx, a);
+            else rc = wgs32 <= cus ? launch_mp<64, 2, 1, false>(ctx, a) : launch_mp<64, 2, 2, false>(ctx, a);
         }
     }
     if (rc) return rc;

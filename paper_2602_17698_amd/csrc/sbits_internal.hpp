@@ -20,6 +20,8 @@ struct sbits_ctx {
     bool d16_zero_fill;    // 16-bit loads into a register half write zeros to the other half (target id "sramecc+")
 };
 constexpr size_t SBITS_PINNED_BYTES = 4096;
+// compute units that work is spread over; a host-only context plans for a whole device
+static inline int sbits_cus(const sbits_ctx *ctx) { return ctx->cus > 0 ? ctx->cus : 256; }
 
 struct sbits_plan {
     sbits_ctx *ctx;

@@ -49,3 +49,47 @@ answer(out)
 def test_offsets_in_one_launch_where_that_is_faster(tmp_path):
     for n, launches in record(tmp_path, OFFSETS).items():
         assert launches == (1 if int(n) <= 196608 else 3), n
+
+
+PARTITION = r"""
+out = {}
+for cus in (256, 32):
+    device(cus, 1)
+    ctx = sb.Context(0, 0)
+    class X:
+        def __init__(self, batch, ld): self.shape, self.ld = (batch, ld), ld
+        def data_ptr(self): return fake(1 << 20)
+        def stride(self, i): return self.ld
+    for name, n, shape, batch in (("narrow, 64 workgroups", 128, (2048, 1024), 3), ("first, 64-column blocks", 64, (2048, 8192), 20),
+                                  ("first, two on a CU", 128, (2048, 16384), 4), ("first, 32 rows", 128, (4096, 8192), 32)):
+        plan = sb.Plan(ctx, [shape], 32, n, [2, 4])
+        a = [fake(1 << 24) for _ in range(8)]
+        log()
+        plan.mp_gemm(0, X(batch, shape[1]), a[0], a[1], a[2], a[3], a[4], a[5], a[6])
+        out["%s %d" % (name, cus)] = [line.split()[1:6] for line in log() if line.startswith("launch")]
+        plan.close()
+    plan = sb.Plan(ctx, [(8192, 512)], 64, 128, [2, 4])
+    mats = [sb.Matrix(fake(1 << 23), fake(1 << 24), 8192, 512, 512, 512)]
+    log()
+    plan.gather_pack_all(mats, *[fake(1 << 23) for _ in range(8)])
+    out["packing %d" % cus] = [line.split()[1:6] for line in log() if line.startswith("launch")]
+    plan.close()
+    ctx.close()
+answer(out)
+"""
+
+
+def test_workgroups_follow_the_compute_units_and_sums_do_not(tmp_path):
+    """On a partition of 32 compute units the shape of the workgroups is another one, the kernel, which decides the order of the
+    sums, the same."""
+    got = record(tmp_path, PARTITION)
+    base = lambda launches: [launch[0].split("sbits")[1].split("kernel")[0] for launch in launches]
+    for key in got:
+        if key.endswith(" 256"):
+            assert base(got[key]) == base(got[key[:-3] + "32"]), key
+    grid = lambda key: [int(v) for v in got[key][0][2].split(",")]
+    block = lambda key: int(got[key][0][4])
+    assert block("narrow, 64 workgroups 256") == 1024 and block("narrow, 64 workgroups 32") == 512
+    assert block("first, 64-column blocks 32") >= block("first, 64-column blocks 256")
+    assert block("first, two on a CU 256") == 256 and block("first, two on a CU 32") == 512
+    assert grid("packing 256")[0] == 512 and grid("packing 32")[0] == 256          # octets: 2 and 4 a workgroup
