@@ -140,6 +140,8 @@ int  sbits_plan_create(sbits_ctx *ctx, const int64_t *rows, const int64_t *cols,
 int  sbits_plan_destroy(sbits_plan *plan);
 int64_t sbits_num_blocks(const sbits_plan *plan, int mat /* -1: all matrices */);
 int64_t sbits_block_base(const sbits_plan *plan, int mat);
+/* What the call that needs most needs: of 32- and 256-column blocks a search (its octet sums, 4 bytes per eight rows of a
+ * block and candidate). */
 size_t  sbits_workspace_bytes(const sbits_plan *plan);
 /* Declares how many bytes the workspace that later calls on this plan receive holds.  From
  * then on every call that "uses ws" returns SBITS_ERR_WORKSPACE (on the host, before
@@ -352,10 +354,12 @@ typedef struct {
     int32_t *col_perm;     /* concatenated: sum(cols) entries                                */
     void    *w_re_bf16;    /* reordered weights, matrices concatenated, each dense           */
     float   *s_re;         /* reordered sensitivities, same layout                           */
-                           /* Both are needed by the two-pass route only.  When              */
-                           /* sbits_gather_cost_supported(plan) and every matrix meets the   */
-                           /* alignment rule, s_re is never written and may be NULL, and     */
-                           /* w_re_bf16 is written if not NULL (costs one more HBM write).   */
+                           /* When sbits_gather_cost_supported(plan), s_re is never written  */
+                           /* and may be NULL, and w_re_bf16 is written if not NULL (costs   */
+                           /* one more HBM write).  Otherwise both are needed and written:   */
+                           /* by the pass that scores the matrices (32- and 256-column       */
+                           /* blocks) or ahead of it.  (On a device that is not "sramecc+"   */
+                           /* both are needed in any case.)                                  */
     float   *cost;         /* [N][K]                                                         */
     uint8_t *level;        /* [N]                                                            */
     int64_t *byte_off;     /* [N+1]                                                          */

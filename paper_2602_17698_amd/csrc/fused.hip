@@ -121,7 +121,7 @@ void gather_pack_kernel(const MatDesc *__restrict__ descs, const int *__restrict
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int rowsrc[FU_OPU * 8];
     constexpr int NIT = RS * CPL;
-    static_assert(8 % RS == 0, "step shape");
+    static_assert(RS == 2 || RS == 4, "a group of four rows is one step or two");
 
     const int tid = (int)threadIdx.x;
     const int T = (int)blockDim.x;                   // a multiple of 64, at most TMAX
@@ -290,12 +290,9 @@ void gather_pack_kernel(const MatDesc *__restrict__ descs, const int *__restrict
                 if constexpr (RS == 4) {
                     *reinterpret_cast<float4 *>(scale + ri) = make_float4(scl[0], scl[1], scl[2], scl[3]);
                     *reinterpret_cast<float4 *>(zero + ri) = make_float4(zr[0], zr[1], zr[2], zr[3]);
-                } else if constexpr (RS == 2) {
+                } else {
                     *reinterpret_cast<float2 *>(scale + ri) = make_float2(scl[0], scl[1]);
                     *reinterpret_cast<float2 *>(zero + ri) = make_float2(zr[0], zr[1]);
-                } else {
-#pragma unroll
-                    for (int rs = 0; rs < RS; ++rs) { scale[ri + rs] = scl[rs]; zero[ri + rs] = zr[rs]; }
                 }
             }
             // the rows of this step, behind those of the steps before it in the same group of four

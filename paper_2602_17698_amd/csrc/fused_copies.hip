@@ -3,8 +3,9 @@
 // written (6 bytes) once, where gather and cost table one after the other read them twice.  Bound by HBM with few candidates, by
 // vector issue with many.  Searches of two 8B-shaped layers, two passes -> one: 64 x 256 blocks, eight candidates 2560 -> 1919 us (gather and
 // table 1760 -> 1120); 128 x 256, four 2040 -> 1828; 128 x 32, four 2270 -> 1971; 1024 x 1024, 256-column blocks 113 -> 106.
-// The line: blocks of 8, 16 and 512 columns keep the two passes (their lane groups are no part of a row of 16 lanes, or more than half
-// a wave).
+// The line: blocks of 512 columns, whose lane groups are a whole wave, and of 8 and 16, a lane or two, keep the two passes.  No instance
+// of this kernel was built or measured for them: the octet sums of a row of 16384 elements (4 B per candidate and block column) would
+// take 72 KiB of LDS at nine candidates in 8-column blocks, beside 96 KiB for the row.
 #include "fused_core.hpp"
 
 using namespace sbits;

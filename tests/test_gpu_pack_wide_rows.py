@@ -1,6 +1,6 @@
 """Packing of rows wider than 16384 elements, whose columns two workgroups share: at the edges of the halves (a chunk past them, the
-second half nearly empty, both full), with rows per step that the LDS still holds and one at a time, for units that do not
-fill the pairs; against packing of the reordered copy."""
+second half nearly empty, both full), for units that do not fill the pairs, next to matrices of other row classes; against
+packing of the reordered copy."""
 import numpy as np
 import pytest
 
