@@ -1205,10 +1205,11 @@ static int launch_wide_rg(sbits_ctx *ctx, int n, const MpArgs &a, dim3 grid, int
 }
 
 // What a product takes in the first kernel (up to 32 rows) and in the narrow one (up to 64), in microseconds, fitted to 2600 and
-// 900 products of 256 .. 28672 x 256 .. 28672, 1 .. 64 rows of x, bitwidths up to 8: with the choice made by these the products
-// take 0.3 .. 2 % longer than with the better kernel each time (always the first 10 %, always the narrow one 18 %); no product
-// takes less than a launch, 5.2.  (The turns are those of a whole device also on a partition of one, here and in wide_split: the choice decides the
-// order of the sums, and a product gives the same bits on either.)
+// 900 products of 256 .. 28672 x 256 .. 28672, 1 .. 64 rows of x, bitwidths up to 8.  With the choice made by these, 1400 others of
+// the same ranges took 1.3 .. 1.5 % longer on average than with the better kernel each time, 23 % at most (always the first, or
+// above 32 rows the wide one, 14 %; always the narrow one 10 .. 12 %); no product takes less than a launch, 5.2.  (The turns are
+// those of a whole device also on a partition of one, here and in wide_split: the choice decides the order of the sums, and a
+// product gives the same bits on either.)
 // First: by the turns of the CUs (32 channels and 16 block columns each, 256 at a time) and their bytes; with several column
 // splits, their number, the partial sums and the second launch (1024 x 17216 in 64-column blocks, 17 splits, 12.5 us).
 // Narrow: by turns of 256 workgroups and block columns in each, x once more per turn; with 17 rows or more a workgroup per
@@ -1240,8 +1241,10 @@ static FewRows few_rows(const sbits_plan *plan, int64_t R, int nbc, int batch)
             o.narrow = 3.34 + 0.0333 * b + nbc * (0.101 + 0.0006 * b) + turns * (0.73 + nbc * (0.0503 + 0.0011 * b + 0.011 * bits));
             o.first = batch <= 16 ? 7.75 + 0.236 * splits + 1.98 * over + load * (0.155 * bits - 0.77) + 3.79 * part
                                   : 10.6 + 0.249 * splits + 2.75 * over + load * (0.244 * bits - 1.26) + 1.89 * part;
-            // at a draw the first: full turns and whole column splits make it faster than fitted (8192 x 8192 at 32 rows 17.5 us, 19
-            // to 21 in the narrow one; with the margin 0.6 % behind the better kernel, 1.4 % without)
+            // at a draw the first: where its workgroups (128 channels, alone on a CU) fill whole turns it is faster than fitted, 8192 x 8192
+            // at 32 rows 16.6 .. 18.1 us and 18.5 .. 20.6 in the narrow one.  Where they just miss one it is slower (6912 x 10496 at 31 rows
+            // 27.7 and 22.5).  Over 604 drawn products of this kind the choice is 0.85 % behind the better kernel with the margin and
+            // 0.72 % without: it stands for the shapes that fill their turns.
             if (batch > 16 && turns > 0) o.narrow *= 1.12;
         } else {
             o.narrow = 3.32 + 0.033 * b + nbc * 0.0775 + turns * (0.40 + nbc * (0.0448 + 0.0005 * b + 0.0101 * bits));
