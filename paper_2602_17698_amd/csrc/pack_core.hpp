@@ -143,8 +143,8 @@ __device__ __forceinline__ void quad_transpose(uint32_t (&a)[4], int lane)
 // those of row j, puts them together and stores them at once; the rows' bytes are consecutive, so a lane group's stores cover one
 // run.  dst: the first row's bytes.  WIDE: c may be more than 4 (else hi is not used).
 // (Collecting a group's bytes in LDS took two or three atomic ORs a lane and row, which with the column gather filled the LDS
-// pipe: two 8B-shaped layers in 64-column blocks at 1 to 8 bits 303 us, 269 this way; the 8192-column rows of the 70B-shaped layer 366,
-// with two row buffers besides 298; the 14336-column rows of the 8B-shaped model 1137, 1056; its 4096-column rows, whose stream of weights is the
+// pipe: two 8B-shaped layers in 64-column blocks at 1 to 8 bits 303 us, 269 this way; the 8192-column rows of the 70B-shaped layer 370,
+// with two row buffers besides 330; the 14336-column rows of the 8B-shaped model 1137, 1076; its 4096-column rows, whose stream of weights is the
 // slower part, 2.7 ms both.)
 template <int LPG, bool WIDE>
 __device__ __forceinline__ void store_codes4(uint8_t *dst, int c, uint32_t (&lo)[4], uint32_t (&hi)[4], int lig)
