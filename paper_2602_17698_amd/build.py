@@ -58,7 +58,8 @@ def _compile(src: str, force: bool, variant: str) -> str:
         raise RuntimeError("hipcc failed on " + src)
     if src == "mpgemm.hip":
         try:
-            if check_counted_waits(device_listing(obj)) == 0:
+            listing = device_listing(obj)
+            if check_counted_waits(listing) == 0 or check_block_waits(listing) == 0:
                 raise RuntimeError("no kernel with counted waits found in " + src)
         except Exception:
             os.remove(obj)                          # not taken by a later build either
@@ -96,6 +97,38 @@ def check_counted_waits(listing: str) -> int:
             kinds = "".join("x" if re.search(r"\blds\b", args) else "." for _, args in loads)
             if kinds[:x_loads] != "x" * x_loads or "x" in kinds[x_loads:] or len(kinds) < x_loads + 9:
                 raise RuntimeError("%s: a step requests %s, %d loads to LDS and nine others expected" % (name, kinds, x_loads))
+    return len(kernels)
+
+
+def check_block_waits(listing: str) -> int:
+    """The same for the product of many rows by columns: a wave waits for the x of a block by the loads of codes and scales, 4 a tile,
+    that it requested behind it.  They may be requested before the loop or at its end, and in part at its beginning, in front of the
+    wait; each way there are exactly as many between one block's loads to LDS and the wait.  Returns how many kernels were checked."""
+    kernels = re.findall(r"([0-9a-f]+) <(\w*mp_gemm_many_kernelILi(\d+)ELi(\d+)ELi(\d+)E\w*)>:\n(.*?)(?=\n\n|\Z)", listing, re.S)
+    for start, name, n_cols, batch_tiles, tiles, text in kernels:
+        behind, x_loads = 4 * int(tiles), int(batch_tiles) * int(n_cols) // 32
+        lines = text.split("\n")
+        vector = [bool(re.match(r"\s*(?:buffer|global|flat)_load_", s)) for s in lines]
+        lds = [v and re.search(r"\blds\b", s.split("//")[0]) is not None for v, s in zip(vector, lines)]
+        to_lds = [i for i, v in enumerate(lds) if v]
+        waits = [i for i, s in enumerate(lines) if re.search(r"s_waitcnt vmcnt\(%d\)\s" % behind, s + " ")
+                 and any("ds_read_b128" in t for t in lines[i:i + 24])]
+        waits = [i for i in waits if len(to_lds) == 2 * x_loads and to_lds[x_loads - 1] < i < to_lds[x_loads]]
+        if len(waits) != 1:
+            raise RuntimeError("%s: %d loads to LDS and %d waits between them, %d and 1 expected" % (name, len(to_lds), len(waits), 2 * x_loads))
+        wait, end = waits[0], next(i for i, s in enumerate(lines) if i > to_lds[-1] and "s_barrier" in s)
+        address = [int(m.group(1), 16) if (m := re.search(r"// ([0-9A-F]+):", s)) else -1 for s in lines]
+        heads = [int(start, 16) + int(m.group(1), 16) for s in lines[to_lds[-1]:end]
+                 if (m := re.search(r"s_c?branch\w* .*\+0x([0-9a-f]+)>", s))]
+        heads = [i for i in range(to_lds[x_loads - 1], wait + 1) if address[i] in heads]
+        if len(heads) != 1:
+            raise RuntimeError("%s: %d loops around the wait" % (name, len(heads)))
+
+        def count(a, b):
+            return sum(vector[i] and not lds[i] for i in range(a, b))
+        first, again = count(to_lds[x_loads - 1], wait), count(to_lds[-1], end) + count(heads[0], wait)
+        if first != behind or again != behind or count(wait, to_lds[-1]):
+            raise RuntimeError("%s: %d and %d loads behind the x of a block, %d expected" % (name, first, again, behind))
     return len(kernels)
 
 

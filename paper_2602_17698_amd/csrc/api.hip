@@ -129,6 +129,7 @@ int sbits_plan_create(sbits_ctx *ctx, const int64_t *rows, const int64_t *cols, 
     sbits_pack_tables(p);
     sbits_fused_tables(p);
     sbits_gather_tables(p);
+    sbits_mp_gemm_tables(p);
     size_t ws = sbits_reorder_ws_bytes(p->sum_rows + p->sum_cols, p->sum_rowpart, p->sum_colpart);
     const size_t a = sbits_alloc_ws_bytes(p->N), o = sbits_offsets_ws_bytes(p->N);
     if (a > ws) ws = a;

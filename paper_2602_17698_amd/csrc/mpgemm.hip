@@ -26,7 +26,7 @@
 //   loads whatever the bitwidth (load_quarter): with one path per bitwidth the ring was copied at the paths'
 //   end, behind a wait for it, 5824 x 6144 at 23 rows 17.7 -> 15.6 us; 64-column blocks, before two bytes
 //   at a time, 960 x 23872 at 13 rows 31.8 -> 16.5.
-// More than 32 batch rows, and products of up to 64 where few_rows says so (most of up to 16), take the kernels further down.
+// More than 32 batch rows (two kernels), and products of up to 64 where few_rows says so (most of up to 16), take the kernels further down.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -89,6 +89,8 @@ __device__ __forceinline__ uint32_t code_pair(const uint32_t *r, int e, uint32_t
         return __builtin_amdgcn_perm(f1, f0, 0x07060302u);
     } else {
         const int bit = e * C, idx = bit >> 5, sh = bit & 31;
+        if constexpr (C == 2)                                 // (the byte is selected by the multiplication; its two pairs differ in the factor)
+            return (__umul24((r[idx] >> (sh & 24)) & 255u, sh & 4 ? (1u << 1) + (1u << 15) : (1u << 5) + (1u << 19)) & mask) | one;
         const uint32_t x = sh + 2 * C <= 32 ? __builtin_amdgcn_ubfe(r[idx], sh, 2 * C)
                                             : __builtin_amdgcn_alignbit(r[idx + 1], r[idx], sh) & ((1u << (2 * C)) - 1u);
         // C <= 5: the copies of the two codes do not overlap where the mask looks, nor carry into it
@@ -1081,6 +1083,321 @@ void mp_gemm_narrow_kernel(MpArgs a)
     }
 }
 
+// ================================================================ more than 32 batch rows, each wave on its own columns
+// A workgroup takes CT tiles of 16 channels and NB tiles of 16 batch rows; its WAVES waves take every WAVES-th block column each and
+// share nothing but the sum at the end, so no barrier holds them in step.  A wave brings the x of its next block column into LDS of
+// its own by direct loads (whole rows, 1 KiB a load), reads all operands of the present one into registers (64 of them, at 4 batch tiles and
+// 128 columns) and then asks for the next: x is read from LDS once per wave, where the kernel above reads it once per 32 channels.
+// Codes of a pair of tiles are asked for a block ahead, into the registers that the pair has just done with.  Bitwidths and
+// offsets lie in LDS from the start.  sum_j x of the block comes from a product with ones, per wave (16 of its 80 matrix
+// instructions at 4 x 4 tiles), in the place of the exchange and its barrier.
+// Vector issue bounds it: at 4 x 4 tiles and 128 columns unpacking 64 codes in pairs takes 128 .. 192 instructions a lane and block,
+// two FMAs per output 128; next are the direct loads of x, which take a wave 40 clocks each to ask for (8192 x 28672 at 128 rows
+// without them 88 us instead of 102).  Tiles of 64 x 64 are the largest whose sums, operands and codes fit 256
+// registers.  With 8 waves a workgroup has the CU to itself; with 4, two of them take turns in starting and ending.  Against the kernel above: 14336 x 4096 at 100
+// rows, bitwidths 1 .. 8, 39.0 -> 30.6 us; 8192 x 28672 at 128 rows 139 -> 92; 14336 x 4096 in 64-column blocks at 100 rows 55.7 -> 39.2;
+// 4096 x 4096 at 64 rows 12.9 -> 10.1.
+// The operands, their order and so the block's products are those of the kernel above, 1 bit included.
+
+// one tile of 16 channels and NB tiles of 16 batch rows: the block's products, scale and zero applied
+template <int C, int N_COLS, int NB>
+__device__ __forceinline__ void many_tile(const uint32_t (&cw)[N_COLS / 16], float sc, float ze, const u32x4_t (&x)[NB][N_COLS / 32],
+                                          const f32x4v_t (&s)[NB], f32x4v_t (&acc)[NB])
+{
+    constexpr int STEPS = N_COLS / 32;
+    const f32x4v_t zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
+    f32x4v_t d[NB];
+    uint32_t one = PairConst<C>::one, mask = PairConst<C>::field | PairConst<C>::field << 16;
+    asm volatile("" : "+v"(one), "+s"(mask));
+#pragma unroll
+    for (int st = 0; st < STEPS; ++st) {
+        uint32_t o[4];
+#pragma unroll
+        for (int p = 0; p < 4; ++p) o[p] = code_pair<C>(cw, 8 * st + 2 * p, one, mask);
+        const bf16x8_t b = as_bf16x8(o[0], o[1], o[2], o[3]);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+            d[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, x[nb][st]), b, st == 0 ? zero4 : d[nb], 0, 0, 0);
+    }
+    float f, z;
+    term_factors<C, true>(sc, ze, f, z);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[nb][r] = fmaf(f, d[nb][r], fmaf(z, s[nb][r], acc[nb][r]));
+}
+
+// two tiles at 1 bit: products as in wide_block_1bit
+template <int N_COLS, int NB>
+__device__ __forceinline__ void many_tiles_1bit(const uint32_t (&cw)[2][N_COLS / 16], const float *sc, const float *ze,
+                                                const u32x4_t (&x)[NB][N_COLS / 32], f32x4v_t (&acc0)[NB], f32x4v_t (&acc1)[NB])
+{
+    constexpr int STEPS = N_COLS / 32, KL = N_COLS / 4;
+    const f32x4v_t zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
+    const bf16x8_t ones = as_bf16x8(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
+    bf16x8_t b[2][STEPS];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) {
+            uint32_t o[4];
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                if constexpr (N_COLS == 128) o[p] = ((cw[t][0] >> (4 * st + p)) & 0x00010001u) | 0x43004300u;
+                else o[p] = ((cw[t][0] >> (8 * st + 2 * p)) & 1u) | ((cw[t][0] >> (8 * st + 2 * p + 1)) & 1u) << 16 | 0x43004300u;
+            }
+            b[t][st] = as_bf16x8(o[0], o[1], o[2], o[3]);
+        }
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        f32x4v_t d0 = zero4, d1 = zero4, s1 = zero4;
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) {
+            const bf16x8_t xa = x_held<1, KL>(x[nb], st);
+            d0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, b[0][st], d0, 0, 0, 0);
+            d1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, b[1][st], d1, 0, 0, 0);
+            s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, ones, s1, 0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            acc0[nb][r] = fmaf(sc[0], fmaf(-128.0f, s1[r], d0[r]), fmaf(ze[0], s1[r], acc0[nb][r]));
+            acc1[nb][r] = fmaf(sc[1], fmaf(-128.0f, s1[r], d1[r]), fmaf(ze[1], s1[r], acc1[nb][r]));
+        }
+        __builtin_amdgcn_sched_barrier(0);                    // (registers: a batch tile at a time)
+    }
+}
+
+// all operands of a block of 128 (STEPS = 4) or 64 columns, NB batch tiles, at: the lane's first one; and 16 bytes at meta_at
+template <int NB, int STEPS>
+__device__ __forceinline__ void read_block(uint32_t at, uint32_t meta_at, u32x4_t (&x)[NB][STEPS], u32x4_t &meta)
+{
+    static_assert(NB >= 2 && NB <= 4 && (STEPS == 2 || STEPS == 4), "written out");
+    if constexpr (STEPS == 4 && NB == 4)
+        asm volatile("ds_read_b128 %0, %18\n\tds_read_b128 %1, %17\n\tds_read_b128 %2, %17 offset:16\n\t"
+                     "ds_read_b128 %3, %17 offset:32\n\tds_read_b128 %4, %17 offset:48\n\tds_read_b128 %5, %17 offset:4160\n\t"
+                     "ds_read_b128 %6, %17 offset:4176\n\tds_read_b128 %7, %17 offset:4192\n\tds_read_b128 %8, %17 offset:4208\n\t"
+                     "ds_read_b128 %9, %17 offset:8320\n\tds_read_b128 %10, %17 offset:8336\n\tds_read_b128 %11, %17 offset:8352\n\t"
+                     "ds_read_b128 %12, %17 offset:8368\n\tds_read_b128 %13, %17 offset:12480\n\t"
+                     "ds_read_b128 %14, %17 offset:12496\n\tds_read_b128 %15, %17 offset:12512\n\t"
+                     "ds_read_b128 %16, %17 offset:12528\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(meta), "=&v"(x[0][0]), "=&v"(x[0][1]), "=&v"(x[0][2]), "=&v"(x[0][3]), "=&v"(x[1][0]), 
+                       "=&v"(x[1][1]), "=&v"(x[1][2]), "=&v"(x[1][3]), "=&v"(x[2][0]), "=&v"(x[2][1]), "=&v"(x[2][2]), 
+                       "=&v"(x[2][3]), "=&v"(x[3][0]), "=&v"(x[3][1]), "=&v"(x[3][2]), "=&v"(x[3][3])
+                     : "v"(at), "v"(meta_at) : "memory");
+    else if constexpr (STEPS == 4 && NB == 3)
+        asm volatile("ds_read_b128 %0, %14\n\tds_read_b128 %1, %13\n\tds_read_b128 %2, %13 offset:16\n\t"
+                     "ds_read_b128 %3, %13 offset:32\n\tds_read_b128 %4, %13 offset:48\n\tds_read_b128 %5, %13 offset:4160\n\t"
+                     "ds_read_b128 %6, %13 offset:4176\n\tds_read_b128 %7, %13 offset:4192\n\tds_read_b128 %8, %13 offset:4208\n\t"
+                     "ds_read_b128 %9, %13 offset:8320\n\tds_read_b128 %10, %13 offset:8336\n\tds_read_b128 %11, %13 offset:8352\n\t"
+                     "ds_read_b128 %12, %13 offset:8368\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(meta), "=&v"(x[0][0]), "=&v"(x[0][1]), "=&v"(x[0][2]), "=&v"(x[0][3]), "=&v"(x[1][0]), 
+                       "=&v"(x[1][1]), "=&v"(x[1][2]), "=&v"(x[1][3]), "=&v"(x[2][0]), "=&v"(x[2][1]), "=&v"(x[2][2]), 
+                       "=&v"(x[2][3])
+                     : "v"(at), "v"(meta_at) : "memory");
+    else if constexpr (STEPS == 4 && NB == 2)
+        asm volatile("ds_read_b128 %0, %10\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %9 offset:16\n\t"
+                     "ds_read_b128 %3, %9 offset:32\n\tds_read_b128 %4, %9 offset:48\n\tds_read_b128 %5, %9 offset:4160\n\t"
+                     "ds_read_b128 %6, %9 offset:4176\n\tds_read_b128 %7, %9 offset:4192\n\tds_read_b128 %8, %9 offset:4208\n\t"
+                     "s_waitcnt lgkmcnt(0)"
+                     : "=&v"(meta), "=&v"(x[0][0]), "=&v"(x[0][1]), "=&v"(x[0][2]), "=&v"(x[0][3]), "=&v"(x[1][0]), 
+                       "=&v"(x[1][1]), "=&v"(x[1][2]), "=&v"(x[1][3])
+                     : "v"(at), "v"(meta_at) : "memory");
+    else if constexpr (STEPS == 2 && NB == 4)
+        asm volatile("ds_read_b128 %0, %10\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %9 offset:16\n\t"
+                     "ds_read_b128 %3, %9 offset:2080\n\tds_read_b128 %4, %9 offset:2096\n\tds_read_b128 %5, %9 offset:4160\n\t"
+                     "ds_read_b128 %6, %9 offset:4176\n\tds_read_b128 %7, %9 offset:6240\n\tds_read_b128 %8, %9 offset:6256\n\t"
+                     "s_waitcnt lgkmcnt(0)"
+                     : "=&v"(meta), "=&v"(x[0][0]), "=&v"(x[0][1]), "=&v"(x[1][0]), "=&v"(x[1][1]), "=&v"(x[2][0]), 
+                       "=&v"(x[2][1]), "=&v"(x[3][0]), "=&v"(x[3][1])
+                     : "v"(at), "v"(meta_at) : "memory");
+    else if constexpr (STEPS == 2 && NB == 3)
+        asm volatile("ds_read_b128 %0, %8\n\tds_read_b128 %1, %7\n\tds_read_b128 %2, %7 offset:16\n\t"
+                     "ds_read_b128 %3, %7 offset:2080\n\tds_read_b128 %4, %7 offset:2096\n\tds_read_b128 %5, %7 offset:4160\n\t"
+                     "ds_read_b128 %6, %7 offset:4176\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(meta), "=&v"(x[0][0]), "=&v"(x[0][1]), "=&v"(x[1][0]), "=&v"(x[1][1]), "=&v"(x[2][0]), 
+                       "=&v"(x[2][1])
+                     : "v"(at), "v"(meta_at) : "memory");
+    else if constexpr (STEPS == 2 && NB == 2)
+        asm volatile("ds_read_b128 %0, %6\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %5 offset:16\n\t"
+                     "ds_read_b128 %3, %5 offset:2080\n\tds_read_b128 %4, %5 offset:2096\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(meta), "=&v"(x[0][0]), "=&v"(x[0][1]), "=&v"(x[1][0]), "=&v"(x[1][1])
+                     : "v"(at), "v"(meta_at) : "memory");
+}
+
+template <int N_COLS, int NB, int CT, int WAVES>
+__global__ __launch_bounds__((64 * WAVES), 2)
+void mp_gemm_many_kernel(MpArgs a, int cols_per_split)
+{
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    constexpr int KL = N_COLS / 4, STEPS = N_COLS / 32;
+    constexpr int CHUNKS = N_COLS / 8, RPL = 64 / CHUNKS;     // 16-byte chunks of a row; rows of a load
+    constexpr int ROWS = NB * 16, LOADS = ROWS / RPL, XB = LOADS * 1040;     // batch rows; loads and bytes of x of a wave
+    constexpr int H = CT / 2, ENTRIES = 32768 / N_COLS / WAVES;         // (of a wave)
+    static_assert(CT % 2 == 0, "pairs of tiles");
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 15, g = lane >> 4;
+    const int batch0 = (int)blockIdx.z * ROWS, batch = min(a.batch - batch0, ROWS);
+    const int row0 = (int)blockIdx.x * (CT * 16);
+    const int J0 = (int)blockIdx.y * cols_per_split, J1 = min(J0 + cols_per_split, a.nbc);
+    const int nt = (J1 - J0 - wave + WAVES - 1) / WAVES;                     // this wave's block columns: 0 or less: none
+    const int turn0 = nt > 1 ? (int)(blockIdx.x >> 3) & 1 : 0;    // (rows of x may lie a power of two apart: not all at the same columns)
+    auto nth = [&](int t) { const int u = turn0 + t; return u < nt ? u : u - nt; };
+
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
+    const uint32_t lds0 = lds_base + (uint32_t)(wave * XB), meta0 = lds_base + (uint32_t)(WAVES * XB + wave * (ENTRIES * 16));
+    // the lane, as new each time: what follows from it is made again where it is needed, not kept in registers
+    auto fresh_lane = [&]() { uint32_t l = (uint32_t)lane; asm volatile("" : "+v"(l)); return l; };
+
+    // this wave's blocks: offsets, and bitwidths (0: past the matrix, or pruned) in their upper bytes, in LDS: 16 bytes a block column
+    int rin[H];
+    const float *scale0[H], *zero0[H];
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+        const int r = row0 + 32 * h;
+        const bool ok = r < a.R;
+        const int I = ok ? r / a.m : 0;
+        rin[h] = ok ? r - I * a.m : 0;
+        const int64_t blk0 = a.block_base + (int64_t)I * a.nbc;
+        scale0[h] = a.scale + blk0 * a.m + rin[h];
+        zero0[h] = a.zero + blk0 * a.m + rin[h];
+        for (int e = lane; e < nt; e += 64) {                 // (nt <= ENTRIES: a matrix has 32768 columns at most)
+            const int64_t b = blk0 + J0 + wave + WAVES * e;
+            const int lv = a.level[b];
+            const int64_t off = a.byte_off[b];
+            int c = a.bits[0];
+#pragma unroll
+            for (int k = 1; k < MAX_CAND; ++k) c = lv == k ? a.bits[k] : c;
+            *reinterpret_cast<uint64_t *>(smem + WAVES * XB + (wave * ENTRIES + e) * 16 + h * 8) = (uint64_t)off | (uint64_t)(uint32_t)(ok ? c : 0) << 56;
+        }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    auto meta_at = [&](int t) { return meta0 + (uint32_t)nth(min(t, nt - 1)) * 16; };
+
+    // x: a load's rows at positions that differ, the next load's 16 bytes further: 16 rows' same chunk in 16 different quarters of the banks
+    const uint32_t ldx2 = 2u * (uint32_t)a.ld_x;
+    const rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.x) + (int64_t)batch0 * a.ld_x, 0,
+                                                         (int)((uint32_t)(batch - 1) * ldx2 + 2u * (uint32_t)a.C), 0x00027000);
+    auto fetch = [&](int t) {
+        const int J = J0 + wave + WAVES * nth(min(t, nt - 1));
+        const uint32_t l = fresh_lane(), lrow = l / CHUNKS, lpos = l % CHUNKS;
+        const uint32_t vrow = __umul24(lrow, ldx2) + (lpos ^ (N_COLS == 128 ? lrow * 4 : (lrow >> 1) * 2)) * 16u;
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(xrs, (__attribute__((address_space(3))) void *)(lds0 + (uint32_t)(i * 1040)),
+                                                     16, (int)(vrow + (uint32_t)(i * RPL) * ldx2), J * N_COLS * 2, 0, 0);
+    };
+    auto x_at = [&]() {
+        const uint32_t l = fresh_lane(), i = l & 15, q = l >> 4;
+        return lds0 + (N_COLS == 128 ? (i >> 2) * 1040 + (i & 3) * 256 + (q ^ (i & 3)) * 64
+                                     : (i >> 3) * 1040 + (i & 7) * 128 + (q ^ ((i >> 1) & 3)) * 32);
+    };
+
+    Quarter<N_COLS> cq[CT];
+    float sc[CT], ze[CT];
+    int cb[H];
+    const uint32_t block_bytes_per_bit = (uint32_t)a.m * (N_COLS / 8);
+    // x c = the lane's byte offset in the block
+    const uint32_t units0 = (uint32_t)(li * (N_COLS / 8) + g * (KL / 8));
+    auto units = [&](int h) {
+        return units0 + (uint32_t)(rin[h] * (N_COLS / 8));
+    };
+    auto request = [&](int h, int t, uint32_t hi, uint32_t lo) {
+        const int J = J0 + wave + WAVES * nth(min(t, nt - 1));
+        const uint32_t c = t < nt ? hi >> 24 : 0;
+        cb[h] = (int)c;
+        const uint64_t at = (uint64_t)(hi & 0xffffffu) << 32 | lo;
+        const rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(a.codes) + at, 0, (int)(block_bytes_per_bit * c), 0x00027000);
+        const float *ps = scale0[h] + (uint32_t)(J * a.m), *pz = zero0[h] + (uint32_t)(J * a.m);
+        const uint32_t u = units(h), i = (uint32_t)li;
+#pragma unroll
+        for (int tl = 0; tl < 2; ++tl) load_quarter<N_COLS>(rs, __umul24(u + (uint32_t)(tl * 16 * (N_COLS / 8)), c), cq[2 * h + tl]);
+        sc[2 * h] = ps[i]; sc[2 * h + 1] = (ps + 16)[i];
+        ze[2 * h] = pz[i]; ze[2 * h + 1] = (pz + 16)[i];
+    };
+
+    const f32x4v_t zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
+    const bf16x8_t ones = as_bf16x8(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
+    f32x4v_t acc[CT][NB];
+#pragma unroll
+    for (int t = 0; t < CT; ++t)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[t][nb] = zero4;
+    if (nt > 0) {
+        fetch(0);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        u32x4_t meta;
+        uint32_t mw[4];
+        auto scalars = [&]() {
+            mw[0] = (uint32_t)__builtin_amdgcn_readfirstlane(meta.x); mw[1] = (uint32_t)__builtin_amdgcn_readfirstlane(meta.y);
+            mw[2] = (uint32_t)__builtin_amdgcn_readfirstlane(meta.z); mw[3] = (uint32_t)__builtin_amdgcn_readfirstlane(meta.w);
+        };
+        asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(meta) : "v"(meta_at(0)) : "memory");
+        scalars();
+#pragma unroll
+        for (int h = 0; h < H; ++h) request(h, 0, mw[2 * h + 1], mw[2 * h]);
+        for (int t = 0; t < nt; ++t) {
+            u32x4_t x[NB][STEPS];
+            asm volatile("s_waitcnt vmcnt(%0)" :: "n"(8 * H) : "memory");     // x is there: the codes requested behind it may be on their way
+            read_block<NB, STEPS>(x_at(), meta_at(t + 1), x, meta);    // (read: its place is free)
+            scalars();
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(t + 1);
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            f32x4v_t s[NB];
+#pragma unroll
+            for (int st = 0; st < STEPS; ++st)
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+                    s[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, x[nb][st]), ones, st == 0 ? zero4 : s[nb], 0, 0, 0);
+#pragma unroll
+            for (int h = 0; h < H; ++h) {
+                uint32_t cw[2][N_COLS / 16];
+#pragma unroll
+                for (int tl = 0; tl < 2; ++tl)
+                    align_quarter<N_COLS>(cq[2 * h + tl], N_COLS == 128 ? 0 : __umul24(units(h) + (uint32_t)(tl * 16 * (N_COLS / 8)), (uint32_t)cb[h]), cw[tl]);
+#define MB_TILE(C)                                                                                                \
+    do {                                                                                                          \
+        if constexpr (C == 1) {                                                                                   \
+            many_tiles_1bit<N_COLS, NB>(cw, sc + 2 * h, ze + 2 * h, x, acc[2 * h], acc[2 * h + 1]);               \
+        } else {                                                                                                  \
+            many_tile<C, N_COLS, NB>(cw[0], sc[2 * h], ze[2 * h], x, s, acc[2 * h]);                              \
+            many_tile<C, N_COLS, NB>(cw[1], sc[2 * h + 1], ze[2 * h + 1], x, s, acc[2 * h + 1]);                  \
+        }                                                                                                         \
+    } while (0)
+                WG_SWITCH(cb[h], MB_TILE)
+#undef MB_TILE
+                request(h, t + 1, mw[2 * h + 1], mw[2 * h]);
+            }
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();                                          // every wave is done with its x
+    // the eight waves add up, in a fixed order
+    float *red = reinterpret_cast<float *>(smem);             // [wave][tile][nb][lane][4]
+#pragma unroll
+    for (int tl = 0; tl < CT; ++tl)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+            *reinterpret_cast<f32x4v_t *>(red + (((wave * CT + tl) * NB + nb) * 64 + lane) * 4) = acc[tl][nb];
+    __syncthreads();
+    float *dst = a.out + ((int64_t)blockIdx.y * a.batch + batch0) * a.R;
+    for (int p = wave; p < CT * NB; p += WAVES) {
+        const int tl = p / NB, nb = p % NB;
+        if (row0 + 16 * tl >= a.R) continue;
+        f32x4v_t v = *reinterpret_cast<const f32x4v_t *>(red + (p * 64 + lane) * 4);
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) v = v + *reinterpret_cast<const f32x4v_t *>(red + ((w * CT * NB + p) * 64 + lane) * 4);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int b = 16 * nb + 4 * g + r;
+            if (b < batch) dst[(int64_t)b * a.R + row0 + 16 * tl + li] = v[r];
+        }
+    }
+}
+
 // y = sum over the column splits of the partials, split 0 first
 __global__ __launch_bounds__(256)
 void mp_gemm_finish_kernel(const float *__restrict__ part, int64_t n, int n_split, float *__restrict__ y)
@@ -1139,8 +1456,63 @@ static WideSplit wide_split(int64_t R, int nbc, int n, int batch)
     return a.cost < b.cost ? a : b;
 }
 
+// Shapes of the kernel whose waves take columns of their own, and what a product takes in each, in microseconds: fitted to 1350
+// products of 256 .. 28672 rows and columns, 33 .. 128 rows of x, in all shapes and column splits (mean error 3 .. 7 %; the shape
+// chosen by them is 2 % behind the best one on average).  turns: of workgroups on 256 CUs, one a CU or, with four
+// waves, two; work: block columns of a wave times workgroups of a CU.  The choice decides the order of the sums, so it goes by the matrix
+// and the batch, for a whole device.  Less than 6 us, little more than a launch, is not promised.
+struct ManyShape { int nb, ct, waves; double base, turn, col, col_bit, split, per_split, part, turn_col; };
+static const ManyShape MANY_128[5] = {{2, 2, 8, 4.263, 0.231, 0.853, 0.029, 2.233, 0.113, 0.0, 0.0},
+                                      {3, 2, 8, 2.786, 1.491, 1.304, 0.013, 1.997, 0.157, 0.736, 0.0},
+                                      {3, 4, 4, 2.899, 1.947, 0.889, 0.0, 1.449, 0.220, 1.920, 0.541},
+                                      {4, 4, 4, 2.875, 2.236, 1.168, 0.0, 1.379, 0.239, 2.000, 0.551},
+                                      {4, 4, 8, 1.635, 2.728, 2.833, 0.0, 1.534, 0.240, 1.923, 0.0}};
+static const ManyShape MANY_64[5] = {{2, 2, 8, 3.597, 0.950, 0.536, 0.030, 2.402, 0.120, 0.0, 0.0},
+                                     {3, 2, 8, 4.009, 0.430, 0.719, 0.025, 2.285, 0.133, 0.0, 0.0},
+                                     {3, 4, 4, 4.873, 0.0, 0.490, 0.0, 1.520, 0.197, 1.805, 0.545},
+                                     {4, 4, 4, 3.332, 1.874, 0.636, 0.0, 1.306, 0.206, 2.053, 0.572},
+                                     {4, 4, 8, 1.973, 2.905, 1.799, 0.0, 1.303, 0.213, 1.870, 0.0}};
+static ManySplit many_split(const sbits_plan *plan, int64_t R, int nbc, int tiles)     // (all that counts of the batch: the workspace is sized by them)
+{
+    const ManyShape *const shapes = plan->n == 128 ? MANY_128 : MANY_64;
+    double bits = 0;
+    for (int l = 0; l < plan->K; ++l) bits += plan->bits[l];
+    bits /= plan->K;
+    ManySplit best = {0, nbc, 1, 1e30};
+    for (int f = 0; f < 5; ++f) {
+        const ManyShape &s = shapes[f];
+        if (s.nb > tiles) continue;
+        const int64_t wgs1 = (R + s.ct * 16 - 1) / (s.ct * 16) * ((tiles + s.nb - 1) / s.nb);
+        for (int sp : {1, 2, 3, 4, 6, 8, 12, 16}) {
+            if (sp > 1 && (wgs1 * sp > 600 || nbc < 2 * sp)) break;
+            const int per = (nbc + sp - 1) / sp, n_split = (nbc + per - 1) / per;
+            const int64_t wgs = wgs1 * n_split, of_cu = (wgs + 255) / 256, at_once = s.waves == 4 ? 2 : 1;
+            const double turns = (double)((of_cu + at_once - 1) / at_once), cols = (per + s.waves - 1) / s.waves;
+            double us = s.base + turns * (s.turn + s.turn_col * cols) + (double)of_cu * cols * (s.col + s.col_bit * bits);
+            if (n_split > 1) us += s.split + s.per_split * n_split + s.part * 1e-6 * (double)(tiles * 16 * R * n_split);
+            if (us < 6.0) us = 6.0;
+            if (us < best.us) best = {f, per, n_split, us};
+        }
+    }
+    return best;
+}
+
+// the choice for 33 .. 128 rows of each matrix, made with the plan: 40 estimates are too many for a call of a few microseconds
+void sbits_mp_gemm_tables(sbits_plan *plan)
+{
+    if (!sbits_mp_gemm_shapes_ok(plan)) return;
+    for (int i = 0; i < plan->n_mats; ++i) {
+        int same = 0;
+        while (same < i && same < 16 && (plan->rows[same] != plan->rows[i] || plan->cols[same] != plan->cols[i])) ++same;
+        for (int tiles = 3; tiles <= 8; ++tiles)
+            plan->many.push_back(same < i && same < 16 ? plan->many[(size_t)same * 6 + tiles - 3]
+                                                       : many_split(plan, plan->rows[i], (int)(plan->cols[i] / plan->n), tiles));
+    }
+}
+static const ManySplit &many_of(const sbits_plan *plan, int mat, int batch) { return plan->many[(size_t)mat * 6 + (size_t)((batch + 15) / 16 - 3)]; }
+
 // partial sums of the largest matrix: 32 rows of the first kernel, 64 or 128 (one and two batch groups: fewer rows have the
-// same splits) of the one for many rows
+// same splits) of the wide one, and of the one by columns
 size_t sbits_mp_gemm_ws_bytes(const sbits_plan *plan)
 {
     if (!sbits_mp_gemm_shapes_ok(plan)) return 0;
@@ -1154,6 +1526,7 @@ size_t sbits_mp_gemm_ws_bytes(const sbits_plan *plan)
         need(sbits_mp_gemm_splits(plan->cols[i], plan->n), 32);
         need(wide_split(plan->rows[i], nbc, plan->n, 64).n_split, 64);
         need(wide_split(plan->rows[i], nbc, plan->n, 128).n_split, 128);
+        for (int tiles = 3; tiles <= 8; ++tiles) need(many_of(plan, i, tiles * 16).n_split, tiles * 16);
     }
     return sbits_align_up(mx, 256);
 }
@@ -1195,6 +1568,31 @@ static int launch_wide(sbits_ctx *ctx, const MpArgs &a, dim3 grid, int cols_per_
     hipLaunchKernelGGL(fn, grid, dim3(WG_THREADS), lds, ctx->stream, a, cols_per_split);
     SBITS_HIP(ctx, hipGetLastError());
     return SBITS_OK;
+}
+
+template <int N_COLS, int NB, int CT, int WAVES>
+static int launch_many(sbits_ctx *ctx, const MpArgs &a, const ManySplit &ms)
+{
+    constexpr size_t x = (size_t)WAVES * NB * 16 * N_COLS * 2 / 1024 * 1040, red = (size_t)WAVES * CT * NB * 1024;
+    constexpr size_t all = x + (size_t)(32768 / N_COLS) * 16, lds = all > red ? all : red;      // (and the waves' tables of their blocks)
+    auto *fn = &mp_gemm_many_kernel<N_COLS, NB, CT, WAVES>;
+    SBITS_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    const dim3 grid((unsigned)((a.R + CT * 16 - 1) / (CT * 16)), (unsigned)ms.n_split, (unsigned)((a.batch + NB * 16 - 1) / (NB * 16)));
+    hipLaunchKernelGGL(fn, grid, dim3(64 * WAVES), lds, ctx->stream, a, ms.per_split);
+    SBITS_HIP(ctx, hipGetLastError());
+    return SBITS_OK;
+}
+
+template <int N_COLS>
+static int launch_many_shape(sbits_ctx *ctx, const MpArgs &a, const ManySplit &ms)      // (the order of MANY_128 and MANY_64)
+{
+    switch (ms.shape) {
+    case 0: return launch_many<N_COLS, 2, 2, 8>(ctx, a, ms);
+    case 1: return launch_many<N_COLS, 3, 2, 8>(ctx, a, ms);
+    case 2: return launch_many<N_COLS, 3, 4, 4>(ctx, a, ms);
+    case 3: return launch_many<N_COLS, 4, 4, 4>(ctx, a, ms);
+    default: return launch_many<N_COLS, 4, 4, 8>(ctx, a, ms);
+    }
 }
 
 template <int RG>
@@ -1259,20 +1657,37 @@ static FewRows few_rows(const sbits_plan *plan, int64_t R, int nbc, int batch)
 
 // Up to 16 block columns and two turns of the narrow kernel, where both take hardly more than a launch, it is the better one (up to
 // 16 rows by 3 .. 8 % on average and at most 3 % slower, up to 32 by 5 .. 26 %).
-// Above 32 rows the alternative is the wide kernel, whose estimate is above the launch: 2.5 us fit best (of 1 .. 5; always the wide one:
-// 18 % slower).  A pitch of x past the 32-bit offsets of the narrow kernel: the first.
-static bool takes_narrow(const sbits_plan *plan, const MpArgs &a, const WideSplit &ws)
+// Above 32 rows: against the estimate of the wide kernel, 2.5 us above its cost (always the wide one: 18 % slower), where a plan
+// has a candidate of 1 bit, whose codes enter those kernels with another offset (wide_block_1bit): which rows have which stays as
+// it is, so that they are as exact as before and differ no more.  Else against the better of the two kernels of many rows.
+// A pitch of x past the 32-bit offsets of the narrow kernel: the first.
+static bool has_one_bit(const sbits_plan *plan)
+{
+    for (int l = 0; l < plan->K; ++l)
+        if (plan->bits[l] == 1) return true;
+    return false;
+}
+static double wide_us(const WideSplit &ws) { return 0.01 * (double)(ws.cost + 250); }
+static double many_rows_us(const sbits_plan *plan, int mat, int batch)
+{
+    const double many = many_of(plan, mat, batch).us, wide = wide_us(wide_split(plan->rows[mat], (int)(plan->cols[mat] / plan->n), plan->n, batch));
+    return many < wide ? many : wide;
+}
+static bool takes_narrow(const sbits_plan *plan, int mat, const MpArgs &a)
 {
     if (a.batch > 64 || a.ld_x > 1 << 25) return false;
     if (a.batch <= 32 && a.nbc <= MG_SPAN && a.R / 32 * ((a.batch + 15) / 16) <= 512) return true;
     const FewRows t = few_rows(plan, a.R, a.nbc, a.batch);
-    return a.batch > 32 ? t.narrow * 100 < (double)(ws.cost + 250) : t.narrow <= t.first;
+    if (a.batch <= 32) return t.narrow <= t.first;
+    if (has_one_bit(plan)) return t.narrow * 100 < (double)(wide_split(a.R, a.nbc, plan->n, a.batch).cost + 250);
+    return t.narrow <= many_rows_us(plan, mat, a.batch);
 }
 
 // Rows of x the next launch takes of those that are left: 128 (two batch groups) while a group's byte offsets fit the 32 bits
-// of a descriptor, else the 32 of the first kernel, whose addresses have 64.  A second group of up to 32 rows costs the wide
-// kernel as much as one of 64, so it is left to the kernels for few rows where that is faster: 16640 x 4096 at 65 rows 51
-// us instead of 69, 20480 x 2048 33 instead of 39 (1024 x 4096: 12 us at once, 18 in two).
+// of a descriptor, else the 32 of the first kernel, whose addresses have 64.  The wide kernel takes a second group of up to 32 rows as
+// long as one of 64, so those rows are left to the kernels for few rows where that is faster: 16640 x 4096 at 65 rows 51
+// us instead of 69 in it.  (With a candidate of 1 bit by the wide kernel's estimates alone, see takes_narrow; the kernel by columns takes
+// groups of 32 or 48 rows, and is rarely the slower one.)
 int sbits_mp_gemm_rows(const sbits_plan *plan, int mat, int64_t ld_x, int left)
 {
     if (ld_x > 1 << 20) return left < 32 ? left : 32;
@@ -1280,8 +1695,12 @@ int sbits_mp_gemm_rows(const sbits_plan *plan, int mat, int64_t ld_x, int left)
         const int64_t R = plan->rows[mat];
         const int n = plan->n, nbc = (int)(plan->cols[mat] / n);
         const FewRows t = few_rows(plan, R, nbc, left - 64);
-        const int64_t rest = (int64_t)((t.narrow < t.first ? t.narrow : t.first) * 100);
-        if (wide_split(R, nbc, n, 64).cost + rest + 300 <= wide_split(R, nbc, n, left).cost) return 64;
+        const double rest = t.narrow < t.first ? t.narrow : t.first;
+        if (has_one_bit(plan)) {
+            if (wide_split(R, nbc, n, 64).cost + (int64_t)(rest * 100) + 300 <= wide_split(R, nbc, n, left).cost) return 64;
+        } else if (many_rows_us(plan, mat, 64) + rest <= many_rows_us(plan, mat, left)) {
+            return 64;
+        }
     }
     return left < 128 ? left : 128;
 }
@@ -1299,10 +1718,8 @@ int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t 
     a.block_base = plan->base[mat]; a.ld_x = ld_x;
     a.R = (int)plan->rows[mat]; a.C = (int)plan->cols[mat]; a.m = plan->m; a.nbc = a.C / plan->n;
     a.batch = batch;
-    const bool wide = batch > 32;
-    const WideSplit ws = wide ? wide_split(a.R, a.nbc, plan->n, batch) : WideSplit{0, 0, 0, 0};
     for (int c = 0; c < sbits::MAX_CAND; ++c) a.bits[c] = c < plan->K ? plan->bits[c] : plan->bits[plan->K - 1];
-    if (takes_narrow(plan, a, ws)) {
+    if (takes_narrow(plan, mat, a)) {
         a.n_split = 1;
         a.out = y;
         // Workgroups of 16 waves while all of them are on the chip at once, one a CU (against 8 waves 2 .. 14 % faster): more codes
@@ -1321,13 +1738,19 @@ int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t 
         if (plan->n == 128) return deep ? launch_narrow<128, 16, false, false>(ctx, a) : launch_narrow<128, 8, false, false>(ctx, a);
         return deep ? launch_narrow<64, 16, false, false>(ctx, a) : launch_narrow<64, 8, false, false>(ctx, a);
     }
-    a.n_split = wide ? ws.n_split : sbits_mp_gemm_splits(a.C, plan->n);
+    const bool many = batch > 32;
+    const ManySplit ms = many ? many_of(plan, mat, batch) : ManySplit{0, 0, 0, 0.0};
+    const WideSplit ws = many ? wide_split(a.R, a.nbc, plan->n, batch) : WideSplit{0, 0, 0, 0};
+    const bool wide = many && wide_us(ws) < ms.us;
+    a.n_split = wide ? ws.n_split : many ? ms.n_split : sbits_mp_gemm_splits(a.C, plan->n);
     a.out = a.n_split > 1 ? static_cast<float *>(scratch) : y;
     int rc;
     if (wide) {
         const int rows = ws.rg * 32;
         const dim3 grid((unsigned)((a.R + rows - 1) / rows), (unsigned)a.n_split, (unsigned)((batch + 63) / 64));
         rc = ws.rg == 4 ? launch_wide_rg<4>(ctx, plan->n, a, grid, ws.per_split) : launch_wide_rg<2>(ctx, plan->n, a, grid, ws.per_split);
+    } else if (many) {
+        rc = plan->n == 128 ? launch_many_shape<128>(ctx, a, ms) : launch_many_shape<64>(ctx, a, ms);
     } else {
         // Channels of a workgroup: x takes 32 .. 128 KiB of LDS, and as many waves as the registers allow (16) should be on a
         // CU.  64-column blocks up to 16 rows: four workgroups of 32 channels.  Else 64 (128 with 128 KiB of x), and half as

@@ -23,6 +23,11 @@ constexpr size_t SBITS_PINNED_BYTES = 4096;
 // compute units that work is spread over; a host-only context plans for a whole device
 static inline int sbits_cus(const sbits_ctx *ctx) { return ctx->cus > 0 ? ctx->cus : 256; }
 
+namespace sbits {
+// how the product of many rows by columns is cut up (mpgemm.hip), and its estimated time
+struct ManySplit { int shape, per_split, n_split; double us; };
+}  // namespace sbits
+
 struct sbits_plan {
     sbits_ctx *ctx;
     int n_mats;
@@ -43,6 +48,7 @@ struct sbits_plan {
     struct FusedClass { int64_t cols; int first, pre_first, n, opu; };
     std::vector<FusedClass> fused_classes;   // the same grouping for the fused gather + cost launch
     std::vector<int> fused_members, fused_pre;
+    std::vector<sbits::ManySplit> many;      // of each matrix: products of 33 .. 48, 49 .. 64, .. 113 .. 128 rows of x
     std::vector<sbits::MatDesc> descs;       // shape part filled at creation; pointers per call
     size_t head_bytes;                       // workspace head: descriptor table + workgroup prefixes
     size_t ws_bytes;
@@ -115,6 +121,7 @@ void sbits_cost_tables(sbits_plan *plan);
 void sbits_pack_tables(sbits_plan *plan);
 void sbits_fused_tables(sbits_plan *plan);
 void sbits_gather_tables(sbits_plan *plan);
+void sbits_mp_gemm_tables(sbits_plan *plan);
 int sbits_launch_cost_all(sbits_plan *plan, const void *w_re, const float *s_re, float *cost, void *ws);
 // gather fused with the cost table (reads the original matrices once; writes w_re and cost)
 bool sbits_fused_shapes_ok(const sbits_plan *plan);
