@@ -112,11 +112,11 @@ int sbits_plan_create(sbits_ctx *ctx, const int64_t *rows, const int64_t *cols, 
         d.elem_off = p->sum_elems; d.block_base = p->N;
         d.row_off = p->sum_rows; d.col_off = p->sum_cols;
         d.nbr = (int)(rows[i] / block_rows); d.nbc = (int)(cols[i] / block_cols);
-        sbits_score_geometry(rows[i], cols[i], p->score_rows, &d.nseg, &d.nband);
+        sbits_score_geometry(rows[i], cols[i], p->score_rows, &d.npanel, &d.nband);
         d.rowpart_off = p->sum_rowpart; d.colpart_off = p->sum_colpart;
-        p->sum_rowpart += rows[i] * d.nseg; p->sum_colpart += (int64_t)d.nband * cols[i];
+        p->sum_rowpart += rows[i] * d.npanel; p->sum_colpart += (int64_t)d.nband * cols[i];
         p->score_wg_start.push_back((int)score_wgs);
-        score_wgs += sbits_score_wgs(d.nseg, d.nband);
+        score_wgs += sbits_score_wgs(d.npanel, d.nband);
         p->descs.push_back(d);
         p->sum_rows += rows[i]; p->sum_cols += cols[i]; p->sum_elems += rows[i] * cols[i];
         p->N += (rows[i] / block_rows) * (cols[i] / block_cols);

@@ -7,11 +7,8 @@
 // column, each summed in the canonical order: runs of 8 consecutive elements
 // left to right from +0, then an adjacent-pair tree over the runs (zero padded
 // to a power of two).  One pass over S serves both directions.  A workgroup of
-// four waves walks a band of up to 256 rows over a panel of 4096 columns, row by row
-// (16 KiB of consecutive bytes per row); a wave owns two 512-column segments of
-// the panel and reads each with two 1 KiB loads, so a run of 8 columns sits in a
-// lane pair and the 16 columns of a lane keep their sums in registers for the
-// whole band.  The partial trees (per row and 512-column segment; per column
+// four waves walks a band of up to 512 rows over a panel of 4096 columns, row by row
+// (16 KiB of consecutive bytes per row).  The partial trees (per row and panel; per column
 // and band) go to the workspace and a small kernel finishes them.
 //
 // Argsort.  Descending by score, ties to the lower index: inverted ordered-float
@@ -32,170 +29,158 @@ namespace sbits {
 
 // ================================================================ scores
 constexpr int SC_THREADS = 256;
-constexpr int SC_ROWS = 256;    // most rows per band (32 octets): one workgroup walks a whole band
+constexpr int SC_ROWS = 512;    // most rows per band (64 octets): one workgroup walks a whole band
 constexpr int SC_COLS = 512;    // columns per segment: one wave, two 1 KiB loads per row
 constexpr int SC_PANEL = 8;     // segments per workgroup: 4 waves x 2 segments = 4096 columns = 16 KiB per row
 
-// rowpart[r][seg]  : tree over the 64 column runs of segment seg (zero beyond C)
-// colpart[band][c] : tree over the row runs (8 rows each) of band (zero beyond R)
+// rowpart[r][panel] : tree over the 8 segments' trees over their 64 column runs (zero beyond C)
+// colpart[band][c]  : tree over the row runs (8 rows each) of band (zero beyond R)
 //
-// A workgroup reads rows of 16 KiB (its panel of 8 segments) top to bottom, so HBM sees long
-// consecutive runs, and every load instruction of a wave covers 1 KiB of consecutive bytes (whole
-// cache lines), which is what non-temporal loads need to run at full rate.  Wave w owns segments
-// w and w + 4 of the panel.  Inside a segment lane l owns columns 4l..4l+3 and 256+4l..256+4l+3:
-// a run of 8 consecutive columns sits in the lane pair (2k, 2k+1).  Column sums stay in registers
-// for the whole band (16 columns per lane, an adjacent-pair tree of up to 5 levels over its octets).
+// A workgroup reads rows of 16 KiB (its panel of 8 segments) top to bottom; wave w owns segments w and w + 4, and of each row
+// brings four contiguous KiB of its own, non-temporal, straight into a ring of rows in LDS: no barrier, no registers
+// for what is on its way.  A lane reads the 8 columns of a run of each segment out of it; a row's runs go through a
+// butterfly over the wave, column sums stay in registers for the whole band (16 columns a lane, an adjacent-pair tree over
+// its octets).
+// What bounds it is HBM, and what keeps it from the 7.0 TB/s of loads alone is writing: a few isolated writes cost the stream
+// of reads far more than their bytes (28 GB in 4.03 ms without any, 4.71 with a partial sum per 512 and per 256 elements, 0.6 % of the
+// bytes).  So a row's 8 segments are added up before they leave, bands have 512 rows where there are many, and what is
+// written goes through the L2 at once (sc1: 4.71 -> 4.36 ms, nontemporal 4.41).  All together 4.71 -> 4.21 ms (6.6 TB/s); four layers of that
+// model 600 -> 527 us, two 283 -> 264, one 144 -> 128, 8192 x 28672 four times 640 -> 547, 2048 x 2048 10.5 -> 8.2.  Its predecessor held the
+// rows on their way in registers.
 // A band has band_rows rows, a power of two: see sbits_score_rows().
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+
+// RING: rows of a wave on their way.  3 where two workgroups with the row sums of 512 rows share a CU, 4 with 256 rows, 8 where a CU has one.
+template <int RING>
 __global__ __launch_bounds__(SC_THREADS, 2)
 void score_partial_kernel(const MatDesc *__restrict__ descs, MatDesc one, const int *__restrict__ wg_start,
                           int n_mats, int band_rows, float *__restrict__ rowpart_all, float *__restrict__ colpart_all)
 {
-    const int mat = descs ? find_matrix(wg_start, n_mats, (int)blockIdx.x) : 0;
-    const MatDesc d = descs ? descs[mat] : one;
+    constexpr int ROW = 2 * SC_COLS * 4;                 // bytes of a wave's part of a row
+    extern __shared__ __attribute__((aligned(1024))) unsigned char ring[];        // [wave][slot], and the band's row sums [row][segment of the panel]
+    float *const rowsum = reinterpret_cast<float *>(ring + SC_THREADS / 64 * RING * ROW);
+    const int mat = descs ? __builtin_amdgcn_readfirstlane(find_matrix(wg_start, n_mats, (int)blockIdx.x)) : 0;
+    const MatDesc &d = descs ? descs[mat] : one;
     const int lid = (int)blockIdx.x - (descs ? wg_start[mat] : 0);
-    const int npanel = (d.nseg + SC_PANEL - 1) / SC_PANEL;
-    const int band = lid / npanel, panel = lid - band * npanel;
-    const int R = (int)d.rows, C = (int)d.cols;
-    const int64_t ld = d.ld_s;
-    // the descriptor's pointer is a generic one for the compiler: say that it is global memory
-    typedef const char __attribute__((address_space(1))) *gcharp;
-    typedef const __attribute__((address_space(1))) f32x4_t *gf4p;
-    gcharp Sg = (gcharp)(reinterpret_cast<const char *>(d.s));
-    float *__restrict__ rowpart = rowpart_all + d.rowpart_off;
-    float *__restrict__ colpart = colpart_all + d.colpart_off;
+    // (uniform, which the compiler does not see where they come through a pointer)
+    auto uniform = [](int64_t v) {
+        return (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)v >> 32)) << 32 |
+                         (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v));
+    };
+    const int npanel = __builtin_amdgcn_readfirstlane(d.npanel);
+    const int band = __builtin_amdgcn_readfirstlane(lid / npanel), panel = __builtin_amdgcn_readfirstlane(lid - band * npanel);
+    const int R = (int)uniform(d.rows), C = (int)uniform(d.cols);
+    float *__restrict__ rowpart = rowpart_all + uniform(d.rowpart_off);
+    float *__restrict__ colpart = colpart_all + uniform(d.colpart_off);
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    int seg[2], col0[2][2];
-    bool ok[2][2];
-    uint32_t voff[2][2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        seg[j] = panel * SC_PANEL + wave + 4 * j;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            col0[j][h] = seg[j] * SC_COLS + h * (SC_COLS / 2) + lane * 4;
-            ok[j][h] = col0[j][h] < C;                   // C is a multiple of 8 (4 columns: all in or all out)
-            voff[j][h] = (uint32_t)(ok[j][h] ? col0[j][h] : C - 4) * 4u;   // clamped: in bounds, value dropped
-        }
-    }
+    const int seg0 = panel * SC_PANEL + wave;            // and seg0 + 4
     const int rbase = band * band_rows;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)ring + (uint32_t)(wave * RING * ROW);
 
-    // two rows of the panel per pipeline stage: 8 loads of 16 bytes per lane
-    struct Stage { float4 v[2][2][2]; };             // [row][segment][half of the segment]
-    auto load_stage = [&](Stage &o, int r0) {
+    const uint32_t rowsum0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)ring + (uint32_t)(SC_THREADS / 64 * RING * ROW);
+    // row r of the band into a slot of the ring; what is past the matrix's columns or rows reads as zero and is not fetched
+    const int64_t pitch = uniform(d.ld_s) * 4;
+    const char *const S = reinterpret_cast<const char *>(uniform((int64_t)(uintptr_t)d.s)) + (int64_t)rbase * pitch;
+    const int rows = min(band_rows, R - rbase);
+    auto fetch = [&](int r, uint32_t slot) {
+        const rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(S) + r * pitch, 0, r < rows ? C * 4 : 0, 0x00027000);
 #pragma unroll
-        for (int rr = 0; rr < 2; ++rr) {
-            int r = rbase + r0 + rr;
-            r = r < R ? r : R - 1;                   // rows beyond R are clamped and dropped
-            gcharp p = Sg + (int64_t)r * ld * 4;
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const f32x4_t t = __builtin_nontemporal_load((gf4p)(p + voff[j][h]));
-                    o.v[rr][j][h] = make_float4(t.x, t.y, t.z, t.w);
-                }
-        }
+        for (int q = 0; q < 4; ++q)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)(slot + (uint32_t)q * 1024), 16,
+                                                     (seg0 + 4 * (q >> 1)) * (SC_COLS * 4) + (q & 1) * 1024 + lane * 16, 0, 0, 2 /* nontemporal */);
     };
 
-    // sum of one run of 8 columns held by a lane pair, left to right; both lanes end with it
-    auto run_sum = [&](const float (&x)[4]) {
-        const float p = ((x[0] + x[1]) + x[2]) + x[3];               // the run's first four (even lane)
-        const float start = dpp_mov<0xA0>(p);                         // quad_perm [0,0,2,2]: odd lane <- even lane
-        const float q = (((start + x[0]) + x[1]) + x[2]) + x[3];      // odd lane: the whole run
-        return dpp_mov<0xF5>(q);                                      // quad_perm [1,1,3,3]: both lanes <- odd lane
-    };
-    // adjacent-pair tree over the 32 runs held by 64 lanes (lane pairs agree on entry)
-    auto tree_runs = [&](float v) {
-        v = v + dpp_mov<DPP_XOR2>(v);
-        v = v + dpp_mov<DPP_HALF_MIRROR>(v);
-        v = v + dpp_mov<DPP_MIRROR>(v);
-        v = v + __shfl_xor(v, 16);
-        v = v + __shfl_xor(v, 32);
-        return v;
-    };
-
-    float colrun[16], t1[16], t2[16], t3[16], t4[16], t5[16], col[16];
-    auto process = [&](const Stage &cur, int r0) {   // rows r0, r0 + 1 of the band
+    constexpr int SC_THROUGH = 16;                       // sc1
+    const rsrc_t cols_out = __builtin_amdgcn_make_buffer_rsrc(colpart + (int64_t)band * C, 0, C * 4, 0x00027000);
+    const rsrc_t rows_out = __builtin_amdgcn_make_buffer_rsrc(rowpart + (int64_t)rbase * npanel + panel, 0, ((rows - 1) * npanel + 1) * 4, 0x00027000);
+    float colrun[16], t1[16], t2[16], t3[16], t4[16], t5[16], t6[16];
+    uint32_t slot = lds0;
+    const uint32_t last = lds0 + (RING - 1) * ROW;
 #pragma unroll
-        for (int rr = 0; rr < 2; ++rr) {
-            const int rb = r0 + rr;                  // row inside the band
-            const bool rok = rbase + rb < R;
-            if ((rb & 7) == 0) {
+    for (int r = 0; r < RING; ++r) fetch(r, lds0 + (uint32_t)(r * ROW));
+#pragma unroll 1
+    for (int oc = 0; oc < band_rows / 8; ++oc) {
+        float keep = 0.0f;
 #pragma unroll
-                for (int e = 0; e < 16; ++e) colrun[e] = 0.0f;
-            }
+        for (int k = 0; k < 8; ++k) {
+            f32x4_t v[2][2];
+            // the row is there (those behind it may be on their way; a store in between makes the wait longer, never shorter)
+            asm volatile("s_waitcnt vmcnt(%0)" :: "n"(4 * (RING - 1)) : "memory");
+            asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:16\n\tds_read_b128 %2, %4 offset:2048\n\t"
+                         "ds_read_b128 %3, %4 offset:2064\n\ts_waitcnt lgkmcnt(0)"
+                         : "=&v"(v[0][0]), "=&v"(v[0][1]), "=&v"(v[1][0]), "=&v"(v[1][1]) : "v"(slot + (uint32_t)lane * 32) : "memory");
+            fetch(8 * oc + k + RING, slot);
+            slot = slot == last ? lds0 : slot + ROW;
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                float x[2][4];
+                float x[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    x[e] = fabsf(v[j][e >> 2][e & 3]);
+                    colrun[j * 8 + e] = (k == 0 ? 0.0f : colrun[j * 8 + e]) + x[e];       // top to bottom, 8 rows
+                }
+                float rs = x[0];                              // a run of 8, left to right
+#pragma unroll
+                for (int e = 1; e < 8; ++e) rs = rs + x[e];
+                rs = group_allreduce<64>(rs, OpAdd());           // the adjacent-pair tree over the segment's 64 runs
+                keep = lane == 8 * j + k ? rs : keep;
+            }
+#pragma unroll
+            for (int e = 0; e < 16; ++e) asm volatile("" : "+v"(colrun[e]));      // (now, not all rows' at the octet's end, which spills)
+        }
+        // (asm: the compiler would wait for the rows on their way before it touches LDS)
+        if (lane < 16)
+            asm volatile("ds_write_b32 %0, %1" :: "v"(rowsum0 + (uint32_t)(((8 * oc + (lane & 7)) * SC_PANEL + wave + 4 * (lane >> 3)) * 4)), "v"(keep) : "memory");
+        // columns: adjacent-pair tree over the band's octets, fed one octet at a time
+        auto add = [&](const float (&t)[16]) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) colrun[e] = t[e] + colrun[e];
+        };
+        auto set = [&](float (&t)[16]) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) t[e] = colrun[e];
+        };
+        if (oc & 1) {
+            add(t1);
+            if (oc & 2) {
+                add(t2);
+                if (oc & 4) {
+                    add(t3);
+                    if (oc & 8) {
+                        add(t4);
+                        if (oc & 16) {
+                            add(t5);
+                            if (oc & 32) add(t6);
+                            else set(t6);
+                        } else set(t5);
+                    } else set(t4);
+                } else set(t3);
+            } else set(t2);
+        } else set(t1);
+        if (oc == band_rows / 8 - 1) {                        // (all the octets, a power of two: the tree's root)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int c = (seg0 + 4 * j) * SC_COLS + lane * 8;
+                if (c >= C) continue;                         // (a run is inside or past the matrix)
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
-                    const float4 t = cur.v[rr][j][h];
-                    const float raw[4] = {t.x, t.y, t.z, t.w};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        x[h][e] = (ok[j][h] && rok) ? fabsf(raw[e]) : 0.0f;
-                        colrun[j * 8 + h * 4 + e] = colrun[j * 8 + h * 4 + e] + x[h][e];   // top to bottom, 8 rows
-                    }
-                }
-                // runs of 8 left to right, then the adjacent-pair tree over the segment's 64 runs
-                // (32 in its first 256 columns, 32 in the second)
-                const float rs = tree_runs(run_sum(x[0])) + tree_runs(run_sum(x[1]));
-                if (lane == 0 && rok && seg[j] < d.nseg) rowpart[(int64_t)(rbase + rb) * d.nseg + seg[j]] = rs;
-            }
-            if ((rb & 7) == 7) {
-                // columns: adjacent-pair tree over the band's octets, fed one octet at a time
-                const int oc = rb >> 3;
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    float v = colrun[e];
-                    if (oc & 1) {
-                        v = t1[e] + v;
-                        if (oc & 2) {
-                            v = t2[e] + v;
-                            if (oc & 4) {
-                                v = t3[e] + v;
-                                if (oc & 8) {
-                                    v = t4[e] + v;
-                                    if (oc & 16) v = t5[e] + v;
-                                    else t5[e] = v;
-                                } else {
-                                    t4[e] = v;
-                                }
-                            } else {
-                                t3[e] = v;
-                            }
-                        } else {
-                            t2[e] = v;
-                        }
-                    } else {
-                        t1[e] = v;
-                    }
-                    col[e] = v;
+                    u32x4_t v;
+                    v.x = __float_as_uint(colrun[j * 8 + h * 4]); v.y = __float_as_uint(colrun[j * 8 + h * 4 + 1]);
+                    v.z = __float_as_uint(colrun[j * 8 + h * 4 + 2]); v.w = __float_as_uint(colrun[j * 8 + h * 4 + 3]);
+                    __builtin_amdgcn_raw_buffer_store_b128(v, cols_out, (c + 4 * h) * 4, 0, SC_THROUGH);
                 }
             }
         }
-    };
-    // two buffers in ping-pong: the next two rows are in flight while the current two are summed
-    Stage A, B;
-    load_stage(A, 0);
-#pragma unroll 1
-    for (int r0 = 0; r0 < band_rows; r0 += 4) {
-        load_stage(B, r0 + 2);
-        process(A, r0);
-        load_stage(A, r0 + 4 < band_rows ? r0 + 4 : band_rows - 2);   // the last reload is redundant and harmless
-        process(B, r0 + 2);
     }
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-            if (ok[j][h]) {
-                float *dst = colpart + (int64_t)band * C + col0[j][h];
-                *reinterpret_cast<float4 *>(dst) = make_float4(col[j * 8 + h * 4], col[j * 8 + h * 4 + 1],
-                                                               col[j * 8 + h * 4 + 2], col[j * 8 + h * 4 + 3]);
-            }
+    // the panel's segments of a row: the next three levels of its tree
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    for (int r = threadIdx.x; r < rows; r += SC_THREADS) {
+        const float *const x = rowsum + r * SC_PANEL;
+        const float v = ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rows_out, r * npanel * 4, 0, SC_THROUGH);
+    }
 }
 
 // adjacent-pair tree over 32 leaves x[(i0 + i) * stride], i < 32, zero beyond n
@@ -248,7 +233,7 @@ __global__ void score_finish_kernel(const MatDesc *__restrict__ descs, MatDesc o
     const MatDesc &d = descs ? descs[mat] : one;
     if (is_row) {
         const int64_t r = ch - d.row_off;
-        rs_all[ch] = tree_upto128(rowpart_all + d.rowpart_off + r * d.nseg, d.nseg, 1);
+        rs_all[ch] = tree_upto128(rowpart_all + d.rowpart_off + r * d.npanel, d.npanel, 1);
     } else {
         const int64_t c = ch - d.col_off;
         cs_all[ch] = tree_upto128(colpart_all + d.colpart_off + c, d.nband, d.cols);
@@ -575,7 +560,7 @@ using namespace sbits;
 
 // ---- workspace of the reorder stage (after the head) ---------------------------------
 //   scores [L] | rowpart [RP] | colpart [CP] | keys [L] | idx [L]
-// with L = channels (rows + cols), RP = sum rows*nseg, CP = sum nband*cols.
+// with L = channels (rows + cols), RP = sum rows*npanel, CP = sum nband*cols.
 struct ReorderWs {
     float *scores, *rowpart, *colpart;
     uint32_t *keys, *idx;
@@ -595,32 +580,36 @@ static size_t reorder_ws_layout(void *base, int64_t L, int64_t RP, int64_t CP, R
     return b;
 }
 
-// workgroups of score_partial_kernel for a matrix with nseg segments and nband bands
-int sbits_score_wgs(int nseg, int nband) { return nband * ((nseg + SC_PANEL - 1) / SC_PANEL); }
+// workgroups of score_partial_kernel for a matrix with npanel panels and nband bands
+int sbits_score_wgs(int npanel, int nband) { return nband * npanel; }
 
-void sbits_score_geometry(int64_t R, int64_t C, int band_rows, int *nseg, int *nband)
+void sbits_score_geometry(int64_t R, int64_t C, int band_rows, int *npanel, int *nband)
 {
-    *nseg = (int)((C + SC_COLS - 1) / SC_COLS);
+    *npanel = (int)((C + SC_PANEL * SC_COLS - 1) / (SC_PANEL * SC_COLS));
     *nband = (int)((R + band_rows - 1) / band_rows);
 }
 
-// Rows per band for a plan of these matrices: as many as the kernel takes (long bands read S in the longest runs and leave
-// the fewest partial sums: a layer with 907 workgroups of 256 rows takes 685 us, with 128 rows a band 694, with 64 716),
+// Rows per band for a plan of these matrices: 512, which leave the fewest partial sums, where they take no more turns of two workgroups a CU
+// than bands of 256 (432 workgroups instead of 864: 527 us and 559; 104 instead of 208, half of the CUs idle: 180 and 130; 5 % is what the
+// fewer sums are worth); else 256,
 // halved while there would be fewer than 192 workgroups, whose rows come one after the other, and as long as one tree of
 // 128 adds up a column.  Scores and permutations: 512 x 512 136 us with 256 rows, 34 with 8; 2048 x 2048 145 -> 47 (16
 // rows); 4096 x 4096 159 -> 58 (32); 2048 x 8192 twice 161 -> 60 (32); a 2048-wide layer (100 workgroups) 163 -> 104 (128).
 // The line: 216 workgroups take 190 us, with half the rows 187, with a quarter 204.
 int sbits_score_rows(const int64_t *rows, const int64_t *cols, int n_mats)
 {
-    int64_t wgs = 0, max_rows = 0;
+    int64_t wgs = 0, tall = 0, max_rows = 0;                  // in bands of 256 and of 512
     for (int i = 0; i < n_mats; ++i) {
-        int nseg, nband;
-        sbits_score_geometry(rows[i], cols[i], SC_ROWS, &nseg, &nband);
-        wgs += sbits_score_wgs(nseg, nband);
+        int npanel, nband;
+        sbits_score_geometry(rows[i], cols[i], SC_ROWS, &npanel, &nband);
+        tall += sbits_score_wgs(npanel, nband);
+        sbits_score_geometry(rows[i], cols[i], SC_ROWS / 2, &npanel, &nband);
+        wgs += sbits_score_wgs(npanel, nband);
         if (rows[i] > max_rows) max_rows = rows[i];
     }
-    int r = SC_ROWS;
-    while (r > 8 && wgs * (SC_ROWS / r) < 192 && max_rows <= 128 * (r / 2)) r >>= 1;
+    if (tall >= 400 && 95 * ((tall + 511) / 512) * 2 <= 100 * ((wgs + 511) / 512)) return SC_ROWS;
+    int r = SC_ROWS / 2;
+    while (r > 8 && wgs * (256 / r) < 192 && max_rows <= 128 * (r / 2)) r >>= 1;
     return r;
 }
 
@@ -637,15 +626,23 @@ static MatDesc single_desc(const void *W, const float *S, int64_t R, int64_t C, 
     d.w = static_cast<const uint16_t *>(W);
     d.s = S;
     d.rows = R; d.cols = C; d.ld_w = ld_w; d.ld_s = ld_s;
-    sbits_score_geometry(R, C, band_rows, &d.nseg, &d.nband);
+    sbits_score_geometry(R, C, band_rows, &d.npanel, &d.nband);
     return d;
 }
 
 static int run_scores(sbits_ctx *ctx, const MatDesc *descs, const MatDesc &one, const int *d_wg_start,
                       int n_mats, int total_wg, int band_rows, int64_t sum_rows, int64_t sum_cols, const ReorderWs &w)
 {
-    hipLaunchKernelGGL(score_partial_kernel, dim3((unsigned)total_wg), dim3(SC_THREADS), 0, ctx->stream,
-                       descs, one, d_wg_start, n_mats, band_rows, w.rowpart, w.colpart);
+    auto launch = [&](auto *kernel, int ring) -> int {
+        const size_t lds = (size_t)SC_THREADS / 64 * ring * 2 * SC_COLS * 4 + (size_t)band_rows * SC_PANEL * 4;
+        if (lds > 65536) SBITS_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        hipLaunchKernelGGL(kernel, dim3((unsigned)total_wg), dim3(SC_THREADS), lds, ctx->stream, descs, one, d_wg_start, n_mats, band_rows,
+                           w.rowpart, w.colpart);
+        return SBITS_OK;
+    };
+    const int rc = band_rows == 512 ? launch(&score_partial_kernel<3>, 3) : band_rows == 256 ? launch(&score_partial_kernel<4>, 4)
+                                                                                              : launch(&score_partial_kernel<8>, 8);
+    if (rc) return rc;
     SBITS_HIP(ctx, hipGetLastError());
     const int64_t L = sum_rows + sum_cols;
     hipLaunchKernelGGL(score_finish_kernel, dim3((unsigned)((L + 255) / 256)), dim3(256), 0, ctx->stream,
@@ -684,8 +681,8 @@ int sbits_launch_scores(sbits_ctx *ctx, const float *S, int64_t R, int64_t C, in
 {
     MatDesc one = single_desc(nullptr, S, R, C, C, ld, band_rows);
     ReorderWs w;
-    reorder_ws_layout(scratch, R + C, R * one.nseg, (int64_t)one.nband * C, &w);
-    int rc = run_scores(ctx, nullptr, one, nullptr, 1, sbits_score_wgs(one.nseg, one.nband), band_rows, R, C, w);
+    reorder_ws_layout(scratch, R + C, R * one.npanel, (int64_t)one.nband * C, &w);
+    int rc = run_scores(ctx, nullptr, one, nullptr, 1, sbits_score_wgs(one.npanel, one.nband), band_rows, R, C, w);
     if (rc) return rc;
     if (row_score)
         SBITS_HIP(ctx, hipMemcpyAsync(row_score, w.scores, (size_t)R * 4, hipMemcpyDeviceToDevice, ctx->stream));
@@ -699,8 +696,8 @@ int sbits_launch_reorder(sbits_ctx *ctx, const float *S, int64_t R, int64_t C, i
 {
     MatDesc one = single_desc(nullptr, S, R, C, C, ld, band_rows);
     ReorderWs w;
-    reorder_ws_layout(scratch, R + C, R * one.nseg, (int64_t)one.nband * C, &w);
-    int rc = run_scores(ctx, nullptr, one, nullptr, 1, sbits_score_wgs(one.nseg, one.nband), band_rows, R, C, w);
+    reorder_ws_layout(scratch, R + C, R * one.npanel, (int64_t)one.nband * C, &w);
+    int rc = run_scores(ctx, nullptr, one, nullptr, 1, sbits_score_wgs(one.npanel, one.nband), band_rows, R, C, w);
     if (rc) return rc;
     const int64_t len = R > C ? R : C;
     return run_argsort(ctx, SortArrays{nullptr, one, 1, 1, R, nullptr, nullptr, row_perm, col_perm}, len, len, w);

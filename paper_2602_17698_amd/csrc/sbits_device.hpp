@@ -100,7 +100,7 @@ struct MatDesc {
     int64_t block_base;       // first global block id
     int64_t row_off, col_off; // offsets into the concatenated row / column permutations
     int nbr, nbc;             // block grid
-    int nseg, nband;          // score partials: 512-column segments, bands of 8 .. 256 rows (the plan's score_rows)
+    int npanel, nband;        // score partials: panels of 4096 columns, bands of 8 .. 512 rows (the plan's score_rows)
     int64_t rowpart_off, colpart_off;   // offsets of this matrix's score partials
 };
 

@@ -89,9 +89,9 @@ static inline size_t sbits_align_up(size_t v, size_t a) { return (v + a - 1) / a
 // ---- stage launchers (each returns an sbits_status) ------------------------
 
 // workspace sizes in bytes
-void sbits_score_geometry(int64_t R, int64_t C, int band_rows, int *nseg, int *nband);
+void sbits_score_geometry(int64_t R, int64_t C, int band_rows, int *npanel, int *nband);
 int sbits_score_rows(const int64_t *rows, const int64_t *cols, int n_mats);
-int sbits_score_wgs(int nseg, int nband);
+int sbits_score_wgs(int npanel, int nband);
 size_t sbits_reorder_ws_bytes(int64_t channels, int64_t rowpart, int64_t colpart);
 size_t sbits_alloc_ws_bytes(int64_t N);
 size_t sbits_offsets_ws_bytes(int64_t N);
