@@ -27,7 +27,7 @@ TEST_VARIANTS = {"impatient": ["-DSBITS_SPIN_LIMIT=0"],
                  "masked": ["-DSBITS_D16_ZERO_FILL=0"],
                  "noretry": ["-DSBITS_SECOND_TRY=0"]}
 ONLY = {v: ["api.hip" if v == "masked" else "alloc.hip"] for v in TEST_VARIANTS}       # sources a variant compiles anew; the rest are the default build's objects
-SOURCES = ["api.hip", "reorder.hip", "cost.hip", "fused.hip", "fused_copies.hip", "alloc.hip", "pack.hip", "mpgemm.hip", "dequant.hip"]
+SOURCES = ["api.hip", "reorder.hip", "cost.hip", "fused.hip", "fused_copies.hip", "fused_wide.hip", "alloc.hip", "pack.hip", "mpgemm.hip", "dequant.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -423,11 +423,10 @@ static int launch_gpack_l(sbits_ctx *ctx, const FusedPackLaunch &a)
 
 using namespace sbits;
 
-// shapes the fused kernel takes: 64- or 128-column blocks, rows of at most FU_MAX_COLS elements
+// shapes the fused kernels take: 64- or 128-column blocks
 // The route is chosen per class of matrices with equal column count.  Rows of up to FU_MAX_COLS
-// elements are staged whole (weights and sensitivities) by the one-pass cost kernel; matrices with
-// wider rows (up to the plan's limit of 32768) take, one by one, the reorder-gather into a copy in the
-// workspace and the cost kernel for reordered matrices.  The packing kernel stages weights only and
+// elements are staged whole (weights and sensitivities) by gather_cost_kernel, wider ones (up to the plan's limit of 32768) by
+// gather_cost_wide_kernel (fused_wide.hip).  The surrogates take the first alone; the packing kernel stages weights only and
 // takes every row length.
 bool sbits_fused_shapes_ok(const sbits_plan *plan)
 {
@@ -446,20 +445,10 @@ static size_t octet_partial_bytes(const sbits_plan *plan)
     const size_t per_octet = (size_t)(plan->K > 2 ? plan->K : 2);     // the surrogates keep two sums per block
     return sbits_align_up((size_t)plan->N * (size_t)(plan->m / 8) * per_octet * 4, 256);
 }
-// octet partials: one float per (block, octet of the block, candidate); then room for the reordered
-// copy (bf16, then fp32) of the largest matrix whose rows are too wide to be staged
+// octet partials: one float per (block, octet of the block, candidate)
 size_t sbits_fused_ws_bytes(const sbits_plan *plan)
 {
-    if (sbits_copies_shapes_ok(plan)) return octet_partial_bytes(plan);
-    if (!sbits_fused_shapes_ok(plan)) return 0;
-    size_t spill = 0;
-    for (int i = 0; i < plan->n_mats; ++i) {
-        if (plan->cols[i] <= FU_MAX_COLS) continue;
-        const size_t el = (size_t)plan->rows[i] * (size_t)plan->cols[i];
-        const size_t b = sbits_align_up(el * 2, 256) + sbits_align_up(el * 4, 256);
-        if (b > spill) spill = b;
-    }
-    return octet_partial_bytes(plan) + spill;
+    return sbits_copies_shapes_ok(plan) || sbits_fused_shapes_ok(plan) ? octet_partial_bytes(plan) : 0;
 }
 
 // The cost and surrogate kernels rely on 16-bit register-half loads filling the other half with
@@ -524,6 +513,7 @@ static int fused_classes(sbits_plan *plan, void *ws, const int **d_mem, const in
 // lane); the descriptor table is already in the workspace head.  w_re may be null, s_re is, except for 32- and 256-column blocks,
 // where both are written.
 int sbits_launch_fused_copies(int n, int K, bool z0, sbits_ctx *ctx, const FusedLaunch &a);
+int sbits_launch_fused_wide(int n, int K, bool z0, sbits_ctx *ctx, const FusedLaunch &a);
 int sbits_launch_gather_cost_all(sbits_plan *plan, const int32_t *row_perm, const int32_t *col_perm,
                                  void *w_re, float *s_re, float *cost, void *ws)
 {
@@ -550,12 +540,13 @@ int sbits_launch_gather_cost_all(sbits_plan *plan, const int32_t *row_perm, cons
         a.total_wg = plan->fused_pre[fc.pre_first + fc.n];
         a.cols = fc.cols;
         a.opu = fc.opu;
-        if (a.total_wg == 0 || fc.cols > FU_MAX_COLS) continue;
+        if (a.total_wg == 0 || (copies && fc.cols > FU_MAX_COLS)) continue;
         const bool z0 = plan->bits[0] == 0;                     // a 0-bit candidate (the first of the list) has no grid
         sbits_fill_grid_consts(plan->bits + z0, plan->K - z0, &a.gc);
         a.kstride = plan->K;
         a.koff = 0;
         const int rc = copies ? sbits_launch_fused_copies(plan->n, plan->K, z0, ctx, a)
+                     : fc.cols > FU_MAX_COLS ? sbits_launch_fused_wide(plan->n, plan->K, z0, ctx, a)
                      : plan->n == 64 ? launch_fused_l<8>(plan->K, z0, ctx, a) : launch_fused_l<16>(plan->K, z0, ctx, a);
         if (rc) return rc;
     }
@@ -565,19 +556,17 @@ int sbits_launch_gather_cost_all(sbits_plan *plan, const int32_t *row_perm, cons
                            a.part, a.descs, plan->n_mats, NK, plan->K, plan->m / 8, cost);
         SBITS_HIP(ctx, hipGetLastError());
     }
-    // matrices with rows too wide to stage: reordered copy (in the workspace, where it is no output), then the cost kernel on it; their
+    // 32- and 256-column blocks: matrices with rows too wide to stage are reordered first, then scored; their
     // rows of the table are written after the tree kernel above (which found nothing of theirs in part[])
-    for (int i = 0; i < plan->n_mats; ++i) {
+    for (int i = 0; copies && i < plan->n_mats; ++i) {
         if (plan->cols[i] <= FU_MAX_COLS) continue;
         const MatDesc &d = plan->descs[i];
-        const size_t el = (size_t)plan->rows[i] * (size_t)plan->cols[i];
-        char *tmp = static_cast<char *>(sbits_scratch(plan, ws)) + octet_partial_bytes(plan);
-        void *w_tmp = w_re ? static_cast<void *>(static_cast<uint16_t *>(w_re) + d.elem_off) : static_cast<void *>(tmp);
-        float *s_tmp = s_re ? s_re + d.elem_off : reinterpret_cast<float *>(tmp + sbits_align_up(el * 2, 256));
+        void *w_i = static_cast<uint16_t *>(w_re) + d.elem_off;
+        float *s_i = s_re + d.elem_off;
         int rc = sbits_launch_gather(ctx, d.w, d.s, plan->rows[i], plan->cols[i], d.ld_w, d.ld_s, row_perm + d.row_off,
-                                     col_perm + d.col_off, w_tmp, s_tmp);
+                                     col_perm + d.col_off, w_i, s_i);
         if (rc) return rc;
-        rc = sbits_launch_cost(ctx, w_tmp, s_tmp, plan->rows[i], plan->cols[i], plan->m, plan->n, plan->bits, plan->K,
+        rc = sbits_launch_cost(ctx, w_i, s_i, plan->rows[i], plan->cols[i], plan->m, plan->n, plan->bits, plan->K,
                                cost + d.block_base * plan->K);
         if (rc) return rc;
     }
