@@ -965,6 +965,214 @@ void step_apply_kernel(const AllocState *st, const u64 *__restrict__ keyU, const
     }
 }
 
+// ---- at most 64 blocks: one wave, a block a lane ------------------------------------------------
+// The same search or step, by itself: no launch before it and none after it.  A round of the search above is the latency of barriers
+// and LDS however few the keys are, and a selection is a round or more; here a lane counts the keys above its own and adds up their
+// step bits, six instructions a key, and has every set that can be a prefix of that order.  What bounds it is the issue of one wave.
+// Measured, calls on three candidates (two launches of a workgroup -> one of a wave): 16 blocks, 7 iterations 69.9 -> 24.4 us; 64 blocks,
+// 26 iterations 188 -> 100; a step 26 -> 17; the kernels of a search of a 512 x 512 matrix 27 to 49 and 4 -> 7 to 12.  The line lies
+// where a lane has one block: an iteration takes 1.5 us for 16 blocks and 3.3 for 64, 6.4 in the rounds, and with two blocks a lane
+// it would be four times the work.
+constexpr int WAVE_BLOCKS = 64;
+
+struct Ranked { int rank, bits; };                   // keys above the lane's own; step bits of those and its own
+// Keys of word 0 take no part (and their lanes' results say nothing).
+__device__ __forceinline__ Ranked rank_keys(unsigned word, unsigned width, int N)
+{
+    const unsigned one = 1u << 16 | width;           // (64 widths of at most 8 stay below 2^16)
+    const u64 key = key_at(word, WAVE_BLOCKS - 1 - (int)threadIdx.x);
+    unsigned sum = one;
+    static_for<0, WAVE_BLOCKS / 8>([&](auto ig) {    // (lanes by immediate numbers: one from a register costs a wait)
+        constexpr int g = 8 * decltype(ig)::value;
+        if (g >= N) return;
+        static_for<0, 8>([&](auto ij) {
+            constexpr int j = g + decltype(ij)::value;
+            const unsigned add = (unsigned)__builtin_amdgcn_readlane((int)one, j);
+            sum += key_at((unsigned)__builtin_amdgcn_readlane((int)word, j), WAVE_BLOCKS - 1 - j) > key ? add : 0u;
+        });
+    });
+    return Ranked{(int)(sum >> 16) - 1, (int)(sum & 0xffffu)};
+}
+
+// A set of blocks, a bit each, that is a prefix of the ranked order; its number and its step bits.
+struct WaveSet { u64 in; int n, w; };
+__device__ __forceinline__ WaveSet prefix_set(const Ranked &r, bool in)
+{
+    WaveSet s;
+    s.in = __ballot(in);
+    s.n = __popcll(s.in);
+    const u64 last = __ballot(in && r.rank == s.n - 1);
+    s.w = s.n ? __builtin_amdgcn_readlane(r.bits, uni(__ffsll((long long)last) - 1)) : 0;
+    return s;
+}
+
+__device__ __forceinline__ u64 wave_value(u64 v) { return (u64)(unsigned)__builtin_amdgcn_readlane((int)(v >> 32), 63) << 32 | (unsigned)__builtin_amdgcn_readlane((int)v, 63); }
+
+template <bool STEP>
+__global__ __launch_bounds__(64)
+void search_wave_kernel(AllocState *st, AllocHead head, const float *__restrict__ cost, const float *__restrict__ s_up,
+                        const float *__restrict__ s_down, const uint8_t *level_in, uint8_t *level_out, sbits_trace *tr, AllocReport *report)
+{
+    constexpr int PITCH = MAX_CAND | 1;
+    __shared__ float table[WAVE_BLOCKS * PITCH];
+    __shared__ int bits[MAX_CAND];
+    const int lane = (int)threadIdx.x, N = (int)head.N, K = head.K;
+    const bool there = lane < N;
+    if (lane == 0) {
+        st->head = head;
+#pragma unroll
+        for (int l = 0; l < MAX_CAND; ++l) bits[l] = head.bits[l];   // (a lane each would index the kernel's arguments: scratch)
+    }
+    __syncthreads();
+
+    // keys as in table_keys and step_keys
+    unsigned ku = 0u, kd = 0u, wu = 0u, wd = 0u;
+    int lv = head.l0;
+    long long used = head.used, k = head.k;
+    u64 most = 0ull;                                 // the largest entry of the table
+    const float *const row = &table[lane * PITCH];
+    if constexpr (STEP) {
+        u64 in_use = 0ull;
+        lv = there ? (int)level_in[lane] : 0;
+        if (there) {
+            const int l = min(lv, K - 1);
+            const float up = s_up[lane], dn = s_down[lane];
+            in_use = (u64)bits[l];
+            if (l < K - 1) { ku = some(ord_f32(up)); wu = (unsigned)(bits[l + 1] - bits[l]); }
+            if (l > 0) { kd = some(~ord_f32(dn)); wd = (unsigned)(bits[l] - bits[l - 1]); }
+        }
+        used = (long long)wave_value(wave_reduce<false>(in_use));
+    } else {
+        if (there) {
+            for (int l = 0; l < K; ++l) {
+                const float c = cost[(int64_t)lane * K + l];
+                if (c > 0.0f) most = max(most, (u64)__float_as_uint(c));
+                table[lane * PITCH + l] = c;
+            }
+        }
+        __syncthreads();
+        if (there) {
+            if (lv < K - 1) {
+                wu = (unsigned)(bits[lv + 1] - bits[lv]);
+                ku = some(ord_f32((row[lv] - row[lv + 1]) / (float)wu));
+            }
+            if (lv > 0) {
+                wd = (unsigned)(bits[lv] - bits[lv - 1]);
+                kd = some(~ord_f32((row[lv - 1] - row[lv]) / (float)wd));
+            }
+        }
+        most = wave_value(wave_reduce<true>(most));
+    }
+
+    // The sets of one iteration (see choose_sets): the blocks to raise and, of a swap, those to lower, outside of the set that the
+    // raised ones are a prefix of.
+    struct Choice { bool expand; WaveSet up, down; };
+    auto choose = [&](long long slack) {
+        const long long h = k / 2 < 1 ? 1 : k / 2;
+        const Ranked up = rank_keys(ku, wu, N);
+        Choice c;
+        c.up = prefix_set(up, ku >= 0x80000001u && up.rank < k && up.bits <= slack);   // (values above +0)
+        c.expand = c.up.n > 0;
+        c.down = WaveSet{0ull, 0, 0};
+        if (!c.expand) {
+            const bool u = ku && up.rank < h;
+            const unsigned word = u ? 0u : kd;
+            const Ranked down = rank_keys(word, wd, N);
+            c.down = prefix_set(down, word && down.rank < h);
+            c.up = prefix_set(up, u && up.bits <= slack + c.down.w);
+        }
+        return c;
+    };
+
+    if constexpr (STEP) {
+        const Choice c = choose(head.T - used);
+        const bool swap = !c.expand && c.up.n && c.down.n;
+        const u64 raised = c.expand || swap ? c.up.in : 0ull, lowered = swap ? c.down.in : 0ull;
+        if (there) level_out[lane] = (uint8_t)(lv + (int)(raised >> lane & 1ull) - (int)(lowered >> lane & 1ull));
+        if (lane == 0 && report) {
+            AllocResult r = {};
+            r.used = used; r.budget = head.T;
+            r.mode = c.expand ? MODE_EXPAND : swap ? MODE_ACCEPT : MODE_NONE;
+            r.prop_up = __popcll(raised);
+            r.prop_dn = __popcll(lowered);
+            r.prop_after = used + (c.expand || swap ? c.up.w - c.down.w : 0);
+            r.valid = 1;
+            report->result = r;
+        }
+    } else {
+        int shift = 0;
+        if (most) {
+            const unsigned int b = (unsigned int)most;
+            const int x = (int)(b >> 23);
+            const int ilog = x ? x - 127 : (31 - __clz((int)(b & 0x7fffffu))) - 149;
+            shift = 61 - head.ceil_log2_n - (ilog + 1);
+        }
+        int iters = 0, expansions = 0, swaps_ok = 0, swaps_rej = 0, status = SBITS_OK;
+        bool done = head.done != 0;
+        // A block that moves: as in search_kernel, what it cost to leave the old level is, complemented, the key of the way back.
+        auto move = [&](int by) {
+            if (!by) return;
+            const bool up = by > 0;
+            lv += by;
+            const int from = up ? lv : lv - 1;       // the next step from there
+            unsigned word = 0u, step = 0u;
+            if (from >= 0 && from < K - 1) {
+                step = (unsigned)(bits[from + 1] - bits[from]);
+                const unsigned o = ord_f32((row[from] - row[from + 1]) / (float)step);
+                word = some(up ? o : ~o);
+            }
+            const unsigned back = some(~(up ? ku : kd)), wide = up ? wu : wd;
+            ku = up ? word : back;
+            kd = up ? back : word;
+            wu = up ? step : wide;
+            wd = up ? wide : step;
+        };
+        while (!done) {
+            const Choice c = choose(head.T - used);
+            const int by = (int)(c.up.in >> lane & 1ull) - (int)(c.down.in >> lane & 1ull);
+            const long long after = used + c.up.w - c.down.w;
+            if (c.expand) {
+                move(by);
+                if (lane == 0) trace_write(tr, iters, 0, k, c.up.n, 0, c.up.n, 0, used, after, 0);
+                used = after;
+                ++expansions;
+            } else {
+                u64 change = 0ull;
+                if (by) {
+                    const float *entry = row + lv + (by > 0 ? 0 : -1);
+                    change = (u64)fx(entry[0] - entry[1], shift);
+                    if (by > 0) change = 0ull - change;
+                }
+                const long long delta = (long long)wave_value(wave_reduce<false>(change));
+                if (c.up.n && c.down.n && delta < 0) {
+                    move(by);
+                    if (lane == 0) trace_write(tr, iters, 1, k, c.up.n, c.down.n, c.up.n, c.down.n, used, after, delta);
+                    used = after;
+                    ++swaps_ok;
+                } else {
+                    if (lane == 0) trace_write(tr, iters, 2, k, 0, 0, c.up.n, c.down.n, used, used, delta);
+                    k = k / 2;
+                    ++swaps_rej;
+                }
+            }
+            ++iters;
+            if (k < head.kmin) done = true;
+            else if (iters >= head.max_iters) { done = true; status = SBITS_ERR_MAX_ITERS; }
+        }
+        if (there) level_out[lane] = (uint8_t)lv;
+        const u64 total = wave_value(wave_reduce<false>(there ? (u64)fx(row[lv], shift) : 0ull));
+        const u64 in_use = wave_value(wave_reduce<false>(there ? (u64)bits[lv] : 0ull));
+        if (lane == 0) {
+            AllocResult r = {};
+            r.used = used; r.k = k; r.budget = head.T; r.shift = shift; r.status = status;
+            r.iters = iters; r.expansions = expansions; r.swaps_ok = swaps_ok; r.swaps_rej = swaps_rej;
+            r.cost_fixed = (long long)total; r.bits_check = (long long)in_use;
+            r.valid = 1;
+            report->result = r;
+        }
+    }
+}
+
 static int ceil_log2_ll(long long v) { int p = 0; while ((1ll << p) < v) ++p; return p; }
 
 // A wait between workgroups polls this often before it is given up (about half a second).
@@ -1077,6 +1285,11 @@ int sbits_enqueue_allocate(sbits_plan *plan, const float *cost, double avg_bits,
     h0.used = N * (long long)plan->bits[h0.l0];
     if (all_max) h0.done = 1;
 
+    if (N <= WAVE_BLOCKS) {
+        hipLaunchKernelGGL(search_wave_kernel<false>, dim3(1), dim3(64), 0, sm, w.st, h0, cost, nullptr, nullptr, nullptr, level, w.tr, report);
+        SBITS_HIP(ctx, hipGetLastError());
+        return SBITS_OK;
+    }
     // The workgroups wait for each other.  Should the device be so full that they never run together, they
     // give up (see give_up) and one workgroup, which waits for nobody, does the search.
     const unsigned G = search_wgs(N, false, ctx->cus);
@@ -1145,14 +1358,18 @@ int sbits_run_propose(sbits_plan *plan, const float *s_up, const float *s_down, 
     AllocHead h = start_head(plan, avg_bits);
     h.k = k;
     // the start state travels as a kernel argument: nothing to keep alive, nothing to wait for
-    const unsigned G = search_wgs(N, true, ctx->cus);
-    uint8_t *const lv = const_cast<uint8_t *>(level_in);             // (only read by the step)
-    hipLaunchKernelGGL(prepare_kernel<true>, dim3(prep_wgs(N)), dim3(PREP_THREADS), 0, sm, w.st, h, nullptr, s_up, s_down, lv, w.keyU, w.keyD);
-    launch_search<true>(sm, G, w, N, nullptr, s_up, s_down, lv, report, 0);
-    if (G > 1 && SBITS_SECOND_TRY) launch_search<true>(sm, 1, w, N, nullptr, s_up, s_down, lv, report, 1);   // returns at once unless the first gave up
-    const unsigned grid = (unsigned)((N + 255) / 256 < 1024 ? (N + 255) / 256 : 1024);
-    hipLaunchKernelGGL(step_apply_kernel, dim3(grid), dim3(256), 0, sm, (const AllocState *)w.st,
-                       (const u64 *)w.keyU, (const u64 *)w.keyD, level_in, level_out);
+    if (N <= WAVE_BLOCKS) {
+        hipLaunchKernelGGL(search_wave_kernel<true>, dim3(1), dim3(64), 0, sm, w.st, h, nullptr, s_up, s_down, level_in, level_out, nullptr, report);
+    } else {
+        const unsigned G = search_wgs(N, true, ctx->cus);
+        uint8_t *const lv = const_cast<uint8_t *>(level_in);             // (only read by the step)
+        hipLaunchKernelGGL(prepare_kernel<true>, dim3(prep_wgs(N)), dim3(PREP_THREADS), 0, sm, w.st, h, nullptr, s_up, s_down, lv, w.keyU, w.keyD);
+        launch_search<true>(sm, G, w, N, nullptr, s_up, s_down, lv, report, 0);
+        if (G > 1 && SBITS_SECOND_TRY) launch_search<true>(sm, 1, w, N, nullptr, s_up, s_down, lv, report, 1);   // returns at once unless the first gave up
+        const unsigned grid = (unsigned)((N + 255) / 256 < 1024 ? (N + 255) / 256 : 1024);
+        hipLaunchKernelGGL(step_apply_kernel, dim3(grid), dim3(256), 0, sm, (const AllocState *)w.st,
+                           (const u64 *)w.keyU, (const u64 *)w.keyD, level_in, level_out);
+    }
     SBITS_HIP(ctx, hipGetLastError());
     if (host_out) {
         SBITS_HIP(ctx, hipStreamSynchronize(sm));
