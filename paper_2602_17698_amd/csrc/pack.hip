@@ -184,9 +184,11 @@ constexpr int PK_THREADS = 256;
 // Geometry as in the cost kernel: the GW = 64/LPG lane groups of a wave sit on BX adjacent
 // blocks of one block row (contiguous reads), the four waves (and the remaining OW groups of a
 // wave) take different octets.  A workgroup is one step of one unit; each lane group packs one
-// octet (8 rows) of one block, staged in LDS and written out as one contiguous run.  Weights and codes pass the caches by (non-temporal), and
-// scale and zero of the octet leave in one store each: two 8B-shaped layers in 256-column blocks 241 -> 182 us (loads alone 209; without
-// them the stores give 1 %).
+// octet (8 rows) of one block, staged in LDS and written out as one contiguous run.  Weights pass the caches by (non-temporal: 5 to 8 %
+// whatever the block width), scale and zero of the octet leave in one store each (64 columns: 20 %).  Codes are non-temporal where a
+// group's store covers whole lines, from 256 columns (2 to 5 %); narrower blocks put lines together from several stores, which is the
+// caches' work (16384 x 16384 at 0 to 8 bits, 128-row blocks: 16 columns 213 us, non-temporal 534; 32 columns 175 and 298, 64 124 and
+// 145, 128 115 and 118).  Two 8B-shaped layers in 256-column blocks 241 -> 182 us in all.
 template <int LPG>
 struct PackGeom {
     static constexpr int GW = 64 / LPG;
@@ -273,7 +275,10 @@ void pack_kernel(const MatDesc *__restrict__ descs, MatDesc one, const int *__re
         const int nbytes = 8 * row_bytes;            // a multiple of 8
         const uint32_t *s32 = reinterpret_cast<const uint32_t *>(&stage[g][0]);
         uint32_t *d32 = reinterpret_cast<uint32_t *>(dst);
-        for (int k = lig; k < nbytes / 4; k += LPG) __builtin_nontemporal_store(s32[k], (__attribute__((address_space(1))) uint32_t *)d32 + k);
+        for (int k = lig; k < nbytes / 4; k += LPG) {
+            if constexpr (LPG >= 32) __builtin_nontemporal_store(s32[k], (__attribute__((address_space(1))) uint32_t *)d32 + k);
+            else d32[k] = s32[k];
+        }
     }
 }
 
