@@ -148,7 +148,9 @@ __device__ __forceinline__ void quad_transpose(uint32_t (&a)[4], int lane)
 // slower part, 2.7 ms both.)
 // The words leave with nontemporal stores: isolated writes that linger in the caches cost the stream of weights more than their bytes
 // (sixteen 8B-shaped layers, 128-column blocks: 1951 -> 1711 us, four at 1 to 8 bits 515 -> 472, the 70B-shaped layer 526 -> 501).  Scale and
-// zero, 16 bytes a block at a time, are put together by the L2: nontemporal they cost 20 %.
+// zero, 16 bytes a block at a time, are put together by the L2: nontemporal they cost 20 %.  So are codes of 7 bits and, in 64-column
+// blocks, of 3, 5 and 6, whose stores end inside of lines (32768 x 4096 at 7 bits, 128 columns 90 us, nontemporal 94, 64 columns 96 and 121, 5
+// bits there 91 and 97; 3 bits and mixed widths within 2 %).
 template <int LPG, bool WIDE>
 __device__ __forceinline__ void store_codes4(uint8_t *dst, int c, uint32_t (&lo)[4], uint32_t (&hi)[4], int lig)
 {
@@ -159,33 +161,52 @@ __device__ __forceinline__ void store_codes4(uint8_t *dst, int c, uint32_t (&lo)
     typedef unsigned int u3_t __attribute__((ext_vector_type(3), aligned(4)));
     typedef unsigned int u4_t __attribute__((ext_vector_type(4), aligned(4)));
     const gp p = (gp)(dst + (lig & 3) * (LPG * c) + (lig >> 2) * 4 * c);
-    auto put1 = [&](int at, uint32_t a) { __builtin_nontemporal_store(a, p + at); };
-    auto put2 = [&](int at, uint32_t a, uint32_t b) { __builtin_nontemporal_store(u2_t{a, b}, (__attribute__((address_space(1))) u2_t *)(p + at)); };
-    auto put3 = [&](int at, uint32_t a, uint32_t b, uint32_t d) { __builtin_nontemporal_store(u3_t{a, b, d}, (__attribute__((address_space(1))) u3_t *)(p + at)); };
-    auto put4 = [&](int at, uint32_t a, uint32_t b, uint32_t d, uint32_t e) { __builtin_nontemporal_store(u4_t{a, b, d, e}, (__attribute__((address_space(1))) u4_t *)(p + at)); };
+    constexpr std::true_type nt{};
+    constexpr std::false_type plain{};
+    constexpr std::integral_constant<bool, (LPG >= 16)> gaps{};
+    auto put1 = [&](auto past, int at, uint32_t a) {
+        __attribute__((address_space(1))) uint32_t *q = (__attribute__((address_space(1))) uint32_t *)(p + at);
+        if constexpr (decltype(past)::value) __builtin_nontemporal_store(a, q);
+        else *q = a;
+    };
+    auto put2 = [&](auto past, int at, uint32_t a, uint32_t b) {
+        __attribute__((address_space(1))) u2_t *q = (__attribute__((address_space(1))) u2_t *)(p + at);
+        if constexpr (decltype(past)::value) __builtin_nontemporal_store(u2_t{a, b}, q);
+        else *q = u2_t{a, b};
+    };
+    auto put3 = [&](auto past, int at, uint32_t a, uint32_t b, uint32_t d) {
+        __attribute__((address_space(1))) u3_t *q = (__attribute__((address_space(1))) u3_t *)(p + at);
+        if constexpr (decltype(past)::value) __builtin_nontemporal_store(u3_t{a, b, d}, q);
+        else *q = u3_t{a, b, d};
+    };
+    auto put4 = [&](auto past, int at, uint32_t a, uint32_t b, uint32_t d, uint32_t e) {
+        __attribute__((address_space(1))) u4_t *q = (__attribute__((address_space(1))) u4_t *)(p + at);
+        if constexpr (decltype(past)::value) __builtin_nontemporal_store(u4_t{a, b, d, e}, q);
+        else *q = u4_t{a, b, d, e};
+    };
     switch (c) {                                     // (a wave has up to eight blocks, of different bitwidths)
     case 0: break;
-    case 1: put1(0, lo[0] | lo[1] << 8 | lo[2] << 16 | lo[3] << 24); break;
-    case 2: put2(0, lo[0] | lo[1] << 16, lo[2] | lo[3] << 16); break;
-    case 3: put3(0, lo[0] | lo[1] << 24, lo[1] >> 8 | lo[2] << 16, lo[2] >> 16 | lo[3] << 8); break;
-    case 4: put4(0, lo[0], lo[1], lo[2], lo[3]); break;
+    case 1: put1(nt, 0, lo[0] | lo[1] << 8 | lo[2] << 16 | lo[3] << 24); break;
+    case 2: put2(nt, 0, lo[0] | lo[1] << 16, lo[2] | lo[3] << 16); break;
+    case 3: put3(gaps, 0, lo[0] | lo[1] << 24, lo[1] >> 8 | lo[2] << 16, lo[2] >> 16 | lo[3] << 8); break;
+    case 4: put4(nt, 0, lo[0], lo[1], lo[2], lo[3]); break;
     default:
         if constexpr (WIDE) switch (c) {
         case 5:
-            put4(0, lo[0], hi[0] | lo[1] << 8, lo[1] >> 24 | hi[1] << 8 | lo[2] << 16, lo[2] >> 16 | hi[2] << 16 | lo[3] << 24);
-            put1(4, lo[3] >> 8 | hi[3] << 24);
+            put4(gaps, 0, lo[0], hi[0] | lo[1] << 8, lo[1] >> 24 | hi[1] << 8 | lo[2] << 16, lo[2] >> 16 | hi[2] << 16 | lo[3] << 24);
+            put1(gaps, 4, lo[3] >> 8 | hi[3] << 24);
             break;
         case 6:
-            put4(0, lo[0], hi[0] | lo[1] << 16, lo[1] >> 16 | hi[1] << 16, lo[2]);
-            put2(4, hi[2] | lo[3] << 16, lo[3] >> 16 | hi[3] << 16);
+            put4(gaps, 0, lo[0], hi[0] | lo[1] << 16, lo[1] >> 16 | hi[1] << 16, lo[2]);
+            put2(gaps, 4, hi[2] | lo[3] << 16, lo[3] >> 16 | hi[3] << 16);
             break;
         case 7:
-            put4(0, lo[0], hi[0] | lo[1] << 24, lo[1] >> 8 | hi[1] << 24, hi[1] >> 8 | lo[2] << 16);
-            put3(4, lo[2] >> 16 | hi[2] << 16, hi[2] >> 16 | lo[3] << 8, lo[3] >> 24 | hi[3] << 8);
+            put4(plain, 0, lo[0], hi[0] | lo[1] << 24, lo[1] >> 8 | hi[1] << 24, hi[1] >> 8 | lo[2] << 16);
+            put3(plain, 4, lo[2] >> 16 | hi[2] << 16, hi[2] >> 16 | lo[3] << 8, lo[3] >> 24 | hi[3] << 8);
             break;
         default:
-            put4(0, lo[0], hi[0], lo[1], hi[1]);
-            put4(4, lo[2], hi[2], lo[3], hi[3]);
+            put4(nt, 0, lo[0], hi[0], lo[1], hi[1]);
+            put4(nt, 4, lo[2], hi[2], lo[3], hi[3]);
             break;
         }
     }
