@@ -244,11 +244,8 @@ int  sbits_cost_table_all(sbits_plan *plan, const void *w_re_bf16, const float *
  * blocks, on a device whose memories run with error correction (target id
  * "sramecc+", as every MI355X reports: the kernel relies on how 16-bit register
  * loads behave there); otherwise returns SBITS_ERR_UNIMPLEMENTED and writes
- * nothing: use the two calls above.  The route is chosen per matrix: rows of at
- * most 16384 elements are read once (6 bytes per weight); a matrix with wider
- * rows is reordered into a copy inside the workspace first and scored from there
- * (18 bytes per weight; sbits_workspace_bytes covers the copy of the largest such
- * matrix), with the same bits in the table.
+ * nothing: use the two calls above.  Rows of every length a plan allows are read
+ * once (6 bytes per weight; beyond 16384 elements by kernels of their own).
  * sbits_gather_cost_supported: 1 if the plan's shapes qualify (the device is
  * checked by the call itself), else 0.  Uses ws.                                  */
 int  sbits_gather_cost_supported(const sbits_plan *plan);
