@@ -50,7 +50,7 @@ constexpr int SC_PANEL = 8;     // segments per workgroup: 4 waves x 2 segments 
 // A band has band_rows rows, a power of two: see sbits_score_rows().
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 
-// RING: rows of a wave on their way.  3 where two workgroups with the row sums of 512 rows share a CU, 4 with 256 rows, 8 where a CU has one.
+// RING: rows of a wave on their way.  3 where two workgroups with the row sums of 512 rows share a CU, 4 with 256 rows or fewer, 8 where a CU has one.
 template <int RING>
 __global__ __launch_bounds__(SC_THREADS, 2)
 void score_partial_kernel(const MatDesc *__restrict__ descs, MatDesc one, const int *__restrict__ wg_start,
@@ -591,11 +591,10 @@ void sbits_score_geometry(int64_t R, int64_t C, int band_rows, int *npanel, int 
 
 // Rows per band for a plan of these matrices: 512, which leave the fewest partial sums, where they take no more turns of two workgroups a CU
 // than bands of 256 (432 workgroups instead of 864: 527 us and 559; 104 instead of 208, half of the CUs idle: 180 and 130; 5 % is what the
-// fewer sums are worth); else 256,
-// halved while there would be fewer than 192 workgroups, whose rows come one after the other, and as long as one tree of
-// 128 adds up a column.  Scores and permutations: 512 x 512 136 us with 256 rows, 34 with 8; 2048 x 2048 145 -> 47 (16
-// rows); 4096 x 4096 159 -> 58 (32); 2048 x 8192 twice 161 -> 60 (32); a 2048-wide layer (100 workgroups) 163 -> 104 (128).
-// The line: 216 workgroups take 190 us, with half the rows 187, with a quarter 204.
+// fewer sums are worth); else 256, halved while twice as many workgroups, whose rows come one after the other, still find a CU each, and as
+// long as one tree of 128 adds up a column.  Scores and permutations: 512 x 512 136 us with 256 rows, 34 with 8; 2048 x 2048 145 -> 47
+// (16 rows); 4096 x 4096 159 -> 58 (32); 2048 x 8192 twice 161 -> 60 (32).  The line: 128 workgroups take 123 us, with half the rows 113; 144
+// take 130 and 147, 160 take 136 and 155 (in 288 and 320, a few CUs have two and the others wait); 132 of 128 rows 72 and, halved, 81.
 int sbits_score_rows(const int64_t *rows, const int64_t *cols, int n_mats)
 {
     int64_t wgs = 0, tall = 0, max_rows = 0;                  // in bands of 256 and of 512
@@ -609,7 +608,7 @@ int sbits_score_rows(const int64_t *rows, const int64_t *cols, int n_mats)
     }
     if (tall >= 400 && 95 * ((tall + 511) / 512) * 2 <= 100 * ((wgs + 511) / 512)) return SC_ROWS;
     int r = SC_ROWS / 2;
-    while (r > 8 && wgs * (256 / r) < 192 && max_rows <= 128 * (r / 2)) r >>= 1;
+    while (r > 8 && wgs * (256 / r) <= 128 && max_rows <= 128 * (r / 2)) r >>= 1;
     return r;
 }
 
@@ -640,8 +639,8 @@ static int run_scores(sbits_ctx *ctx, const MatDesc *descs, const MatDesc &one, 
                            w.rowpart, w.colpart);
         return SBITS_OK;
     };
-    const int rc = band_rows == 512 ? launch(&score_partial_kernel<3>, 3) : band_rows == 256 ? launch(&score_partial_kernel<4>, 4)
-                                                                                              : launch(&score_partial_kernel<8>, 8);
+    const int rc = band_rows == 512 ? launch(&score_partial_kernel<3>, 3)
+                 : band_rows == 256 || total_wg > sbits_cus(ctx) ? launch(&score_partial_kernel<4>, 4) : launch(&score_partial_kernel<8>, 8);
     if (rc) return rc;
     SBITS_HIP(ctx, hipGetLastError());
     const int64_t L = sum_rows + sum_cols;

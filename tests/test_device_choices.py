@@ -93,3 +93,33 @@ def test_workgroups_follow_the_compute_units_and_sums_do_not(tmp_path):
     assert block("first, 64-column blocks 32") >= block("first, 64-column blocks 256")
     assert block("first, two on a CU 256") == 256 and block("first, two on a CU 32") == 512
     assert grid("packing 256")[0] == 512 and grid("packing 32")[0] == 256          # octets: 2 and 4 a workgroup
+
+
+SCORES = r"""
+out = []
+for cus in (256, 32):
+    device(cus, 1)
+    ctx = sb.Context(0, 0)
+    for shapes in ([(2048, 2048)], [(4096, 4096)], [(16384, 8192)], [(12288, 12288)], [(9728, 16384)], [(1536, 4096)] * 11, [(768, 8)] * 43, [(4104, 8)] * 30,
+                   [(8192, 20480)], [(3072, 3072)] * 3, [(8192, 16384)], [(4096, 4096)] * 12, [(14336, 4096)] * 16):
+        plan = sb.Plan(ctx, shapes, 8, 8, [2, 4])
+        mats = [sb.Matrix(fake(1 << 28), fake(1 << 29), r, c, c, c) for r, c in shapes]
+        log()
+        plan.reorder_all(mats, fake(1 << 20), fake(1 << 20), fake(1 << 28))
+        launch = [line.split() for line in log() if "score_partial" in line]
+        tall = sum(-(-r // 256) * -(-c // 4096) for r, c in shapes)
+        out.append([cus, tall, int(launch[0][3].split(",")[0]), int(launch[0][-1])])
+        plan.close()
+    ctx.close()
+answer(out)
+"""
+
+
+def test_workgroups_of_the_scores_have_a_cu_each_or_share_it_evenly(tmp_path):
+    """Bands of fewer than 256 rows are made only while every workgroup finds a CU of its own; where there are more workgroups than CUs
+    all the same, two of them fit a CU's 160 KiB of LDS."""
+    seen = record(tmp_path, SCORES)
+    for cus, tall, grid, lds in seen:
+        assert grid <= max(256, tall), (cus, tall, grid)
+        assert lds <= (80 if grid > cus else 160) * 1024, (cus, tall, grid, lds)
+    assert sum(128 < tall < 192 for _, tall, _, _ in seen) >= 4 and sum(128 < grid < 192 for _, _, grid, _ in seen) >= 8
