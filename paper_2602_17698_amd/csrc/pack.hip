@@ -185,7 +185,7 @@ constexpr int PK_THREADS = 256;
 // blocks of one block row (contiguous reads), the four waves (and the remaining OW groups of a
 // wave) take different octets.  A workgroup is one step of one unit; each lane group packs one
 // octet (8 rows) of one block, staged in LDS and written out as one contiguous run.  Weights pass the caches by (non-temporal: 5 to 8 %
-// whatever the block width), scale and zero of the octet leave in one store each (64 columns: 20 %).  Codes are non-temporal where a
+// whatever the block width) unless CACHED, see caches_weights(); scale and zero of the octet leave in one store each (64 columns: 20 %).  Codes are non-temporal where a
 // group's store covers whole lines, from 256 columns (2 to 5 %); narrower blocks put lines together from several stores, which is the
 // caches' work (16384 x 16384 at 0 to 8 bits, 128-row blocks: 16 columns 213 us, non-temporal 534; 32 columns 175 and 298, 64 124 and
 // 145, 128 115 and 118).  Two 8B-shaped layers in 256-column blocks 241 -> 182 us in all.
@@ -199,7 +199,7 @@ struct PackGeom {
     static int steps(int m) { const int opb = m / 8; return opb >= OS ? opb / OS : 1; }
 };
 
-template <int LPG>
+template <int LPG, bool CACHED>
 __global__ __launch_bounds__(PK_THREADS)
 void pack_kernel(const MatDesc *__restrict__ descs, MatDesc one, const int *__restrict__ wg_start, int n_mats,
                  const uint16_t *__restrict__ W, int m, const uint8_t *__restrict__ level,
@@ -241,7 +241,10 @@ void pack_kernel(const MatDesc *__restrict__ descs, MatDesc one, const int *__re
     uint4 raw[8];
 #pragma unroll
     for (int rr = 0; rr < 8; ++rr) {
-        const u32x4_t v = __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x4_t *)(src + (int64_t)rr * d.cols));
+        const __attribute__((address_space(1))) u32x4_t *const p = (const __attribute__((address_space(1))) u32x4_t *)(src + (int64_t)rr * d.cols);
+        u32x4_t v;
+        if constexpr (CACHED) v = *p;
+        else v = __builtin_nontemporal_load(p);
         raw[rr] = make_uint4(v.x, v.y, v.z, v.w);
     }
 
@@ -289,6 +292,7 @@ struct PackLaunch {
     int n_mats;
     int64_t total_wg;
     const uint16_t *W;
+    int64_t weights;
     int m;
     const uint8_t *level;
     const int64_t *byte_off;
@@ -298,12 +302,26 @@ struct PackLaunch {
     const unsigned *aborted;
 };
 
+// Ordinary loads where weights that are packed again and again, with other levels each time, stay in the 256 MiB memory-side cache beside
+// their codes, which non-temporal loads read past in blocks of up to 64 columns.  Again / non-temporal: 8 columns 48 MiB 30 us and 33, 128 MiB 59 and
+// 69, 160 MiB 90 and 84; 32 columns 64 MiB 25.6 and 27.9, 192 MiB 50 and 66, 224 MiB 76 and 76; 64 columns 192 MiB 44 and 52, 32 MiB 17.8 and
+// 17.0.  From 128 columns on they gain little (192 MiB 45 and 49) and cost as much where the weights have just been reordered.
+static bool caches_weights(int n, int64_t weights)
+{
+    const int64_t mib = weights * 2 >> 20;
+    return n <= 64 && mib > 40 && mib <= (n < 32 ? 144 : 208);
+}
+
 template <int LPG>
 static int launch_pack_l(sbits_ctx *ctx, const PackLaunch &a)
 {
     if (a.total_wg > 0x7fffffff) return SBITS_ERR_BAD_SHAPE;
     if (a.total_wg == 0) return SBITS_OK;
-    hipLaunchKernelGGL((pack_kernel<LPG>), dim3((unsigned)a.total_wg), dim3(PK_THREADS), 0, ctx->stream,
+    auto *fn = &pack_kernel<LPG, false>;
+    if constexpr (LPG <= 8) {
+        if (caches_weights(8 * LPG, a.weights)) fn = &pack_kernel<LPG, true>;
+    }
+    hipLaunchKernelGGL(fn, dim3((unsigned)a.total_wg), dim3(PK_THREADS), 0, ctx->stream,
                        a.descs, a.one, a.wg_start, a.n_mats, a.W, a.m, a.level, a.byte_off, a.codes, a.scale,
                        a.zero, a.gc, a.aborted);
     SBITS_HIP(ctx, hipGetLastError());
@@ -424,6 +442,7 @@ int sbits_launch_pack(sbits_ctx *ctx, const void *Wp, int64_t R, int64_t C, int 
     a.n_mats = 1;
     a.total_wg = pack_wgs(m, n, a.one.nbr, a.one.nbc);
     a.W = static_cast<const uint16_t *>(Wp);
+    a.weights = R * C;
     a.m = m;
     a.level = level; a.byte_off = byte_off; a.codes = codes; a.scale = scale; a.zero = zero;
     return launch_pack(n, ctx, a);
@@ -456,6 +475,7 @@ int sbits_launch_pack_all(sbits_plan *plan, const void *w_re, const uint8_t *lev
     a.n_mats = plan->n_mats;
     a.total_wg = plan->pack_wg_start.back();
     a.W = static_cast<const uint16_t *>(w_re);
+    a.weights = plan->sum_elems;
     a.m = plan->m;
     a.level = level; a.byte_off = byte_off; a.codes = codes; a.scale = scale; a.zero = zero;
     return launch_pack(plan->n, ctx, a);

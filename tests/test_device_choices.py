@@ -123,3 +123,25 @@ def test_workgroups_of_the_scores_have_a_cu_each_or_share_it_evenly(tmp_path):
         assert grid <= max(256, tall), (cus, tall, grid)
         assert lds <= (80 if grid > cus else 160) * 1024, (cus, tall, grid, lds)
     assert sum(128 < tall < 192 for _, tall, _, _ in seen) >= 4 and sum(128 < grid < 192 for _, _, grid, _ in seen) >= 8
+
+
+PACK_ALL = r"""
+ctx = sb.Context(0, 0)
+out = []
+for n in (8, 16, 32, 64, 128, 512):
+    for rows in (1024, 2624, 8192, 12288, 16384):
+        plan = sb.Plan(ctx, [(rows, 8192)], 8, n, [2, 4])
+        a = [fake(1 << 28) for _ in range(7)]
+        log()
+        plan.pack_all(*a)
+        out.append([n, rows, [line.split()[1] for line in log() if "pack_kernel" in line]])
+        plan.close()
+answer(out)
+"""
+
+
+def test_packing_of_copies_keeps_weights_in_the_caches_where_they_fit(tmp_path):
+    """Blocks of up to 64 columns, weights of 40 to 208 MiB (144 in blocks of up to 16): by ordinary loads."""
+    for n, rows, kernels in record(tmp_path, PACK_ALL):
+        cached = n <= 64 and 40 < rows // 64 <= (144 if n < 32 else 208)
+        assert len(kernels) == 1 and ("pack_kernelILi%dELb%dE" % (n // 8, cached)) in kernels[0], (n, rows, kernels)

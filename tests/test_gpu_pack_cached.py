@@ -1,0 +1,42 @@
+"""Packing of reordered copies large enough that their weights are read through the caches (blocks of up to 64 columns): the bits of the matrices
+packed one by one, which are too small for that."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2602_17698_amd import binding as sb
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [8, 16, 32, 64])
+def test_packing_through_the_caches(n):
+    print("[case] packing through the caches", n, flush=True)
+    dev, m, bits = torch.device("cuda:0"), 32, [0, 1, 3, 7, 8]
+    shapes = [(1152, 4096), (1472, 8192), (960, 8192 - 64)]
+    g = torch.Generator(device=dev)
+    g.manual_seed(n)
+    ctx = sb.Context(0, torch.cuda.current_stream().cuda_stream)
+    plan = sb.Plan(ctx, shapes, m, n, bits)
+    N = plan.num_blocks()
+    assert 40 << 20 < 2 * sum(r * c for r, c in shapes) <= 144 << 20
+    ws = torch.empty(plan.workspace_bytes(), dtype=torch.uint8, device=dev)
+    W = [torch.randn(r, c, generator=g, device=dev).to(torch.bfloat16) for r, c in shapes]
+    level = torch.randint(0, len(bits), (N,), generator=g, device=dev).to(torch.uint8)
+    off = torch.empty(N + 1, dtype=torch.int64, device=dev)
+    plan.offsets(level, off, ws)
+    outs = []
+    for whole in (True, False):
+        codes = torch.full((int(off[-1]) + 64,), 0x5A, dtype=torch.uint8, device=dev)
+        scale, zero = torch.full((N * m + 8,), -7.0, device=dev), torch.full((N * m + 8,), -7.0, device=dev)
+        if whole:
+            plan.pack_all(torch.cat([w.reshape(-1) for w in W]), level, off, codes, scale, zero, ws)
+        else:
+            for i, w in enumerate(W):
+                plan.pack(i, w, level, off, codes, scale, zero)
+        torch.cuda.synchronize()
+        outs.append((codes, scale, zero))
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+    plan.close()
+    ctx.close()
