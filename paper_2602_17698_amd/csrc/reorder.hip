@@ -591,24 +591,36 @@ void sbits_score_geometry(int64_t R, int64_t C, int band_rows, int *npanel, int 
 
 // Rows per band for a plan of these matrices: 512, which leave the fewest partial sums, where they take no more turns of two workgroups a CU
 // than bands of 256 (432 workgroups instead of 864: 527 us and 559; 104 instead of 208, half of the CUs idle: 180 and 130; 5 % is what the
-// fewer sums are worth); else 256, halved while twice as many workgroups, whose rows come one after the other, still find a CU each, and as
-// long as one tree of 128 adds up a column.  Scores and permutations: 512 x 512 136 us with 256 rows, 34 with 8; 2048 x 2048 145 -> 47
-// (16 rows); 4096 x 4096 159 -> 58 (32); 2048 x 8192 twice 161 -> 60 (32).  The line: 128 workgroups take 123 us, with half the rows 113; 144
-// take 130 and 147, 160 take 136 and 155 (in 288 and 320, a few CUs have two and the others wait); 132 of 128 rows 72 and, halved, 81.
+// fewer sums are worth); else 256, halved while the workgroups, whose rows come one after the other, still find a CU each, or, where
+// narrow matrices leave many of them with little to do, while their work fills 200 whole panels at most (and there were fewer than 192); and
+// as long as one tree of 128 adds up a column.  Scores and permutations: 512 x 512 136 us with 256 rows, 34 with 8; 2048 x 2048 145 -> 47 (16 rows); 4096 x 4096
+// 159 -> 58 (32); 2048 x 8192 twice 161 -> 60 (32).  The line: 128 workgroups take 123 us, halved 113; 144 take 130 and 147, 160 take
+// 136 and 155 (in 288 and 320, a few CUs have two and the others wait); 166 with the work of 100 take 125, halved 119.  Over 550 drawn plans
+// 3 % behind the best height; with 192 alone for the line, whatever their work, 4 %.
 int sbits_score_rows(const int64_t *rows, const int64_t *cols, int n_mats)
 {
-    int64_t wgs = 0, tall = 0, max_rows = 0;                  // in bands of 256 and of 512
+    int64_t max_rows = 0, elems = 0;
     for (int i = 0; i < n_mats; ++i) {
-        int npanel, nband;
-        sbits_score_geometry(rows[i], cols[i], SC_ROWS, &npanel, &nband);
-        tall += sbits_score_wgs(npanel, nband);
-        sbits_score_geometry(rows[i], cols[i], SC_ROWS / 2, &npanel, &nband);
-        wgs += sbits_score_wgs(npanel, nband);
+        elems += rows[i] * cols[i];
         if (rows[i] > max_rows) max_rows = rows[i];
     }
-    if (tall >= 400 && 95 * ((tall + 511) / 512) * 2 <= 100 * ((wgs + 511) / 512)) return SC_ROWS;
+    auto wgs = [&](int band) {
+        int64_t w = 0;
+        for (int i = 0; i < n_mats; ++i) {
+            int npanel, nband;
+            sbits_score_geometry(rows[i], cols[i], band, &npanel, &nband);
+            w += sbits_score_wgs(npanel, nband);
+        }
+        return w;
+    };
+    const int64_t tall = wgs(SC_ROWS), half = wgs(SC_ROWS / 2);
+    if (tall >= 400 && 95 * ((tall + 511) / 512) * 2 <= 100 * ((half + 511) / 512)) return SC_ROWS;
     int r = SC_ROWS / 2;
-    while (r > 8 && wgs * (256 / r) <= 128 && max_rows <= 128 * (r / 2)) r >>= 1;
+    auto halves = [&]() {
+        const int64_t w = wgs(r / 2);
+        return w <= 256 || (w <= 512 && half * (256 / r) < 192 && elems <= (int64_t)200 * (r / 2) * (SC_PANEL * SC_COLS));
+    };
+    while (r > 8 && max_rows <= 128 * (r / 2) && halves()) r >>= 1;
     return r;
 }
 

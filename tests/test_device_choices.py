@@ -101,14 +101,15 @@ for cus in (256, 32):
     device(cus, 1)
     ctx = sb.Context(0, 0)
     for shapes in ([(2048, 2048)], [(4096, 4096)], [(16384, 8192)], [(12288, 12288)], [(9728, 16384)], [(1536, 4096)] * 11, [(768, 8)] * 43, [(4104, 8)] * 30,
-                   [(8192, 20480)], [(3072, 3072)] * 3, [(8192, 16384)], [(4096, 4096)] * 12, [(14336, 4096)] * 16):
+                   [(8192, 20480)], [(3072, 3072)] * 3, [(8192, 16384)], [(4096, 4096)] * 12, [(14336, 4096)] * 16,
+                   [(8704, 5120), (8192, 4608)]):
         plan = sb.Plan(ctx, shapes, 8, 8, [2, 4])
         mats = [sb.Matrix(fake(1 << 28), fake(1 << 29), r, c, c, c) for r, c in shapes]
         log()
         plan.reorder_all(mats, fake(1 << 20), fake(1 << 20), fake(1 << 28))
         launch = [line.split() for line in log() if "score_partial" in line]
         tall = sum(-(-r // 256) * -(-c // 4096) for r, c in shapes)
-        out.append([cus, tall, int(launch[0][3].split(",")[0]), int(launch[0][-1])])
+        out.append([cus, tall, int(launch[0][3].split(",")[0]), int(launch[0][-1]), sum(r * c for r, c in shapes) / (256 * 4096)])
         plan.close()
     ctx.close()
 answer(out)
@@ -116,13 +117,14 @@ answer(out)
 
 
 def test_workgroups_of_the_scores_have_a_cu_each_or_share_it_evenly(tmp_path):
-    """Bands of fewer than 256 rows are made only while every workgroup finds a CU of its own; where there are more workgroups than CUs
-    all the same, two of them fit a CU's 160 KiB of LDS."""
+    """Bands of fewer than 256 rows are made only while every workgroup finds a CU of its own, or while the work is that of 200; where there
+    are more workgroups than CUs all the same, two of them fit a CU's 160 KiB of LDS."""
     seen = record(tmp_path, SCORES)
-    for cus, tall, grid, lds in seen:
-        assert grid <= max(256, tall), (cus, tall, grid)
+    for cus, tall, grid, lds, work in seen:
+        assert grid <= max(256, tall) or (grid <= 512 and work * grid / tall <= 205), (cus, tall, grid)
         assert lds <= (80 if grid > cus else 160) * 1024, (cus, tall, grid, lds)
-    assert sum(128 < tall < 192 for _, tall, _, _ in seen) >= 4 and sum(128 < grid < 192 for _, _, grid, _ in seen) >= 8
+    assert sum(128 < tall < 192 for _, tall, _, _, _ in seen) >= 4 and sum(128 < grid < 192 for _, _, grid, _, _ in seen) >= 8
+    assert sum(256 < grid <= 512 and grid > tall for _, tall, grid, _, _ in seen) == 4
 
 
 PACK_ALL = r"""
