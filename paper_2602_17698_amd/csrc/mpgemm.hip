@@ -26,7 +26,7 @@
 //   loads whatever the bitwidth (load_quarter): with one path per bitwidth the ring was copied at the paths'
 //   end, behind a wait for it, 5824 x 6144 at 23 rows 17.7 -> 15.6 us; 64-column blocks, before two bytes
 //   at a time, 960 x 23872 at 13 rows 31.8 -> 16.5.
-// More than 32 batch rows (two kernels), and products of up to 64 where few_rows says so (most of up to 16), take the kernels further down.
+// More than 32 batch rows, and products of up to 64 where few_rows says so (most of up to 16), take the kernels further down.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -99,11 +99,10 @@ __device__ __forceinline__ uint32_t code_pair(const uint32_t *r, int e, uint32_t
     }
 }
 
-// the block's scale and zero as they apply to sum B x (ONE_BIT_PLAIN and 1 bit: to sum q x) and sum x
-template <int C, bool ONE_BIT_PLAIN>
+// the block's scale and zero as they apply to sum B x and sum x
+template <int C>
 __device__ __forceinline__ void term_factors(float sc, float ze, float &f, float &z)
 {
-    if constexpr (C == 1 && ONE_BIT_PLAIN) { f = sc; z = ze; return; }
     f = C <= 5 ? sc * (float)(1 << C) : sc;
     z = C <= 5 ? fmaf(-(float)(1 << C), sc, ze) : C < 8 ? fmaf(-128.0f, sc, ze) : ze;
 }
@@ -246,7 +245,7 @@ __device__ __forceinline__ void block_product(const uint32_t (&cw)[2][8], const 
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
         float f = sc[t], zz = C < 8 ? fmaf(-128.0f, sc[t], ze[t]) : ze[t];
-        if constexpr (FINE) term_factors<C, false>(sc[t], ze[t], f, zz);
+        if constexpr (FINE) term_factors<C>(sc[t], ze[t], f, zz);
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -414,195 +413,7 @@ void mp_gemm_kernel(MpArgs a)
             }
 }
 
-// ================================================================ more than 32 batch rows
-// A workgroup of 8 waves takes RG = 4 or 2 row groups of 32 channels and up to 64 batch rows (NB tiles of 16; more rows
-// are the grid's third dimension); the JL = 8 / RG waves of a row group walk the block columns together, JL columns a
-// step.  Codes are unpacked once for all NB tiles.  x goes straight into LDS, one or two steps ahead of its use (two or
-// three stages, what fits): a wave reads whole rows of a block column (256 or 128 bytes each), and a row's 16-byte
-// chunks land at positions exclusive-ored with the row, so that the operand reads (16 rows, the same chunk) are free of
-// bank conflicts.  Workgroups start at different block columns: rows of x lie a power of two apart, and all of them at
-// the same column would queue at one L2 channel.  sum_j x of a block column is the same for every channel: the waves of
-// a column share the batch tiles (a product with ones) and exchange the sums through LDS.
-// Codes and scales are requested two steps ahead, block offsets four: loads come back in order, and whoever waits for
-// one request waits for every older one, so with everything one step ahead a step is as long as a load from memory
-// (47 us for 14336 x 4096 at 100 rows).  The operand reads are written out with their wait: the compiler would wait for
-// the requests under way before any read of LDS.
-// What bounds it: steps of 270 vector and 37 matrix instructions a wave, two waves per SIMD, with a barrier each (14336 x 4096
-// at 100 rows, by counters: vector issue 39 % of the clocks, matrix cores 21 %, 37 % of the waves' cycles wait for loads or the
-// barrier).
-// Against launches of the kernel above, 32 rows each: 14336 x 4096 at 100 rows, bitwidths 1 .. 8, 72 -> 39 us (300 TFLOP/s), at 64 rows
-// 40 -> 26 us, at 33 rows 35 -> 23 us; 8192 x 8192 at 100 rows 78 -> 45 us; 4096 x 4096 in 64-column blocks at 70 rows
-// 47 -> 32 us.  (128 batch rows in one workgroup, 64 channels: 45 us at 100 rows.)
-// Operands are unpacked in stream order, two codes in three instructions whatever the bitwidth c <= 7:
-// field extraction, spread to the two halves, mask and exponent.  c <= 5: B = 1 + q / 2^c (the code at the top of the
-// mantissa: the offset taken out again is no larger than the codes' range), c = 6, 7: B = 128 + q, c = 8: B = q.  1 bit has a
-// block product of its own.
-constexpr int WG_WAVES = 8, WG_THREADS = WG_WAVES * 64;
-constexpr int WG_LDS = 144 * 1024;                            // for the stages of x
-
-template <int NB, int SUMS>
-struct WideState {
-    f32x4v_t d[2][NB], s[SUMS];                               // sum B x of the block; sum x of this wave's batch tiles
-};
-
-// the operands of NB batch tiles, TILE bytes apart, of one step, and those of the tiles (every WG_WAVES / JL-th) whose sums
-// this wave makes
-template <int NB, int TILE, int SUMS>
-__device__ __forceinline__ void read_operands(uint32_t at, uint32_t sum_at, u32x4_t (&x)[NB], u32x4_t (&xs)[SUMS])
-{
-    static_assert((NB == 3 || NB == 4) && (SUMS == 1 || SUMS == 2), "written out");
-    if constexpr (NB == 3 && SUMS == 1)
-        asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:%6\n\tds_read_b128 %2, %4 offset:%7\n\tds_read_b128 %3, %5\n\t"
-                     "s_waitcnt lgkmcnt(0)"
-                     : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(xs[0]) : "v"(at), "v"(sum_at), "n"(TILE), "n"(2 * TILE) : "memory");
-    else if constexpr (NB == 3)
-        asm volatile("ds_read_b128 %0, %5\n\tds_read_b128 %1, %5 offset:%7\n\tds_read_b128 %2, %5 offset:%8\n\tds_read_b128 %3, %6\n\t"
-                     "ds_read_b128 %4, %6 offset:%8\n\ts_waitcnt lgkmcnt(0)"
-                     : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(xs[0]), "=&v"(xs[SUMS - 1])
-                     : "v"(at), "v"(sum_at), "n"(TILE), "n"(2 * TILE) : "memory");
-    else if constexpr (SUMS == 1)
-        asm volatile("ds_read_b128 %0, %5\n\tds_read_b128 %1, %5 offset:%7\n\tds_read_b128 %2, %5 offset:%8\n\tds_read_b128 %3, %5 offset:%9\n\t"
-                     "ds_read_b128 %4, %6\n\ts_waitcnt lgkmcnt(0)"
-                     : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[NB - 1]), "=&v"(xs[0])
-                     : "v"(at), "v"(sum_at), "n"(TILE), "n"(2 * TILE), "n"(3 * TILE) : "memory");
-    else
-        asm volatile("ds_read_b128 %0, %6\n\tds_read_b128 %1, %6 offset:%8\n\tds_read_b128 %2, %6 offset:%9\n\tds_read_b128 %3, %6 offset:%10\n\t"
-                     "ds_read_b128 %4, %7\n\tds_read_b128 %5, %7 offset:%9\n\ts_waitcnt lgkmcnt(0)"
-                     : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[NB - 1]), "=&v"(xs[0]), "=&v"(xs[SUMS - 1])
-                     : "v"(at), "v"(sum_at), "n"(TILE), "n"(2 * TILE), "n"(3 * TILE) : "memory");
-}
-
-// the two halves, as the kernel above takes them for 1 bit, of NB operands TILE bytes apart
-template <int NB, int TILE, int HALF>
-__device__ __forceinline__ void read_halves(uint32_t at, uint32_t bt, u32x2_t (&a)[NB], u32x2_t (&b)[NB])
-{
-    if constexpr (NB == 3)
-        asm volatile("ds_read_b64 %0, %6 offset:%8\n\tds_read_b64 %1, %6 offset:%9\n\tds_read_b64 %2, %6 offset:%10\n\t"
-                     "ds_read_b64 %3, %7 offset:%8\n\tds_read_b64 %4, %7 offset:%9\n\tds_read_b64 %5, %7 offset:%10\n\t"
-                     "s_waitcnt lgkmcnt(0)"
-                     : "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(b[0]), "=&v"(b[1]), "=&v"(b[2])
-                     : "v"(at), "v"(bt), "n"(HALF), "n"(TILE + HALF), "n"(2 * TILE + HALF) : "memory");
-    else
-        asm volatile("ds_read_b64 %0, %8 offset:%10\n\tds_read_b64 %1, %8 offset:%11\n\tds_read_b64 %2, %8 offset:%12\n\tds_read_b64 %3, %8 offset:%13\n\t"
-                     "ds_read_b64 %4, %9 offset:%10\n\tds_read_b64 %5, %9 offset:%11\n\tds_read_b64 %6, %9 offset:%12\n\tds_read_b64 %7, %9 offset:%13\n\t"
-                     "s_waitcnt lgkmcnt(0)"
-                     : "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[NB - 1]), "=&v"(b[0]), "=&v"(b[1]), "=&v"(b[2]), "=&v"(b[NB - 1])
-                     : "v"(at), "v"(bt), "n"(HALF), "n"(TILE + HALF), "n"(2 * TILE + HALF), "n"(3 * TILE + HALF) : "memory");
-}
-
-// A block of 1 bit: the same products as in the kernel above, 128 + q and columns in its order (pair order for 128
-// columns), with sums of x of its own.  d = sum q x then has the rounding of that kernel, which for 1 bit is the largest
-// there is (128 against codes of 0 and 1), and what a row of x gives differs less between that kernel and this one:
-// 14336 x 4096, bitwidths 1 .. 8: by 1.3e-4 of the root mean square at most, 4.3e-4 with 1 + q / 2.  (The narrow kernel has 1 + q / 2 from 33 to
-// 64 rows: what it gives is nearer to the exact sum, 1e-6 .. 3e-5 at most, and so differs from either by their error, 1e-4 at most with
-// ordinary weights and 3e-4 .. 1e-3 with outliers.)
-template <int N_COLS, int NB, int SUMS>
-__device__ __forceinline__ void wide_block_1bit(const uint32_t (&cw)[2][N_COLS / 16], const uint32_t (&at)[N_COLS / 32], uint32_t sum_tile,
-                                                WideState<NB, SUMS> &w)
-{
-    constexpr int STEPS = N_COLS / 32, TILE = 16 * N_COLS * 2;
-    const bf16x8_t ones = as_bf16x8(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
-    const f32x4v_t zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
-    f32x4v_t s1[NB];
-    auto products = [&](int st, const bf16x8_t (&x)[NB], const bf16x8_t (&b)[2]) {
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            w.d[0][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[nb], b[0], st == 0 ? zero4 : w.d[0][nb], 0, 0, 0);
-            w.d[1][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[nb], b[1], st == 0 ? zero4 : w.d[1][nb], 0, 0, 0);
-            s1[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[nb], ones, st == 0 ? zero4 : s1[nb], 0, 0, 0);
-        }
-    };
-    bf16x8_t x[NB], b[2];
-#pragma unroll
-    for (int st = 0; st < STEPS; ++st) {
-        u32x2_t wa[NB], wb[NB];
-        if constexpr (N_COLS == 128) {
-            if (st & 1) read_halves<NB, TILE, 8>(at[st >> 1], at[2 + (st >> 1)], wa, wb);
-            else read_halves<NB, TILE, 0>(at[st >> 1], at[2 + (st >> 1)], wa, wb);
-        } else {
-            read_halves<NB, TILE, 0>(at[st], at[st] + 8u, wa, wb);
-        }
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-            x[nb] = N_COLS == 64 ? as_bf16x8(wa[nb].x, wa[nb].y, wb[nb].x, wb[nb].y)
-                                 : as_bf16x8(__builtin_amdgcn_perm(wb[nb].x, wa[nb].x, 0x05040100u), __builtin_amdgcn_perm(wb[nb].x, wa[nb].x, 0x07060302u),
-                                             __builtin_amdgcn_perm(wb[nb].y, wa[nb].y, 0x05040100u), __builtin_amdgcn_perm(wb[nb].y, wa[nb].y, 0x07060302u));
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            uint32_t o[4];
-#pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                if constexpr (N_COLS == 128) o[p] = ((cw[t][0] >> (4 * st + p)) & 0x00010001u) | 0x43004300u;
-                else o[p] = ((cw[t][0] >> (8 * st + 2 * p)) & 1u) | ((cw[t][0] >> (8 * st + 2 * p + 1)) & 1u) << 16 | 0x43004300u;
-            }
-            b[t] = as_bf16x8(o[0], o[1], o[2], o[3]);
-        }
-        products(st, x, b);
-    }
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            w.d[0][nb][r] = fmaf(-128.0f, s1[nb][r], w.d[0][nb][r]);
-            w.d[1][nb][r] = fmaf(-128.0f, s1[nb][r], w.d[1][nb][r]);
-        }
-#pragma unroll
-    for (int q = 0; q < SUMS; ++q) {                          // (tile 3 of three: dropped by the caller)
-        w.s[q] = s1[(4 / SUMS) * q];
-#pragma unroll
-        for (int k = 1; k < 4 / SUMS; ++k)
-            if ((4 / SUMS) * q + k < NB) w.s[q] = sum_tile == (uint32_t)(k * TILE) ? s1[(4 / SUMS) * q + k] : w.s[q];
-    }
-}
-
-// all steps (32 columns each) of a block; at[st]: the LDS address of the lane's operand of step st, sum_tile: how far from
-// there that of the wave's first tile for the sums of x is.  The first step starts the sums.
-template <int C, int N_COLS, int NB, int SUMS>
-__device__ __forceinline__ void wide_block(const uint32_t (&cw)[2][N_COLS / 16], const uint32_t (&at)[N_COLS / 32], uint32_t sum_tile,
-                                           WideState<NB, SUMS> &w)
-{
-    if constexpr (C == 1) { wide_block_1bit<N_COLS, NB, SUMS>(cw, at, sum_tile, w); return; }
-    const bf16x8_t ones = as_bf16x8(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
-    const f32x4v_t zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
-    uint32_t one = PairConst<C>::one, mask = PairConst<C>::field | PairConst<C>::field << 16;
-    asm volatile("" : "+v"(one), "+s"(mask));
-#pragma unroll
-    for (int st = 0; st < N_COLS / 32; ++st) {
-        u32x4_t x[NB], xs[SUMS];
-        read_operands<NB, 16 * N_COLS * 2, SUMS>(at[st], at[st] + sum_tile, x, xs);
-        bf16x8_t b[2];
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            uint32_t o[4];
-#pragma unroll
-            for (int p = 0; p < 4; ++p) o[p] = code_pair<C>(cw[t], 8 * st + 2 * p, one, mask);
-            b[t] = as_bf16x8(o[0], o[1], o[2], o[3]);
-        }
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            const bf16x8_t xa = __builtin_bit_cast(bf16x8_t, x[nb]);
-            w.d[0][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, b[0], st == 0 ? zero4 : w.d[0][nb], 0, 0, 0);
-            w.d[1][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, b[1], st == 0 ? zero4 : w.d[1][nb], 0, 0, 0);
-        }
-#pragma unroll
-        for (int q = 0; q < SUMS; ++q)
-            w.s[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, xs[q]), ones, st == 0 ? zero4 : w.s[q], 0, 0, 0);
-    }
-}
-
-// the sums of x of this lane's rows, NB batch tiles
-template <int NB>
-__device__ __forceinline__ void read_sums(uint32_t at, f32x4v_t (&s)[NB])
-{
-    if constexpr (NB == 3)
-        asm volatile("ds_read_b128 %0, %3\n\tds_read_b128 %1, %3 offset:64\n\tds_read_b128 %2, %3 offset:128\n\ts_waitcnt lgkmcnt(0)"
-                     : "=&v"(s[0]), "=&v"(s[1]), "=&v"(s[2]) : "v"(at) : "memory");
-    else
-        asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:64\n\tds_read_b128 %2, %4 offset:128\n\tds_read_b128 %3, %4 offset:192\n\t"
-                     "s_waitcnt lgkmcnt(0)" : "=&v"(s[0]), "=&v"(s[1]), "=&v"(s[2]), "=&v"(s[3]) : "v"(at) : "memory");
-}
-
-#define WG_SWITCH(c, F)                                                                                           \
+#define MP_SWITCH(c, F)                                                                                           \
     switch (c) {                                                                                                  \
     case 0: break;                                                                                                \
     case 1: F(1); break;                                                                                          \
@@ -614,249 +425,6 @@ __device__ __forceinline__ void read_sums(uint32_t at, f32x4v_t (&s)[NB])
     case 7: F(7); break;                                                                                          \
     default: F(8); break;                                                                                         \
     }
-
-template <int N_COLS, int NB, int RG>
-__global__ __launch_bounds__(WG_THREADS, 2)
-void mp_gemm_wide_kernel(MpArgs a, int cols_per_split)
-{
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    constexpr int KL = N_COLS / 4;                            // codes per lane and block row
-    constexpr int STEPS = N_COLS / 32;                        // of a block: 32 columns each
-    constexpr int CHUNKS = N_COLS / 8, RPL = 64 / CHUNKS;     // 16-byte chunks of a row; rows a wave reads with one load
-    constexpr int ROWS = NB * 16;                             // batch rows
-    constexpr int JL = WG_WAVES / RG, SUMS = 4 / RG;          // block columns of a step; tiles whose sum of x a wave makes
-    constexpr int STAGE = JL * ROWS * N_COLS * 2;          // [block column][batch row][chunk ^ row]
-    constexpr int LPW = STAGE / 1024 / WG_WAVES;              // loads of a wave and stage
-    constexpr int LPC = ROWS / RPL;                           // loads of one block column
-    constexpr int STAGES = 3 * STAGE <= WG_LDS ? 3 : 2, AHEAD = STAGES - 1;
-    static_assert(LPW * 1024 * WG_WAVES == STAGE && LPC % LPW == 0, "whole loads per wave, of one block column");
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int rg = wave & (RG - 1), jl = wave / RG;
-    const int li = lane & 15, g = lane >> 4;
-    const int batch0 = (int)blockIdx.z * 64, batch = min(a.batch - batch0, 64);   // this workgroup's batch rows
-    const int row0 = (int)blockIdx.x * (RG * 32) + rg * 32;               // this wave's 32 channels
-    const bool rows_ok = row0 < a.R;                          // (R is a multiple of 32)
-    const int I = rows_ok ? row0 / a.m : 0, rin = rows_ok ? row0 - I * a.m : 0;
-    const int J0 = (int)blockIdx.y * cols_per_split, J1 = min(J0 + cols_per_split, a.nbc);
-    const int nblk = (J1 - J0 + JL - 1) / JL;           // steps of JL block columns
-    const int turn0 = (int)(blockIdx.x >> 3) % nblk;          // the one this workgroup starts with (workgroups go round the 8 XCDs, each with an L2)
-    float *const xsum = reinterpret_cast<float *>(smem + STAGES * STAGE);          // [parity][jl][ROWS]
-
-    // What this wave brings in of a stage: loads wave * LPW + i, each RPL rows of one block column, through a descriptor
-    // of the batch's rows (rows beyond it read as zero; their outputs are not stored).
-    const int lrow = lane / CHUNKS, lpos = lane % CHUNKS;
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
-    const uint32_t ldx2 = 2u * (uint32_t)a.ld_x;
-    const rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.x) + (int64_t)batch0 * a.ld_x, 0,
-                                                         (int)((uint32_t)(batch - 1) * ldx2 + 2u * (uint32_t)a.C), 0x00027000);
-    const int fj = wave * LPW / LPC, frow = wave * LPW % LPC * RPL;
-    const uint32_t vrow = (uint32_t)(frow + lrow) * ldx2, vchunk = (uint32_t)((lpos ^ lrow) & (CHUNKS - 1));
-    auto fetch = [&](int t, int stage) {
-        const int J = min(J0 + t * JL + fj, a.nbc - 1);    // (past the split: in bounds, not used)
-#pragma unroll
-        for (int i = 0; i < LPW; ++i) {                       // row frow + RPL i + lrow; frow and RPL i are multiples of RPL > lrow
-            const uint32_t at = vrow + (uint32_t)(i * RPL) * ldx2 + (vchunk ^ (uint32_t)((frow + i * RPL) & (CHUNKS - 1))) * 16u;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(xrs, (__attribute__((address_space(3))) void *)(lds0 + (uint32_t)(stage * STAGE + (wave * LPW + i) * 1024)),
-                                                     16, (int)at, J * N_COLS * 2, 0, 0);
-        }
-    };
-    // Everybody's x of the step is in LDS.  A step requests the x of the step AHEAD of it, then codes, scales and offsets of
-    // later ones (LATER loads, all of them used): what this wave has requested behind this step's x may still be under way.
-    // (build.py counts the loads of a step in what the compiler made of them.)
-    constexpr int LATER = 9;
-    auto sync_x = [&]() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(AHEAD * LATER + (AHEAD - 1) * LPW) : "memory"); };
-    auto sync_all = [&]() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
-
-    // the wave's blocks: bitwidth (0: no such block column, or a pruned block), codes, scales
-    const uint32_t lane_units = (uint32_t)((rin + li) * (N_COLS / 8) + g * (KL / 8));   // x c = the lane's byte offset in the block
-    const uint32_t block_bytes_per_bit = (uint32_t)a.m * (N_COLS / 8);
-    // The bitwidths of all steps, a step per lane (at most 256 steps: 512 block columns): a level is a byte, and a byte
-    // loaded step by step is masked, hence waited for, as soon as the compiler likes.
-    constexpr int LVL = N_COLS == 128 ? 2 : 4;
-    int lvl[LVL];
-#pragma unroll
-    for (int k = 0; k < LVL; ++k)
-        lvl[k] = a.level[a.block_base + (int64_t)I * a.nbc + min(J0 + (64 * k + lane) * JL + jl, a.nbc - 1)];
-    struct Meta { int64_t off, blk; };
-    auto meta = [&](int t) {
-        Meta o;
-        o.blk = a.block_base + (int64_t)I * a.nbc + min(J0 + t * JL + jl, a.nbc - 1);
-        o.off = a.byte_off[o.blk];
-        return o;
-    };
-    auto bits_of = [&](int t) {
-        int lv = __builtin_amdgcn_readlane(lvl[0], t & 63);
-#pragma unroll
-        for (int k = 1; k < LVL; ++k) lv = t >> 6 == k ? __builtin_amdgcn_readlane(lvl[k], t & 63) : lv;
-        int b = a.bits[0];
-#pragma unroll
-        for (int k = 1; k < MAX_CAND; ++k) b = lv == k ? a.bits[k] : b;
-        return rows_ok && J0 + t * JL + jl < J1 ? b : 0;
-    };
-    struct Block { Quarter<N_COLS> q[2]; float sc[2], ze[2]; };
-    // metadata that has arrived, as scalars
-    auto scalars = [&](const Meta &mt) {
-        Meta o;
-        o.off = (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)mt.off >> 32)) << 32 |
-                          (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)mt.off));
-        o.blk = mt.blk;
-        return o;
-    };
-    auto request = [&](Block &o, int c, const Meta &mt) {
-        const uint64_t off = (uint64_t)mt.off;
-        const rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(a.codes) + off, 0,
-                                                            (int)(block_bytes_per_bit * (uint32_t)c), 0x00027000);
-#pragma unroll
-        for (int tl = 0; tl < 2; ++tl) {
-            o.sc[tl] = a.scale[mt.blk * a.m + rin + 16 * tl + li];
-            o.ze[tl] = a.zero[mt.blk * a.m + rin + 16 * tl + li];
-            load_quarter<N_COLS>(rs, (lane_units + (uint32_t)(tl * 16 * (N_COLS / 8))) * (uint32_t)c, o.q[tl]);
-        }
-    };
-
-    f32x4v_t acc[2][NB];
-    WideState<NB, SUMS> w;
-    const f32x4v_t zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) acc[0][nb] = acc[1][nb] = w.d[0][nb] = w.d[1][nb] = zero4;
-
-    // a finished block: its sums with scale and zero applied (xsum of its parity is complete)
-    auto apply = [&](const float (&sc)[2], const float (&ze)[2], int c, int u) {
-        if (c == 0) return;
-        float f[2], z[2];
-#define WG_TERM(C) term_factors<C, true>(sc[0], ze[0], f[0], z[0]); term_factors<C, true>(sc[1], ze[1], f[1], z[1])
-        f[0] = f[1] = z[0] = z[1] = 0.0f;
-        WG_SWITCH(c, WG_TERM)
-#undef WG_TERM
-        f32x4v_t xs[NB];
-        read_sums<NB>(lds0 + (uint32_t)(STAGES * STAGE + ((u & 1) * JL + jl) * (ROWS * 4) + 16 * g), xs);
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-            for (int tl = 0; tl < 2; ++tl)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc[tl][nb][r] = fmaf(f[tl], w.d[tl][nb][r], fmaf(z[tl], xs[nb][r], acc[tl][nb][r]));
-    };
-
-    // the u-th step's block columns (past the last: the last once more, requested so that every step makes the same number
-    // of loads, and not used)
-    auto nth = [&](int u) { const int t = turn0 + min(u, nblk - 1); return t < nblk ? t : t - nblk; };
-    // slots of even and odd steps: the codes of that step, and the metadata of the one after next
-    Meta me = meta(nth(0)), mo = meta(nth(1));
-    Block ce, co;
-    int bits_e, bits_o, c_cur = 0;
-    {
-        const Meta m0 = scalars(me), m1 = scalars(mo);
-        bits_e = bits_of(nth(0));
-        bits_o = nblk > 1 ? bits_of(nth(1)) : 0;
-        request(ce, bits_e, m0);
-        request(co, bits_o, m1);
-    }
-    me = meta(nth(2));
-    mo = meta(nth(3));
-    for (int u = 0; u < AHEAD; ++u) fetch(nth(u), u);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    auto arrived = [](Block &k, Meta &mt) {                   // (for the compiler, which would wait in the loop for what the loop never leaves open)
-#pragma unroll
-        for (int tl = 0; tl < 2; ++tl) {
-#pragma unroll
-            for (uint32_t &r : k.q[tl].r) asm volatile("" : "+v"(r));
-            asm volatile("" : "+v"(k.sc[tl]), "+v"(k.ze[tl]));
-        }
-        asm volatile("" : "+v"(mt.off));
-    };
-    arrived(ce, me);
-    arrived(co, mo);
-    Quarter<N_COLS> cq[2];
-    float sc[2] = {0.0f, 0.0f}, ze[2] = {0.0f, 0.0f};
-    // Step u takes over the codes that slot k received and requests those of step u + 2 into it.  The copies are written
-    // out: the compiler cannot merge them with the slot, whose new values would then be moved, and waited for, at the
-    // loop's end.
-    auto turn_over = [&](int u, int stage, Block &k, Meta &mt, int &bits_k) {
-#pragma unroll
-        for (int tl = 0; tl < 2; ++tl) {
-#pragma unroll
-            for (size_t i = 0; i < sizeof cq[tl].r / 4; ++i) asm volatile("v_mov_b32 %0, %1" : "=v"(cq[tl].r[i]) : "v"(k.q[tl].r[i]));
-            asm volatile("v_mov_b32 %0, %2\n\tv_mov_b32 %1, %3" : "=&v"(sc[tl]), "=&v"(ze[tl]) : "v"(k.sc[tl]), "v"(k.ze[tl]));
-        }
-        c_cur = bits_k;
-        const Meta m2 = scalars(mt);
-        bits_k = u + 2 < nblk ? bits_of(nth(u + 2)) : 0;
-        __builtin_amdgcn_sched_barrier(0);
-        fetch(nth(u + AHEAD), stage);
-        asm volatile("" ::: "memory");                        // (x first, then the LATER ones)
-        __builtin_amdgcn_sched_barrier(0);
-        request(k, bits_k, m2);
-        mt = meta(nth(u + 4));
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    int stage = 0;                                            // of step u
-    auto step = [&](int u, Block &slot, Meta &mt, int &bits_slot) {
-        sync_x();                                             // (and the stage before has been read)
-        const float sc_old[2] = {sc[0], sc[1]}, ze_old[2] = {ze[0], ze[1]};
-        const int c_old = c_cur;
-        turn_over(u, stage == 0 ? STAGES - 1 : stage - 1, slot, mt, bits_slot);
-        if (u > 0) apply(sc_old, ze_old, c_old, u - 1);       // the step before, whose sums of x the barrier completed
-        uint32_t cw[2][N_COLS / 16], at[STEPS];
-#pragma unroll
-        for (int tl = 0; tl < 2; ++tl) align_quarter<N_COLS>(cq[tl], (lane_units + (uint32_t)(tl * 16 * (N_COLS / 8))) * (uint32_t)c_cur, cw[tl]);
-        const uint32_t xl = lds0 + (uint32_t)(stage * STAGE + (jl * ROWS + li) * (N_COLS * 2));
-#pragma unroll
-        for (int st = 0; st < STEPS; ++st) at[st] = xl + (uint32_t)(((g * STEPS + st) ^ li) & (CHUNKS - 1)) * 16u;
-        // (tile 3 of three is read all the same: it is inside the stages, or among the sums behind them, and its sum dropped)
-        const uint32_t sum_tile = (uint32_t)(rg * 16 * N_COLS * 2);
-#define WG_BLOCK(C) wide_block<C, N_COLS, NB, SUMS>(cw, at, sum_tile, w)
-        if (c_cur != 0) { WG_SWITCH(c_cur, WG_BLOCK) }
-        else {                                                // (the other row groups may still need this column's sum of x)
-            const uint32_t none[2][N_COLS / 16] = {};
-            wide_block<8, N_COLS, NB, SUMS>(none, at, sum_tile, w);
-        }
-#undef WG_BLOCK
-        // (column 0 of the product with ones: every channel's column is the same)
-        if (li == 0) {
-#pragma unroll
-            for (int q = 0; q < SUMS; ++q)
-                if (rg + RG * q < NB) *reinterpret_cast<f32x4v_t *>(xsum + ((u & 1) * JL + jl) * ROWS + 16 * (rg + RG * q) + 4 * g) = w.s[q];
-        }
-        stage = stage == STAGES - 1 ? 0 : stage + 1;
-    };
-    // Two steps at a time, so that each slot stays in its registers: a slot chosen at run time ends in copies, which wait.
-    // (With an odd number of steps the last one has no codes and adds nothing.)
-    const int nstep = (nblk + 1) & ~1;
-    for (int u = 0; u < nstep; u += 2) {
-        step(u, ce, me, bits_e);
-        step(u + 1, co, mo, bits_o);
-    }
-    sync_all();
-    apply(sc, ze, c_cur, nstep - 1);
-    sync_all();                                               // x has been read: LDS is free
-
-    // the JL waves of a row group add up, in a fixed order; wave jl finishes the batch tiles jl, jl + JL, ..
-    float *red = reinterpret_cast<float *>(smem);             // [wave][tile][nb][lane][4]
-#pragma unroll
-    for (int tl = 0; tl < 2; ++tl)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-            *reinterpret_cast<f32x4v_t *>(red + (((wave * 2 + tl) * NB + nb) * 64 + lane) * 4) = acc[tl][nb];
-    __syncthreads();
-    if (!rows_ok) return;
-    float *dst = a.out + ((int64_t)blockIdx.y * a.batch + batch0) * a.R;
-    for (int nb = jl; nb < NB; nb += JL) {
-#pragma unroll
-        for (int tl = 0; tl < 2; ++tl) {
-            f32x4v_t v = *reinterpret_cast<const f32x4v_t *>(red + (((rg * 2 + tl) * NB + nb) * 64 + lane) * 4);
-#pragma unroll
-            for (int j = 1; j < JL; ++j) v = v + *reinterpret_cast<const f32x4v_t *>(red + ((((j * RG + rg) * 2 + tl) * NB + nb) * 64 + lane) * 4);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int b = 16 * nb + 4 * g + r;
-                if (b < batch) dst[(int64_t)b * a.R + row0 + 16 * tl + li] = v[r];
-            }
-        }
-    }
-}
 
 // ================================================================ few batch rows
 // Few rows of x are small next to the codes, so nothing is staged and no columns are split off: a workgroup takes 32
@@ -922,7 +490,7 @@ __device__ __forceinline__ void narrow_block(const uint32_t (&cw)[2][8], const f
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
         float f = sc[t], zz = C < 8 ? fmaf(-128.0f, sc[t], ze[t]) : ze[t];
-        if constexpr (FINE) term_factors<C, false>(sc[t], ze[t], f, zz);
+        if constexpr (FINE) term_factors<C>(sc[t], ze[t], f, zz);
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc[t][r] = fmaf(f, d[t][r], fmaf(zz, d1[r], acc[t][r]));
     }
@@ -1042,10 +610,10 @@ void mp_gemm_narrow_kernel(MpArgs a)
             asm volatile("" : "+v"(from));
             const StagedX<KL> x{xl, from};
 #define ND_BLOCK(C) narrow_block<C, N_COLS, FINE>(cw, o.sc, o.ze, x, acc)
-            WG_SWITCH(o.c, ND_BLOCK)
+            MP_SWITCH(o.c, ND_BLOCK)
         } else {
             const HeldX<KL> x{o.x};
-            WG_SWITCH(o.c, ND_BLOCK)
+            MP_SWITCH(o.c, ND_BLOCK)
 #undef ND_BLOCK
         }
     };
@@ -1083,21 +651,21 @@ void mp_gemm_narrow_kernel(MpArgs a)
     }
 }
 
-// ================================================================ more than 32 batch rows, each wave on its own columns
+// ================================================================ more than 32 batch rows
 // A workgroup takes CT tiles of 16 channels and NB tiles of 16 batch rows; its WAVES waves take every WAVES-th block column each and
 // share nothing but the sum at the end, so no barrier holds them in step.  A wave brings the x of its next block column into LDS of
 // its own by direct loads (whole rows, 1 KiB a load), reads all operands of the present one into registers (64 of them, at 4 batch tiles and
-// 128 columns) and then asks for the next: x is read from LDS once per wave, where the kernel above reads it once per 32 channels.
+// 128 columns) and then asks for the next: x is read from LDS once per wave.
 // Codes of a pair of tiles are asked for a block ahead, into the registers that the pair has just done with.  Bitwidths and
 // offsets lie in LDS from the start.  sum_j x of the block comes from a product with ones, per wave (16 of its 80 matrix
-// instructions at 4 x 4 tiles), in the place of the exchange and its barrier.
+// instructions at 4 x 4 tiles).
 // Vector issue bounds it: at 4 x 4 tiles and 128 columns unpacking 64 codes in pairs takes 128 .. 192 instructions a lane and block,
 // two FMAs per output 128; next are the direct loads of x, which take a wave 40 clocks each to ask for (8192 x 28672 at 128 rows
 // without them 88 us instead of 102).  Tiles of 64 x 64 are the largest whose sums, operands and codes fit 256
-// registers.  With 8 waves a workgroup has the CU to itself; with 4, two of them take turns in starting and ending.  Against the kernel above: 14336 x 4096 at 100
+// registers.  With 8 waves a workgroup has the CU to itself; with 4, two of them take turns in starting and ending.
+// Its predecessor held 8 waves in step, a barrier a step, x read from LDS once per 32 channels.  Against that one: 14336 x 4096 at 100
 // rows, bitwidths 1 .. 8, 39.0 -> 30.6 us; 8192 x 28672 at 128 rows 139 -> 92; 14336 x 4096 in 64-column blocks at 100 rows 55.7 -> 39.2;
-// 4096 x 4096 at 64 rows 12.9 -> 10.1.
-// The operands, their order and so the block's products are those of the kernel above, 1 bit included.
+// 4096 x 4096 at 64 rows 12.9 -> 10.1; in 41 drawn products of which the estimates had said the contrary it takes 0.88 of the time, 0.95 at most.
 
 // one tile of 16 channels and NB tiles of 16 batch rows: the block's products, scale and zero applied
 template <int C, int N_COLS, int NB>
@@ -1120,14 +688,17 @@ __device__ __forceinline__ void many_tile(const uint32_t (&cw)[N_COLS / 16], flo
             d[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, x[nb][st]), b, st == 0 ? zero4 : d[nb], 0, 0, 0);
     }
     float f, z;
-    term_factors<C, true>(sc, ze, f, z);
+    term_factors<C>(sc, ze, f, z);
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc[nb][r] = fmaf(f, d[nb][r], fmaf(z, s[nb][r], acc[nb][r]));
 }
 
-// two tiles at 1 bit: products as in wide_block_1bit
+// Two tiles at 1 bit: 128 + q and columns in the order of the kernel for up to 32 rows (pair order for 128 columns), with sums of x of
+// their own.  What a row of x gives then differs little between that kernel and this one (14336 x 4096, bitwidths 1 .. 8: by 1.3e-4 of the root
+// mean square at most, 4.3e-4 with 1 + q / 2 here), but both are 1e-5 from the exact product, by the norm, where 1 + q / 2 would be 3e-7: see
+// one_bit_line.
 template <int N_COLS, int NB>
 __device__ __forceinline__ void many_tiles_1bit(const uint32_t (&cw)[2][N_COLS / 16], const float *sc, const float *ze,
                                                 const u32x4_t (&x)[NB][N_COLS / 32], f32x4v_t (&acc0)[NB], f32x4v_t (&acc1)[NB])
@@ -1367,7 +938,7 @@ void mp_gemm_many_kernel(MpArgs a, int cols_per_split)
             many_tile<C, N_COLS, NB>(cw[1], sc[2 * h + 1], ze[2 * h + 1], x, s, acc[2 * h + 1]);                  \
         }                                                                                                         \
     } while (0)
-                WG_SWITCH(cb[h], MB_TILE)
+                MP_SWITCH(cb[h], MB_TILE)
 #undef MB_TILE
                 request(h, t + 1, mw[2 * h + 1], mw[2 * h]);
             }
@@ -1375,7 +946,7 @@ void mp_gemm_many_kernel(MpArgs a, int cols_per_split)
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();                                          // every wave is done with its x
-    // the eight waves add up, in a fixed order
+    // the waves add up, in a fixed order
     float *red = reinterpret_cast<float *>(smem);             // [wave][tile][nb][lane][4]
 #pragma unroll
     for (int tl = 0; tl < CT; ++tl)
@@ -1420,43 +991,7 @@ bool sbits_mp_gemm_shapes_ok(const sbits_plan *plan)
     return (plan->n == 64 || plan->n == 128) && plan->m % 32 == 0;
 }
 
-// Work split of the product of more than 32 rows, by the matrix and the batch groups alone, so that a product's sums do not
-// depend on what else is in its plan.
-// Workgroups of 128 or of 64 channels, one per CU at a time.  Column splits while every CU has at most one: an even number of
-// steps each (the kernel takes them in pairs: three cost as much as four; three in all of a small matrix are split one by one), at most 32 of
-// them (one thread adds their partial sums: 64 x 32768 in 64-column blocks 128 splits of one step 37 us, 64 of two 23, 32 of
-// four 19), and not to save two steps where the partial sums are large (8192 x 1024, 64-column blocks, 64 rows: 11.6 us,
-// 12.5 with two splits).  They take 8 MiB at most.
-// The shape that takes less time by this estimate is taken (in hundredths of a microsecond above the launch: a turn of the CUs
-// costs 3 us and 1.65 or, in 64-column blocks, 1.25 a step): 14336 x 4096 at 64 rows 26 us with 224 workgroups of 64, 38 with
-// 112 of 128; 11008 x 4096 at 100 rows 36 with 172 of 128, 43 with 344 of 64 in two turns; 10240 x 8192 at 33 rows 29 with three
-// splits of 80 of 128, 36 with 160 of 64.
-struct WideSplit { int rg, per_split, n_split; int64_t cost; };
-static WideSplit wide_split(int64_t R, int nbc, int n, int batch)
-{
-    const int64_t z = (batch + 63) / 64;
-    auto with = [&](int rg) {
-        WideSplit o;
-        const int64_t tiles = (R + rg * 32 - 1) / (rg * 32) * z, jl = WG_WAVES / rg, steps = (nbc + jl - 1) / jl;
-        const int64_t most = 256 / tiles < 32 ? 256 / tiles : 32;
-        o.rg = rg;
-        o.per_split = nbc;
-        if (most > 1 && !(steps <= 4 && R * z * 64 > 1 << 18)) {
-            const int64_t cols = (steps == 3 && most > 2 && R * z * 64 <= 1 << 17 ? 1 : ((steps + most - 1) / most + 1) / 2 * 2) * jl;
-            if (cols < nbc) o.per_split = (int)cols;
-        }
-        o.n_split = (nbc + o.per_split - 1) / o.per_split;
-        const int64_t pairs = ((o.per_split + jl - 1) / jl + 1) / 2, turns = (tiles * o.n_split + 255) / 256;
-        o.cost = turns * (300 + pairs * 2 * (n == 128 ? 165 : 125));
-        if (turns > 1 && rg == 2) o.cost += o.cost / 20;
-        if (o.n_split > 1) o.cost += 200 + 20 * o.n_split + o.n_split * z * R / 160;   // the second launch and the partial sums
-        return o;
-    };
-    const WideSplit a = with(4), b = with(2);
-    return a.cost < b.cost ? a : b;
-}
-
-// Shapes of the kernel whose waves take columns of their own, and what a product takes in each, in microseconds: fitted to 1350
+// Shapes of the kernel of many rows, and what a product takes in each, in microseconds: fitted to 1350
 // products of 256 .. 28672 rows and columns, 33 .. 128 rows of x, in all shapes and column splits (mean error 3 .. 7 %; the shape
 // chosen by them is 2 % behind the best one on average).  turns: of workgroups on 256 CUs, one a CU or, with four
 // waves, two; work: block columns of a wave times workgroups of a CU.  The choice decides the order of the sums, so it goes by the matrix
@@ -1511,21 +1046,17 @@ void sbits_mp_gemm_tables(sbits_plan *plan)
 }
 static const ManySplit &many_of(const sbits_plan *plan, int mat, int batch) { return plan->many[(size_t)mat * 6 + (size_t)((batch + 15) / 16 - 3)]; }
 
-// partial sums of the largest matrix: 32 rows of the first kernel, 64 or 128 (one and two batch groups: fewer rows have the
-// same splits) of the wide one, and of the one by columns
+// partial sums of the largest matrix: 32 rows of the first kernel, and each number of tiles of the one for many rows
 size_t sbits_mp_gemm_ws_bytes(const sbits_plan *plan)
 {
     if (!sbits_mp_gemm_shapes_ok(plan)) return 0;
     size_t mx = 0;
     for (int i = 0; i < plan->n_mats; ++i) {
-        const int nbc = (int)(plan->cols[i] / plan->n);
         auto need = [&](int splits, int batch) {
             const size_t b = splits > 1 ? (size_t)splits * batch * (size_t)plan->rows[i] * 4 : 0;
             if (b > mx) mx = b;
         };
         need(sbits_mp_gemm_splits(plan->cols[i], plan->n), 32);
-        need(wide_split(plan->rows[i], nbc, plan->n, 64).n_split, 64);
-        need(wide_split(plan->rows[i], nbc, plan->n, 128).n_split, 128);
         for (int tiles = 3; tiles <= 8; ++tiles) need(many_of(plan, i, tiles * 16).n_split, tiles * 16);
     }
     return sbits_align_up(mx, 256);
@@ -1555,21 +1086,6 @@ static int launch_narrow(sbits_ctx *ctx, const MpArgs &a)
     return SBITS_OK;
 }
 
-template <int N_COLS, int NB, int RG>
-static int launch_wide(sbits_ctx *ctx, const MpArgs &a, dim3 grid, int cols_per_split)
-{
-    constexpr int stage = (WG_WAVES / RG) * NB * 16 * N_COLS * 2;
-    constexpr size_t stages = (size_t)(3 * stage <= WG_LDS ? 3 : 2) * stage + (size_t)2 * (WG_WAVES / RG) * NB * 16 * 4;
-    constexpr size_t past = (size_t)16 * N_COLS * 2;          // (a tile more than three may be read behind the last stage)
-    constexpr size_t red = (size_t)WG_WAVES * 2 * NB * 64 * 16;
-    constexpr size_t lds = stages + past > red ? stages + past : red;
-    auto *fn = &mp_gemm_wide_kernel<N_COLS, NB, RG>;
-    SBITS_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL(fn, grid, dim3(WG_THREADS), lds, ctx->stream, a, cols_per_split);
-    SBITS_HIP(ctx, hipGetLastError());
-    return SBITS_OK;
-}
-
 template <int N_COLS, int NB, int CT, int WAVES>
 static int launch_many(sbits_ctx *ctx, const MpArgs &a, const ManySplit &ms)
 {
@@ -1595,18 +1111,11 @@ static int launch_many_shape(sbits_ctx *ctx, const MpArgs &a, const ManySplit &m
     }
 }
 
-template <int RG>
-static int launch_wide_rg(sbits_ctx *ctx, int n, const MpArgs &a, dim3 grid, int cols_per_split)
-{
-    if (n == 64) return launch_wide<64, 4, RG>(ctx, a, grid, cols_per_split);
-    return a.batch <= 48 ? launch_wide<128, 3, RG>(ctx, a, grid, cols_per_split) : launch_wide<128, 4, RG>(ctx, a, grid, cols_per_split);
-}
-
 // What a product takes in the first kernel (up to 32 rows) and in the narrow one (up to 64), in microseconds, fitted to 2600 and
 // 900 products of 256 .. 28672 x 256 .. 28672, 1 .. 64 rows of x, bitwidths up to 8.  With the choice made by these, 1400 others of
 // the same ranges took 1.3 .. 1.5 % longer on average than with the better kernel each time, 23 % at most (always the first, or
-// above 32 rows the wide one, 14 %; always the narrow one 10 .. 12 %); no product takes less than a launch, 5.2.  (The turns are
-// those of a whole device also on a partition of one, here and in wide_split: the choice decides the order of the sums, and a
+// above 32 rows this one's predecessor for many, 14 %; always the narrow one 10 .. 12 %); no product takes less than a launch, 5.2.  (The turns are
+// those of a whole device also on a partition of one, here and in one_bit_line: the choice decides the order of the sums, and a
 // product gives the same bits on either.)
 // First: by the turns of the CUs (32 channels and 16 block columns each, 256 at a time) and their bytes; with several column
 // splits, their number, the partial sums and the second launch (1024 x 17216 in 64-column blocks, 17 splits, 12.5 us).
@@ -1657,9 +1166,7 @@ static FewRows few_rows(const sbits_plan *plan, int64_t R, int nbc, int batch)
 
 // Up to 16 block columns and two turns of the narrow kernel, where both take hardly more than a launch, it is the better one (up to
 // 16 rows by 3 .. 8 % on average and at most 3 % slower, up to 32 by 5 .. 26 %).
-// Above 32 rows: against the estimate of the wide kernel, 2.5 us above its cost (always the wide one: 18 % slower), where a plan
-// has a candidate of 1 bit, whose codes enter those kernels with another offset (wide_block_1bit): which rows have which stays as
-// it is, so that they are as exact as before and differ no more.  Else against the better of the two kernels of many rows.
+// Above 32 rows: against the kernel of many rows, or one_bit_line.
 // A pitch of x past the 32-bit offsets of the narrow kernel: the first.
 static bool has_one_bit(const sbits_plan *plan)
 {
@@ -1667,11 +1174,34 @@ static bool has_one_bit(const sbits_plan *plan)
         if (plan->bits[l] == 1) return true;
     return false;
 }
-static double wide_us(const WideSplit &ws) { return 0.01 * (double)(ws.cost + 250); }
-static double many_rows_us(const sbits_plan *plan, int mat, int batch)
+
+// Where codes of 1 bit enter as 1 + q / 2 (the kernels of few rows) and where as 128 + q (that of many) is part of what a product of 33
+// .. 96 rows gives: by the norm it is 3e-7 from the exact one, or 1e-5; in single values the two differ by up to 3e-4 of the root mean square, with
+// outlier channels by up to 4e-3.  The line goes by the time, in hundredths of a microsecond above the launch, that such a product took in the
+// predecessor of the kernel of many rows: 8 waves, 128 or 64 channels and 4 or 2 block columns a step, two steps at a time, up to 64 rows a
+// workgroup; a turn of the CUs costs 3 us and 1.65 or, in 64-column blocks, 1.25 a step.  By the kernel that there is now it would lie lower, and a
+// quarter of the products of 33 .. 64 rows be 1.2 times as fast and 30 times less exact.  (With 1 + q / 2 in both, 150 drawn products of 33 .. 128 rows
+// take 0.94 of the time and no line is needed; but 31 of them, with outliers, give values 4e-4 .. 4e-3 of the root mean square from those of now.)
+static int64_t one_bit_line(int64_t R, int nbc, int n, int batch)
 {
-    const double many = many_of(plan, mat, batch).us, wide = wide_us(wide_split(plan->rows[mat], (int)(plan->cols[mat] / plan->n), plan->n, batch));
-    return many < wide ? many : wide;
+    const int64_t z = (batch + 63) / 64;
+    auto with = [&](int rg) {
+        const int64_t tiles = (R + rg * 32 - 1) / (rg * 32) * z, jl = 8 / rg, steps = (nbc + jl - 1) / jl;
+        const int64_t most = 256 / tiles < 32 ? 256 / tiles : 32;
+        int64_t per_split = nbc;
+        if (most > 1 && !(steps <= 4 && R * z * 64 > 1 << 18)) {
+            const int64_t cols = (steps == 3 && most > 2 && R * z * 64 <= 1 << 17 ? 1 : ((steps + most - 1) / most + 1) / 2 * 2) * jl;
+            if (cols < nbc) per_split = cols;
+        }
+        const int64_t n_split = (nbc + per_split - 1) / per_split;
+        const int64_t pairs = ((per_split + jl - 1) / jl + 1) / 2, turns = (tiles * n_split + 255) / 256;
+        int64_t cost = turns * (300 + pairs * 2 * (n == 128 ? 165 : 125));
+        if (turns > 1 && rg == 2) cost += cost / 20;
+        if (n_split > 1) cost += 200 + 20 * n_split + n_split * z * R / 160;   // the second launch and the partial sums
+        return cost;
+    };
+    const int64_t a = with(4), b = with(2);
+    return a < b ? a : b;
 }
 static bool takes_narrow(const sbits_plan *plan, int mat, const MpArgs &a)
 {
@@ -1679,15 +1209,14 @@ static bool takes_narrow(const sbits_plan *plan, int mat, const MpArgs &a)
     if (a.batch <= 32 && a.nbc <= MG_SPAN && a.R / 32 * ((a.batch + 15) / 16) <= 512) return true;
     const FewRows t = few_rows(plan, a.R, a.nbc, a.batch);
     if (a.batch <= 32) return t.narrow <= t.first;
-    if (has_one_bit(plan)) return t.narrow * 100 < (double)(wide_split(a.R, a.nbc, plan->n, a.batch).cost + 250);
-    return t.narrow <= many_rows_us(plan, mat, a.batch);
+    if (has_one_bit(plan)) return t.narrow * 100 < (double)(one_bit_line(a.R, a.nbc, plan->n, a.batch) + 250);
+    return t.narrow <= many_of(plan, mat, a.batch).us;
 }
 
 // Rows of x the next launch takes of those that are left: 128 (two batch groups) while a group's byte offsets fit the 32 bits
-// of a descriptor, else the 32 of the first kernel, whose addresses have 64.  The wide kernel takes a second group of up to 32 rows as
-// long as one of 64, so those rows are left to the kernels for few rows where that is faster: 16640 x 4096 at 65 rows 51
-// us instead of 69 in it.  (With a candidate of 1 bit by the wide kernel's estimates alone, see takes_narrow; the kernel by columns takes
-// groups of 32 or 48 rows, and is rarely the slower one.)
+// of a descriptor, else the 32 of the first kernel, whose addresses have 64.  65 .. 96 rows go as 64 and the rest where the kernels for
+// few rows take the rest in less than the kernel of many rows takes longer for it (whose groups of 32 .. 64 rows make that rare), or by
+// one_bit_line.
 int sbits_mp_gemm_rows(const sbits_plan *plan, int mat, int64_t ld_x, int left)
 {
     if (ld_x > 1 << 20) return left < 32 ? left : 32;
@@ -1697,16 +1226,15 @@ int sbits_mp_gemm_rows(const sbits_plan *plan, int mat, int64_t ld_x, int left)
         const FewRows t = few_rows(plan, R, nbc, left - 64);
         const double rest = t.narrow < t.first ? t.narrow : t.first;
         if (has_one_bit(plan)) {
-            if (wide_split(R, nbc, n, 64).cost + (int64_t)(rest * 100) + 300 <= wide_split(R, nbc, n, left).cost) return 64;
-        } else if (many_rows_us(plan, mat, 64) + rest <= many_rows_us(plan, mat, left)) {
+            if (one_bit_line(R, nbc, n, 64) + (int64_t)(rest * 100) + 300 <= one_bit_line(R, nbc, n, left)) return 64;
+        } else if (many_of(plan, mat, 64).us + rest <= many_of(plan, mat, left).us) {
             return 64;
         }
     }
     return left < 128 ? left : 128;
 }
 
-// fine: rows of a product of more than 32, whose codes enter with the smaller offset in every kernel (1 bit not in the wide one, see
-// wide_block_1bit)
+// fine: rows of a product of more than 32, whose codes enter with the smaller offset in every kernel (1 bit not in that of many rows)
 int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t ld_x, int batch, bool fine,
                          const uint8_t *level, const int64_t *byte_off, const uint8_t *codes, const float *scale,
                          const float *zero, float *y, void *scratch)
@@ -1740,16 +1268,10 @@ int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t 
     }
     const bool many = batch > 32;
     const ManySplit ms = many ? many_of(plan, mat, batch) : ManySplit{0, 0, 0, 0.0};
-    const WideSplit ws = many ? wide_split(a.R, a.nbc, plan->n, batch) : WideSplit{0, 0, 0, 0};
-    const bool wide = many && wide_us(ws) < ms.us;
-    a.n_split = wide ? ws.n_split : many ? ms.n_split : sbits_mp_gemm_splits(a.C, plan->n);
+    a.n_split = many ? ms.n_split : sbits_mp_gemm_splits(a.C, plan->n);
     a.out = a.n_split > 1 ? static_cast<float *>(scratch) : y;
     int rc;
-    if (wide) {
-        const int rows = ws.rg * 32;
-        const dim3 grid((unsigned)((a.R + rows - 1) / rows), (unsigned)a.n_split, (unsigned)((batch + 63) / 64));
-        rc = ws.rg == 4 ? launch_wide_rg<4>(ctx, plan->n, a, grid, ws.per_split) : launch_wide_rg<2>(ctx, plan->n, a, grid, ws.per_split);
-    } else if (many) {
+    if (many) {
         rc = plan->n == 128 ? launch_many_shape<128>(ctx, a, ms) : launch_many_shape<64>(ctx, a, ms);
     } else {
         // Channels of a workgroup: x takes 32 .. 128 KiB of LDS, and as many waves as the registers allow (16) should be on a

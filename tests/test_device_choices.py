@@ -147,3 +147,34 @@ def test_packing_of_copies_keeps_weights_in_the_caches_where_they_fit(tmp_path):
     for n, rows, kernels in record(tmp_path, PACK_ALL):
         cached = n <= 64 and 40 < rows // 64 <= (144 if n < 32 else 208)
         assert len(kernels) == 1 and ("pack_kernelILi%dELb%dE" % (n // 8, cached)) in kernels[0], (n, rows, kernels)
+
+
+PRODUCTS = r"""
+class X:
+    def __init__(self, batch, ld): self.shape, self.ld = (batch, ld), ld
+    def data_ptr(self): return fake(1 << 20)
+    def stride(self, i): return self.ld
+ctx = sb.Context(0, 0)
+out = []
+for R, C, m, n, bits, batch in %r:
+    plan = sb.Plan(ctx, [(R, C)], m, n, bits)
+    a = [fake(1 << 24) for _ in range(7)]
+    log()
+    plan.mp_gemm(0, X(batch, C), *a)
+    out.append([line.split()[1] for line in log() if line.startswith("launch")])
+    plan.close()
+answer(out)
+"""
+
+
+def launched(tmp_path, products):
+    """The kernels of each product (R, C, m, n, bits, rows of x), by name."""
+    return record(tmp_path, PRODUCTS % (products,))
+
+
+def test_wide_matrices_take_the_kernel_of_many_rows(tmp_path):
+    """Shapes for which the estimates once favoured a kernel that is up to 1.23 times slower there."""
+    products = [(704, 22144, 64, 128, [3, 5, 6], 110), (2304, 25856, 128, 128, [2, 3, 4], 53), (6400, 22784, 128, 128, [4], 63),
+                (1536, 25088, 128, 128, [1, 2, 3, 4, 8], 98), (2304, 24832, 32, 128, [2, 3, 4], 61), (1088, 28160, 32, 128, [0, 1, 2, 3, 4], 115)]
+    for product, kernels in zip(products, launched(tmp_path, products)):
+        assert "mp_gemm_many_kernel" in kernels[0], (product, kernels)
