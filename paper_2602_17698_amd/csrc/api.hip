@@ -559,7 +559,7 @@ int sbits_pack_all(sbits_plan *plan, const void *w_re_bf16, const uint8_t *level
     int rc = need_device(plan);
     if (rc) return rc;
     if ((rc = sbits_upload_head(plan, nullptr, nullptr, ws))) return rc;
-    return sbits_launch_pack_all(plan, w_re_bf16, level, byte_off, codes, scale, zero, ws);
+    return sbits_launch_pack_all(plan, w_re_bf16, level, byte_off, codes, scale, zero, true, ws);
 }
 
 }  // extern "C"
@@ -608,7 +608,7 @@ static int run_search(sbits_plan *plan, const sbits_matrix *mats, const sbits_co
                                               out->scale, out->zero, ws, aborted);
         else
             rc = sbits_launch_pack_all(plan, out->w_re_bf16, out->level, out->byte_off, out->codes, out->scale,
-                                       out->zero, ws, aborted);
+                                       out->zero, false, ws, aborted);
         if (rc) return rc;
         SBITS_HIP(plan->ctx, hipStreamSynchronize(plan->ctx->stream));
         if (attempt || !sbits_allocation_failed(plan)) return sbits_finish_allocate(plan, host_stats, nullptr, 0, scratch);

@@ -292,7 +292,7 @@ struct PackLaunch {
     int n_mats;
     int64_t total_wg;
     const uint16_t *W;
-    int64_t weights;
+    bool cached;
     int m;
     const uint8_t *level;
     const int64_t *byte_off;
@@ -302,14 +302,16 @@ struct PackLaunch {
     const unsigned *aborted;
 };
 
-// Ordinary loads where weights that are packed again and again, with other levels each time, stay in the 256 MiB memory-side cache beside
-// their codes, which non-temporal loads read past in blocks of up to 64 columns.  Again / non-temporal: 8 columns 48 MiB 30 us and 33, 128 MiB 59 and
-// 69, 160 MiB 90 and 84; 32 columns 64 MiB 25.6 and 27.9, 192 MiB 50 and 66, 224 MiB 76 and 76; 64 columns 192 MiB 44 and 52, 32 MiB 17.8 and
-// 17.0.  From 128 columns on they gain little (192 MiB 45 and 49) and cost as much where the weights have just been reordered.
+// Ordinary loads where weights that a program packs again and again, with other levels each time, stay in the 256 MiB memory-side cache
+// beside their codes, which non-temporal loads read past in blocks of up to 64 columns.  Packed again, ordinary / non-temporal: 8 columns
+// 20 MiB 20.0 us and 20.4, 28 22.8 and 24.4, 80 47.4 and 56.4, 150 112 and 100; 16 columns 36 MiB 23.5 and 25.2, 170 56 and 69, 190 100 and 97; 32
+// columns 44 MiB 23.2 and 26.4, 170 48.6 and 62.9, 215 84 and 82; 64 columns 60 MiB 24.3 and 23.8, 110 41.1 and 47.8, 215 64.2 and 64.3.  From
+// 128 columns on they gain little.  Just after the copies were made both take the same from 60 MiB on.  Not in a search: there they
+// cost more (32 columns, 16864 x 3104: 445 us and, with ordinary loads, 456; 32 searches of 60 .. 180 MiB 1.2 % on average).
 static bool caches_weights(int n, int64_t weights)
 {
     const int64_t mib = weights * 2 >> 20;
-    return n <= 64 && mib > 40 && mib <= (n < 32 ? 144 : 208);
+    return n <= 64 && mib > (n == 8 ? 24 : n < 64 ? 40 : 72) && mib <= (n == 8 ? 144 : n == 16 ? 176 : 208);
 }
 
 template <int LPG>
@@ -319,7 +321,7 @@ static int launch_pack_l(sbits_ctx *ctx, const PackLaunch &a)
     if (a.total_wg == 0) return SBITS_OK;
     auto *fn = &pack_kernel<LPG, false>;
     if constexpr (LPG <= 8) {
-        if (caches_weights(8 * LPG, a.weights)) fn = &pack_kernel<LPG, true>;
+        if (a.cached) fn = &pack_kernel<LPG, true>;
     }
     hipLaunchKernelGGL(fn, dim3((unsigned)a.total_wg), dim3(PK_THREADS), 0, ctx->stream,
                        a.descs, a.one, a.wg_start, a.n_mats, a.W, a.m, a.level, a.byte_off, a.codes, a.scale,
@@ -442,7 +444,7 @@ int sbits_launch_pack(sbits_ctx *ctx, const void *Wp, int64_t R, int64_t C, int 
     a.n_mats = 1;
     a.total_wg = pack_wgs(m, n, a.one.nbr, a.one.nbc);
     a.W = static_cast<const uint16_t *>(Wp);
-    a.weights = R * C;
+    a.cached = caches_weights(n, R * C);
     a.m = m;
     a.level = level; a.byte_off = byte_off; a.codes = codes; a.scale = scale; a.zero = zero;
     return launch_pack(n, ctx, a);
@@ -460,9 +462,9 @@ void sbits_pack_tables(sbits_plan *plan)
     plan->pack_wg_start.push_back((int)tot);
 }
 
-// all matrices of the plan in one launch; the descriptor table is already in the workspace head
+// all matrices of the plan in one launch; the descriptor table is already in the workspace head.  again: see caches_weights
 int sbits_launch_pack_all(sbits_plan *plan, const void *w_re, const uint8_t *level, const int64_t *byte_off,
-                          uint8_t *codes, float *scale, float *zero, void *ws, const unsigned *aborted)
+                          uint8_t *codes, float *scale, float *zero, bool again, void *ws, const unsigned *aborted)
 {
     sbits_ctx *ctx = plan->ctx;
     PackLaunch a;
@@ -475,7 +477,7 @@ int sbits_launch_pack_all(sbits_plan *plan, const void *w_re, const uint8_t *lev
     a.n_mats = plan->n_mats;
     a.total_wg = plan->pack_wg_start.back();
     a.W = static_cast<const uint16_t *>(w_re);
-    a.weights = plan->sum_elems;
+    a.cached = again && caches_weights(plan->n, plan->sum_elems);
     a.m = plan->m;
     a.level = level; a.byte_off = byte_off; a.codes = codes; a.scale = scale; a.zero = zero;
     return launch_pack(plan->n, ctx, a);

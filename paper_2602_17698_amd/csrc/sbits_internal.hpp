@@ -108,7 +108,7 @@ int sbits_launch_reorder_coupled_all(sbits_plan *plan, const sbits_coupling &cpl
 int sbits_launch_gather_all(sbits_plan *plan, const int32_t *row_perm, const int32_t *col_perm,
                             void *w_re, float *s_re, void *ws);
 int sbits_launch_pack_all(sbits_plan *plan, const void *w_re, const uint8_t *level, const int64_t *byte_off,
-                          uint8_t *codes, float *scale, float *zero, void *ws, const unsigned *aborted = nullptr);
+                          uint8_t *codes, float *scale, float *zero, bool again, void *ws, const unsigned *aborted = nullptr);
 int sbits_launch_gather(sbits_ctx *ctx, const void *W, const float *S, int64_t R, int64_t C,
                         int64_t ld_w, int64_t ld_s, const int32_t *rp, const int32_t *cp,
                         void *w_out, float *s_out);

@@ -131,22 +131,32 @@ PACK_ALL = r"""
 ctx = sb.Context(0, 0)
 out = []
 for n in (8, 16, 32, 64, 128, 512):
-    for rows in (1024, 2624, 8192, 12288, 16384):
-        plan = sb.Plan(ctx, [(rows, 8192)], 8, n, [2, 4])
-        a = [fake(1 << 28) for _ in range(7)]
+    for mib in (16, 32, 41, 64, 128, 160, 192, 256):
+        plan = sb.Plan(ctx, [(64 * mib, 8192)], 8, n, [2, 4])
+        a = [fake(1 << 29) for _ in range(12)]
+        packs = lambda: [line.split()[1] for line in log() if " _ZN5sbits11pack_kernel" in line]
         log()
-        plan.pack_all(*a)
-        out.append([n, rows, [line.split()[1] for line in log() if "pack_kernel" in line]])
+        plan.pack_all(*a[:7])
+        again = packs()
+        if n != 64 and n != 128:                  # (those are packed from the matrices themselves)
+            try:
+                plan.search([sb.Matrix(a[0], a[1], 64 * mib, 8192, 8192, 8192)], 3.0, sb.Outputs(*a[2:10], 1 << 40, *a[10:12]), fake(1 << 29))
+            except sb.SbitsError:                 # (nothing ran: there is no result to finish with)
+                pass
+        out.append([n, mib, again, packs()])
         plan.close()
 answer(out)
 """
 
 
 def test_packing_of_copies_keeps_weights_in_the_caches_where_they_fit(tmp_path):
-    """Blocks of up to 64 columns, weights of 40 to 208 MiB (144 in blocks of up to 16): by ordinary loads."""
-    for n, rows, kernels in record(tmp_path, PACK_ALL):
-        cached = n <= 64 and 40 < rows // 64 <= (144 if n < 32 else 208)
-        assert len(kernels) == 1 and ("pack_kernelILi%dELb%dE" % (n // 8, cached)) in kernels[0], (n, rows, kernels)
+    """Blocks of up to 64 columns, weights that fit the memory-side cache with their codes: by ordinary loads where they are packed again, not in a search."""
+    bounds = {8: (24, 144), 16: (40, 176), 32: (40, 208), 64: (72, 208)}
+    for n, mib, again, search in record(tmp_path, PACK_ALL):
+        lo, hi = bounds.get(n, (0, 0))
+        name = "pack_kernelILi%dELb%dE"
+        assert len(again) == 1 and name % (n // 8, lo < mib <= hi) in again[0], (n, mib, again)
+        assert len(search) >= (n not in (64, 128)) and all(name % (n // 8, 0) in kernel for kernel in search), (n, mib, search)
 
 
 PRODUCTS = r"""

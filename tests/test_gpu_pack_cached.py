@@ -13,13 +13,13 @@ pytestmark = pytest.mark.gpu
 def test_packing_through_the_caches(n):
     print("[case] packing through the caches", n, flush=True)
     dev, m, bits = torch.device("cuda:0"), 32, [0, 1, 3, 7, 8]
-    shapes = [(1152, 4096), (1472, 8192), (960, 8192 - 64)]
+    shapes = [(1152, 4096), (1472, 8192), (960, 8192 - 64), (1472, 8192), (1472, 8192)]
     g = torch.Generator(device=dev)
     g.manual_seed(n)
     ctx = sb.Context(0, torch.cuda.current_stream().cuda_stream)
     plan = sb.Plan(ctx, shapes, m, n, bits)
     N = plan.num_blocks()
-    assert 40 << 20 < 2 * sum(r * c for r, c in shapes) <= 144 << 20
+    assert 72 << 20 < 2 * sum(r * c for r, c in shapes) <= 144 << 20 and all(2 * r * c <= 24 << 20 for r, c in shapes)
     ws = torch.empty(plan.workspace_bytes(), dtype=torch.uint8, device=dev)
     W = [torch.randn(r, c, generator=g, device=dev).to(torch.bfloat16) for r, c in shapes]
     level = torch.randint(0, len(bits), (N,), generator=g, device=dev).to(torch.uint8)
