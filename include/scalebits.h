@@ -245,7 +245,9 @@ int  sbits_cost_table_all(sbits_plan *plan, const void *w_re_bf16, const float *
  * "sramecc+", as every MI355X reports: the kernel relies on how 16-bit register
  * loads behave there); otherwise returns SBITS_ERR_UNIMPLEMENTED and writes
  * nothing: use the two calls above.  Rows of every length a plan allows are read
- * once (6 bytes per weight; beyond 16384 elements by kernels of their own).
+ * once (6 bytes per weight; beyond 16384 elements by kernels of their own); only a
+ * matrix of few such rows, the one of its width, is reordered into a copy inside
+ * the workspace first and scored from there, with the same bits in the table.
  * sbits_gather_cost_supported: 1 if the plan's shapes qualify (the device is
  * checked by the call itself), else 0.  Uses ws.                                  */
 int  sbits_gather_cost_supported(const sbits_plan *plan);

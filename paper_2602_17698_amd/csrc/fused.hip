@@ -426,7 +426,7 @@ using namespace sbits;
 // shapes the fused kernels take: 64- or 128-column blocks
 // The route is chosen per class of matrices with equal column count.  Rows of up to FU_MAX_COLS
 // elements are staged whole (weights and sensitivities) by gather_cost_kernel, wider ones (up to the plan's limit of 32768) by
-// gather_cost_wide_kernel (fused_wide.hip).  The surrogates take the first alone; the packing kernel stages weights only and
+// gather_cost_wide_kernel (fused_wide.hip) or, one matrix of few rows, by way of a reordered copy (few_wide_rows).  The surrogates take the first alone; the packing kernel stages weights only and
 // takes every row length.
 bool sbits_fused_shapes_ok(const sbits_plan *plan)
 {
@@ -445,10 +445,29 @@ static size_t octet_partial_bytes(const sbits_plan *plan)
     const size_t per_octet = (size_t)(plan->K > 2 ? plan->K : 2);     // the surrogates keep two sums per block
     return sbits_align_up((size_t)plan->N * (size_t)(plan->m / 8) * per_octet * 4, 256);
 }
-// octet partials: one float per (block, octet of the block, candidate)
+// One matrix of few wide rows, reordered into a copy in the workspace and scored there: eight rows of an octet one after the other, as
+// gather_cost_wide_kernel takes them, are 25 us and more however few workgroups there are, the passes over such a copy 24 to 44.  Copy /
+// one pass, 128-column blocks: 8 x 32768 at three candidates 28.9 us and 33.2, at nine 32.6 and 43.5; 128 x 32768 32.8 and 34.6, 36.5 and 43.8;
+// 224 x 16512 29.4 and 27.4, 33.2 and 36.0; 224 x 24576 36.4 and 30.4, 45.3 and 38.3.  64 columns: two candidates 8 x 28672 27.4 and 32.3 (128
+// columns 27.2 and 30.8, but 8 x 16512 25.0 and 25.6), nine 160 x 16512 38.4 and 36.6, 96 x 28672 40.3 and 44.3.  Two matrices of 8 x 16512: 41.2 and 29.4.
+static bool few_wide_rows(const sbits_plan *plan, const sbits_plan::FusedClass &fc)
+{
+    if (!sbits_fused_shapes_ok(plan) || fc.cols <= FU_MAX_COLS || fc.n != 1 || plan->K < (plan->n == 64 ? 2 : 3)) return false;
+    return plan->rows[plan->fused_members[fc.first]] * fc.cols <= (int64_t)4 << 20;
+}
+
+// octet partials: one float per (block, octet of the block, candidate); then room for the largest such copy (bf16, then fp32)
 size_t sbits_fused_ws_bytes(const sbits_plan *plan)
 {
-    return sbits_copies_shapes_ok(plan) || sbits_fused_shapes_ok(plan) ? octet_partial_bytes(plan) : 0;
+    if (!sbits_copies_shapes_ok(plan) && !sbits_fused_shapes_ok(plan)) return 0;
+    size_t copy = 0;
+    for (const sbits_plan::FusedClass &fc : plan->fused_classes) {
+        if (!few_wide_rows(plan, fc)) continue;
+        const size_t el = (size_t)plan->rows[plan->fused_members[fc.first]] * (size_t)fc.cols;
+        const size_t b = sbits_align_up(el * 2, 256) + sbits_align_up(el * 4, 256);
+        if (b > copy) copy = b;
+    }
+    return octet_partial_bytes(plan) + copy;
 }
 
 // The cost and surrogate kernels rely on 16-bit register-half loads filling the other half with
@@ -540,7 +559,7 @@ int sbits_launch_gather_cost_all(sbits_plan *plan, const int32_t *row_perm, cons
         a.total_wg = plan->fused_pre[fc.pre_first + fc.n];
         a.cols = fc.cols;
         a.opu = fc.opu;
-        if (a.total_wg == 0 || (copies && fc.cols > FU_MAX_COLS)) continue;
+        if (a.total_wg == 0 || (copies && fc.cols > FU_MAX_COLS) || few_wide_rows(plan, fc)) continue;
         const bool z0 = plan->bits[0] == 0;                     // a 0-bit candidate (the first of the list) has no grid
         sbits_fill_grid_consts(plan->bits + z0, plan->K - z0, &a.gc);
         a.kstride = plan->K;
@@ -556,19 +575,23 @@ int sbits_launch_gather_cost_all(sbits_plan *plan, const int32_t *row_perm, cons
                            a.part, a.descs, plan->n_mats, NK, plan->K, plan->m / 8, cost);
         SBITS_HIP(ctx, hipGetLastError());
     }
-    // 32- and 256-column blocks: matrices with rows too wide to stage are reordered first, then scored; their
+    // matrices with rows too wide to stage (32- and 256-column blocks), or few of them: reordered first, then scored; their
     // rows of the table are written after the tree kernel above (which found nothing of theirs in part[])
-    for (int i = 0; copies && i < plan->n_mats; ++i) {
-        if (plan->cols[i] <= FU_MAX_COLS) continue;
-        const MatDesc &d = plan->descs[i];
-        void *w_i = static_cast<uint16_t *>(w_re) + d.elem_off;
-        float *s_i = s_re + d.elem_off;
-        int rc = sbits_launch_gather(ctx, d.w, d.s, plan->rows[i], plan->cols[i], d.ld_w, d.ld_s, row_perm + d.row_off,
-                                     col_perm + d.col_off, w_i, s_i);
-        if (rc) return rc;
-        rc = sbits_launch_cost(ctx, w_i, s_i, plan->rows[i], plan->cols[i], plan->m, plan->n, plan->bits, plan->K,
-                               cost + d.block_base * plan->K);
-        if (rc) return rc;
+    char *const room = static_cast<char *>(sbits_scratch(plan, ws)) + octet_partial_bytes(plan);
+    for (const sbits_plan::FusedClass &fc : plan->fused_classes) {
+        if (copies ? fc.cols <= FU_MAX_COLS : !few_wide_rows(plan, fc)) continue;
+        for (int k = 0; k < fc.n; ++k) {
+            const int i = plan->fused_members[fc.first + k];
+            const MatDesc &d = plan->descs[i];
+            void *w_i = w_re ? static_cast<void *>(static_cast<uint16_t *>(w_re) + d.elem_off) : static_cast<void *>(room);
+            float *s_i = copies ? s_re + d.elem_off : reinterpret_cast<float *>(room + sbits_align_up((size_t)plan->rows[i] * (size_t)plan->cols[i] * 2, 256));
+            int rc = sbits_launch_gather(ctx, d.w, d.s, plan->rows[i], plan->cols[i], d.ld_w, d.ld_s, row_perm + d.row_off,
+                                         col_perm + d.col_off, w_i, s_i);
+            if (rc) return rc;
+            rc = sbits_launch_cost(ctx, w_i, s_i, plan->rows[i], plan->cols[i], plan->m, plan->n, plan->bits, plan->K,
+                                   cost + d.block_base * plan->K);
+            if (rc) return rc;
+        }
     }
     return SBITS_OK;
 }

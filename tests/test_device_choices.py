@@ -159,6 +159,34 @@ def test_packing_of_copies_keeps_weights_in_the_caches_where_they_fit(tmp_path):
         assert len(search) >= (n not in (64, 128)) and all(name % (n // 8, 0) in kernel for kernel in search), (n, mib, search)
 
 
+COST = r"""
+ctx = sb.Context(0, 0)
+out = []
+for shapes, n, bits in %r:
+    plan = sb.Plan(ctx, shapes, 8, n, bits)
+    mats = [sb.Matrix(fake(2 * r * c), fake(4 * r * c), r, c, c, c) for r, c in shapes]
+    a = [fake(1 << 24) for _ in range(4)]
+    log()
+    plan.gather_cost_all(mats, a[0], a[1], None, a[2], a[3])
+    out.append([[line.split()[1] for line in log() if line.startswith("launch")], plan.workspace_bytes()])
+    plan.close()
+answer(out)
+"""
+
+
+def test_cost_of_few_wide_rows_goes_by_a_copy(tmp_path):
+    """One matrix of its width with few rows beyond 16384 elements: reordered into the workspace, then scored; else in one pass."""
+    nine, five, three, two = list(range(9)), [1, 2, 3, 4, 8], [2, 3, 4], [2, 8]
+    cases = [([(8, 32768)], 128, three, 1), ([(128, 32768)], 64, three, 1), ([(136, 32768)], 128, three, 0), ([(128, 32768)], 128, five, 1),
+             ([(136, 32768)], 64, nine, 0), ([(248, 16512)], 128, nine, 1), ([(8, 16512)], 128, two, 0), ([(8, 16448)], 64, two, 1), ([(8, 20480), (8, 20480)], 64, three, 0),
+             ([(64, 4096), (8, 20480), (160, 25088)], 64, nine, 2), ([(64, 16384)], 64, nine, 0)]
+    for (shapes, n, bits, copies), (kernels, ws) in zip(cases, record(tmp_path, COST % ([c[:3] for c in cases],))):
+        assert sum("13gather_kernel" in k for k in kernels) == 2 * copies, (shapes, kernels)
+        assert sum("gather_cost_wide" in k for k in kernels) == len({c for _, c in shapes if c > 16384}) - copies, (shapes, kernels)
+        wide = [r * c for r, c in shapes if c > 16384]
+        assert ws > (6 * max(wide) if copies else 0), (shapes, ws)
+
+
 PRODUCTS = r"""
 class X:
     def __init__(self, batch, ld): self.shape, self.ld = (batch, ld), ld

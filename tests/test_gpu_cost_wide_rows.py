@@ -1,6 +1,7 @@
 """The cost table of rows wider than 16384 elements, whose weights and sensitivities share LDS and whose columns two or four workgroups share,
 bit for bit against the oracle: the narrowest and the widest row, rows with and without overlapping pieces, parts that end inside a lane group's chunks or
-have none at all, both numbers of parts, every number of candidates, the reordered weights as an output, and a pitch."""
+have none at all, both numbers of parts, every number of candidates, the reordered weights as an output, and a pitch; and a matrix of few such rows, by
+way of a copy in the workspace."""
 import numpy as np
 import pytest
 
@@ -14,16 +15,20 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("n,R,C,m,bits,pad", [
     (64, 64, 16448, 32, [3], 0),                            # four parts, the last one empty
-    (128, 64, 16512, 8, [1, 2, 3, 4, 5, 6, 7, 8], 0),
-    (64, 136, 26816, 8, [0, 2, 4], 8),                      # no overlapping piece, pitched
-    (128, 64, 27264, 64, [2, 3, 4], 0),                     # the first of them
-    (64, 64, 28608, 64, [0, 1, 2, 3, 4, 5, 6, 7, 8], 0),
-    (64, 72, 32768, 8, [0, 1, 2, 3, 4, 5, 6, 7, 8], 0),     # the most overlap
+    (128, 256, 16512, 8, [1, 2, 3, 4, 5, 6, 7, 8], 0),
+    (64, 160, 26816, 8, [0, 2, 4], 8),                      # no overlapping piece, pitched
+    (128, 192, 27264, 64, [2, 3, 4], 0),                    # the first of them
+    (64, 192, 28608, 64, [0, 1, 2, 3, 4, 5, 6, 7, 8], 0),
+    (64, 136, 32768, 8, [0, 1, 2, 3, 4, 5, 6, 7, 8], 0),    # the most overlap
     (128, 64, 32768, 16, [1, 8], 0),
     (128, 1160, 16640, 8, [2, 5], 0),                       # 145 units of one octet: two parts
     (64, 1096, 17344, 8, [0, 1, 2, 3, 4, 5, 6, 7, 8], 0),
     (128, 1040, 28672, 16, [1, 2, 3, 4, 5, 6], 0),
     (64, 1048, 24640, 8, [1, 2, 4, 8], 16),
+    (64, 8, 16448, 8, [2, 8], 8),                           # few rows: the copy
+    (128, 128, 32768, 32, [0, 1, 4], 0),
+    (128, 248, 16512, 8, [1, 2, 3, 4, 8], 16),
+    (64, 64, 28672, 64, [0, 1, 2, 3, 4, 5, 6, 7, 8], 0),
 ])
 def test_cost_of_wide_rows(orc, n, R, C, m, bits, pad):
     print("[case] cost of wide rows", n, R, C, bits, flush=True)

@@ -386,7 +386,7 @@ ONE_PASS_CASES = [
     ([(64, 8320), (192, 320)], 64, 64, [0, 2, 4]),
 ]
 
-# rows wider than the cost kernel stages (16384): those matrices go through a reordered copy in the
+# few rows wider than the cost kernel stages (16384): those matrices go through a reordered copy in the
 # workspace, the others of the same plan through the one-pass kernel; the packing kernel stages every row
 WIDE_ROW_CASES = [
     ([(64, 28672), (128, 4096), (64, 14336)], 64, 128, [2, 3, 4]),
