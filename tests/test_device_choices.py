@@ -1,4 +1,8 @@
 """Choices that the host makes by size and by device, on devices that need not be there."""
+import re
+
+import pytest
+
 from recording_runtime import record
 
 PACK = r"""
@@ -194,11 +198,11 @@ class X:
     def stride(self, i): return self.ld
 ctx = sb.Context(0, 0)
 out = []
-for R, C, m, n, bits, batch in %r:
-    plan = sb.Plan(ctx, [(R, C)], m, n, bits)
+for R, C, m, n, bits, batch, pad in %r:
+    plan = sb.Plan(ctx, [(m, n), (R, C)], m, n, bits)
     a = [fake(1 << 24) for _ in range(7)]
     log()
-    plan.mp_gemm(0, X(batch, C), *a)
+    plan.mp_gemm(1, X(batch, C + pad), *a)
     out.append([line.split()[1] for line in log() if line.startswith("launch")])
     plan.close()
 answer(out)
@@ -206,13 +210,28 @@ answer(out)
 
 
 def launched(tmp_path, products):
-    """The kernels of each product (R, C, m, n, bits, rows of x), by name."""
-    return record(tmp_path, PRODUCTS % (products,))
+    """The kernels of each product (R, C, m, n, bits, rows of x, pitch - C): "first", "narrow" or "many" and the instance."""
+    out = []
+    for kernels in record(tmp_path, PRODUCTS % (products,)):
+        names = [re.search(r"mp_gemm_(narrow_|many_|finish_)?kernel(?:I(\w+)E)?E", k) for k in kernels]
+        out.append(" ".join((m[1] or "first_")[:-1] + " " + ",".join(re.findall(r"L[ib](\d+)E", m[2] + "E")) for m in names if m[1] != "finish_"))
+    return out
 
 
 def test_wide_matrices_take_the_kernel_of_many_rows(tmp_path):
     """Shapes for which the estimates once favoured a kernel that is up to 1.23 times slower there."""
-    products = [(704, 22144, 64, 128, [3, 5, 6], 110), (2304, 25856, 128, 128, [2, 3, 4], 53), (6400, 22784, 128, 128, [4], 63),
-                (1536, 25088, 128, 128, [1, 2, 3, 4, 8], 98), (2304, 24832, 32, 128, [2, 3, 4], 61), (1088, 28160, 32, 128, [0, 1, 2, 3, 4], 115)]
+    products = [(704, 22144, 64, 128, [3, 5, 6], 110, 0), (2304, 25856, 128, 128, [2, 3, 4], 53, 0), (6400, 22784, 128, 128, [4], 63, 0),
+                (1536, 25088, 128, 128, [1, 2, 3, 4, 8], 98, 0), (2304, 24832, 32, 128, [2, 3, 4], 61, 0), (1088, 28160, 32, 128, [0, 1, 2, 3, 4], 115, 0)]
     for product, kernels in zip(products, launched(tmp_path, products)):
-        assert "mp_gemm_many_kernel" in kernels[0], (product, kernels)
+        assert kernels.startswith("many "), (product, kernels)
+
+
+def test_cases_of_the_products_run_the_kernels_that_they_are_meant_for(tmp_path):
+    """The tests of the products on the device, whose cases are chosen by kernel and instance: which one a product takes goes by estimates."""
+    pytest.importorskip("torch")
+    import test_gpu_mp_gemm_columns as columns
+    import test_gpu_mp_gemm_edges as edges
+    cases = edges.CASES + [case + (name,) for name, group in columns.CASES.items() for case in group]
+    for case, kernels in zip(cases, launched(tmp_path, [case[:7] for case in cases])):
+        assert kernels == case[7], case
+    assert len(columns.CASES) == 10                          # (all instances)

@@ -1,5 +1,5 @@
 """The products for up to 16 and for more than 32 batch rows at the edges of their work split: batch tiles and groups, row
-groups past the matrix's end, odd numbers of block columns, column splits, both workgroup shapes, every bitwidth with and
+groups past the matrix's end, odd numbers of block columns, column splits, workgroup shapes, every bitwidth with and
 without pruned blocks.  Tolerance: a kernel sums terms of size |B| scale |x| in fp32, where B scale is at most the span of
 the block row (2^c scale) and the offset that the codes carry (128 scale; 2^c scale for most bitwidths of the products for
 many rows), and zero |x|.  The bound is 2^-22 of the sum of all of them for the largest error and 2^-24 for the root mean
@@ -17,44 +17,54 @@ pytestmark = pytest.mark.gpu
 ALL = [1, 2, 3, 4, 5, 6, 7, 8]
 
 
-@pytest.mark.parametrize("R,C,m,n,bits,batch,pad", [
-    # up to 16 rows: fewer block columns than waves, one more than the waves, odd numbers of blocks a wave (the narrow kernel)
-    (32, 128, 32, 128, [3], 1, 0),
-    (96, 128 * 17, 32, 128, [0] + ALL, 3, 8),
-    (64, 128 * 35, 64, 128, ALL, 8, 0),
-    (96, 128 * 16, 32, 128, ALL, 9, 0),
-    (64, 128 * 48, 64, 128, [2, 5, 7], 16, 24),
-    (64, 64 * 33, 32, 64, [0] + ALL, 2, 0),
-    (160, 64 * 130, 32, 64, [1, 3, 6, 8], 16, 8),
-    (64, 128 * 80, 32, 128, [2, 4], 1, 0),                # 5 blocks a wave
-    (64, 64 * 144, 32, 64, [2, 4], 5, 0),                 # 9
-    (32, 128, 32, 128, [4], 33, 0),                       # one block; three of four row groups past the end
-    (160, 128 * 5, 32, 128, ALL, 48, 8),                  # odd block columns, three tiles, ragged row groups, wide pitch
-    (192, 128 * 8, 64, 128, [0] + ALL, 49, 0),            # pruned blocks, four tiles
-    (96, 64 * 9, 32, 64, ALL, 64, 16),
-    (128, 64 * 16, 64, 64, [0, 3, 5, 7, 8], 65, 0),       # a second batch group of one row
-    (256, 128 * 6, 128, 128, [2, 6], 113, 0),
-    (8192, 256, 128, 128, [1, 4, 8], 70, 0),              # 64 workgroups of 128 channels a batch group: half of the CUs, so 64 channels
-    (12288, 256, 128, 128, [3, 8], 128, 0),               # 192 in all: 128 channels
-    (12288, 192, 64, 64, ALL, 100, 0),
-    (64, 128 * 3, 32, 128, [2, 4, 8], 200, 0),            # a second launch
-    (32, 128, 32, 128, ALL[2:3], 40, 1 << 20),            # a pitch past 32-bit offsets of a batch group: 32 rows a launch, then 8
-    (64, 128 * 4, 32, 128, [1], 80, 0),                   # 1 bit: products of its own
-    (64, 64 * 5, 32, 64, [1], 50, 0),
-    (96, 128 * 10, 32, 128, ALL, 40, 0),                  # column splits: three of one step, 25 of four, six of an even number
-    (64, 64 * 400, 64, 64, [2, 5, 8], 64, 0),
-    (320, 128 * 46, 32, 128, [1, 3, 7], 90, 0),
-    (16512, 128 * 16, 128, 128, [2, 3], 70, 0),           # two batch groups would take turns: 64 rows, then 6 (first kernel)
-    (16512, 64 * 40, 128, 64, [3, 4], 81, 0),             # two groups at once all the same: 17 rows more by themselves cost as much
-    (16512, 64 * 12, 128, 64, [1], 70, 0),                # 64-column blocks: 64 rows, then 6 (first kernel)
-    (24704, 64 * 16, 128, 64, [1], 81, 0),                # 64, then 17
-    (8320, 128 * 32, 128, 128, [2, 3], 65, 0),            # 64, then one (narrow kernel)
-    (32, 128 * 49, 32, 128, [2, 6], 16, 0),               # 4 blocks a wave: the first kernel, four column splits
-    (32, 64 * 80, 32, 64, [1, 2], 16, 0),                 # five
-    (8320, 64 * 16, 128, 64, [1, 2], 7, 0),               # several turns, one split
-    (12288, 128 * 16, 128, 128, [2, 6], 16, 0),           # few rows, several turns: the first kernel, then the narrow one
-    (8224, 128 * 3, 32, 128, [4, 8], 7, 0),
-])
+# A product, and the kernels that it runs on a whole device: "first", "narrow" or "many", and the instance (columns of a block and, of the
+# first, batch tiles, row groups, small offset; narrow, waves, small offset, x by way of LDS; many, see the test of its instances).
+CASES = [
+    # up to 16 rows: fewer block columns than waves, one more than the waves, odd numbers of blocks a wave
+    (32, 128, 32, 128, [3], 1, 0, "narrow 128,16,0,0"),
+    (96, 128 * 17, 32, 128, [0] + ALL, 3, 8, "narrow 128,16,0,0"),
+    (64, 128 * 35, 64, 128, ALL, 8, 0, "narrow 128,16,0,1"),
+    (96, 128 * 16, 32, 128, ALL, 9, 0, "narrow 128,16,0,1"),
+    (64, 128 * 48, 64, 128, [2, 5, 7], 16, 24, "first 128,1,1,0"),
+    (64, 64 * 33, 32, 64, [0] + ALL, 2, 0, "narrow 64,16,0,0"),
+    (160, 64 * 130, 32, 64, [1, 3, 6, 8], 16, 8, "first 64,1,1,0"),
+    (64, 128 * 80, 32, 128, [2, 4], 1, 0, "first 128,1,1,0"),         # 5 blocks a wave
+    (64, 64 * 144, 32, 64, [2, 4], 5, 0, "first 64,1,1,0"),           # 9
+    # more: few block columns and rows
+    (32, 128, 32, 128, [4], 33, 0, "narrow 128,16,1,1"),              # one block, three groups of rows, the last of one
+    (160, 128 * 5, 32, 128, ALL, 48, 8, "narrow 128,16,1,1"),
+    (192, 128 * 8, 64, 128, [0] + ALL, 49, 0, "narrow 128,16,1,1"),   # four groups
+    (96, 64 * 9, 32, 64, ALL, 64, 16, "narrow 64,16,1,1"),
+    (64, 64 * 5, 32, 64, [1], 50, 0, "narrow 64,16,1,1"),
+    (96, 128 * 10, 32, 128, ALL, 40, 0, "narrow 128,16,1,1"),
+    (32, 128, 32, 128, ALL[2:3], 40, 1 << 20, "narrow 128,16,1,1 narrow 128,16,1,1"),     # a pitch past 32-bit offsets of a batch group: 32 rows a launch, then 8
+    # many rows: a last group of one row; one with a ragged last tile; 1 bit; column splits
+    (128, 64 * 16, 64, 64, [0, 3, 5, 7, 8], 65, 0, "many 64,2,2,8"),
+    (256, 128 * 6, 128, 128, [2, 6], 113, 0, "many 128,2,2,8"),
+    (8192, 256, 128, 128, [1, 4, 8], 70, 0, "many 128,3,4,4"),
+    (12288, 256, 128, 128, [3, 8], 128, 0, "many 128,4,4,4"),
+    (12288, 192, 64, 64, ALL, 100, 0, "many 64,4,4,4"),
+    (64, 128 * 3, 32, 128, [2, 4, 8], 200, 0, "many 128,2,2,8 many 128,2,2,8"),           # a second launch
+    (64, 128 * 4, 32, 128, [1], 80, 0, "many 128,2,2,8"),
+    (64, 64 * 400, 64, 64, [2, 5, 8], 64, 0, "many 64,2,2,8"),
+    (320, 128 * 46, 32, 128, [1, 3, 7], 90, 0, "many 128,2,2,8"),
+    (16512, 128 * 16, 128, 128, [2, 3], 70, 0, "many 128,2,2,8"),
+    (16512, 64 * 40, 128, 64, [3, 4], 81, 0, "many 64,3,2,8"),
+    (8320, 128 * 32, 128, 128, [2, 3], 65, 0, "many 128,2,2,8"),
+    # 64 rows, and the rest by the kernels for few
+    (16512, 64 * 12, 128, 64, [1], 70, 0, "many 64,4,4,4 first 64,1,1,1"),
+    (24704, 64 * 16, 128, 64, [1], 81, 0, "many 64,4,4,4 first 64,2,2,1"),
+    (16416, 128 * 9, 32, 128, [1, 4, 8], 66, 0, "many 128,4,4,4 narrow 128,8,1,1"),
+    # up to 16 rows: column splits, several turns
+    (32, 128 * 49, 32, 128, [2, 6], 16, 0, "first 128,1,1,0"),        # 4 blocks a wave, four column splits
+    (32, 64 * 80, 32, 64, [1, 2], 16, 0, "first 64,1,1,0"),           # five
+    (8320, 64 * 16, 128, 64, [1, 2], 7, 0, "narrow 64,8,0,1"),
+    (12288, 128 * 16, 128, 128, [2, 6], 16, 0, "narrow 128,8,0,1"),
+    (8224, 128 * 3, 32, 128, [4, 8], 7, 0, "narrow 128,8,0,1"),
+]
+
+
+@pytest.mark.parametrize("R,C,m,n,bits,batch,pad", [case[:7] for case in CASES])
 def test_product_edges(orc, R, C, m, n, bits, batch, pad):
     print("[case] product", R, C, m, n, bits, batch, flush=True)
     dev = torch.device("cuda:0")
