@@ -5,7 +5,8 @@
 // the grid, so that they share an L2 and walk the same rows at the same time.  A row passes through LDS in two overlapping
 // halves of a step:
 //   pieces (1 KiB)   sensitivities 0 .. nS, weights w0 .. w0 + nW with w0 = nS - O: the last O pieces of the sensitivities and the first O of
-//                    the weights have the same place, O as small as the room allows (none up to 27000 elements, a dozen for 28672)
+//                    the weights have the same place, O as small as the room beside the octet sums allows (none up to 26880 elements at
+//                    one candidate, up to 25600 at nine in 64-column blocks and two parts; a dozen for 28672, 34 to 42 for 32768)
 //   weights out of LDS | barrier | request the O late pieces of the sensitivities | minimum, range, divisions, x = w - min
 //   | wait, barrier | request the next row's weights but the first O | sensitivities out of LDS | barrier | request the next
 //   row's sensitivities but the last O, and its first O weights | candidates, sums | wait, barrier

@@ -166,13 +166,14 @@ def test_packing_of_copies_keeps_weights_in_the_caches_where_they_fit(tmp_path):
 COST = r"""
 ctx = sb.Context(0, 0)
 out = []
-for shapes, n, bits in %r:
-    plan = sb.Plan(ctx, shapes, 8, n, bits)
+for shapes, n, bits, m in %r:
+    plan = sb.Plan(ctx, shapes, m, n, bits)
     mats = [sb.Matrix(fake(2 * r * c), fake(4 * r * c), r, c, c, c) for r, c in shapes]
     a = [fake(1 << 24) for _ in range(4)]
     log()
     plan.gather_cost_all(mats, a[0], a[1], None, a[2], a[3])
-    out.append([[line.split()[1] for line in log() if line.startswith("launch")], plan.workspace_bytes()])
+    launches = [line.split()[1:] for line in log() if line.startswith("launch")]
+    out.append([[v[0] for v in launches], plan.workspace_bytes(), [[int(v[2].split(",")[0]), int(v[4]), int(v[6])] for v in launches if "gather_cost_wide" in v[0]]])
     plan.close()
 answer(out)
 """
@@ -184,11 +185,24 @@ def test_cost_of_few_wide_rows_goes_by_a_copy(tmp_path):
     cases = [([(8, 32768)], 128, three, 1), ([(128, 32768)], 64, three, 1), ([(136, 32768)], 128, three, 0), ([(128, 32768)], 128, five, 1),
              ([(136, 32768)], 64, nine, 0), ([(248, 16512)], 128, nine, 1), ([(8, 16512)], 128, two, 0), ([(8, 16448)], 64, two, 1), ([(8, 20480), (8, 20480)], 64, three, 0),
              ([(64, 4096), (8, 20480), (160, 25088)], 64, nine, 2), ([(64, 16384)], 64, nine, 0)]
-    for (shapes, n, bits, copies), (kernels, ws) in zip(cases, record(tmp_path, COST % ([c[:3] for c in cases],))):
+    for (shapes, n, bits, copies), (kernels, ws, _) in zip(cases, record(tmp_path, COST % ([c[:3] + (8,) for c in cases],))):
         assert sum("13gather_kernel" in k for k in kernels) == 2 * copies, (shapes, kernels)
         assert sum("gather_cost_wide" in k for k in kernels) == len({c for _, c in shapes if c > 16384}) - copies, (shapes, kernels)
         wide = [r * c for r, c in shapes if c > 16384]
         assert ws > (6 * max(wide) if copies else 0), (shapes, ws)
+
+
+def test_cases_of_wide_rows_have_the_parts_and_the_overlap_that_they_are_meant_for(tmp_path):
+    """The tests of the cost of wide rows on the device, against the grid and the LDS of their launches."""
+    pytest.importorskip("torch")
+    import test_gpu_cost_wide_rows as wide
+    seen = record(tmp_path, COST % ([([(R, C)], n, bits, m) for n, R, C, m, bits, *_ in wide.CASES],))
+    for (n, R, C, m, bits, pad, parts, overlap), (_, _, launches) in zip(wide.CASES, seen):
+        assert len(launches) == (parts > 0), (n, R, C)
+        for grid, threads, lds in launches:
+            sums = 4 // parts * threads // (n // 8) * len(bits) * 4
+            assert grid == -(-R // 64) * 8 * parts, (n, R, C, grid)          # (an octet a workgroup, eight apart)
+            assert -(-2 * C // 1024) - -(4 * C) // 1024 - (lds - sums) // 1024 == overlap, (n, R, C, lds)
 
 
 PRODUCTS = r"""

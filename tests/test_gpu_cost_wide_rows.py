@@ -13,23 +13,32 @@ from paper_2602_17698_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n,R,C,m,bits,pad", [
-    (64, 64, 16448, 32, [3], 0),                            # four parts, the last one empty
-    (128, 256, 16512, 8, [1, 2, 3, 4, 5, 6, 7, 8], 0),
-    (64, 160, 26816, 8, [0, 2, 4], 8),                      # no overlapping piece, pitched
-    (128, 192, 27264, 64, [2, 3, 4], 0),                    # the first of them
-    (64, 192, 28608, 64, [0, 1, 2, 3, 4, 5, 6, 7, 8], 0),
-    (64, 136, 32768, 8, [0, 1, 2, 3, 4, 5, 6, 7, 8], 0),    # the most overlap
-    (128, 64, 32768, 16, [1, 8], 0),
-    (128, 1160, 16640, 8, [2, 5], 0),                       # 145 units of one octet: two parts
-    (64, 1096, 17344, 8, [0, 1, 2, 3, 4, 5, 6, 7, 8], 0),
-    (128, 1040, 28672, 16, [1, 2, 3, 4, 5, 6], 0),
-    (64, 1048, 24640, 8, [1, 2, 4, 8], 16),
-    (64, 8, 16448, 8, [2, 8], 8),                           # few rows: the copy
-    (128, 128, 32768, 32, [0, 1, 4], 0),
-    (128, 248, 16512, 8, [1, 2, 3, 4, 8], 16),
-    (64, 64, 28672, 64, [0, 1, 2, 3, 4, 5, 6, 7, 8], 0),
-])
+# n, R, C, m, bits, pad; workgroups that share a row (0: a copy in the workspace), and 1 KiB pieces of sensitivities and weights with the same place
+CASES = [
+    (64, 64, 16448, 32, [3], 0, 4, 0),                      # four parts, the last one empty
+    (128, 256, 16512, 8, [1, 2, 3, 4, 5, 6, 7, 8], 0, 4, 0),
+    (64, 160, 26624, 8, [0, 2, 4], 8, 4, 0),                # the last row without overlap, pitched
+    (64, 160, 26688, 8, [0, 2, 4], 0, 4, 1),                # and the first with it
+    (64, 160, 26816, 8, [0, 2, 4], 8, 4, 1),
+    (128, 192, 27264, 64, [2, 3, 4], 0, 4, 3),
+    (64, 192, 28608, 64, [0, 1, 2, 3, 4, 5, 6, 7, 8], 0, 4, 14),
+    (64, 136, 32768, 8, [0, 1, 2, 3, 4, 5, 6, 7, 8], 0, 4, 38),
+    (128, 64, 32768, 16, [1, 8], 0, 4, 34),
+    (128, 1160, 16640, 8, [2, 5], 0, 2, 0),                 # 145 units of one octet
+    (64, 1096, 17344, 8, [0, 1, 2, 3, 4, 5, 6, 7, 8], 0, 2, 0),
+    (64, 520, 25600, 8, [0, 1, 2, 3, 4, 5, 6, 7, 8], 0, 2, 0),     # 65 units; the last row without overlap
+    (64, 520, 25664, 8, [0, 1, 2, 3, 4, 5, 6, 7, 8], 8, 2, 2),
+    (128, 1040, 28672, 16, [1, 2, 3, 4, 5, 6], 0, 2, 12),
+    (64, 1048, 24640, 8, [1, 2, 4, 8], 16, 2, 0),
+    (64, 520, 32768, 8, [0, 1, 2, 3, 4, 5, 6, 7, 8], 0, 2, 42),    # the most overlap
+    (64, 8, 16448, 8, [2, 8], 8, 0, 0),                     # few rows
+    (128, 128, 32768, 32, [0, 1, 4], 0, 0, 0),
+    (128, 248, 16512, 8, [1, 2, 3, 4, 8], 16, 0, 0),
+    (64, 64, 28672, 64, [0, 1, 2, 3, 4, 5, 6, 7, 8], 0, 0, 0),
+]
+
+
+@pytest.mark.parametrize("n,R,C,m,bits,pad", [case[:6] for case in CASES])
 def test_cost_of_wide_rows(orc, n, R, C, m, bits, pad):
     print("[case] cost of wide rows", n, R, C, bits, flush=True)
     dev = torch.device("cuda:0")
