@@ -695,7 +695,7 @@ __device__ __forceinline__ void many_tile(const uint32_t (&cw)[N_COLS / 16], flo
         for (int r = 0; r < 4; ++r) acc[nb][r] = fmaf(f, d[nb][r], fmaf(z, s[nb][r], acc[nb][r]));
 }
 
-// Two tiles at 1 bit: 128 + q and columns in the order of the kernel for up to 32 rows (pair order for 128 columns), with sums of x of
+// Two tiles at 1 bit, unless ONE_BIT_FINE (an instance of its own: a choice in the kernel cost the other widths 3 .. 5 %): 128 + q and columns in the order of the kernel for up to 32 rows (pair order for 128 columns), with sums of x of
 // their own.  What a row of x gives then differs little between that kernel and this one (14336 x 4096, bitwidths 1 .. 8: by 1.3e-4 of the root
 // mean square at most, 4.3e-4 with 1 + q / 2 here), but both are 1e-5 from the exact product, by the norm, where 1 + q / 2 would be 3e-7: see
 // one_bit_line.
@@ -795,7 +795,7 @@ __device__ __forceinline__ void read_block(uint32_t at, uint32_t meta_at, u32x4_
                      : "v"(at), "v"(meta_at) : "memory");
 }
 
-template <int N_COLS, int NB, int CT, int WAVES>
+template <int N_COLS, int NB, int CT, int WAVES, bool ONE_BIT_FINE>
 __global__ __launch_bounds__((64 * WAVES), 2)
 void mp_gemm_many_kernel(MpArgs a, int cols_per_split)
 {
@@ -931,7 +931,7 @@ void mp_gemm_many_kernel(MpArgs a, int cols_per_split)
                     align_quarter<N_COLS>(cq[2 * h + tl], N_COLS == 128 ? 0 : __umul24(units(h) + (uint32_t)(tl * 16 * (N_COLS / 8)), (uint32_t)cb[h]), cw[tl]);
 #define MB_TILE(C)                                                                                                \
     do {                                                                                                          \
-        if constexpr (C == 1) {                                                                                   \
+        if constexpr (C == 1 && !ONE_BIT_FINE) {                                                                  \
             many_tiles_1bit<N_COLS, NB>(cw, sc + 2 * h, ze + 2 * h, x, acc[2 * h], acc[2 * h + 1]);               \
         } else {                                                                                                  \
             many_tile<C, N_COLS, NB>(cw[0], sc[2 * h], ze[2 * h], x, s, acc[2 * h]);                              \
@@ -1086,12 +1086,12 @@ static int launch_narrow(sbits_ctx *ctx, const MpArgs &a)
     return SBITS_OK;
 }
 
-template <int N_COLS, int NB, int CT, int WAVES>
+template <int N_COLS, int NB, int CT, int WAVES, bool FINE>
 static int launch_many(sbits_ctx *ctx, const MpArgs &a, const ManySplit &ms)
 {
     constexpr size_t x = (size_t)WAVES * NB * 16 * N_COLS * 2 / 1024 * 1040, red = (size_t)WAVES * CT * NB * 1024;
     constexpr size_t all = x + (size_t)(32768 / N_COLS) * 16, lds = all > red ? all : red;      // (and the waves' tables of their blocks)
-    auto *fn = &mp_gemm_many_kernel<N_COLS, NB, CT, WAVES>;
+    auto *fn = &mp_gemm_many_kernel<N_COLS, NB, CT, WAVES, FINE>;
     SBITS_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     const dim3 grid((unsigned)((a.R + CT * 16 - 1) / (CT * 16)), (unsigned)ms.n_split, (unsigned)((a.batch + NB * 16 - 1) / (NB * 16)));
     hipLaunchKernelGGL(fn, grid, dim3(64 * WAVES), lds, ctx->stream, a, ms.per_split);
@@ -1099,15 +1099,15 @@ static int launch_many(sbits_ctx *ctx, const MpArgs &a, const ManySplit &ms)
     return SBITS_OK;
 }
 
-template <int N_COLS>
+template <int N_COLS, bool FINE>
 static int launch_many_shape(sbits_ctx *ctx, const MpArgs &a, const ManySplit &ms)      // (the order of MANY_128 and MANY_64)
 {
     switch (ms.shape) {
-    case 0: return launch_many<N_COLS, 2, 2, 8>(ctx, a, ms);
-    case 1: return launch_many<N_COLS, 3, 2, 8>(ctx, a, ms);
-    case 2: return launch_many<N_COLS, 3, 4, 4>(ctx, a, ms);
-    case 3: return launch_many<N_COLS, 4, 4, 4>(ctx, a, ms);
-    default: return launch_many<N_COLS, 4, 4, 8>(ctx, a, ms);
+    case 0: return launch_many<N_COLS, 2, 2, 8, FINE>(ctx, a, ms);
+    case 1: return launch_many<N_COLS, 3, 2, 8, FINE>(ctx, a, ms);
+    case 2: return launch_many<N_COLS, 3, 4, 4, FINE>(ctx, a, ms);
+    case 3: return launch_many<N_COLS, 4, 4, 4, FINE>(ctx, a, ms);
+    default: return launch_many<N_COLS, 4, 4, 8, FINE>(ctx, a, ms);
     }
 }
 
@@ -1166,7 +1166,8 @@ static FewRows few_rows(const sbits_plan *plan, int64_t R, int nbc, int batch)
 
 // Up to 16 block columns and two turns of the narrow kernel, where both take hardly more than a launch, it is the better one (up to
 // 16 rows by 3 .. 8 % on average and at most 3 % slower, up to 32 by 5 .. 26 %).
-// Above 32 rows: against the kernel of many rows, or one_bit_line.
+// Above 32 rows: against the kernel of many rows, where codes of 1 bit have the offset that they have here on this side of one_bit_line (6368 x 2624
+// at 33 rows, 1 .. 4 bits, 15.3 us here and 8.9 there: the line alone had them here); on the other side that kernel takes them all.
 // A pitch of x past the 32-bit offsets of the narrow kernel: the first.
 static bool has_one_bit(const sbits_plan *plan)
 {
@@ -1175,13 +1176,12 @@ static bool has_one_bit(const sbits_plan *plan)
     return false;
 }
 
-// Where codes of 1 bit enter as 1 + q / 2 (the kernels of few rows) and where as 128 + q (that of many) is part of what a product of 33
-// .. 96 rows gives: by the norm it is 3e-7 from the exact one, or 1e-5; in single values the two differ by up to 3e-4 of the root mean square, with
-// outlier channels by up to 4e-3.  The line goes by the time, in hundredths of a microsecond above the launch, that such a product took in the
-// predecessor of the kernel of many rows: 8 waves, 128 or 64 channels and 4 or 2 block columns a step, two steps at a time, up to 64 rows a
-// workgroup; a turn of the CUs costs 3 us and 1.65 or, in 64-column blocks, 1.25 a step.  By the kernel that there is now it would lie lower, and a
-// quarter of the products of 33 .. 64 rows be 1.2 times as fast and 30 times less exact.  (With 1 + q / 2 in both, 150 drawn products of 33 .. 128 rows
-// take 0.94 of the time and no line is needed; but 31 of them, with outliers, give values 4e-4 .. 4e-3 of the root mean square from those of now.)
+// Where codes of 1 bit enter as 1 + q / 2 and where as 128 + q is part of what a product of 33 .. 96 rows gives: by the norm it is 3e-7 from the
+// exact one, or 1e-5; in single values the two differ by up to 3e-4 of the root mean square, with outlier channels by up to 4e-3.  So this line
+// stays where it was drawn, when 128 + q was all that the kernel of many rows had: by the time, in hundredths of a microsecond above the launch, that
+// a product took in that kernel's predecessor: 8 waves, 128 or 64 channels and 4 or 2 block columns a step, two steps at a time, up to 64 rows a
+// workgroup; a turn of the CUs costs 3 us and 1.65 or, in 64-column blocks, 1.25 a step.  (1 + q / 2 for all: 150 drawn products of 33 .. 128 rows
+// take 0.94 of the time, but 31 of them, with outliers, give values 4e-4 .. 4e-3 of the root mean square from those of now.)
 static int64_t one_bit_line(int64_t R, int nbc, int n, int batch)
 {
     const int64_t z = (batch + 63) / 64;
@@ -1203,14 +1203,18 @@ static int64_t one_bit_line(int64_t R, int nbc, int n, int batch)
     const int64_t a = with(4), b = with(2);
     return a < b ? a : b;
 }
+// of a launch of 33 .. 64 rows: by the line, whichever kernel then takes it
+static bool fine_one_bit(const sbits_plan *plan, int64_t R, int nbc, int batch)
+{
+    return has_one_bit(plan) && few_rows(plan, R, nbc, batch).narrow * 100 < (double)(one_bit_line(R, nbc, plan->n, batch) + 250);
+}
 static bool takes_narrow(const sbits_plan *plan, int mat, const MpArgs &a)
 {
     if (a.batch > 64 || a.ld_x > 1 << 25) return false;
     if (a.batch <= 32 && a.nbc <= MG_SPAN && a.R / 32 * ((a.batch + 15) / 16) <= 512) return true;
     const FewRows t = few_rows(plan, a.R, a.nbc, a.batch);
     if (a.batch <= 32) return t.narrow <= t.first;
-    if (has_one_bit(plan)) return t.narrow * 100 < (double)(one_bit_line(a.R, a.nbc, plan->n, a.batch) + 250);
-    return t.narrow <= many_of(plan, mat, a.batch).us;
+    return t.narrow <= many_of(plan, mat, a.batch).us && (!has_one_bit(plan) || fine_one_bit(plan, a.R, a.nbc, a.batch));
 }
 
 // Rows of x the next launch takes of those that are left: 128 (two batch groups) while a group's byte offsets fit the 32 bits
@@ -1234,7 +1238,7 @@ int sbits_mp_gemm_rows(const sbits_plan *plan, int mat, int64_t ld_x, int left)
     return left < 128 ? left : 128;
 }
 
-// fine: rows of a product of more than 32, whose codes enter with the smaller offset in every kernel (1 bit not in that of many rows)
+// fine: rows of a product of more than 32, whose codes enter with the smaller offset in every kernel (1 bit in that of many rows by one_bit_line)
 int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t ld_x, int batch, bool fine,
                          const uint8_t *level, const int64_t *byte_off, const uint8_t *codes, const float *scale,
                          const float *zero, float *y, void *scratch)
@@ -1247,6 +1251,7 @@ int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t 
     a.R = (int)plan->rows[mat]; a.C = (int)plan->cols[mat]; a.m = plan->m; a.nbc = a.C / plan->n;
     a.batch = batch;
     for (int c = 0; c < sbits::MAX_CAND; ++c) a.bits[c] = c < plan->K ? plan->bits[c] : plan->bits[plan->K - 1];
+    const bool one_bit = batch > 32 && batch <= 64 && fine_one_bit(plan, a.R, a.nbc, batch);
     if (takes_narrow(plan, mat, a)) {
         a.n_split = 1;
         a.out = y;
@@ -1272,7 +1277,8 @@ int sbits_launch_mp_gemm(sbits_plan *plan, int mat, const void *x_bf16, int64_t 
     a.out = a.n_split > 1 ? static_cast<float *>(scratch) : y;
     int rc;
     if (many) {
-        rc = plan->n == 128 ? launch_many_shape<128>(ctx, a, ms) : launch_many_shape<64>(ctx, a, ms);
+        if (one_bit) rc = plan->n == 128 ? launch_many_shape<128, true>(ctx, a, ms) : launch_many_shape<64, true>(ctx, a, ms);
+        else rc = plan->n == 128 ? launch_many_shape<128, false>(ctx, a, ms) : launch_many_shape<64, false>(ctx, a, ms);
     } else {
         // Channels of a workgroup: x takes 32 .. 128 KiB of LDS, and as many waves as the registers allow (16) should be on a
         // CU.  64-column blocks up to 16 rows: four workgroups of 32 channels.  Else 64 (128 with 128 KiB of x), and half as

@@ -19,12 +19,12 @@ def listing():
 
 
 def test_the_loads_behind_the_x_of_a_block_are_as_many_as_its_wait_counts(listing):
-    assert build.check_block_waits(listing) == 10
+    assert build.check_block_waits(listing) == 20
 
 
 @pytest.mark.parametrize("change", ["merged", "more", "other wait"])
 def test_a_block_with_other_loads_is_refused(listing, change):
-    at = listing.index("mp_gemm_many_kernelILi128ELi4ELi4ELi8E")
+    at = listing.index("mp_gemm_many_kernelILi128ELi4ELi4ELi8ELb0E")
     wait = re.compile(r"s_waitcnt vmcnt\(16\)\s[^\n]*\n(?:(?!s_barrier|s_cbranch)[^\n]*\n){0,16}?\s*ds_read_b128").search(listing, at)
     scale = re.compile(r"\n[^\n]*global_load_dword v[^\n]*").search(listing, wait.end())
     if change == "merged":                                  # two scales in one load

@@ -240,6 +240,14 @@ def test_wide_matrices_take_the_kernel_of_many_rows(tmp_path):
         assert kernels.startswith("many "), (product, kernels)
 
 
+def test_products_with_codes_of_1_bit_take_the_faster_kernel(tmp_path):
+    """33 to 64 rows whose codes of 1 bit enter as 1 + q / 2: in the narrow kernel or in that of many rows, by their times; 128 + q stays in the latter."""
+    products = [(19968, 8576, 64, 64, [1, 2, 3, 4], 42, 0), (6368, 2624, 32, 64, [1, 2, 3, 4], 33, 0), (1984, 14336, 32, 128, [1, 2, 3, 4], 44, 0),
+                (96, 640, 32, 64, [1, 4], 40, 0), (14304, 4032, 32, 64, [0, 1, 2, 3, 4], 62, 0), (14304, 4032, 32, 64, [0, 2, 3, 4], 62, 0)]
+    kinds = [k.split(" ")[0] + k[-1] for k in launched(tmp_path, products)]
+    assert kinds == ["many1", "many1", "many1", "narrow1", "many0", "many0"]
+
+
 def test_cases_of_the_products_run_the_kernels_that_they_are_meant_for(tmp_path):
     """The tests of the products on the device, whose cases are chosen by kernel and instance: which one a product takes goes by estimates."""
     pytest.importorskip("torch")
@@ -248,4 +256,4 @@ def test_cases_of_the_products_run_the_kernels_that_they_are_meant_for(tmp_path)
     cases = edges.CASES + [case + (name,) for name, group in columns.CASES.items() for case in group]
     for case, kernels in zip(cases, launched(tmp_path, [case[:7] for case in cases])):
         assert kernels == case[7], case
-    assert len(columns.CASES) == 10                          # (all instances)
+    assert len(columns.CASES) == 20                          # (all instances)

@@ -39,22 +39,22 @@ CASES = [
     (96, 128 * 10, 32, 128, ALL, 40, 0, "narrow 128,16,1,1"),
     (32, 128, 32, 128, ALL[2:3], 40, 1 << 20, "narrow 128,16,1,1 narrow 128,16,1,1"),     # a pitch past 32-bit offsets of a batch group: 32 rows a launch, then 8
     # many rows: a last group of one row; one with a ragged last tile; 1 bit; column splits
-    (128, 64 * 16, 64, 64, [0, 3, 5, 7, 8], 65, 0, "many 64,2,2,8"),
-    (256, 128 * 6, 128, 128, [2, 6], 113, 0, "many 128,2,2,8"),
-    (8192, 256, 128, 128, [1, 4, 8], 70, 0, "many 128,3,4,4"),
-    (12288, 256, 128, 128, [3, 8], 128, 0, "many 128,4,4,4"),
-    (12288, 192, 64, 64, ALL, 100, 0, "many 64,4,4,4"),
-    (64, 128 * 3, 32, 128, [2, 4, 8], 200, 0, "many 128,2,2,8 many 128,2,2,8"),           # a second launch
-    (64, 128 * 4, 32, 128, [1], 80, 0, "many 128,2,2,8"),
-    (64, 64 * 400, 64, 64, [2, 5, 8], 64, 0, "many 64,2,2,8"),
-    (320, 128 * 46, 32, 128, [1, 3, 7], 90, 0, "many 128,2,2,8"),
-    (16512, 128 * 16, 128, 128, [2, 3], 70, 0, "many 128,2,2,8"),
-    (16512, 64 * 40, 128, 64, [3, 4], 81, 0, "many 64,3,2,8"),
-    (8320, 128 * 32, 128, 128, [2, 3], 65, 0, "many 128,2,2,8"),
+    (128, 64 * 16, 64, 64, [0, 3, 5, 7, 8], 65, 0, "many 64,2,2,8,0"),
+    (256, 128 * 6, 128, 128, [2, 6], 113, 0, "many 128,2,2,8,0"),
+    (8192, 256, 128, 128, [1, 4, 8], 70, 0, "many 128,3,4,4,0"),
+    (12288, 256, 128, 128, [3, 8], 128, 0, "many 128,4,4,4,0"),
+    (12288, 192, 64, 64, ALL, 100, 0, "many 64,4,4,4,0"),
+    (64, 128 * 3, 32, 128, [2, 4, 8], 200, 0, "many 128,2,2,8,0 many 128,2,2,8,0"),           # a second launch
+    (64, 128 * 4, 32, 128, [1], 80, 0, "many 128,2,2,8,0"),
+    (64, 64 * 400, 64, 64, [2, 5, 8], 64, 0, "many 64,2,2,8,0"),
+    (320, 128 * 46, 32, 128, [1, 3, 7], 90, 0, "many 128,2,2,8,0"),
+    (16512, 128 * 16, 128, 128, [2, 3], 70, 0, "many 128,2,2,8,0"),
+    (16512, 64 * 40, 128, 64, [3, 4], 81, 0, "many 64,3,2,8,0"),
+    (8320, 128 * 32, 128, 128, [2, 3], 65, 0, "many 128,2,2,8,0"),
     # 64 rows, and the rest by the kernels for few
-    (16512, 64 * 12, 128, 64, [1], 70, 0, "many 64,4,4,4 first 64,1,1,1"),
-    (24704, 64 * 16, 128, 64, [1], 81, 0, "many 64,4,4,4 first 64,2,2,1"),
-    (16416, 128 * 9, 32, 128, [1, 4, 8], 66, 0, "many 128,4,4,4 narrow 128,8,1,1"),
+    (16512, 64 * 12, 128, 64, [1], 70, 0, "many 64,4,4,4,0 first 64,1,1,1"),
+    (24704, 64 * 16, 128, 64, [1], 81, 0, "many 64,4,4,4,0 first 64,2,2,1"),
+    (16416, 128 * 9, 32, 128, [1, 4, 8], 66, 0, "many 128,4,4,4,0 narrow 128,8,1,1"),
     # up to 16 rows: column splits, several turns
     (32, 128 * 49, 32, 128, [2, 6], 16, 0, "first 128,1,1,0"),        # 4 blocks a wave, four column splits
     (32, 64 * 80, 32, 64, [1, 2], 16, 0, "first 64,1,1,0"),           # five
@@ -65,7 +65,7 @@ CASES = [
 
 
 @pytest.mark.parametrize("R,C,m,n,bits,batch,pad", [case[:7] for case in CASES])
-def test_product_edges(orc, R, C, m, n, bits, batch, pad):
+def test_product_edges(orc, R, C, m, n, bits, batch, pad, one_bit=128):
     print("[case] product", R, C, m, n, bits, batch, flush=True)
     dev = torch.device("cuda:0")
     rng = np.random.default_rng(R + C + batch)
@@ -93,7 +93,7 @@ def test_product_edges(orc, R, C, m, n, bits, batch, pad):
     xf = orc.bf16_to_f32(xb).astype(np.float64)
     ref = xf @ What.T
     nbc = C // n
-    offset = {1: 128, 6: 128, 7: 128} if batch > 32 else {b: 128 for b in range(1, 8)}
+    offset = {1: one_bit, 6: 128, 7: 128} if batch > 32 else {b: 128 for b in range(1, 8)}
     most = np.array([2.0 ** b + offset.get(b, 2.0 ** b) for b in bits])      # of |B|, in codes
     mag = (np.abs(zero.reshape(N, m)) + scale.reshape(N, m) * most[level][:, None])[base:]
     mag = mag.reshape(R // m, nbc, m).transpose(0, 2, 1).reshape(R, nbc)

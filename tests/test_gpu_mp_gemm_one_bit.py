@@ -1,5 +1,5 @@
-"""Blocks of 1 bit, whose codes enter as 128 + q in the kernels of up to 32 rows and in the one for many rows, and as 1 + q / 2 in the
-narrow kernel of 33 to 64 rows (`narrow`: the sizes that it takes).  Bound of a result: terms of size |B| scale |x| and |zero| |x| in fp32, with |B| up to 129 or, in units of
+"""Blocks of 1 bit, whose codes enter as 128 + q in the kernels of up to 32 rows and as that or, in some products of 33 to 64 rows, as 1 + q / 2 in
+those of more (`narrow`: the sizes of these, which the narrow kernel takes or that of many rows).  Bound of a result: terms of size |B| scale |x| and |zero| |x| in fp32, with |B| up to 129 or, in units of
 scale, 4; 2^-22 of their sum for the largest error.  What a row of x gives in products of 32 and of more rows then differs by the sum of both bounds at
 most."""
 import numpy as np
